@@ -7,12 +7,16 @@
 
 #include "gs.h"
 
-#define GS_STEP_BLOCK 128             // threads per workgroup of the step kernel for many gradient streams, and of the
-                                      // staged norm kernel (2 wave64)
-#define GS_WAVE_BLOCK 64              // single-wave workgroups: the step kernel otherwise, and the fast shapes of the
-                                      // kernels that step or add and leave a norm partial per workgroup
-#define GS_STEP_WIDE_MIN_K 15         // gradient streams from which the step kernel takes GS_STEP_BLOCK lanes
-#define GS_STATE_WAIT_MAX_K 7         // up to this many gradient streams each state load is waited for on its own
+#define GS_STEP_BLOCK 128             // threads per workgroup of the staged norm kernel (2 wave64)
+#define GS_WAVE_BLOCK 64              // single-wave workgroups: the fast shapes of the kernels that add and leave a
+                                      // norm partial per workgroup
+// limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
+#define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
+#define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
+#define GS_FEW_MAX 7000000            // elements up to which stores go out back to back
+#define GS_SERIAL_MIN (1 << 27)       // elements from which few gradient streams are taken one load at a time
+#define GS_SERIAL_MAX_K 7             // "few gradient streams"
+#define GS_SPEC_SERIAL_MIN 80000000   // GS_SERIAL_MIN of the speculative pass
 #define GS_BLOCK 256                  // threads per workgroup of the norm kernel (4 wave64)
 #define GS_TILE (GS_BLOCK * 4)        // elements per norm tile: one group of 4 per lane
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels

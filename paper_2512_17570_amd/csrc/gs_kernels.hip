@@ -4,24 +4,25 @@
 // the fp32 p/m/v streams in, p/m/v and the bf16 weight out) with ~100 VALU lane-ops per
 // element: HBM-bound, so there is no MFMA here.  Measured on MI355X, what decides the achieved
 // bandwidth of such a many-stream read+write pass is the shape of the memory traffic:
-//   * every wave-level memory instruction covers whole, contiguous 128-byte lines -- a lane owns
-//     4 consecutive elements, i.e. one 8-byte load per bf16 stream (512 B per wave) and one
-//     16-byte load/store per fp32 stream (1 KB per wave); lanes that own 8 elements would split
-//     each fp32 line across two instructions and fetch it twice;
-//   * workgroups are NOT persistent: one 512-element tile per 128-lane workgroup, dispatched in
-//     order, keeps the set of addresses in flight compact, which HBM rewards (a grid-stride loop
-//     costs 30-40 % on stores on this part);
-//   * a wave keeps its memory queues shallow in the step kernels: the three state loads up
-//     front, then one gradient load in flight at a time, then the four stores one by one;
+//   * every wave-level memory instruction covers whole, contiguous 128-byte lines.  A lane of the
+//     step owns 2 consecutive elements (a 4-byte load per bf16 stream, an 8-byte one per fp32
+//     stream): the window of addresses that all resident waves touch together is then half as wide
+//     as with 4 elements per lane, and HBM serves it 1-12 % faster;
+//   * workgroups are NOT persistent: one 256-element tile per workgroup, dispatched in order, keeps
+//     the set of addresses in flight compact, which HBM rewards (a grid-stride loop costs 30-40 %
+//     on stores on this part);
+//   * up to four gradient loads of a wave are in flight; its four stores go out one by one;
+//   * ranges that do not fill the chip are bound by the latency of a wave's serial chain instead,
+//     and take shapes that put every load in flight (step_shape);
 //   * every stream is touched once, so loads and stores carry the non-temporal hint.
 // The norm pass is read-only and does best with short contiguous spans of tiles per workgroup.
 //
 // Partition independence (Sec. 6.5 of the paper: results must not depend on the partition
 // ratio): every element goes through the same update function `adamw_element`, compiled with
-// floating-point contraction off, whether it is reached through the 4-wide body or through
+// floating-point contraction off, whether it is reached through a vector body or through
 // the per-element path used for ragged range ends.  Grouping is by ABSOLUTE element index
-// (groups of 4 starting at multiples of 4), so a range split at any point is processed with
-// bit-identical arithmetic.
+// (groups of 2 or 4 starting at multiples of their size), and no element's result depends on its
+// group, so a range split at any point is processed with bit-identical arithmetic.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
@@ -32,7 +33,13 @@
 namespace gs {
 
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// The group of EL consecutive elements a lane owns: its fp32 and its bf16 vector.
+template <int EL> struct Group;
+template <> struct Group<2> { typedef f32x2 F; typedef uint32_t H; };
+template <> struct Group<4> { typedef f32x4 F; typedef u32x2 H; };
 
 // ---- memory access helpers: streams are touched exactly once => non-temporal ------------
 template <typename T>
@@ -94,6 +101,46 @@ __device__ __forceinline__ void adamw_element(float a, float c, const StepConsts
     p = t5 - t6;
     m = mn;
     v = vn;
+}
+
+// k-way accumulation of one group, j ascending from +0 (Sec. 2.1: micro-batch gradients are
+// accumulated in full precision).  The loads go out in batches of DEPTH, each batch consumed before
+// the next is issued; what is left of k after the whole batches is one batch too.
+__device__ __forceinline__ void add_bf16(float (&a)[4], u32x2 g)
+{
+    a[0] += bf16_lo(g.x); a[1] += bf16_hi(g.x);
+    a[2] += bf16_lo(g.y); a[3] += bf16_hi(g.y);
+}
+__device__ __forceinline__ void add_bf16(float (&a)[2], uint32_t g)
+{
+    a[0] += bf16_lo(g); a[1] += bf16_hi(g);
+}
+
+template <int EL, int DEPTH>
+__device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, int64_t lo, float (&a)[EL])
+{
+    typedef typename Group<EL>::H H;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) a[e] = 0.0f;
+    int j = 0;
+#pragma unroll 1
+    for (; j + DEPTH <= k; j += DEPTH) {
+        H g[DEPTH];
+#pragma unroll
+        for (int q = 0; q < DEPTH; ++q) g[q] = ld_stream(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+#pragma unroll
+        for (int q = 0; q < DEPTH; ++q) add_bf16(a, g[q]);
+    }
+    const int rest = k - j;
+    if (rest > 0) {
+        H g[DEPTH];
+#pragma unroll
+        for (int q = 0; q < DEPTH - 1; ++q)
+            if (q < rest) g[q] = ld_stream(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+#pragma unroll
+        for (int q = 0; q < DEPTH - 1; ++q)
+            if (q < rest) add_bf16(a, g[q]);
+    }
 }
 
 // k-way accumulation of one 4-element group, j ascending from +0 (Sec. 2.1: micro-batch
@@ -194,79 +241,69 @@ __device__ __forceinline__ double block_sum(double x, double *lds)
 }
 
 // ---- fused accumulate + clip + AdamW + bf16 emit -----------------------------------------
-// The group of 4 elements starting at `lo` (a multiple of 4): whole-group vector path when the
-// group lies inside [begin,end), per-element path for ragged range ends -- same arithmetic.
-// States are read from A.p/m/v and written to A.po/mo/vo (the same arrays for the in-place
-// entry points).  NORM: also add the squares of the accumulated gradients to acc0/acc1.
-template <int K, bool NORM, int DEPTH = 1>
-__device__ __forceinline__ void step_group(const StepArgs &A, int k, int64_t lo, float c, const StepConsts &s,
-                                           double &acc0, double &acc1)
+// The group of EL elements starting at `lo` (a multiple of EL): vector path when the group lies
+// inside [begin,end), per-element path for ragged range ends -- same arithmetic.  States are read
+// from A.p/m/v and written to A.po/mo/vo (the same arrays for the in-place entry points).
+// STAGED: the gradient sum comes from A.acc instead of the k streams.  NORM: also add the squares
+// of the accumulated gradients to acc0/acc1.  DEPTH: gradient loads in flight per batch.  LWAIT:
+// the fp32 loads are waited for one by one.  SWAIT: each store waits for the previous one.
+template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT>
+__device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
 {
-    if (lo >= A.begin && lo + 4 <= A.end) {
-        f32x4 p, m, v;
-        float a[4];
-        if constexpr (K < 0) {
-            // four fp32 read streams against four write streams (a 1:1 mix): here even the loads
-            // do best one at a time -- 3.75 ms against 4.05 ms with the four in flight together
-            // (805 M elements)
-            p = ld_stream(reinterpret_cast<const f32x4 *>(A.p + lo));
-            wait_vm_idle();
-            m = ld_stream(reinterpret_cast<const f32x4 *>(A.m + lo));
-            wait_vm_idle();
-            v = ld_stream(reinterpret_cast<const f32x4 *>(A.v + lo));
-            wait_vm_idle();
-            f32x4 av = ld_stream(reinterpret_cast<const f32x4 *>(A.acc + lo));
-            a[0] = av.x; a[1] = av.y; a[2] = av.z; a[3] = av.w;
-        } else {
-            // State loads go first.  With many gradient streams they stay in flight while the
-            // gradient loads are walked one by one (k = 16: 7.46 ms against 7.83 ms when each state
-            // load is waited for); with few (where reads and writes are nearly balanced) waiting
-            // for each wins by 2-4 %, as in the staged case above.
-            p = ld_stream(reinterpret_cast<const f32x4 *>(A.p + lo));
-            if (DEPTH != 0 && k <= GS_STATE_WAIT_MAX_K) wait_vm_idle();
-            m = ld_stream(reinterpret_cast<const f32x4 *>(A.m + lo));
-            if (DEPTH != 0 && k <= GS_STATE_WAIT_MAX_K) wait_vm_idle();
-            v = ld_stream(reinterpret_cast<const f32x4 *>(A.v + lo));
-            if (DEPTH != 0 && k <= GS_STATE_WAIT_MAX_K) wait_vm_idle();
-            accumulate_group<K, DEPTH>(A.gt, k, lo, a);
-        }
-        float P[4] = {p.x, p.y, p.z, p.w};
-        float M[4] = {m.x, m.y, m.z, m.w};
-        float V[4] = {v.x, v.y, v.z, v.w};
-        if constexpr (NORM) {
-            acc0 = fma((double)a[0], (double)a[0], acc0);
-            acc1 = fma((double)a[1], (double)a[1], acc1);
-            acc0 = fma((double)a[2], (double)a[2], acc0);
-            acc1 = fma((double)a[3], (double)a[3], acc1);
-        }
+    typedef typename Group<EL>::F F;
+    typedef typename Group<EL>::H H;
+    const StepConsts &s = A.c;
+    if (lo >= A.begin && lo + EL <= A.end) {
+        float c = 1.0f;
+        if constexpr (LWAIT) c = clip_coefficient(d_sqnorm, A.max_norm);
+        const F p = ld_stream(reinterpret_cast<const F *>(A.p + lo));
+        if constexpr (LWAIT) wait_vm_idle();
+        const F m = ld_stream(reinterpret_cast<const F *>(A.m + lo));
+        if constexpr (LWAIT) wait_vm_idle();
+        const F v = ld_stream(reinterpret_cast<const F *>(A.v + lo));
+        if constexpr (LWAIT) wait_vm_idle();
+        float a[EL];
+        if constexpr (STAGED) {
+            const F av = ld_stream(reinterpret_cast<const F *>(A.acc + lo));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) adamw_element(a[e], c, s, P[e], M[e], V[e]);
-        u32x2 wv;
-        wv.x = f32_to_bf16_bits(P[0]) | (f32_to_bf16_bits(P[1]) << 16);
-        wv.y = f32_to_bf16_bits(P[2]) | (f32_to_bf16_bits(P[3]) << 16);
-        if constexpr (DEPTH == 0) {
-            st_stream(reinterpret_cast<f32x4 *>(A.po + lo), f32x4{P[0], P[1], P[2], P[3]});
-            st_stream(reinterpret_cast<f32x4 *>(A.mo + lo), f32x4{M[0], M[1], M[2], M[3]});
-            st_stream(reinterpret_cast<f32x4 *>(A.vo + lo), f32x4{V[0], V[1], V[2], V[3]});
-            st_stream(reinterpret_cast<u32x2 *>(A.w + lo), wv);
+            for (int e = 0; e < EL; ++e) a[e] = av[e];
         } else {
-            // like the gradient loads, the four stores of a wave go out one at a time (each waits
-            // for the previous one): another ~3 % on MI355X from keeping the queues shallow
-            __builtin_amdgcn_sched_barrier(0);
-            st_stream(reinterpret_cast<f32x4 *>(A.po + lo), f32x4{P[0], P[1], P[2], P[3]});
-            wait_vm_idle();
-            st_stream(reinterpret_cast<f32x4 *>(A.mo + lo), f32x4{M[0], M[1], M[2], M[3]});
-            wait_vm_idle();
-            st_stream(reinterpret_cast<f32x4 *>(A.vo + lo), f32x4{V[0], V[1], V[2], V[3]});
-            wait_vm_idle();
-            st_stream(reinterpret_cast<u32x2 *>(A.w + lo), wv);
+            accumulate_batches<EL, DEPTH>(A.gt, A.k, lo, a);
         }
+        if constexpr (!LWAIT) c = clip_coefficient(d_sqnorm, A.max_norm);     // under the loads in flight
+        F P, M, V;
+        uint32_t W[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e) {
+            float pe = p[e], me = m[e], ve = v[e];
+            if constexpr (NORM) {
+                if (e & 1) acc1 = fma((double)a[e], (double)a[e], acc1);
+                else acc0 = fma((double)a[e], (double)a[e], acc0);
+            }
+            adamw_element(a[e], c, s, pe, me, ve);
+            P[e] = pe;
+            M[e] = me;
+            V[e] = ve;
+            W[e] = f32_to_bf16_bits(pe);
+        }
+        H w;
+        if constexpr (EL == 2) w = W[0] | (W[1] << 16);
+        else w = H{W[0] | (W[1] << 16), W[2] | (W[3] << 16)};
+        if constexpr (SWAIT) __builtin_amdgcn_sched_barrier(0);
+        st_stream(reinterpret_cast<F *>(A.po + lo), P);
+        if constexpr (SWAIT) wait_vm_idle();
+        st_stream(reinterpret_cast<F *>(A.mo + lo), M);
+        if constexpr (SWAIT) wait_vm_idle();
+        st_stream(reinterpret_cast<F *>(A.vo + lo), V);
+        if constexpr (SWAIT) wait_vm_idle();
+        st_stream(reinterpret_cast<H *>(A.w + lo), w);
     } else {
+        const float c = clip_coefficient(d_sqnorm, A.max_norm);
         const int64_t i0 = lo > A.begin ? lo : A.begin;
-        const int64_t i1 = lo + 4 < A.end ? lo + 4 : A.end;
+        const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
         for (int64_t i = i0; i < i1; ++i) {
             float a;
-            if constexpr (K < 0) a = A.acc[i]; else a = accumulate_one(A.gt, k, i);
+            if constexpr (STAGED) a = A.acc[i]; else a = accumulate_one(A.gt, A.k, i);
             if constexpr (NORM) acc0 = fma((double)a, (double)a, acc0);
             float pi = A.p[i], mi = A.m[i], vi = A.v[i];
             adamw_element(a, c, s, pi, mi, vi);
@@ -278,45 +315,37 @@ __device__ __forceinline__ void step_group(const StepArgs &A, int k, int64_t lo,
     }
 }
 
-// One workgroup = one tile of BLOCK*4 consecutive elements, one group of 4 per lane.  BLOCK is 64
-// (one wave) up to 14 gradient streams and for the staged step, 128 from 15 on: measured on
-// 805 M elements, single-wave workgroups are 1-3.5 % faster for k = 1..14 (k = 8: 5.50 ms against
-// 5.70 ms) and level or 1 % slower at k = 16; 256 lanes lose 4-6 % everywhere.  Tiles start at multiples of the tile size counted from element 0 of the arrays, not from
-// `begin`: the grouping does not move with the range (partition independence), and a wave's
-// 1 KB accesses stay line-aligned for any `begin` (a split point in the middle of a layer would
-// otherwise make every wave straddle two extra lines).
-template <int K, int BLOCK>
+// One workgroup = one tile of BLOCK*EL consecutive elements, one group per lane; which shape a range
+// takes is step_shape's choice.  Tiles start at multiples of the tile size counted from element 0 of
+// the arrays, not from `begin`: the grouping does not move with the range (partition independence),
+// and a wave's accesses stay line-aligned for any `begin` (a split point in the middle of a layer
+// would otherwise make every wave straddle two extra lines).
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A)
 {
-    constexpr int TILE = BLOCK * 4;
-    const int k = (K > 0) ? K : A.k;     // K < 0: gradients come as one staged fp32 sum (A.acc)
-    const int64_t lo = (A.begin / TILE + (int64_t)blockIdx.x) * TILE + (int64_t)threadIdx.x * 4;
-    if (lo >= A.end || lo + 4 <= A.begin) return;
-    const float c = clip_coefficient(A.d_sqnorm, A.max_norm);
+    constexpr int TILE = BLOCK * EL;
+    const int64_t lo = (A.begin / TILE + (int64_t)blockIdx.x) * TILE + (int64_t)threadIdx.x * EL;
+    if (lo >= A.end || lo + EL <= A.begin) return;
     double unused0 = 0.0, unused1 = 0.0;
-    step_group<K, false>(A, k, lo, c, A.c, unused0, unused1);
+    step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT>(A, lo, A.d_sqnorm, unused0, unused1);
 }
 
 // Speculative single pass (Sec. 2.1 of the paper: prior work steps before the global norm is
 // known because clipping rarely changes the gradients): the step is applied with c = 1 and the
 // squared norm of the same accumulated gradients is reduced on the way, so the gradients are
-// read once.  Every workgroup leaves a partial.  Fast shape: the step kernel's own 512-element
-// tiles, one per workgroup, shallow queues (needs a workspace of one double per tile);
-// fallback for the fixed-size workspace: 4096-element tiles, all loads in flight, `span` tiles
-// per workgroup.
-template <int K, int BLOCK, int DEPTH>
+// read once.  Every workgroup leaves a partial for its `span` consecutive tiles.
+template <int BLOCK, int EL, int DEPTH, bool LWAIT, bool SWAIT>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *partials, int span)
 {
-    constexpr int TILE = BLOCK * 4;
+    constexpr int TILE = BLOCK * EL;
     __shared__ double lds[BLOCK / 64];
-    const int k = (K > 0) ? K : A.k;
-    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
+    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
-        if (lo + 4 <= A.begin) continue;
-        step_group<K, true, DEPTH>(A, k, lo, 1.0f, A.c, acc0, acc1);
+        if (lo + EL <= A.begin) continue;
+        step_group<EL, false, true, DEPTH, LWAIT, SWAIT>(A, lo, nullptr, acc0, acc1);
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -489,29 +518,70 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile = GS_TILE)
     return (end - 1) / tile - begin / tile + 1;
 }
 
+// How a step over `elems` elements is laid out; every line below is where the two sides met when both
+// were timed with cold caches (us per launch, k = 1 / 4 / 8 / 16 / 32).  The chip holds 8192 waves
+// (256 CUs x 32): up to 2^20 elements the waves of a 2-element shape, and up to 2^21 those of a
+// 4-element shape, are resident together.
+//   <= 2^19   LATENCY: a wave's chain of dependent loads is the time, so all of them go out at once.
+//             100 k elements: 2.9/3.1/3.0/3.2/4.1 against 4.4/5.9/6.6/10.1/17.2 for loads one at a
+//             time; at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
+//   <= 2^21   RESIDENT: no second, nearly empty generation of waves: 1.3 M elements 6.7/8.5/10.3/14.7/20.7
+//             against 8.8/10.0/12.3/16.0/23.1 in the STREAM shape and 7.4/9.4/11.8/17.4/27.1 one at a
+//             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
+//             wins (2.0 M: 10.3/12.8 against 10.3/13.4 for k = 1 / 4).
+//   <= 7 M    FEW: 2.5 M elements 13.8/16.3/19.7/26.5/39.1 against 14.7/17.1/21.0/27.4/40.0 (STREAM)
+//             and 15.0/18.7/23.5/33.1/51.6 (one load at a time, 4 elements per lane).
+//   above     STREAM: 12.6 M 57.6/68.6/85.3/119/193 against 57.1/69.6/87.2/123/197 (FEW) and
+//             61.3/75.4/93.4/133/200 (one load at a time, 4 elements); 805 M, k = 16: 7.55 ms against 7.67.
+//   >= 2^27   with up to 7 streams SERIAL: reads and writes are nearly balanced, and waiting for each
+//             keeps the memory queues shallow (805 M elements, k = 1 / 4: 3.49 / 4.30 ms against
+//             3.53 / 4.34); from 8 streams on STREAM is ahead (201 M, k = 8: 1.31 ms against 1.34),
+//             and for the staged step it is ahead at every size (3.76 ms against 3.79).
+enum Shape {
+    SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once
+    SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
+    SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
+    SHAPE_FEW,        // 2 elements per lane, stores back to back
+    SHAPE_STREAM      // 2 elements per lane, stores one at a time
+};
+
+// k == 0: the staged step (one fp32 sum instead of gradient streams)
+static Shape step_shape(int64_t elems, int k)
+{
+    if (elems <= GS_LATENCY_MAX) return SHAPE_LATENCY;
+    if (elems <= GS_RESIDENT_MAX)
+        return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
+    if (elems <= GS_FEW_MAX) return SHAPE_FEW;
+    return elems >= GS_SERIAL_MIN && k > 0 && k <= GS_SERIAL_MAX_K ? SHAPE_SERIAL : SHAPE_STREAM;
+}
+
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
+static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
+{
+    const int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
+    if (tiles < 1 || tiles > 0x7fffffff) return hipErrorInvalidValue;
+    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT><<<(int)tiles, BLOCK, 0, stream>>>(A);
+    return hipGetLastError();
+}
+
+template <bool STAGED>
+static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
+{
+    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k)) {
+    case SHAPE_LATENCY:
+        if (A.k <= 8) return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
+        return launch_step<64, 2, STAGED, 16, false, false>(A, stream);
+    case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
+    case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
+    case SHAPE_FEW: return launch_step<128, 2, STAGED, 4, false, false>(A, stream);
+    case SHAPE_STREAM: break;
+    }
+    return launch_step<128, 2, STAGED, 4, false, true>(A, stream);
+}
+
 hipError_t launch_accum_adamw(const StepArgs &A, hipStream_t stream)
 {
-    const bool wide = !A.acc && A.k >= GS_STEP_WIDE_MIN_K;
-    const int64_t tiles = tiles_of(A.begin, A.end, (int64_t)(wide ? GS_STEP_BLOCK : GS_WAVE_BLOCK) * 4);
-    if (tiles < 1 || tiles > 0x7fffffff) return hipErrorInvalidValue;
-    const int grid = (int)tiles;
-    if (A.acc) {
-        k_accum_adamw<-1, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A);
-        return hipGetLastError();
-    }
-    // k = 1, 2 unrolled; every other k takes the runtime loop, which keeps one gradient load in
-    // flight per wave with the fewest registers (27 VGPRs: full occupancy) and measured as fast
-    // as or faster than unrolled bodies for k = 4, 8, 16
-    if (wide) {
-        k_accum_adamw<0, GS_STEP_BLOCK><<<grid, GS_STEP_BLOCK, 0, stream>>>(A);
-        return hipGetLastError();
-    }
-    switch (A.k) {
-    case 1: k_accum_adamw<1, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A); break;
-    case 2: k_accum_adamw<2, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A); break;
-    default: k_accum_adamw<0, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A); break;
-    }
-    return hipGetLastError();
+    return A.acc ? launch_step_shape<true>(A, stream) : launch_step_shape<false>(A, stream);
 }
 
 // Partials the workspace can hold (its last GS_FINAL_SLICES doubles serve the folding stage).
@@ -520,49 +590,45 @@ static int64_t partial_capacity(size_t workspace_bytes)
     return (int64_t)(workspace_bytes / sizeof(double)) - GS_FINAL_SLICES;
 }
 
+template <int BLOCK, int EL, int DEPTH, bool LWAIT, bool SWAIT>
+static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
+    if (tiles < 1) tiles = 1;
+    const int64_t span = tiles > cap ? (tiles + cap - 1) / cap : 1;
+    const int64_t grid = (tiles + span - 1) / span;
+    if (span > 0x7fffffff || grid > 0x7fffffff) return hipErrorInvalidValue;
+    k_accum_adamw_spec<BLOCK, EL, DEPTH, LWAIT, SWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, partials, (int)span);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fold(partials, cap, (int)grid, d_out, accumulate, stream);
+}
+
+// The step's shapes with a partial per workgroup; a wave reduction per 128 or 256 elements moves the
+// lines a little (us or ms per launch, before = one load at a time, 4 elements per lane, 64 lanes):
+//   * up to 2 streams the shallow 64-lane shape stays (50 M, k = 1: 226 us against 239);
+//   * up to 7 M elements everything in flight, 256 lanes: 600 k, k = 3 / 8 / 16: 7.7/8.9/11.0 against
+//     9.7/11.9/16.3;
+//   * then 128 lanes with four loads in flight: 4 elements per lane (12.6 M, k = 3 / 8: 71.5/91.8
+//     against 73.9/100), or 2 from 12 streams on (k = 16: 50 M 465 us against 488; 478 with 4);
+//   * from 80 M elements the step's own choice: shallow up to 7 streams, else 2 elements per lane
+//     (201 M, k = 16: 1.81 ms against 1.83).
+// A workspace too small for a partial per 256 elements takes 512-element tiles, then 4096-element
+// ones in runs (201 M, 2 MB workspace, k = 8 / 16: 1.33/1.93 ms).
 hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t workspace_bytes, double *d_out,
                                    int accumulate, hipStream_t stream)
 {
     const int64_t cap = partial_capacity(workspace_bytes);
-    // fastest shape the workspace has room for: one tile per workgroup, runtime gradient loop,
-    // shallow queues -- single-wave workgroups (k = 16: 7.42 ms, k = 8: 5.28 ms on 805 M elements),
-    // else two waves (7.58 / 5.54 ms)
-    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)GS_WAVE_BLOCK * 4);
-    if (tiles < 1) tiles = 1;
-    if (tiles <= cap && tiles <= 0x7fffffff) {
-        const int grid = (int)tiles;
-        k_accum_adamw_spec<0, GS_WAVE_BLOCK, 1><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, partials, 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return launch_fold(partials, cap, grid, d_out, accumulate, stream);
-    }
-    tiles = tiles_of(A.begin, A.end, (int64_t)GS_STEP_BLOCK * 4);
-    if (tiles < 1) tiles = 1;
-    if (tiles <= cap && tiles <= 0x7fffffff) {
-        const int grid = (int)tiles;
-        k_accum_adamw_spec<0, GS_STEP_BLOCK, 1><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, partials, 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return launch_fold(partials, cap, grid, d_out, accumulate, stream);
-    }
-    tiles = tiles_of(A.begin, A.end, (int64_t)GS_STAGE_BLOCK * 4);
-    if (tiles < 1) tiles = 1;
-    int64_t span = 1;
-    if (tiles > cap) span = (tiles + cap - 1) / cap;
-    if (span > 0x7fffffff) return hipErrorInvalidValue;
-    const int grid = (int)((tiles + span - 1) / span);
-    const int sp = (int)span;
-    switch (A.k) {
-    case 1: k_accum_adamw_spec<1, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    case 2: k_accum_adamw_spec<2, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    case 4: k_accum_adamw_spec<4, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    case 8: k_accum_adamw_spec<8, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    case 16: k_accum_adamw_spec<16, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    default: k_accum_adamw_spec<0, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, partials, sp); break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_fold(partials, cap, grid, d_out, accumulate, stream);
+    const int64_t n = A.end - A.begin;
+    const bool fits256 = tiles_of(A.begin, A.end, 256) <= cap;
+    if (fits256 && (A.k <= 2 ? n > GS_LATENCY_MAX : A.k <= GS_SERIAL_MAX_K && n >= GS_SPEC_SERIAL_MIN))
+        return launch_spec<64, 4, 1, true, true>(A, partials, cap, d_out, accumulate, stream);
+    if (n <= GS_FEW_MAX) return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
+    if (fits256 && (A.k >= 12 || n >= GS_SPEC_SERIAL_MIN))
+        return launch_spec<128, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+    if (tiles_of(A.begin, A.end, 512) <= cap)
+        return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+    return launch_spec<1024, 4, 8, false, false>(A, partials, cap, d_out, accumulate, stream);
 }
 
 hipError_t launch_grad_sqnorm(const SqnormArgs &A, size_t workspace_bytes, double *d_out, int accumulate,

@@ -1,0 +1,93 @@
+"""GPU tests at the sizes where the launchers change the shape of a pass: the last range of one shape and
+the first of the next, with ragged begins and every remainder of the gradient batches.
+
+Sizes are lengths of [begin,end); the limits are those of csrc/gs_internal.h.
+"""
+from __future__ import annotations
+
+import pytest
+import torch
+
+from gpu_util import DEV, DeviceCase, O, assert_bf16_close, assert_f32_close, gs, np_bf16, np_f32
+
+pytestmark = pytest.mark.gpu
+
+LATENCY, RESIDENT, FEW, SERIAL = 1 << 19, 1 << 21, 7_000_000, 1 << 27
+HP = gs.HParams(step=10, max_grad_norm=0.1)
+
+
+def check(got, want, b, e, tag):
+    """p, m, v, w of [b,e) against the oracle; nothing outside the range may have moved."""
+    for nm, g, w in zip("pmv", got[:3], want[:3]):
+        assert_f32_close(np_f32(g)[b:e], w[b:e], f"{tag}.{nm}")
+    assert_bf16_close(np_bf16(got[3])[b:e], want[3][b:e], f"{tag}.w")
+
+
+def untouched(got, before, b, e):
+    for g, o in zip(got, before):
+        assert torch.equal(g[:b], o[:b]) and torch.equal(g[e:], o[e:])
+
+
+# (length, k): both sides of every line; k covers whole batches and every kind of remainder
+EDGES = [(1, 1), (2, 9), (255, 3), (257, 17), (LATENCY, 8), (LATENCY, 9), (LATENCY + 1, 7), (LATENCY + 1, 19),
+         (RESIDENT // 4 * 3, 7), (RESIDENT // 4 * 3 + 1, 7), (RESIDENT // 4 * 3 + 1, 8), (RESIDENT, 5), (RESIDENT, 32),
+         (RESIDENT + 1, 6), (FEW, 2), (FEW + 1, 1), (FEW + 1, 11)]
+
+
+@pytest.mark.parametrize("length,k", EDGES)
+@pytest.mark.parametrize("begin", [0, 1, 6])
+def test_step_and_staged_step_at_shape_edges(length, k, begin):
+    n = begin + length + 3
+    case = DeviceCase(n, k, seed=length % 97 + k)
+    e = begin + length
+    S = case.gpu_sqnorm(begin, e)
+    c = O.clip_coef(O.grad_sqnorm(case.h_g, begin, e), HP.max_grad_norm)
+    want = case.oracle_step(HP, c, begin, e)
+    before = case.clone_states()
+    got = case.clone_states()
+    gs.gs_accum_adamw(*got, case.grads, begin, e, HP, case.sq)
+    check(got, want, begin, e, f"step S={S}")
+    untouched(got, before, begin, e)
+    acc = torch.zeros(n, dtype=torch.float32, device=DEV)
+    for j, g in enumerate(case.grads):
+        gs.gs_accum_add(acc, g, j == 0, begin, e)
+    staged = case.clone_states()
+    gs.gs_adamw_from_acc(*staged, acc, begin, e, HP, case.sq)
+    for a, b in zip(got, staged):
+        assert torch.equal(a, b)                 # same sum, same update: same bits
+
+
+@pytest.mark.parametrize("length,k", EDGES + [(RESIDENT, 2), (FEW, 16), (FEW + 1, 12)])
+@pytest.mark.parametrize("big_ws", [False, True])
+def test_speculative_step_at_shape_edges(length, k, big_ws):
+    begin, n = 5, length + 9
+    case = DeviceCase(n, k, seed=length % 89 + k)
+    e = begin + length
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(n), dtype=torch.uint8, device=DEV) if big_ws else case.ws
+    want = case.oracle_step(HP, 1.0, begin, e)
+    out = [torch.full((n,), 7.0, device=DEV) for _ in range(3)] + [torch.zeros_like(case.w)]
+    before = [x.clone() for x in out]
+    case.sq.fill_(float("nan"))                  # overwritten, not added to
+    gs.gs_accum_adamw_spec(case.p, case.m, case.v, *out, case.grads, begin, e, HP, case.sq, ws)
+    check(out, want, begin, e, "spec")
+    untouched(out, before, begin, e)
+    S = O.grad_sqnorm(case.h_g, begin, e)
+    # every square is exact in fp64; the oracle adds the `length` non-negative terms one after another, which
+    # is within length * 2^-53 of the exact sum (the kernel's tree is far closer)
+    assert abs(float(case.sq.item()) - S) <= max(length * 2.0 ** -53, 1e-13) * S
+
+
+@pytest.mark.parametrize("k", [2, 7, 8])
+def test_largest_shape_equals_its_pieces(k):
+    """From 2^27 elements on (the shallow shape up to 7 streams): bit for bit what the other shapes give
+    over the range cut into pieces of every size class."""
+    n = SERIAL + 3
+    case = DeviceCase(n, k, seed=k, keep_host=False)
+    case.gpu_sqnorm()
+    whole, parts = case.clone_states(), case.clone_states()
+    gs.gs_accum_adamw(*whole, case.grads, 0, n, HP, case.sq)
+    cuts = [0, 77, LATENCY + 77, LATENCY + RESIDENT + 77, LATENCY + RESIDENT + FEW + 78, n // 2 + 1, n]
+    for x, y in zip(cuts, cuts[1:]):
+        gs.gs_accum_adamw(*parts, case.grads, x, y, HP, case.sq)
+    for a, b in zip(whole, parts):
+        assert torch.equal(a, b)

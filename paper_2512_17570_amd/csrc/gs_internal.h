@@ -17,14 +17,19 @@
 #define GS_SERIAL_MIN (1 << 27)       // elements from which few gradient streams are taken one load at a time
 #define GS_SERIAL_MAX_K 7             // "few gradient streams"
 #define GS_SPEC_SERIAL_MIN 80000000   // GS_SERIAL_MIN of the speculative pass
-#define GS_BLOCK 256                  // threads per workgroup of the norm kernel (4 wave64)
-#define GS_TILE (GS_BLOCK * 4)        // elements per norm tile: one group of 4 per lane
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels
 #define GS_FINAL_SLICES 128           // workgroups of the first folding stage for large partial counts
 #define GS_FINAL_DIRECT_MAX 8192      // up to this many partials are folded by one workgroup directly
 #define GS_STAGE_BLOCK 1024           // threads per workgroup of the staged norm kernel
 #define GS_SQNORM_MAX_BLOCKS 262144   // upper bound on block partials => workspace size (2 MB)
-#define GS_NORM_SPAN 8                // consecutive tiles per norm workgroup (grows for huge ranges)
+// limits of the norm's shapes (launch_grad_norm)
+#define GS_NORM_SMALL_MAX (1 << 22)   // up to 4 streams: elements up to which workgroups are kept small
+#define GS_NORM_256_MAX (1 << 20)     // from 5 streams on: elements up to which they have 256, 512 and 1024 lanes
+#define GS_NORM_512_MAX (1 << 21)
+#define GS_NORM_1024_MAX (1 << 23)
+#define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two
+#define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
+#define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup
 
 namespace gs {
 
@@ -56,6 +61,8 @@ struct SqnormArgs {
     int64_t begin, end;
     double *partials;
     float *acc;         // non-null: also write the fp32 gradient sum here
+    double *out;        // norm in a single workgroup: the result, added to if accumulate is set
+    int accumulate;
 };
 
 struct AccumAddArgs {

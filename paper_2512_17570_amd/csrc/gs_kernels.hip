@@ -132,7 +132,7 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
         for (int q = 0; q < DEPTH; ++q) add_bf16(a, g[q]);
     }
     const int rest = k - j;
-    if (rest > 0) {
+    if (DEPTH > 1 && rest > 0) {
         H g[DEPTH];
 #pragma unroll
         for (int q = 0; q < DEPTH - 1; ++q)
@@ -206,11 +206,31 @@ __device__ __forceinline__ void accumulate_group(const GradTable &gt, int k, int
     }
 }
 
-__device__ __forceinline__ float accumulate_one(const GradTable &gt, int k, int64_t i)
+// The same sum for the elements [i0,i1) of a group that a range end cuts (the others get 0).  One lane
+// works alone here while the rest of the chip runs dry, so its loads go out several streams at a time: at
+// 16 streams one load after another took longer than all the whole groups of a small range together.
+template <int EL>
+__device__ __forceinline__ void accumulate_cut(const GradTable &gt, int k, int64_t lo, int64_t i0, int64_t i1, float (&a)[EL])
 {
-    float a = 0.0f;
-    for (int j = 0; j < k; ++j) a += __uint_as_float((uint32_t)gt.g[j][i] << 16);
-    return a;
+#pragma unroll
+    for (int e = 0; e < EL; ++e) a[e] = 0.0f;
+    constexpr int BATCH = 16 / EL;
+#pragma unroll 1
+    for (int j = 0; j < k; j += BATCH) {
+        uint32_t g[BATCH][EL];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q)
+            if (j + q < k)
+#pragma unroll
+                for (int e = 0; e < EL; ++e)
+                    if (lo + e >= i0 && lo + e < i1) g[q][e] = gt.g[j + q][lo + e];
+#pragma unroll
+        for (int q = 0; q < BATCH; ++q)
+            if (j + q < k)
+#pragma unroll
+                for (int e = 0; e < EL; ++e)
+                    if (lo + e >= i0 && lo + e < i1) a[e] += __uint_as_float(g[q][e] << 16);
+    }
 }
 
 // ---- block reduction used by the norm kernels ----------------------------------------------
@@ -298,20 +318,29 @@ __device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const 
         if constexpr (SWAIT) wait_vm_idle();
         st_stream(reinterpret_cast<H *>(A.w + lo), w);
     } else {
-        const float c = clip_coefficient(d_sqnorm, A.max_norm);
         const int64_t i0 = lo > A.begin ? lo : A.begin;
         const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
-        for (int64_t i = i0; i < i1; ++i) {
-            float a;
-            if constexpr (STAGED) a = A.acc[i]; else a = accumulate_one(A.gt, A.k, i);
-            if constexpr (NORM) acc0 = fma((double)a, (double)a, acc0);
-            float pi = A.p[i], mi = A.m[i], vi = A.v[i];
-            adamw_element(a, c, s, pi, mi, vi);
-            A.po[i] = pi;
-            A.mo[i] = mi;
-            A.vo[i] = vi;
-            A.w[i] = (uint16_t)f32_to_bf16_bits(pi);
-        }
+        float a[EL], p[EL], m[EL], v[EL];
+#pragma unroll
+        for (int e = 0; e < EL; ++e)
+            if (lo + e >= i0 && lo + e < i1) {
+                p[e] = A.p[lo + e];
+                m[e] = A.m[lo + e];
+                v[e] = A.v[lo + e];
+                if constexpr (STAGED) a[e] = A.acc[lo + e];
+            }
+        if constexpr (!STAGED) accumulate_cut<EL>(A.gt, A.k, lo, i0, i1, a);
+        const float c = clip_coefficient(d_sqnorm, A.max_norm);
+#pragma unroll
+        for (int e = 0; e < EL; ++e)
+            if (lo + e >= i0 && lo + e < i1) {
+                if constexpr (NORM) acc0 = fma((double)a[e], (double)a[e], acc0);
+                adamw_element(a[e], c, s, p[e], m[e], v[e]);
+                A.po[lo + e] = p[e];
+                A.mo[lo + e] = m[e];
+                A.vo[lo + e] = v[e];
+                A.w[lo + e] = (uint16_t)f32_to_bf16_bits(p[e]);
+            }
     }
 }
 
@@ -352,16 +381,82 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *
 }
 
 // ---- squared norm of the accumulated gradient --------------------------------------------
-// Workgroup b reads `span` consecutive tiles starting at tile b*span (tiles counted from the
-// GS_TILE-aligned start of the range): a short contiguous run per workgroup is what the read
-// path likes best.
-// STAGE: also write the fp32 sum a_i to A.acc (the staged two-pass variant: the step then reads
-// one fp32 stream instead of re-reading k bf16 streams).  Once a store stream is involved, runs
-// of tiles per workgroup cost bandwidth again (stores want in-order, one-tile workgroups), so
-// the staged kernel uses 1024-lane workgroups (4096-element tiles) and a span of 1 wherever the
-// partials still fit the workspace.
-template <int K, bool STAGE, int BLOCK, int DEPTH>
+__device__ __forceinline__ void add_squares(const float (&a)[4], double &acc0, double &acc1)
+{
+    acc0 = fma((double)a[0], (double)a[0], acc0);
+    acc1 = fma((double)a[1], (double)a[1], acc1);
+    acc0 = fma((double)a[2], (double)a[2], acc0);
+    acc1 = fma((double)a[3], (double)a[3], acc1);
+}
+
+// Read-only, 2k bytes per element.  Workgroup b reads `span` consecutive tiles starting at tile
+// b*span: a short contiguous run per workgroup is what the read path likes best.  What else bounds
+// it is how much a wave has in flight: with few streams (compile-time K) the same groups of U tiles
+// are loaded together, otherwise (K == 0) up to 16 streams are.
+// ONE: a single workgroup reads the whole range and leaves the norm itself in A.out.
+template <int K, int U, int BLOCK, bool ONE>
 __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
+{
+    constexpr int TILE = BLOCK * 4;
+    __shared__ double lds[BLOCK / 64];
+    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
+    double acc0 = 0.0, acc1 = 0.0;
+    for (int it = 0; it < span; it += U) {
+        const int64_t lo = first + (int64_t)it * TILE;
+        if (lo >= A.end) break;
+        if (lo >= A.begin && lo + (int64_t)(U - 1) * TILE + 4 <= A.end) {
+            if constexpr (K > 0) {
+                u32x2 g[U][K];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < K; ++j)
+                        g[u][j] = ld_stream(reinterpret_cast<const u32x2 *>(A.gt.g[j] + lo + (int64_t)u * TILE));
+#pragma unroll
+                for (int u = 0; u < U; ++u) {
+                    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+                    for (int j = 0; j < K; ++j) add_bf16(a, g[u][j]);
+                    add_squares(a, acc0, acc1);
+                }
+            } else {
+                static_assert(K > 0 || U == 1, "tiles are grouped for a compile-time K only");
+                float a[4];
+                accumulate_batches<4, 16>(A.gt, A.k, lo, a);
+                add_squares(a, acc0, acc1);
+            }
+        } else {
+            // a range end lies among these tiles: group by group, and by element in the group it cuts
+            for (int u = 0; u < U; ++u) {
+                const int64_t l = lo + (int64_t)u * TILE;
+                if (l >= A.begin && l + 4 <= A.end) {
+                    float a[4];
+                    accumulate_batches<4, K == 0 ? 16 : K>(A.gt, A.k, l, a);
+                    add_squares(a, acc0, acc1);
+                    continue;
+                }
+                const int64_t i0 = l > A.begin ? l : A.begin;
+                const int64_t i1 = l + 4 < A.end ? l + 4 : A.end;
+                if (i0 >= i1) continue;
+                float a[4];
+                accumulate_cut<4>(A.gt, A.k, l, i0, i1, a);
+                add_squares(a, acc0, acc1);
+            }
+        }
+    }
+    double t = block_sum<BLOCK>(acc0 + acc1, lds);
+    if (threadIdx.x == 0) {
+        if constexpr (ONE) *A.out = A.accumulate ? *A.out + t : t;
+        else A.partials[blockIdx.x] = t;
+    }
+}
+
+// The same norm that also writes the fp32 sum a_i to A.acc (the staged two-pass variant: the step
+// then reads one fp32 stream instead of re-reading k bf16 streams).  Once a store stream is
+// involved, runs of tiles per workgroup cost bandwidth (stores want in-order, one-tile workgroups),
+// so it uses a span of 1 wherever the partials still fit the workspace.
+template <int K, int BLOCK, int DEPTH>
+__global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int span)
 {
     constexpr int TILE = BLOCK * 4;
     __shared__ double lds[BLOCK / 64];
@@ -375,19 +470,15 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
         if (lo >= A.begin && lo + 4 <= A.end) {
             float a[4];
             accumulate_group<K, DEPTH>(A.gt, k, lo, a);
-            if constexpr (STAGE) st_stream(reinterpret_cast<f32x4 *>(A.acc + lo), f32x4{a[0], a[1], a[2], a[3]});
-            acc0 = fma((double)a[0], (double)a[0], acc0);
-            acc1 = fma((double)a[1], (double)a[1], acc1);
-            acc0 = fma((double)a[2], (double)a[2], acc0);
-            acc1 = fma((double)a[3], (double)a[3], acc1);
+            st_stream(reinterpret_cast<f32x4 *>(A.acc + lo), f32x4{a[0], a[1], a[2], a[3]});
+            add_squares(a, acc0, acc1);
         } else {
             const int64_t i0 = lo > A.begin ? lo : A.begin;
             const int64_t i1 = lo + 4 < A.end ? lo + 4 : A.end;
-            for (int64_t i = i0; i < i1; ++i) {
-                float a = accumulate_one(A.gt, k, i);
-                if constexpr (STAGE) A.acc[i] = a;
-                acc0 = fma((double)a, (double)a, acc0);
-            }
+            float a[4];
+            accumulate_cut<4>(A.gt, k, lo, i0, i1, a);
+            for (int64_t i = i0; i < i1; ++i) A.acc[i] = a[i - lo];
+            add_squares(a, acc0, acc1);
         }
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
@@ -445,32 +536,46 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
 
 // Norm of a finished fp32 accumulation buffer (the buffer gs_accum_add builds, or one that came
 // back from a reduction across devices): 4 bytes read per element, the read-only shape of the
-// gradient norm -- a short contiguous run of tiles per workgroup.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t begin, int64_t end, double *partials, int span)
+// gradient norm -- U tiles of a short contiguous run in flight together.
+template <int U, int BLOCK, bool ONE>
+__global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t begin, int64_t end, double *out, int accumulate, int span)
 {
     constexpr int TILE = BLOCK * 4;
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
-    for (int it = 0; it < span; ++it) {
+    for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= end) break;
-        if (lo + 4 <= begin) continue;
-        if (lo >= begin && lo + 4 <= end) {
-            const f32x4 a = ld_stream(reinterpret_cast<const f32x4 *>(acc + lo));
-            acc0 = fma((double)a.x, (double)a.x, acc0);
-            acc1 = fma((double)a.y, (double)a.y, acc1);
-            acc0 = fma((double)a.z, (double)a.z, acc0);
-            acc1 = fma((double)a.w, (double)a.w, acc1);
+        if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
+            f32x4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = ld_stream(reinterpret_cast<const f32x4 *>(acc + lo + (int64_t)u * TILE));
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float a[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
+                add_squares(a, acc0, acc1);
+            }
         } else {
-            const int64_t i0 = lo > begin ? lo : begin;
-            const int64_t i1 = lo + 4 < end ? lo + 4 : end;
-            for (int64_t i = i0; i < i1; ++i) acc0 = fma((double)acc[i], (double)acc[i], acc0);
+            for (int u = 0; u < U; ++u) {
+                const int64_t l = lo + (int64_t)u * TILE;
+                if (l >= begin && l + 4 <= end) {
+                    const f32x4 v = ld_stream(reinterpret_cast<const f32x4 *>(acc + l));
+                    const float a[4] = {v.x, v.y, v.z, v.w};
+                    add_squares(a, acc0, acc1);
+                    continue;
+                }
+                const int64_t i0 = l > begin ? l : begin;
+                const int64_t i1 = l + 4 < end ? l + 4 : end;
+                for (int64_t i = i0; i < i1; ++i) acc0 = fma((double)acc[i], (double)acc[i], acc0);
+            }
         }
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
-    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+    if (threadIdx.x == 0) {
+        if constexpr (ONE) *out = accumulate ? *out + t : t;
+        else out[blockIdx.x] = t;        // the workgroup partials
+    }
 }
 
 // Folding the workgroup partials, in a fixed order (deterministic).  Up to 262144 partials are too
@@ -512,7 +617,7 @@ static hipError_t launch_fold(double *partials, int64_t cap, int nparts, double 
 }
 
 // ---- launchers -----------------------------------------------------------------------------
-static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile = GS_TILE)
+static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
 {
     if (end <= begin) return 0;
     return (end - 1) / tile - begin / tile + 1;
@@ -631,73 +736,155 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
     return launch_spec<1024, 4, 8, false, false>(A, partials, cap, d_out, accumulate, stream);
 }
 
-hipError_t launch_grad_sqnorm(const SqnormArgs &A, size_t workspace_bytes, double *d_out, int accumulate,
-                              hipStream_t stream)
+// The span (tiles per workgroup) that keeps the partials within `cap`: `span` itself, or the next
+// multiple of U that does.  0: not possible.
+static int64_t fit_span(int64_t tiles, int64_t span, int64_t U, int64_t cap)
 {
-    const int64_t cap = partial_capacity(workspace_bytes);
-    const bool stage = A.acc != nullptr;
-    if (stage) {
-        // staged norm, fast shapes: one tile per workgroup, two gradient loads in flight -- single-wave
-        // workgroups up to 8 streams (k = 4: 1.44 ms against 1.47 ms on 805 M elements; level at k = 8),
-        // two waves beyond (k = 16: 4.65 ms against 4.72 ms)
-        const int64_t t64 = tiles_of(A.begin, A.end, (int64_t)GS_WAVE_BLOCK * 4);
-        if (A.k <= 8 && t64 >= 1 && t64 <= cap && t64 <= 0x7fffffff) {
-            const int grid = (int)t64;
-            k_grad_sqnorm<0, true, GS_WAVE_BLOCK, 2><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, 1);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
-        }
-        int64_t t128 = tiles_of(A.begin, A.end, (int64_t)GS_STEP_BLOCK * 4);
-        if (t128 < 1) t128 = 1;
-        if (t128 <= cap && t128 <= 0x7fffffff) {
-            const int grid = (int)t128;
-            k_grad_sqnorm<0, true, GS_STEP_BLOCK, 2><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, 1);
-            hipError_t e = hipGetLastError();
-            if (e != hipSuccess) return e;
-            return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
-        }
-    }
-    const int block = stage ? GS_STAGE_BLOCK : GS_BLOCK;
-    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)block * 4);
+    if ((tiles + span - 1) / span > cap) span = ((tiles + cap - 1) / cap + U - 1) / U * U;
+    return span > 0x7fffffff || (tiles + span - 1) / span > 0x7fffffff ? 0 : span;
+}
+
+template <int K, int U, int BLOCK>
+static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * 4);
     if (tiles < 1) tiles = 1;
-    int64_t span = stage ? 1 : GS_NORM_SPAN;
-    if ((tiles + span - 1) / span > cap) span = (tiles + cap - 1) / cap;
-    if (span > 0x7fffffff) return hipErrorInvalidValue;
+    span = fit_span(tiles, span, U, cap);
+    if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    const int sp = (int)span;
-#define GS_NORM_CASE(KK)                                                                                 \
-    if (stage) k_grad_sqnorm<KK, true, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp);   \
-    else k_grad_sqnorm<KK, false, GS_BLOCK, 0><<<grid, GS_BLOCK, 0, stream>>>(A, sp);                    \
-    break
-    switch (A.k) {
-    case 1: GS_NORM_CASE(1);
-    case 2: GS_NORM_CASE(2);
-    case 4: GS_NORM_CASE(4);
-    case 8: GS_NORM_CASE(8);
-    case 16: GS_NORM_CASE(16);
-    default: GS_NORM_CASE(0);
-    }
-#undef GS_NORM_CASE
+    k_grad_sqnorm<K, U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
 
+// the whole range in one workgroup and one launch
+template <int K, int U>
+static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, hipStream_t stream)
+{
+    A.out = d_out;
+    A.accumulate = accumulate;
+    k_grad_sqnorm<K, U, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(A, U);
+    return hipGetLastError();
+}
+
+// Up to four 4096-element tiles (one, from 5 streams on) a single workgroup has everything in flight at
+// once and no fold has to follow (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).
+// Above that: with up to 4 streams 256 lanes and one group of U tiles up to 4 M elements, 512 lanes and
+// two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %); one stream is best in 256
+// lanes at every size.  From 5 streams on the workgroups grow with the range, so that they are many
+// enough to fill the chip and no more: 256, 512 and 1024 lanes up to 2^20, 2^21 and 2^23 elements (8 M,
+// k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, before (256 lanes, 8 tiles one
+// after another; k = 3, 7 and 32 in batches of 4, 2 and 1 loads) -> now:
+//   100 k  k = 1/3/8/32  3.5/6.3/8.1/38 -> 2.4/2.6/3.3/4.5      12.6 M  8.4/15.8/35.4/151 -> 6.2/14.0/33.0/127
+//   1 M    k = 1/3/8/32  5.8/10.6/8.6/40 -> 2.9/3.4/5.2/11.9    201 M   89/191/474/1932 -> 61/176/466/1882
+//   3.3 M  k = 1/3/8/32  6.5/11.5/11.0/51 -> 4.0/5.4/11.0/37    805 M   347/737/1851/7903 -> 231/713/1848/7849
+static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    const int64_t n = A.end - A.begin;
+    const bool small = n <= GS_NORM_SMALL_MAX;
+    const int64_t run = n < GS_NORM_LONG_MIN ? 2 : 4;
+    const int64_t tiles = tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4);
+    if (tiles <= (A.k <= 4 ? 4 : 1)) {
+        switch (A.k) {
+        case 1: return launch_norm_one<1, 4>(A, d_out, accumulate, stream);
+        case 2: return launch_norm_one<2, 4>(A, d_out, accumulate, stream);
+        case 3: return launch_norm_one<3, 4>(A, d_out, accumulate, stream);
+        case 4: return launch_norm_one<4, 4>(A, d_out, accumulate, stream);
+        }
+        return launch_norm_one<0, 1>(A, d_out, accumulate, stream);
+    }
+    switch (A.k) {
+    case 1: return launch_norm<1, 4, 256>(A, 4, cap, d_out, accumulate, stream);
+    case 2:
+        if (small) return launch_norm<2, 2, 256>(A, 2, cap, d_out, accumulate, stream);
+        return launch_norm<2, 4, 512>(A, 4, cap, d_out, accumulate, stream);
+    case 3:
+        if (small) return launch_norm<3, 2, 256>(A, 2, cap, d_out, accumulate, stream);
+        return launch_norm<3, 2, 512>(A, run, cap, d_out, accumulate, stream);
+    case 4:
+        if (small) return launch_norm<4, 2, 256>(A, 2, cap, d_out, accumulate, stream);
+        return launch_norm<4, 2, 512>(A, run, cap, d_out, accumulate, stream);
+    }
+    if (n <= GS_NORM_256_MAX) return launch_norm<0, 1, 256>(A, 1, cap, d_out, accumulate, stream);
+    if (n <= GS_NORM_512_MAX) return launch_norm<0, 1, 512>(A, 1, cap, d_out, accumulate, stream);
+    if (n <= GS_NORM_1024_MAX) return launch_norm<0, 1, 1024>(A, 2, cap, d_out, accumulate, stream);
+    return launch_norm<0, 1, 512>(A, run, cap, d_out, accumulate, stream);
+}
+
+hipError_t launch_grad_sqnorm(const SqnormArgs &A, size_t workspace_bytes, double *d_out, int accumulate,
+                              hipStream_t stream)
+{
+    const int64_t cap = partial_capacity(workspace_bytes);
+    if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
+    // staged norm, fast shapes: one tile per workgroup, two gradient loads in flight -- single-wave
+    // workgroups up to 8 streams (k = 4: 1.44 ms against 1.47 ms on 805 M elements; level at k = 8),
+    // two waves beyond (k = 16: 4.65 ms against 4.72 ms)
+    const int64_t t64 = tiles_of(A.begin, A.end, (int64_t)GS_WAVE_BLOCK * 4);
+    if (A.k <= 8 && t64 >= 1 && t64 <= cap && t64 <= 0x7fffffff) {
+        const int grid = (int)t64;
+        k_grad_accum_sqnorm<0, GS_WAVE_BLOCK, 2><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, 1);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+    }
+    int64_t t128 = tiles_of(A.begin, A.end, (int64_t)GS_STEP_BLOCK * 4);
+    if (t128 < 1) t128 = 1;
+    if (t128 <= cap && t128 <= 0x7fffffff) {
+        const int grid = (int)t128;
+        k_grad_accum_sqnorm<0, GS_STEP_BLOCK, 2><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, 1);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+    }
+    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)GS_STAGE_BLOCK * 4);
+    if (tiles < 1) tiles = 1;
+    const int64_t span = fit_span(tiles, 1, 1, cap);
+    if (span == 0) return hipErrorInvalidValue;
+    const int grid = (int)((tiles + span - 1) / span);
+    const int sp = (int)span;
+    switch (A.k) {
+    case 1: k_grad_accum_sqnorm<1, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    case 2: k_grad_accum_sqnorm<2, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    case 4: k_grad_accum_sqnorm<4, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    case 8: k_grad_accum_sqnorm<8, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    case 16: k_grad_accum_sqnorm<16, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    default: k_grad_accum_sqnorm<0, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
+    }
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+}
+
+template <int U, int BLOCK>
+static hipError_t launch_acc_norm(const float *acc, int64_t begin, int64_t end, double *partials, int64_t span, int64_t cap,
+                                  double *d_out, int accumulate, hipStream_t stream)
+{
+    const int64_t tiles = tiles_of(begin, end, (int64_t)BLOCK * 4);
+    span = fit_span(tiles, span, U, cap);
+    if (span == 0) return hipErrorInvalidValue;
+    const int grid = (int)((tiles + span - 1) / span);
+    k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, partials, 0, (int)span);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fold(partials, cap, grid, d_out, accumulate, stream);
+}
+
+// As for the gradient norm: one workgroup, then 256 lanes, then 512 with four tiles in flight (50 M
+// elements 34.4 us against 37.1); from 2^27 elements on eight tiles one after another, 256 lanes (805 M:
+// 458 us against 477).
 hipError_t launch_acc_sqnorm(const float *acc, int64_t begin, int64_t end, double *partials, size_t workspace_bytes,
                              double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t cap = partial_capacity(workspace_bytes);
-    int64_t tiles = tiles_of(begin, end, GS_TILE);
-    if (tiles < 1) tiles = 1;
-    int64_t span = GS_NORM_SPAN;
-    if ((tiles + span - 1) / span > cap) span = (tiles + cap - 1) / cap;
-    if (span > 0x7fffffff) return hipErrorInvalidValue;
-    const int grid = (int)((tiles + span - 1) / span);
-    k_acc_sqnorm<GS_BLOCK><<<grid, GS_BLOCK, 0, stream>>>(acc, begin, end, partials, (int)span);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_fold(partials, cap, grid, d_out, accumulate, stream);
+    const int64_t n = end - begin;
+    if (tiles_of(begin, end, GS_ONE_BLOCK * 4) <= 4) {
+        k_acc_sqnorm<4, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(acc, begin, end, d_out, accumulate, 4);
+        return hipGetLastError();
+    }
+    if (n <= GS_NORM_SMALL_MAX) return launch_acc_norm<4, 256>(acc, begin, end, partials, 4, cap, d_out, accumulate, stream);
+    if (n < GS_ACC_NORM_LONG_MIN) return launch_acc_norm<4, 512>(acc, begin, end, partials, 4, cap, d_out, accumulate, stream);
+    return launch_acc_norm<1, 256>(acc, begin, end, partials, 8, cap, d_out, accumulate, stream);
 }
 
 hipError_t launch_accum_add(const AccumAddArgs &A, int first, size_t workspace_bytes, double *d_out, int accumulate,

@@ -77,6 +77,50 @@ def test_speculative_step_at_shape_edges(length, k, big_ws):
     assert abs(float(case.sq.item()) - S) <= max(length * 2.0 ** -53, 1e-13) * S
 
 
+# the norm's lines: one workgroup | many, and the sizes where the workgroups change; each with a range that
+# ends inside a group and one that does not
+NORM_SIZES = [1, 3, 4096, 4097, 16384, 16385, (1 << 20), (1 << 20) + 1, (1 << 21) + 2, (1 << 22) + 1, (1 << 23) + 3]
+
+
+@pytest.mark.parametrize("length", NORM_SIZES)
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 16, 23])
+@pytest.mark.parametrize("begin", [0, 7])
+def test_norms_at_shape_edges(length, k, begin):
+    e = begin + length
+    case = DeviceCase(e + 5, k, seed=length % 83 + k)
+    tol = max(length * 2.0 ** -53, 1e-13)        # the oracle's serial fp64 sum, as above
+    S = O.grad_sqnorm(case.h_g, begin, e)
+    case.sq.fill_(float("nan"))
+    got = case.gpu_sqnorm(begin, e)
+    assert abs(got - S) <= tol * S
+    assert abs(case.gpu_sqnorm(begin, e, accumulate=True) - 2 * got) <= 1e-15 * got
+    acc = torch.full((case.n,), 3.0, device=DEV)
+    gs.gs_grad_accum_sqnorm(case.grads, begin, e, acc, case.sq, case.ws)
+    assert abs(float(case.sq.item()) - S) <= tol * S
+    assert bool((acc[:begin] == 3.0).all()) and bool((acc[e:] == 3.0).all())
+    case.sq.fill_(float("nan"))
+    gs.gs_acc_sqnorm(acc, begin, e, case.sq, case.ws)
+    assert abs(float(case.sq.item()) - S) <= tol * S
+    case.sq.fill_(1.0)
+    gs.gs_acc_sqnorm(acc, begin, begin, case.sq, case.ws)
+    gs.gs_grad_sqnorm(case.grads, begin, begin, case.sq, case.ws, accumulate=True)
+    assert float(case.sq.item()) == 0.0           # an empty range writes 0, or adds nothing
+
+
+@pytest.mark.parametrize("k", [1, 3, 6])
+def test_norms_of_long_runs(k):
+    """From 2^29 gradient elements (2^27 of the fp32 buffer) on a workgroup reads longer runs."""
+    n = (1 << 29) + 1
+    g = [torch.ones(n, dtype=torch.bfloat16, device=DEV)] * k          # one buffer k times: read only
+    sq = torch.zeros(1, dtype=torch.float64, device=DEV)
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes(), dtype=torch.uint8, device=DEV)
+    gs.gs_grad_sqnorm(g, 1, n, sq, ws)
+    assert float(sq.item()) == float(k * k * (n - 1))                   # whole numbers: exact in fp64
+    acc = torch.full(((1 << 27) + 7,), 2.0, device=DEV)
+    gs.gs_acc_sqnorm(acc, 3, acc.numel(), sq, ws)
+    assert float(sq.item()) == 4.0 * (acc.numel() - 3)
+
+
 @pytest.mark.parametrize("k", [2, 7, 8])
 def test_largest_shape_equals_its_pieces(k):
     """From 2^27 elements on (the shallow shape up to 7 streams): bit for bit what the other shapes give

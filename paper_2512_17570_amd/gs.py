@@ -12,6 +12,7 @@ from __future__ import annotations
 
 import ctypes
 import os
+import struct
 from dataclasses import dataclass
 
 _PKG = os.path.dirname(os.path.abspath(__file__))
@@ -63,7 +64,7 @@ class HParams:
 
 _vp = ctypes.c_void_p
 _i64 = ctypes.c_int64
-_pp = ctypes.POINTER(ctypes.c_void_p)
+_pp = ctypes.c_void_p      # a table of addresses, as bytes
 
 _lib.gs_sqnorm_workspace_bytes.argtypes = []
 _lib.gs_sqnorm_workspace_bytes.restype = ctypes.c_size_t
@@ -127,6 +128,11 @@ class GsError(RuntimeError):
         super().__init__(msg)
 
 
+# A step of a small range is a few microseconds on the GPU, and a call's marshalling is what the host adds
+# to it (13 k elements, k = 4 / 16 gradients: 11.3 / 15.7 us per gs_accum_adamw before, of which 3.5 the
+# launch; 7.1 / 9.9 now).  So each tensor is checked and its address taken in one pass, the address table is packed into bytes (ctypes hands their address over; the library copies the table
+# before the call returns), and the current stream is asked for as the raw handle.
+
 def _addr(x) -> int | None:
     if x is None:
         return None
@@ -135,30 +141,53 @@ def _addr(x) -> int | None:
     return x.data_ptr()
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_current_device = getattr(torch._C, "_cuda_getDevice", None)
+_cuda_ready = torch.cuda.is_initialized
+
+
 def _stream(s) -> int | None:
     if s is None:
-        import torch
+        if _raw_stream is not None and _current_device is not None and _cuda_ready():
+            return _raw_stream(_current_device())
         return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
     if isinstance(s, int):
         return s
     return s.cuda_stream
 
 
-def _need(x, end: int, elem_bytes: int, name: str) -> None:
-    """When a tensor (not a raw address) is passed, refuse a range that runs past its end --
-    the C ABI sees plain pointers and cannot know."""
-    if hasattr(x, "numel"):
+def _ptr(x, end: int, elem_bytes: int, name: str) -> int | None:
+    """Address of x.  When a tensor (not a raw address) is passed, refuse a range that runs past its
+    end -- the C ABI sees plain pointers and cannot know."""
+    if isinstance(x, torch.Tensor) or hasattr(x, "numel"):
         if x.element_size() != elem_bytes:
             raise TypeError(f"{name}: expected {elem_bytes}-byte elements, got {x.dtype}")
         if x.numel() < end:
             raise ValueError(f"{name}: holds {x.numel()} elements, range ends at {end}")
         if not x.is_contiguous():
             raise ValueError(f"{name}: tensor must be contiguous")
+        return x.data_ptr()
+    return _addr(x)
 
 
-def _table(grads):
-    addrs = [_addr(g) for g in grads]
-    return (ctypes.c_void_p * max(len(addrs), 1))(*addrs), len(addrs)
+_pack_table = [struct.Struct(f"{n}P").pack for n in range(GS_MAX_K + 1)]
+
+
+def _table(grads, end: int, name: str = "grads"):
+    """(address table, number of buffers) of the gradient buffers, each checked as in _ptr."""
+    if grads is None:
+        return None, 0
+    addrs = []
+    for g in grads:
+        # the same checks as _ptr; its call alone would double the cost per buffer
+        if isinstance(g, torch.Tensor) and g.element_size() == 2 and g.numel() >= end and g.is_contiguous():
+            addrs.append(g.data_ptr())
+        else:
+            addrs.append(_ptr(g, end, 2, f"{name}[{len(addrs)}]") or 0)
+    n = len(addrs)
+    if not 1 <= n <= GS_MAX_K:                 # refused by the library
+        return struct.pack(f"{max(n, 1)}P", *(addrs or (0,))), n
+    return _pack_table[n](*addrs), n
 
 
 def _hp(hp):
@@ -191,9 +220,7 @@ def gs_sqnorm_workspace_bytes_for(range_elems: int) -> int:
 
 def gs_grad_sqnorm(grads, begin: int, end: int, d_sqnorm, d_workspace, workspace_bytes: int | None = None,
                    accumulate: bool = False, stream=None, check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
+    tab, kk = _table(grads, end)
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
     st = _lib.gs_grad_sqnorm(tab, kk if k is None else k, begin, end, _addr(d_sqnorm), int(bool(accumulate)),
@@ -203,9 +230,7 @@ def gs_grad_sqnorm(grads, begin: int, end: int, d_sqnorm, d_workspace, workspace
 
 def gs_grad_sqnorm_noalloc(grads, begin: int, end: int, d_sqnorm, accumulate: bool = False, stream=None,
                            check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
+    tab, kk = _table(grads, end)
     st = _lib.gs_grad_sqnorm_noalloc(tab, kk if k is None else k, begin, end, _addr(d_sqnorm), int(bool(accumulate)),
                                      _stream(stream))
     return _check(st, "gs_grad_sqnorm_noalloc", check)
@@ -213,12 +238,12 @@ def gs_grad_sqnorm_noalloc(grads, begin: int, end: int, d_sqnorm, accumulate: bo
 
 def gs_accum_adamw(p, m, v, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=None, stream=None,
                    check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
-    for x, eb, nm in ((p, 4, "p"), (m, 4, "m"), (v, 4, "v"), (w_bf16, 2, "w_bf16")):
-        _need(x, end, eb, nm)
-    st = _lib.gs_accum_adamw(_addr(p), _addr(m), _addr(v), _addr(w_bf16), tab, kk if k is None else k,
+    tab, kk = _table(grads, end)
+    p = _ptr(p, end, 4, "p")
+    m = _ptr(m, end, 4, "m")
+    v = _ptr(v, end, 4, "v")
+    w_bf16 = _ptr(w_bf16, end, 2, "w_bf16")
+    st = _lib.gs_accum_adamw(p, m, v, w_bf16, tab, kk if k is None else k,
                              begin, end, _hp(hp), _addr(d_sqnorm), _stream(stream))
     return _check(st, "gs_accum_adamw", check)
 
@@ -226,13 +251,11 @@ def gs_accum_adamw(p, m, v, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=No
 def gs_grad_accum_sqnorm(grads, begin: int, end: int, acc_f32, d_sqnorm, d_workspace,
                          workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                          check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
-    _need(acc_f32, end, 4, "acc_f32")
+    tab, kk = _table(grads, end)
+    acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
-    st = _lib.gs_grad_accum_sqnorm(tab, kk if k is None else k, begin, end, _addr(acc_f32), _addr(d_sqnorm),
+    st = _lib.gs_grad_accum_sqnorm(tab, kk if k is None else k, begin, end, acc_f32, _addr(d_sqnorm),
                                    int(bool(accumulate)), _addr(d_workspace), workspace_bytes, _stream(stream))
     return _check(st, "gs_grad_accum_sqnorm", check)
 
@@ -240,44 +263,49 @@ def gs_grad_accum_sqnorm(grads, begin: int, end: int, acc_f32, d_sqnorm, d_works
 def gs_accum_add(acc_f32, grad_bf16, first: bool, begin: int, end: int, d_sqnorm=None, d_workspace=None,
                  workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                  check: bool = True) -> int:
-    _need(acc_f32, end, 4, "acc_f32")
-    _need(grad_bf16, end, 2, "grad_bf16")
+    acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
+    grad_bf16 = _ptr(grad_bf16, end, 2, "grad_bf16")
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
-    st = _lib.gs_accum_add(_addr(acc_f32), _addr(grad_bf16), int(bool(first)), begin, end, _addr(d_sqnorm),
+    st = _lib.gs_accum_add(acc_f32, grad_bf16, int(bool(first)), begin, end, _addr(d_sqnorm),
                            int(bool(accumulate)), _addr(d_workspace), workspace_bytes, _stream(stream))
     return _check(st, "gs_accum_add", check)
 
 
 def gs_acc_sqnorm(acc_f32, begin: int, end: int, d_sqnorm, d_workspace, workspace_bytes: int | None = None,
                   accumulate: bool = False, stream=None, check: bool = True) -> int:
-    _need(acc_f32, end, 4, "acc_f32")
+    acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
-    st = _lib.gs_acc_sqnorm(_addr(acc_f32), begin, end, _addr(d_sqnorm), int(bool(accumulate)), _addr(d_workspace),
+    st = _lib.gs_acc_sqnorm(acc_f32, begin, end, _addr(d_sqnorm), int(bool(accumulate)), _addr(d_workspace),
                             workspace_bytes, _stream(stream))
     return _check(st, "gs_acc_sqnorm", check)
 
 
 def gs_adamw_from_acc(p, m, v, w_bf16, acc_f32, begin: int, end: int, hp, d_sqnorm=None, stream=None,
                       check: bool = True) -> int:
-    for x, eb, nm in ((p, 4, "p"), (m, 4, "m"), (v, 4, "v"), (w_bf16, 2, "w_bf16"), (acc_f32, 4, "acc_f32")):
-        _need(x, end, eb, nm)
-    st = _lib.gs_adamw_from_acc(_addr(p), _addr(m), _addr(v), _addr(w_bf16), _addr(acc_f32), begin, end,
+    p = _ptr(p, end, 4, "p")
+    m = _ptr(m, end, 4, "m")
+    v = _ptr(v, end, 4, "v")
+    w_bf16 = _ptr(w_bf16, end, 2, "w_bf16")
+    acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
+    st = _lib.gs_adamw_from_acc(p, m, v, w_bf16, acc_f32, begin, end,
                                 _hp(hp), _addr(d_sqnorm), _stream(stream))
     return _check(st, "gs_adamw_from_acc", check)
 
 
 def gs_accum_adamw_oop(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=None,
                        stream=None, check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
-    for x, eb, nm in ((p, 4, "p"), (m, 4, "m"), (v, 4, "v"), (p_out, 4, "p_out"), (m_out, 4, "m_out"),
-                      (v_out, 4, "v_out"), (w_bf16, 2, "w_bf16")):
-        _need(x, end, eb, nm)
-    st = _lib.gs_accum_adamw_oop(_addr(p), _addr(m), _addr(v), _addr(p_out), _addr(m_out), _addr(v_out),
-                                 _addr(w_bf16), tab, kk if k is None else k, begin, end, _hp(hp), _addr(d_sqnorm),
+    tab, kk = _table(grads, end)
+    p = _ptr(p, end, 4, "p")
+    m = _ptr(m, end, 4, "m")
+    v = _ptr(v, end, 4, "v")
+    p_out = _ptr(p_out, end, 4, "p_out")
+    m_out = _ptr(m_out, end, 4, "m_out")
+    v_out = _ptr(v_out, end, 4, "v_out")
+    w_bf16 = _ptr(w_bf16, end, 2, "w_bf16")
+    st = _lib.gs_accum_adamw_oop(p, m, v, p_out, m_out, v_out,
+                                 w_bf16, tab, kk if k is None else k, begin, end, _hp(hp), _addr(d_sqnorm),
                                  _stream(stream))
     return _check(st, "gs_accum_adamw_oop", check)
 
@@ -285,16 +313,18 @@ def gs_accum_adamw_oop(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, 
 def gs_accum_adamw_spec(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, end: int, hp, d_sqnorm,
                         d_workspace, workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                         check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
-    for x, eb, nm in ((p, 4, "p"), (m, 4, "m"), (v, 4, "v"), (p_out, 4, "p_out"), (m_out, 4, "m_out"),
-                      (v_out, 4, "v_out"), (w_bf16, 2, "w_bf16")):
-        _need(x, end, eb, nm)
+    tab, kk = _table(grads, end)
+    p = _ptr(p, end, 4, "p")
+    m = _ptr(m, end, 4, "m")
+    v = _ptr(v, end, 4, "v")
+    p_out = _ptr(p_out, end, 4, "p_out")
+    m_out = _ptr(m_out, end, 4, "m_out")
+    v_out = _ptr(v_out, end, 4, "v_out")
+    w_bf16 = _ptr(w_bf16, end, 2, "w_bf16")
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
-    st = _lib.gs_accum_adamw_spec(_addr(p), _addr(m), _addr(v), _addr(p_out), _addr(m_out), _addr(v_out),
-                                  _addr(w_bf16), tab, kk if k is None else k, begin, end, _hp(hp), _addr(d_sqnorm),
+    st = _lib.gs_accum_adamw_spec(p, m, v, p_out, m_out, v_out,
+                                  w_bf16, tab, kk if k is None else k, begin, end, _hp(hp), _addr(d_sqnorm),
                                   int(bool(accumulate)), _addr(d_workspace), workspace_bytes, _stream(stream))
     return _check(st, "gs_accum_adamw_spec", check)
 
@@ -349,12 +379,12 @@ def gs_stream_ctx_sync(ctx, check: bool = True) -> int:
 
 def gs_stream_layer_step(ctx, h_p, h_m, h_v, d_w_bf16, d_grads, n: int, hp, d_sqnorm=None,
                          producer_stream=None, check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(d_grads) if d_grads is not None else (None, 0)
-    for j, g in enumerate(d_grads or ()):
-        _need(g, n, 2, f"d_grads[{j}]")
-    for x, eb, nm in ((h_p, 4, "h_p"), (h_m, 4, "h_m"), (h_v, 4, "h_v"), (d_w_bf16, 2, "d_w_bf16")):
-        _need(x, n, eb, nm)
-    st = _lib.gs_stream_layer_step(ctx, _addr(h_p), _addr(h_m), _addr(h_v), _addr(d_w_bf16), tab,
+    tab, kk = _table(d_grads, n, "d_grads")
+    h_p = _ptr(h_p, n, 4, "h_p")
+    h_m = _ptr(h_m, n, 4, "h_m")
+    h_v = _ptr(h_v, n, 4, "h_v")
+    d_w_bf16 = _ptr(d_w_bf16, n, 2, "d_w_bf16")
+    st = _lib.gs_stream_layer_step(ctx, h_p, h_m, h_v, d_w_bf16, tab,
                                    kk if k is None else k, n, _hp(hp), _addr(d_sqnorm), _stream(producer_stream))
     return _check(st, "gs_stream_layer_step", check)
 
@@ -406,16 +436,15 @@ def gs_tier_layer_step(ctx, h_p, h_m, h_v, n_host: int, fds, offsets, d_w_bf16, 
     ready-made descriptor (or None with check=False to exercise the rejection).  The call queues
     the layer and returns: keep the tensors alive and untouched until gs_tier_ctx_sync, which also
     reports I/O failures."""
-    tab, kk = _table(d_grads) if d_grads is not None else (None, 0)
-    for j, g in enumerate(d_grads or ()):
-        _need(g, n, 2, f"d_grads[{j}]")
-    _need(d_w_bf16, n, 2, "d_w_bf16")
+    tab, kk = _table(d_grads, n, "d_grads")
+    d_w_bf16 = _ptr(d_w_bf16, n, 2, "d_w_bf16")
     if layer is None and fds is not None:
-        for x, nm in ((h_p, "h_p"), (h_m, "h_m"), (h_v, "h_v")):
-            _need(x, n_host, 4, nm)
-        layer = gs_tier_layer(_addr(h_p), _addr(h_m), _addr(h_v), n_host, fds[0], fds[1], fds[2],
+        h_p = _ptr(h_p, n_host, 4, "h_p")
+        h_m = _ptr(h_m, n_host, 4, "h_m")
+        h_v = _ptr(h_v, n_host, 4, "h_v")
+        layer = gs_tier_layer(h_p, h_m, h_v, n_host, fds[0], fds[1], fds[2],
                               offsets[0], offsets[1], offsets[2])
-    st = _lib.gs_tier_layer_step(ctx, ctypes.byref(layer) if layer is not None else None, _addr(d_w_bf16), tab,
+    st = _lib.gs_tier_layer_step(ctx, ctypes.byref(layer) if layer is not None else None, d_w_bf16, tab,
                                  kk if k is None else k, n, _hp(hp), _addr(d_sqnorm), _stream(producer_stream))
     return _check(st, "gs_tier_layer_step", check)
 
@@ -429,12 +458,12 @@ _lib.gs_tier_layer_step_range.restype = ctypes.c_int
 
 def gs_stream_layer_step_range(ctx, h_p, h_m, h_v, d_w_bf16, d_grads, begin: int, end: int, hp, d_sqnorm=None,
                                producer_stream=None, check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(d_grads) if d_grads is not None else (None, 0)
-    for j, g in enumerate(d_grads or ()):
-        _need(g, end, 2, f"d_grads[{j}]")
-    for x, eb, nm in ((h_p, 4, "h_p"), (h_m, 4, "h_m"), (h_v, 4, "h_v"), (d_w_bf16, 2, "d_w_bf16")):
-        _need(x, end, eb, nm)
-    st = _lib.gs_stream_layer_step_range(ctx, _addr(h_p), _addr(h_m), _addr(h_v), _addr(d_w_bf16), tab,
+    tab, kk = _table(d_grads, end, "d_grads")
+    h_p = _ptr(h_p, end, 4, "h_p")
+    h_m = _ptr(h_m, end, 4, "h_m")
+    h_v = _ptr(h_v, end, 4, "h_v")
+    d_w_bf16 = _ptr(d_w_bf16, end, 2, "d_w_bf16")
+    st = _lib.gs_stream_layer_step_range(ctx, h_p, h_m, h_v, d_w_bf16, tab,
                                          kk if k is None else k, begin, end, _hp(hp), _addr(d_sqnorm),
                                          _stream(producer_stream))
     return _check(st, "gs_stream_layer_step_range", check)
@@ -443,15 +472,14 @@ def gs_stream_layer_step_range(ctx, h_p, h_m, h_v, d_w_bf16, d_grads, begin: int
 def gs_tier_layer_step_range(ctx, h_p, h_m, h_v, n_host: int, fds, offsets, d_w_bf16, d_grads, n: int, begin: int,
                              end: int, hp, d_sqnorm=None, producer_stream=None, check: bool = True,
                              k: int | None = None) -> int:
-    tab, kk = _table(d_grads) if d_grads is not None else (None, 0)
-    for j, g in enumerate(d_grads or ()):
-        _need(g, n, 2, f"d_grads[{j}]")
-    _need(d_w_bf16, n, 2, "d_w_bf16")
-    for x, nm in ((h_p, "h_p"), (h_m, "h_m"), (h_v, "h_v")):
-        _need(x, n_host, 4, nm)
-    layer = gs_tier_layer(_addr(h_p), _addr(h_m), _addr(h_v), n_host, fds[0], fds[1], fds[2],
+    tab, kk = _table(d_grads, n, "d_grads")
+    d_w_bf16 = _ptr(d_w_bf16, n, 2, "d_w_bf16")
+    h_p = _ptr(h_p, n_host, 4, "h_p")
+    h_m = _ptr(h_m, n_host, 4, "h_m")
+    h_v = _ptr(h_v, n_host, 4, "h_v")
+    layer = gs_tier_layer(h_p, h_m, h_v, n_host, fds[0], fds[1], fds[2],
                           offsets[0], offsets[1], offsets[2])
-    st = _lib.gs_tier_layer_step_range(ctx, ctypes.byref(layer), _addr(d_w_bf16), tab, kk if k is None else k, n,
+    st = _lib.gs_tier_layer_step_range(ctx, ctypes.byref(layer), d_w_bf16, tab, kk if k is None else k, n,
                                        begin, end, _hp(hp), _addr(d_sqnorm), _stream(producer_stream))
     return _check(st, "gs_tier_layer_step_range", check)
 
@@ -533,12 +561,12 @@ def gs_defer_ctx_sync(ctx, check: bool = True) -> int:
 
 def gs_defer_layer_step(ctx, layer: int, p, m, v, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=None,
                         producer_stream=None, check: bool = True, k: int | None = None) -> int:
-    tab, kk = _table(grads) if grads is not None else (None, 0)
-    for j, g in enumerate(grads or ()):
-        _need(g, end, 2, f"grads[{j}]")
-    for x, eb, nm in ((p, 4, "p"), (m, 4, "m"), (v, 4, "v"), (w_bf16, 2, "w_bf16")):
-        _need(x, end, eb, nm)
-    st = _lib.gs_defer_layer_step(ctx, layer, _addr(p), _addr(m), _addr(v), _addr(w_bf16), tab, kk if k is None else k,
+    tab, kk = _table(grads, end)
+    p = _ptr(p, end, 4, "p")
+    m = _ptr(m, end, 4, "m")
+    v = _ptr(v, end, 4, "v")
+    w_bf16 = _ptr(w_bf16, end, 2, "w_bf16")
+    st = _lib.gs_defer_layer_step(ctx, layer, p, m, v, w_bf16, tab, kk if k is None else k,
                                   begin, end, _hp(hp), _addr(d_sqnorm), _stream(producer_stream))
     return _check(st, "gs_defer_layer_step", check)
 

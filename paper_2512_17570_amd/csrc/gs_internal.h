@@ -7,9 +7,6 @@
 
 #include "gs.h"
 
-#define GS_STEP_BLOCK 128             // threads per workgroup of the staged norm kernel (2 wave64)
-#define GS_WAVE_BLOCK 64              // single-wave workgroups: the fast shapes of the kernels that add and leave a
-                                      // norm partial per workgroup
 // limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
 #define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
 #define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
@@ -17,11 +14,17 @@
 #define GS_SERIAL_MIN (1 << 27)       // elements from which few gradient streams are taken one load at a time
 #define GS_SERIAL_MAX_K 7             // "few gradient streams"
 #define GS_SPEC_SERIAL_MIN 80000000   // GS_SERIAL_MIN of the speculative pass
+#define GS_SPEC_RUN_MAX (1 << 28)     // small workspace, few streams: elements up to which 512-element tiles are run
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels
 #define GS_FINAL_SLICES 128           // workgroups of the first folding stage for large partial counts
 #define GS_FINAL_DIRECT_MAX 8192      // up to this many partials are folded by one workgroup directly
-#define GS_STAGE_BLOCK 1024           // threads per workgroup of the staged norm kernel
+#define GS_PARTIAL_ELEMS 256          // elements per norm partial in the shapes that leave most of them
 #define GS_SQNORM_MAX_BLOCKS 262144   // upper bound on block partials => workspace size (2 MB)
+// limits of the staged norm's and the adding kernel's shapes (launch_staged_norm, launch_accum_add)
+#define GS_STAGED_WIDE_MAX (1 << 22)  // elements up to which a workgroup takes 4096 of them
+#define GS_STAGED_PAIR_MIN (1 << 25)  // elements from which, with 8 streams or more, a lane takes 2 of them
+#define GS_ADD_SMALL_MAX (1 << 22)    // without the norm: elements up to which both loads are in flight together
+#define GS_ADD_WIDE_MAX (1 << 23)     // with the norm: elements up to which a workgroup takes 4096 of them
 // limits of the norm's shapes (launch_grad_norm)
 #define GS_NORM_SMALL_MAX (1 << 22)   // up to 4 streams: elements up to which workgroups are kept small
 #define GS_NORM_256_MAX (1 << 20)     // from 5 streams on: elements up to which they have 256, 512 and 1024 lanes

@@ -143,69 +143,6 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
     }
 }
 
-// k-way accumulation of one 4-element group, j ascending from +0 (Sec. 2.1: micro-batch
-// gradients are accumulated in full precision).  K > 0: compile-time count; K == 0: runtime.
-// DEPTH is how many gradient loads a wave keeps in flight:
-//   0  all of them (compile-time K) or four and two at a time (runtime k) -- what the read-only
-//      norm kernel wants;
-//   1  one: each load is consumed before the next is issued -- the kernels that mix many read
-//      streams with the four write streams of a step do best with shallow memory queues;
-//   2  two at a time -- the optimum measured for the staged norm kernel (k reads + one write).
-__device__ __forceinline__ void add_pair(float (&a)[4], u32x2 g)
-{
-    a[0] += bf16_lo(g.x); a[1] += bf16_hi(g.x);
-    a[2] += bf16_lo(g.y); a[3] += bf16_hi(g.y);
-}
-
-template <int K, int DEPTH>
-__device__ __forceinline__ void accumulate_group(const GradTable &gt, int k, int64_t lo, float (&a)[4])
-{
-#pragma unroll
-    for (int e = 0; e < 4; ++e) a[e] = 0.0f;
-    if constexpr (K > 0 && DEPTH == 0) {
-        u32x2 gv[K];
-#pragma unroll
-        for (int j = 0; j < K; ++j) gv[j] = ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j] + lo));
-#pragma unroll
-        for (int j = 0; j < K; ++j) add_pair(a, gv[j]);
-    } else if constexpr (K > 0) {
-#pragma unroll
-        for (int j = 0; j < K; j += DEPTH) {
-            u32x2 gv[DEPTH];
-#pragma unroll
-            for (int q = 0; q < DEPTH; ++q)
-                if (j + q < K) gv[q] = ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j + q] + lo));
-#pragma unroll
-            for (int q = 0; q < DEPTH; ++q)
-                if (j + q < K) add_pair(a, gv[q]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-    } else {
-        // runtime k; the adds stay in ascending order of j
-        int j = 0;
-        if constexpr (DEPTH == 0) {
-            for (; j + 4 <= k; j += 4) {
-                u32x2 gv[4];
-#pragma unroll
-                for (int q = 0; q < 4; ++q) gv[q] = ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j + q] + lo));
-#pragma unroll
-                for (int q = 0; q < 4; ++q) add_pair(a, gv[q]);
-            }
-        }
-        if constexpr (DEPTH == 0 || DEPTH == 2) {
-#pragma unroll 1
-            for (; j + 2 <= k; j += 2) {
-                u32x2 g0 = ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j] + lo));
-                u32x2 g1 = ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j + 1] + lo));
-                add_pair(a, g0);
-                add_pair(a, g1);
-            }
-        }
-#pragma unroll 1
-        for (; j < k; ++j) add_pair(a, ld_stream(reinterpret_cast<const u32x2 *>(gt.g[j] + lo)));
-    }
-}
-
 // The same sum for the elements [i0,i1) of a group that a range end cuts (the others get 0).  One lane
 // works alone here while the rest of the chip runs dry, so its loads go out several streams at a time: at
 // 16 streams one load after another took longer than all the whole groups of a small range together.
@@ -381,12 +318,14 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *
 }
 
 // ---- squared norm of the accumulated gradient --------------------------------------------
-__device__ __forceinline__ void add_squares(const float (&a)[4], double &acc0, double &acc1)
+template <int EL>
+__device__ __forceinline__ void add_squares(const float (&a)[EL], double &acc0, double &acc1)
 {
-    acc0 = fma((double)a[0], (double)a[0], acc0);
-    acc1 = fma((double)a[1], (double)a[1], acc1);
-    acc0 = fma((double)a[2], (double)a[2], acc0);
-    acc1 = fma((double)a[3], (double)a[3], acc1);
+#pragma unroll
+    for (int e = 0; e < EL; e += 2) {
+        acc0 = fma((double)a[e], (double)a[e], acc0);
+        acc1 = fma((double)a[e + 1], (double)a[e + 1], acc1);
+    }
 }
 
 // Read-only, 2k bytes per element.  Workgroup b reads `span` consecutive tiles starting at tile
@@ -455,31 +394,34 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
 // then reads one fp32 stream instead of re-reading k bf16 streams).  Once a store stream is
 // involved, runs of tiles per workgroup cost bandwidth (stores want in-order, one-tile workgroups),
 // so it uses a span of 1 wherever the partials still fit the workspace.
-template <int K, int BLOCK, int DEPTH>
+template <int BLOCK, int EL, int DEPTH>
 __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int span)
 {
-    constexpr int TILE = BLOCK * 4;
+    typedef typename Group<EL>::F F;
+    constexpr int TILE = BLOCK * EL;
     __shared__ double lds[BLOCK / 64];
-    const int k = (K > 0) ? K : A.k;
-    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
+    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
-        if (lo + 4 <= A.begin) continue;
-        if (lo >= A.begin && lo + 4 <= A.end) {
-            float a[4];
-            accumulate_group<K, DEPTH>(A.gt, k, lo, a);
-            st_stream(reinterpret_cast<f32x4 *>(A.acc + lo), f32x4{a[0], a[1], a[2], a[3]});
-            add_squares(a, acc0, acc1);
+        if (lo + EL <= A.begin) continue;
+        float a[EL];
+        if (lo >= A.begin && lo + EL <= A.end) {
+            accumulate_batches<EL, DEPTH>(A.gt, A.k, lo, a);
+            F sum;
+#pragma unroll
+            for (int e = 0; e < EL; ++e) sum[e] = a[e];
+            st_stream(reinterpret_cast<F *>(A.acc + lo), sum);
         } else {
             const int64_t i0 = lo > A.begin ? lo : A.begin;
-            const int64_t i1 = lo + 4 < A.end ? lo + 4 : A.end;
-            float a[4];
-            accumulate_cut<4>(A.gt, k, lo, i0, i1, a);
-            for (int64_t i = i0; i < i1; ++i) A.acc[i] = a[i - lo];
-            add_squares(a, acc0, acc1);
+            const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
+            accumulate_cut<EL>(A.gt, A.k, lo, i0, i1, a);
+#pragma unroll
+            for (int e = 0; e < EL; ++e)
+                if (lo + e >= i0 && lo + e < i1) A.acc[lo + e] = a[e];
         }
+        add_squares(a, acc0, acc1);
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) A.partials[blockIdx.x] = t;
@@ -490,43 +432,43 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
 // backward adds its gradient into it (Sec. 3.4, Sec. 4.3).  acc = (FIRST ? +0 : acc) + widen(g):
 // 2 + 4 bytes read and 4 written per element (2 + 4 for the first micro-batch).  NORM: the call
 // that adds the last micro-batch also reduces the squared norm of the finished sum.
-template <bool FIRST, bool NORM, int BLOCK>
+template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT>
 __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
 {
-    constexpr int TILE = BLOCK * 4;
+    typedef typename Group<EL>::F F;
+    typedef typename Group<EL>::H H;
+    constexpr int TILE = BLOCK * EL;
     __shared__ double lds[BLOCK / 64];
-    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
+    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
-        if (lo + 4 <= A.begin) continue;
-        if (lo >= A.begin && lo + 4 <= A.end) {
-            const u32x2 g = ld_stream(reinterpret_cast<const u32x2 *>(A.g + lo));
-            f32x4 a = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-            if constexpr (!FIRST) {
-                wait_vm_idle();          // one load at a time per wave: +1-2 % on this 2:1 read/write mix
-                a = ld_stream(reinterpret_cast<const f32x4 *>(A.acc + lo));
-            }
-            a.x += bf16_lo(g.x); a.y += bf16_hi(g.x);
-            a.z += bf16_lo(g.y); a.w += bf16_hi(g.y);
-            st_stream(reinterpret_cast<f32x4 *>(A.acc + lo), a);
-            if constexpr (NORM) {
-                acc0 = fma((double)a.x, (double)a.x, acc0);
-                acc1 = fma((double)a.y, (double)a.y, acc1);
-                acc0 = fma((double)a.z, (double)a.z, acc0);
-                acc1 = fma((double)a.w, (double)a.w, acc1);
-            }
+        if (lo + EL <= A.begin) continue;
+        float a[EL];
+        if (lo >= A.begin && lo + EL <= A.end) {
+            const H g = ld_stream(reinterpret_cast<const H *>(A.g + lo));
+            if constexpr (LWAIT && !FIRST) wait_vm_idle();
+            F old, sum;
+            if constexpr (!FIRST) old = ld_stream(reinterpret_cast<const F *>(A.acc + lo));
+#pragma unroll
+            for (int e = 0; e < EL; ++e) a[e] = FIRST ? 0.0f : old[e];
+            add_bf16(a, g);
+#pragma unroll
+            for (int e = 0; e < EL; ++e) sum[e] = a[e];
+            st_stream(reinterpret_cast<F *>(A.acc + lo), sum);
         } else {
-            const int64_t i0 = lo > A.begin ? lo : A.begin;
-            const int64_t i1 = lo + 4 < A.end ? lo + 4 : A.end;
-            for (int64_t i = i0; i < i1; ++i) {
-                float a = FIRST ? 0.0f : A.acc[i];
-                a += __uint_as_float((uint32_t)A.g[i] << 16);
-                A.acc[i] = a;
-                if constexpr (NORM) acc0 = fma((double)a, (double)a, acc0);
+#pragma unroll
+            for (int e = 0; e < EL; ++e) {
+                a[e] = 0.0f;
+                if (lo + e >= A.begin && lo + e < A.end) {
+                    if constexpr (!FIRST) a[e] = A.acc[lo + e];
+                    a[e] += __uint_as_float((uint32_t)A.g[lo + e] << 16);
+                    A.acc[lo + e] = a[e];
+                }
             }
         }
+        if constexpr (NORM) add_squares(a, acc0, acc1);
     }
     if constexpr (NORM) {
         double t = block_sum<BLOCK>(acc0 + acc1, lds);
@@ -718,8 +660,9 @@ static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, 
 //     against 73.9/100), or 2 from 12 streams on (k = 16: 50 M 465 us against 488; 478 with 4);
 //   * from 80 M elements the step's own choice: shallow up to 7 streams, else 2 elements per lane
 //     (201 M, k = 16: 1.81 ms against 1.83).
-// A workspace too small for a partial per 256 elements takes 512-element tiles, then 4096-element
-// ones in runs (201 M, 2 MB workspace, k = 8 / 16: 1.33/1.93 ms).
+// A workspace too small for a partial per 256 elements takes 512-element tiles, then runs of them (160 M
+// elements, 2 MB workspace, k = 3 / 8 / 16: 0.81/1.08/1.55 ms against 0.82/1.12/1.59 in 4096-element tiles); few
+// streams over 2^28 elements keep the 4096-element tiles (runs of 8 small ones lose 4 % at 805 M, k = 2).
 hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t workspace_bytes, double *d_out,
                                    int accumulate, hipStream_t stream)
 {
@@ -733,6 +676,8 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
         return launch_spec<128, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
     if (tiles_of(A.begin, A.end, 512) <= cap)
         return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+    if (A.k >= 8) return launch_spec<256, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+    if (n < GS_SPEC_RUN_MAX) return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
     return launch_spec<1024, 4, 8, false, false>(A, partials, cap, d_out, accumulate, stream);
 }
 
@@ -812,48 +757,49 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
     return launch_norm<0, 1, 512>(A, run, cap, d_out, accumulate, stream);
 }
 
+template <int BLOCK, int EL, int DEPTH>
+static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
+    if (tiles < 1) tiles = 1;
+    const int64_t span = fit_span(tiles, 1, 1, cap);
+    if (span == 0) return hipErrorInvalidValue;
+    const int grid = (int)((tiles + span - 1) / span);
+    k_grad_accum_sqnorm<BLOCK, EL, DEPTH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+}
+
+// One tile per workgroup wherever the partials fit.  us per launch, before (two gradient loads in
+// flight, 64 lanes up to 8 streams, 128 beyond) -> now, k = 2 / 4 / 8 / 16:
+//   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.1/5.7/6.6/8.7 -> 5.0/5.1/5.6/6.4
+//   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4
+//   >= 2^25, from 8 streams on 2 elements per lane, 256 lanes, four in flight: 201 M  639/1159 -> 629/1136
+//   else the shape as before (12.6 M  24.1/29.4/44.8/76.3; 2 elements per lane lose 3-40 % there)
+static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    const int64_t n = A.end - A.begin;
+    if (n <= GS_LATENCY_MAX) {
+        if (A.k < 8) return launch_staged<128, 4, 4>(A, cap, d_out, accumulate, stream);
+        return launch_staged<64, 4, 8>(A, cap, d_out, accumulate, stream);
+    }
+    if (n <= GS_STAGED_WIDE_MAX) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
+    if (tiles_of(A.begin, A.end, 512) > cap) {
+        if (A.k < 8) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
+        return launch_staged<1024, 4, 8>(A, cap, d_out, accumulate, stream);
+    }
+    if (A.k >= 8 && n >= GS_STAGED_PAIR_MIN) return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);
+    if (A.k <= 8 && tiles_of(A.begin, A.end, 256) <= cap) return launch_staged<64, 4, 2>(A, cap, d_out, accumulate, stream);
+    return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);
+}
+
 hipError_t launch_grad_sqnorm(const SqnormArgs &A, size_t workspace_bytes, double *d_out, int accumulate,
                               hipStream_t stream)
 {
     const int64_t cap = partial_capacity(workspace_bytes);
     if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
-    // staged norm, fast shapes: one tile per workgroup, two gradient loads in flight -- single-wave
-    // workgroups up to 8 streams (k = 4: 1.44 ms against 1.47 ms on 805 M elements; level at k = 8),
-    // two waves beyond (k = 16: 4.65 ms against 4.72 ms)
-    const int64_t t64 = tiles_of(A.begin, A.end, (int64_t)GS_WAVE_BLOCK * 4);
-    if (A.k <= 8 && t64 >= 1 && t64 <= cap && t64 <= 0x7fffffff) {
-        const int grid = (int)t64;
-        k_grad_accum_sqnorm<0, GS_WAVE_BLOCK, 2><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
-    }
-    int64_t t128 = tiles_of(A.begin, A.end, (int64_t)GS_STEP_BLOCK * 4);
-    if (t128 < 1) t128 = 1;
-    if (t128 <= cap && t128 <= 0x7fffffff) {
-        const int grid = (int)t128;
-        k_grad_accum_sqnorm<0, GS_STEP_BLOCK, 2><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, 1);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-        return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
-    }
-    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)GS_STAGE_BLOCK * 4);
-    if (tiles < 1) tiles = 1;
-    const int64_t span = fit_span(tiles, 1, 1, cap);
-    if (span == 0) return hipErrorInvalidValue;
-    const int grid = (int)((tiles + span - 1) / span);
-    const int sp = (int)span;
-    switch (A.k) {
-    case 1: k_grad_accum_sqnorm<1, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    case 2: k_grad_accum_sqnorm<2, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    case 4: k_grad_accum_sqnorm<4, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    case 8: k_grad_accum_sqnorm<8, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    case 16: k_grad_accum_sqnorm<16, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    default: k_grad_accum_sqnorm<0, GS_STAGE_BLOCK, 0><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp); break;
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+    return launch_staged_norm(A, cap, d_out, accumulate, stream);
 }
 
 template <int U, int BLOCK>
@@ -887,46 +833,43 @@ hipError_t launch_acc_sqnorm(const float *acc, int64_t begin, int64_t end, doubl
     return launch_acc_norm<1, 256>(acc, begin, end, partials, 8, cap, d_out, accumulate, stream);
 }
 
+template <bool NORM, int BLOCK, int EL, bool LWAIT>
+static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
+    if (tiles < 1) tiles = 1;
+    const int64_t span = NORM ? fit_span(tiles, 1, 1, cap) : 1;
+    const int64_t grid = span == 0 ? 0 : (tiles + span - 1) / span;
+    if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
+    if (first) k_accum_add<true, NORM, BLOCK, EL, LWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, (int)span);
+    else k_accum_add<false, NORM, BLOCK, EL, LWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, (int)span);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || !NORM) return e;
+    return launch_fold(A.partials, cap, (int)grid, d_out, accumulate, stream);
+}
+
+// us per launch, before (64 lanes, the buffer's load after the gradient's) -> now:
+//   first micro-batch, <= 2^22: 256 lanes               1 M 3.2 -> 2.6, 2 M 4.4 -> 3.6; level with 64 above
+//   later ones, <= 2^22: both loads in flight           1 M 3.7 -> 3.2, 2 M 5.2 -> 4.9; from 200 M on waiting
+//                                                       is 0.5 % ahead, level in between
+//   with the norm: both loads in flight; 256 lanes up to 2^19, 1024 up to 2^23 (fewer partials), then 64:
+//                                                       2 M 9.7 -> 7.5, 12.6 M 26.2 -> 25.1, 201 M 320 -> 306
+//   with a workspace too small for a partial per 256 elements, per 1024 or 4096.
 hipError_t launch_accum_add(const AccumAddArgs &A, int first, size_t workspace_bytes, double *d_out, int accumulate,
                             hipStream_t stream)
 {
+    const int64_t n = A.end - A.begin;
     if (!d_out) {
-        // no partials to leave behind: single-wave workgroups over 256-element tiles measured best
-        // (1.17 ms against 1.23 ms with two waves per workgroup, 805 M elements)
-        const int64_t t64 = tiles_of(A.begin, A.end, 64 * 4);
-        if (t64 > 0x7fffffff) return hipErrorInvalidValue;
-        const int grid = (int)(t64 < 1 ? 1 : t64);
-        if (first) k_accum_add<true, false, 64><<<grid, 64, 0, stream>>>(A, 1);
-        else k_accum_add<false, false, 64><<<grid, 64, 0, stream>>>(A, 1);
-        return hipGetLastError();
+        if (n > GS_ADD_SMALL_MAX) return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
+        if (first) return launch_add<false, 256, 4, false>(A, first, 0, nullptr, 0, stream);
+        return launch_add<false, 64, 4, false>(A, first, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
-    int grid;
-    const int64_t tiles64 = tiles_of(A.begin, A.end, (int64_t)GS_WAVE_BLOCK * 4);
-    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)GS_STEP_BLOCK * 4);
-    if (tiles64 >= 1 && tiles64 <= cap && tiles64 <= 0x7fffffff) {
-        // single-wave workgroups here too: 1.24 ms against 1.29 ms with two waves (805 M elements)
-        grid = (int)tiles64;
-        if (first) k_accum_add<true, true, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, 1);
-        else k_accum_add<false, true, GS_WAVE_BLOCK><<<grid, GS_WAVE_BLOCK, 0, stream>>>(A, 1);
-    } else if (tiles >= 1 && tiles <= cap && tiles <= 0x7fffffff) {
-        grid = (int)tiles;
-        if (first) k_accum_add<true, true, GS_STEP_BLOCK><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, 1);
-        else k_accum_add<false, true, GS_STEP_BLOCK><<<grid, GS_STEP_BLOCK, 0, stream>>>(A, 1);
-    } else {
-        tiles = tiles_of(A.begin, A.end, (int64_t)GS_STAGE_BLOCK * 4);
-        if (tiles < 1) tiles = 1;
-        int64_t span = 1;
-        if (tiles > cap) span = (tiles + cap - 1) / cap;
-        if (span > 0x7fffffff) return hipErrorInvalidValue;
-        grid = (int)((tiles + span - 1) / span);
-        const int sp = (int)span;
-        if (first) k_accum_add<true, true, GS_STAGE_BLOCK><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp);
-        else k_accum_add<false, true, GS_STAGE_BLOCK><<<grid, GS_STAGE_BLOCK, 0, stream>>>(A, sp);
-    }
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+    if (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 256) <= cap)
+        return launch_add<true, 64, 4, false>(A, first, cap, d_out, accumulate, stream);
+    if (n <= GS_LATENCY_MAX || (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 1024) <= cap))
+        return launch_add<true, 256, 4, false>(A, first, cap, d_out, accumulate, stream);
+    return launch_add<true, 1024, 4, false>(A, first, cap, d_out, accumulate, stream);
 }
 
 }  // namespace gs

@@ -107,6 +107,33 @@ def test_norms_at_shape_edges(length, k, begin):
     assert float(case.sq.item()) == 0.0           # an empty range writes 0, or adds nothing
 
 
+# the adding and the staged kernels' lines (2^19, 2^22, 2^23, 2^25), with a workspace for every partial and
+# with the smallest one
+@pytest.mark.parametrize("length,k", [(1, 3), (LATENCY, 8), (LATENCY + 1, 5), ((1 << 22) + 2, 9), ((1 << 22) + 3, 2),
+                                      ((1 << 23) + 1, 4), ((1 << 25) + 5, 8)])
+@pytest.mark.parametrize("big_ws", [False, True])
+def test_staged_and_adding_kernels_at_shape_edges(length, k, big_ws):
+    begin, e = 3, 3 + length
+    case = DeviceCase(e + 2, k, seed=length % 79 + k, keep_host=False)
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(length), dtype=torch.uint8, device=DEV) if big_ws else case.ws
+    want = torch.zeros(e - begin, dtype=torch.float32, device=DEV)
+    for g in case.grads:
+        want += g[begin:e].float()                # fp32, in order: the exact same sum
+    S = float((want.double() ** 2).sum())
+    for staged in (True, False):
+        acc = torch.full((case.n,), 5.0, device=DEV)
+        case.sq.fill_(float("nan"))
+        if staged:
+            gs.gs_grad_accum_sqnorm(case.grads, begin, e, acc, case.sq, ws)
+        else:
+            for j, g in enumerate(case.grads):
+                last = j == k - 1
+                gs.gs_accum_add(acc, g, j == 0, begin, e, case.sq if last else None, ws if last else None)
+        assert torch.equal(acc[begin:e], want)
+        assert bool((acc[:begin] == 5.0).all()) and bool((acc[e:] == 5.0).all())
+        assert abs(float(case.sq.item()) - S) <= 1e-12 * S       # two fp64 trees over exact squares
+
+
 @pytest.mark.parametrize("k", [1, 3, 6])
 def test_norms_of_long_runs(k):
     """From 2^29 gradient elements (2^27 of the fp32 buffer) on a workgroup reads longer runs."""

@@ -15,6 +15,7 @@
 #define GS_SERIAL_MAX_K 7             // "few gradient streams"
 #define GS_SPEC_SERIAL_MIN 80000000   // GS_SERIAL_MIN of the speculative pass
 #define GS_SPEC_RUN_MAX (1 << 28)     // small workspace, few streams: elements up to which 512-element tiles are run
+#define GS_KEEP_BYTES ((int64_t)256 << 20)  // of a re-read stream: left in the memory-side cache (keep_from)
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels
 #define GS_FINAL_SLICES 128           // workgroups of the first folding stage for large partial counts
 #define GS_FINAL_DIRECT_MAX 8192      // up to this many partials are folded by one workgroup directly
@@ -64,6 +65,7 @@ struct SqnormArgs {
     int64_t begin, end;
     double *partials;
     float *acc;         // non-null: also write the fp32 gradient sum here
+    int64_t keep_from;  // elements from here on are left in the memory-side cache
     double *out;        // norm in a single workgroup: the result, added to if accumulate is set
     int accumulate;
 };
@@ -73,6 +75,7 @@ struct AccumAddArgs {
     const uint16_t *g;
     int64_t begin, end;
     double *partials;   // used only when a norm is asked for
+    int64_t keep_from;  // elements of acc from here on are left in the memory-side cache
 };
 
 hipError_t launch_accum_adamw(const StepArgs &A, hipStream_t stream);

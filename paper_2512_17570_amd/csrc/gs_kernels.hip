@@ -26,6 +26,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "gs_internal.h"
 
 #pragma clang fp contract(off)
@@ -42,15 +44,27 @@ template <> struct Group<2> { typedef f32x2 F; typedef uint32_t H; };
 template <> struct Group<4> { typedef f32x4 F; typedef u32x2 H; };
 
 // ---- memory access helpers: streams are touched exactly once => non-temporal ------------
-template <typename T>
+// KEEP: without the hint, which leaves the line in the memory-side cache.
+template <bool KEEP = false, typename T>
 __device__ __forceinline__ T ld_stream(const T *p)
 {
-    return __builtin_nontemporal_load(p);
+    if constexpr (KEEP) return *p;
+    else return __builtin_nontemporal_load(p);
 }
-template <typename T>
+template <bool KEEP = false, typename T>
 __device__ __forceinline__ void st_stream(T *p, T v)
 {
-    __builtin_nontemporal_store(v, p);
+    if constexpr (KEEP) *p = v;
+    else __builtin_nontemporal_store(v, p);
+}
+
+// body(true_type) in a workgroup whose elements are to be kept, else body(false_type): the choice is
+// made once for the whole workgroup, around its loop.
+template <typename F>
+__device__ __forceinline__ void with_keep(bool keep, F body)
+{
+    if (keep) body(std::true_type{});
+    else body(std::false_type{});
 }
 
 // s_waitcnt vmcnt(0) (expcnt and lgkmcnt left at their maxima), pinned in place
@@ -116,7 +130,7 @@ __device__ __forceinline__ void add_bf16(float (&a)[2], uint32_t g)
     a[0] += bf16_lo(g); a[1] += bf16_hi(g);
 }
 
-template <int EL, int DEPTH>
+template <int EL, int DEPTH, bool KEEP = false>
 __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, int64_t lo, float (&a)[EL])
 {
     typedef typename Group<EL>::H H;
@@ -127,7 +141,7 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
     for (; j + DEPTH <= k; j += DEPTH) {
         H g[DEPTH];
 #pragma unroll
-        for (int q = 0; q < DEPTH; ++q) g[q] = ld_stream(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+        for (int q = 0; q < DEPTH; ++q) g[q] = ld_stream<KEEP>(reinterpret_cast<const H *>(gt.g[j + q] + lo));
 #pragma unroll
         for (int q = 0; q < DEPTH; ++q) add_bf16(a, g[q]);
     }
@@ -136,7 +150,7 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
         H g[DEPTH];
 #pragma unroll
         for (int q = 0; q < DEPTH - 1; ++q)
-            if (q < rest) g[q] = ld_stream(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+            if (q < rest) g[q] = ld_stream<KEEP>(reinterpret_cast<const H *>(gt.g[j + q] + lo));
 #pragma unroll
         for (int q = 0; q < DEPTH - 1; ++q)
             if (q < rest) add_bf16(a, g[q]);
@@ -340,6 +354,8 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
+    with_keep(first - (int64_t)threadIdx.x * 4 >= A.keep_from, [&](auto keep) {
+    constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
@@ -350,7 +366,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int j = 0; j < K; ++j)
-                        g[u][j] = ld_stream(reinterpret_cast<const u32x2 *>(A.gt.g[j] + lo + (int64_t)u * TILE));
+                        g[u][j] = ld_stream<KEEP>(reinterpret_cast<const u32x2 *>(A.gt.g[j] + lo + (int64_t)u * TILE));
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -361,7 +377,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
             } else {
                 static_assert(K > 0 || U == 1, "tiles are grouped for a compile-time K only");
                 float a[4];
-                accumulate_batches<4, 16>(A.gt, A.k, lo, a);
+                accumulate_batches<4, 16, KEEP>(A.gt, A.k, lo, a);
                 add_squares(a, acc0, acc1);
             }
         } else {
@@ -370,7 +386,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
                 const int64_t l = lo + (int64_t)u * TILE;
                 if (l >= A.begin && l + 4 <= A.end) {
                     float a[4];
-                    accumulate_batches<4, K == 0 ? 16 : K>(A.gt, A.k, l, a);
+                    accumulate_batches<4, K == 0 ? 16 : K, KEEP>(A.gt, A.k, l, a);
                     add_squares(a, acc0, acc1);
                     continue;
                 }
@@ -383,6 +399,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
             }
         }
     }
+    });
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) {
         if constexpr (ONE) *A.out = A.accumulate ? *A.out + t : t;
@@ -402,6 +419,8 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
+    with_keep(first - (int64_t)threadIdx.x * EL >= A.keep_from, [&](auto keep) {
+    constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
@@ -412,7 +431,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
             F sum;
 #pragma unroll
             for (int e = 0; e < EL; ++e) sum[e] = a[e];
-            st_stream(reinterpret_cast<F *>(A.acc + lo), sum);
+            st_stream<KEEP>(reinterpret_cast<F *>(A.acc + lo), sum);
         } else {
             const int64_t i0 = lo > A.begin ? lo : A.begin;
             const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
@@ -423,6 +442,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
         }
         add_squares(a, acc0, acc1);
     }
+    });
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) A.partials[blockIdx.x] = t;
 }
@@ -441,6 +461,8 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
+    with_keep(first - (int64_t)threadIdx.x * EL >= A.keep_from, [&](auto keep) {
+    constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
@@ -450,13 +472,13 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
             const H g = ld_stream(reinterpret_cast<const H *>(A.g + lo));
             if constexpr (LWAIT && !FIRST) wait_vm_idle();
             F old, sum;
-            if constexpr (!FIRST) old = ld_stream(reinterpret_cast<const F *>(A.acc + lo));
+            if constexpr (!FIRST) old = ld_stream<KEEP>(reinterpret_cast<const F *>(A.acc + lo));
 #pragma unroll
             for (int e = 0; e < EL; ++e) a[e] = FIRST ? 0.0f : old[e];
             add_bf16(a, g);
 #pragma unroll
             for (int e = 0; e < EL; ++e) sum[e] = a[e];
-            st_stream(reinterpret_cast<F *>(A.acc + lo), sum);
+            st_stream<KEEP>(reinterpret_cast<F *>(A.acc + lo), sum);
         } else {
 #pragma unroll
             for (int e = 0; e < EL; ++e) {
@@ -470,6 +492,7 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
         }
         if constexpr (NORM) add_squares(a, acc0, acc1);
     }
+    });
     if constexpr (NORM) {
         double t = block_sum<BLOCK>(acc0 + acc1, lds);
         if (threadIdx.x == 0) A.partials[blockIdx.x] = t;
@@ -480,19 +503,21 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
 // back from a reduction across devices): 4 bytes read per element, the read-only shape of the
 // gradient norm -- U tiles of a short contiguous run in flight together.
 template <int U, int BLOCK, bool ONE>
-__global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t begin, int64_t end, double *out, int accumulate, int span)
+__global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t begin, int64_t end, int64_t keep_from, double *out, int accumulate, int span)
 {
     constexpr int TILE = BLOCK * 4;
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
+    with_keep(first - (int64_t)threadIdx.x * 4 >= keep_from, [&](auto keep) {
+    constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= end) break;
         if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
             f32x4 v[U];
 #pragma unroll
-            for (int u = 0; u < U; ++u) v[u] = ld_stream(reinterpret_cast<const f32x4 *>(acc + lo + (int64_t)u * TILE));
+            for (int u = 0; u < U; ++u) v[u] = ld_stream<KEEP>(reinterpret_cast<const f32x4 *>(acc + lo + (int64_t)u * TILE));
 #pragma unroll
             for (int u = 0; u < U; ++u) {
                 const float a[4] = {v[u].x, v[u].y, v[u].z, v[u].w};
@@ -502,7 +527,7 @@ __global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t 
             for (int u = 0; u < U; ++u) {
                 const int64_t l = lo + (int64_t)u * TILE;
                 if (l >= begin && l + 4 <= end) {
-                    const f32x4 v = ld_stream(reinterpret_cast<const f32x4 *>(acc + l));
+                    const f32x4 v = ld_stream<KEEP>(reinterpret_cast<const f32x4 *>(acc + l));
                     const float a[4] = {v.x, v.y, v.z, v.w};
                     add_squares(a, acc0, acc1);
                     continue;
@@ -513,6 +538,7 @@ __global__ __launch_bounds__(BLOCK) void k_acc_sqnorm(const float *acc, int64_t 
             }
         }
     }
+    });
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) {
         if constexpr (ONE) *out = accumulate ? *out + t : t;
@@ -681,6 +707,22 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
     return launch_spec<1024, 4, 8, false, false>(A, partials, cap, d_out, accumulate, stream);
 }
 
+// Where a pass leaves its lines in the 256 MB memory-side cache.  A step reads again what the norm has
+// just read (the gradients, or their fp32 sum), and the adding kernel what it wrote a micro-batch ago.
+// Accesses with the non-temporal hint hit lines that are in that cache but put none there, so if only the
+// last 256 MB of the re-read stream are accessed without it, they stay until the next pass.  norm + step,
+// us, with the hint everywhere -> now: 3.3 M k=3 32.8 -> 31.9, 12.6 M k=4 93.7 -> 89.2, 50 M k=8 457 -> 444,
+// 805 M k=16 11.23 -> 11.13 ms; fp32 norm + step 50 M 276 -> 264, 201 M 1058 -> 1042; adding a micro-batch
+// 50 M 79.0 -> 74.5.  192 and 320 MB gain less (201 M: 1749 and 1747 us against 1745).
+//   * Up to 2^21 elements the lines are there anyway, and plain accesses cost 2-3 %.
+//   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
+//     would push these out again.
+static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate)
+{
+    if (accumulate || end - begin <= GS_RESIDENT_MAX) return end;
+    return end - GS_KEEP_BYTES / bytes_per_elem;
+}
+
 // The span (tiles per workgroup) that keeps the partials within `cap`: `span` itself, or the next
 // multiple of U that does.  0: not possible.
 static int64_t fit_span(int64_t tiles, int64_t span, int64_t U, int64_t cap)
@@ -794,10 +836,12 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
     return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);
 }
 
-hipError_t launch_grad_sqnorm(const SqnormArgs &A, size_t workspace_bytes, double *d_out, int accumulate,
+hipError_t launch_grad_sqnorm(const SqnormArgs &args, size_t workspace_bytes, double *d_out, int accumulate,
                               hipStream_t stream)
 {
     const int64_t cap = partial_capacity(workspace_bytes);
+    SqnormArgs A = args;
+    A.keep_from = keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate);
     if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
     return launch_staged_norm(A, cap, d_out, accumulate, stream);
 }
@@ -810,7 +854,7 @@ static hipError_t launch_acc_norm(const float *acc, int64_t begin, int64_t end, 
     span = fit_span(tiles, span, U, cap);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, partials, 0, (int)span);
+    k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, keep_from(begin, end, 4, accumulate), partials, 0, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(partials, cap, grid, d_out, accumulate, stream);
@@ -825,7 +869,7 @@ hipError_t launch_acc_sqnorm(const float *acc, int64_t begin, int64_t end, doubl
     const int64_t cap = partial_capacity(workspace_bytes);
     const int64_t n = end - begin;
     if (tiles_of(begin, end, GS_ONE_BLOCK * 4) <= 4) {
-        k_acc_sqnorm<4, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(acc, begin, end, d_out, accumulate, 4);
+        k_acc_sqnorm<4, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(acc, begin, end, end, d_out, accumulate, 4);
         return hipGetLastError();
     }
     if (n <= GS_NORM_SMALL_MAX) return launch_acc_norm<4, 256>(acc, begin, end, partials, 4, cap, d_out, accumulate, stream);
@@ -855,9 +899,11 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
 //   with the norm: both loads in flight; 256 lanes up to 2^19, 1024 up to 2^23 (fewer partials), then 64:
 //                                                       2 M 9.7 -> 7.5, 12.6 M 26.2 -> 25.1, 201 M 320 -> 306
 //   with a workspace too small for a partial per 256 elements, per 1024 or 4096.
-hipError_t launch_accum_add(const AccumAddArgs &A, int first, size_t workspace_bytes, double *d_out, int accumulate,
+hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspace_bytes, double *d_out, int accumulate,
                             hipStream_t stream)
 {
+    AccumAddArgs A = args;
+    A.keep_from = keep_from(A.begin, A.end, 4, 0);
     const int64_t n = A.end - A.begin;
     if (!d_out) {
         if (n > GS_ADD_SMALL_MAX) return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
@@ -865,6 +911,8 @@ hipError_t launch_accum_add(const AccumAddArgs &A, int first, size_t workspace_b
         return launch_add<false, 64, 4, false>(A, first, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
+    // 1024 lanes and plain stores: the fold waits for the write-back (3.3 M elements: 16.6 us against 13.3)
+    if (accumulate || n <= GS_ADD_WIDE_MAX) A.keep_from = A.end;
     if (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 256) <= cap)
         return launch_add<true, 64, 4, false>(A, first, cap, d_out, accumulate, stream);
     if (n <= GS_LATENCY_MAX || (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 1024) <= cap))

@@ -57,6 +57,7 @@ struct StepArgs {
     float max_norm;
     const double *d_sqnorm;
     const float *acc;   // non-null: staged fp32 gradient sum replaces the k bf16 streams
+    bool over_link;     // the states are host memory, reached over PCIe
 };
 
 struct SqnormArgs {

@@ -618,9 +618,14 @@ enum Shape {
     SHAPE_STREAM      // 2 elements per lane, stores one at a time
 };
 
+//   States in host memory take LATENCY at every size: the link is the bound, and a wave that waits between
+//             its accesses leaves it idle (16 CUs, 12.6 M elements, k = 2 / 8 / 16: 3.23/3.19/3.23 ms against
+//             3.26/3.37/3.35 in the STREAM shape and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
+//             25.5 ms against 26.4 and 27.3).
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
-static Shape step_shape(int64_t elems, int k)
+static Shape step_shape(int64_t elems, int k, bool over_link)
 {
+    if (over_link) return SHAPE_LATENCY;
     if (elems <= GS_LATENCY_MAX) return SHAPE_LATENCY;
     if (elems <= GS_RESIDENT_MAX)
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
@@ -640,7 +645,7 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
 template <bool STAGED>
 static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
 {
-    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k)) {
+    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link)) {
     case SHAPE_LATENCY:
         if (A.k <= 8) return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
         return launch_step<64, 2, STAGED, 16, false, false>(A, stream);

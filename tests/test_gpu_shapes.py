@@ -57,6 +57,32 @@ def test_step_and_staged_step_at_shape_edges(length, k, begin):
         assert torch.equal(a, b)                 # same sum, same update: same bits
 
 
+@pytest.mark.parametrize("k", [1, 9, 32])
+@pytest.mark.parametrize("staged", [False, True])
+def test_every_cut_of_short_ranges(k, staged):
+    """Begins and ends at every offset within a group, with and without whole groups between them: the
+    elements that a range end cuts off a group are stepped on their own."""
+    n = 160
+    case = DeviceCase(n, k, seed=k)
+    case.sq.fill_(4.0)
+    c = O.clip_coef(4.0, HP.max_grad_norm)
+    full = case.oracle_step(HP, c)
+    acc = torch.zeros(n, dtype=torch.float32, device=DEV)
+    for j, g in enumerate(case.grads):
+        gs.gs_accum_add(acc, g, j == 0, 0, n)
+    for b in list(range(0, 9)) + [126, 127, 128, 129]:
+        for e in [b + 1, b + 2, b + 3, b + 5, b + 8, 130, 133, n - 1, n]:
+            if e <= b or e > n:
+                continue
+            got = case.clone_states()
+            if staged:
+                gs.gs_adamw_from_acc(*got, acc, b, e, HP, case.sq)
+            else:
+                gs.gs_accum_adamw(*got, case.grads, b, e, HP, case.sq)
+            check(got, full, b, e, f"[{b},{e})")
+            untouched(got, (case.p, case.m, case.v, case.w), b, e)
+
+
 @pytest.mark.parametrize("length,k", EDGES + [(RESIDENT, 2), (FEW, 16), (FEW + 1, 12)])
 @pytest.mark.parametrize("big_ws", [False, True])
 def test_speculative_step_at_shape_edges(length, k, big_ws):

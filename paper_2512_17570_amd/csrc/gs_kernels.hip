@@ -643,20 +643,43 @@ enum Shape {
     SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
     SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
     SHAPE_FEW,        // 2 elements per lane, stores back to back
-    SHAPE_STREAM      // 2 elements per lane, stores one at a time
+    SHAPE_STREAM,     // 2 elements per lane, stores one at a time
+    SHAPE_BUDGET      // 4 elements per lane, two gradient loads in flight, stores one at a time
 };
 
+// Whether `stream` may use only some of the device's CUs.  The runtime looks the mask up in the stream's own
+// host-side record; a stream it cannot tell about counts as unconfined (only the shape depends on this).
+static bool on_cu_budget(hipStream_t stream)
+{
+    if (!stream) return false;
+    uint32_t mask[64] = {0};
+    int dev = 0, cus = 0, in_mask = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipExtStreamGetCUMask(stream, 64, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    for (uint32_t word : mask) in_mask += __builtin_popcount(word);
+    return in_mask > 0 && in_mask < cus;
+}
+
+//   A stream confined to some of the CUs (any size over 2^21) takes BUDGET: there the bytes each CU keeps in
+//             flight are the bound, and 4 elements per lane hold twice as many (k = 2 / 8, 100 M elements:
+//             16 CUs 3.39/4.97 ms against 4.71/5.95 in the STREAM shape and 4.11/5.83 one load at a time,
+//             128 CUs 0.60/0.84 against 0.74/0.95 and 0.67/0.91).
 //   States in host memory take LATENCY at every size: the link is the bound, and a wave that waits between
 //             its accesses leaves it idle (16 CUs, 12.6 M elements, k = 2 / 8 / 16: 3.23/3.19/3.23 ms against
 //             3.26/3.37/3.35 in the STREAM shape and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
 //             25.5 ms against 26.4 and 27.3).
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
-static Shape step_shape(int64_t elems, int k, bool over_link)
+static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream)
 {
     if (over_link) return SHAPE_LATENCY;
     if (elems <= GS_LATENCY_MAX) return SHAPE_LATENCY;
     if (elems <= GS_RESIDENT_MAX)
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
+    if (on_cu_budget(stream)) return SHAPE_BUDGET;
     if (elems <= GS_FEW_MAX) return SHAPE_FEW;
     return elems >= GS_SERIAL_MIN && k > 0 && k <= GS_SERIAL_MAX_K ? SHAPE_SERIAL : SHAPE_STREAM;
 }
@@ -675,13 +698,14 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
 template <bool STAGED>
 static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
 {
-    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link)) {
+    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream)) {
     case SHAPE_LATENCY:
         if (A.k <= 8) return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
         return launch_step<64, 2, STAGED, 16, false, false>(A, stream);
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_FEW: return launch_step<128, 2, STAGED, 4, false, false>(A, stream);
+    case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);
     case SHAPE_STREAM: break;
     }
     return launch_step<128, 2, STAGED, 4, false, true>(A, stream);
@@ -730,6 +754,8 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
     const int64_t cap = partial_capacity(workspace_bytes);
     const int64_t n = A.end - A.begin;
     const bool fits256 = tiles_of(A.begin, A.end, 256) <= cap;
+    if (fits256 && n > GS_RESIDENT_MAX && on_cu_budget(stream))
+        return launch_spec<64, 4, 2, false, true>(A, partials, cap, d_out, accumulate, stream);
     if (fits256 && (A.k <= 2 ? n > GS_LATENCY_MAX : A.k <= GS_SERIAL_MAX_K && n >= GS_SPEC_SERIAL_MIN))
         return launch_spec<64, 4, 1, true, true>(A, partials, cap, d_out, accumulate, stream);
     if (n <= GS_FEW_MAX) return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
@@ -752,9 +778,10 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //   * Up to 2^21 elements the lines are there anyway, and plain accesses cost 2-3 %.
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
-static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate)
+//   * On some of the CUs the memory is not the bound, and plain accesses cost 3-7 %.
+static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate, hipStream_t stream)
 {
-    if (accumulate || end - begin <= GS_RESIDENT_MAX) return end;
+    if (accumulate || end - begin <= GS_RESIDENT_MAX || on_cu_budget(stream)) return end;
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
@@ -788,6 +815,17 @@ static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, h
     A.accumulate = accumulate;
     k_grad_sqnorm<K, U, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(A, U);
     return hipGetLastError();
+}
+
+// from 5 streams on (K = 8: without the tests for streams that are not there, 1-2 % at 8 streams)
+template <int K>
+static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    const int64_t n = A.end - A.begin;
+    if (n <= GS_NORM_256_MAX) return launch_norm<K, 1, 256>(A, 1, cap, d_out, accumulate, stream);
+    if (n <= GS_NORM_512_MAX) return launch_norm<K, 1, 512>(A, 1, cap, d_out, accumulate, stream);
+    if (n <= GS_NORM_1024_MAX) return launch_norm<K, 1, 1024>(A, 2, cap, d_out, accumulate, stream);
+    return launch_norm<K, 1, 512>(A, run, cap, d_out, accumulate, stream);
 }
 
 // Up to four 4096-element tiles (one, from 5 streams on) a single workgroup has everything in flight at
@@ -828,10 +866,8 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
         if (small) return launch_norm<4, 2, 256>(A, 2, cap, d_out, accumulate, stream);
         return launch_norm<4, 2, 512>(A, run, cap, d_out, accumulate, stream);
     }
-    if (n <= GS_NORM_256_MAX) return launch_norm<0, 1, 256>(A, 1, cap, d_out, accumulate, stream);
-    if (n <= GS_NORM_512_MAX) return launch_norm<0, 1, 512>(A, 1, cap, d_out, accumulate, stream);
-    if (n <= GS_NORM_1024_MAX) return launch_norm<0, 1, 1024>(A, 2, cap, d_out, accumulate, stream);
-    return launch_norm<0, 1, 512>(A, run, cap, d_out, accumulate, stream);
+    return A.k == 8 ? launch_norm_many<8>(A, run, cap, d_out, accumulate, stream)
+                    : launch_norm_many<0>(A, run, cap, d_out, accumulate, stream);
 }
 
 template <int BLOCK, int EL, int DEPTH>
@@ -853,6 +889,7 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
 //   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.1/5.7/6.6/8.7 -> 5.0/5.1/5.6/6.4
 //   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4
 //   >= 2^25, from 8 streams on 2 elements per lane, 256 lanes, four in flight: 201 M  639/1159 -> 629/1136
+//            (not on some of the CUs only: 100 M, k = 8, 16 CUs 3.39 ms against 2.78)
 //   else the shape as before (12.6 M  24.1/29.4/44.8/76.3; 2 elements per lane lose 3-40 % there)
 static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
@@ -866,7 +903,8 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
         if (A.k < 8) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
         return launch_staged<1024, 4, 8>(A, cap, d_out, accumulate, stream);
     }
-    if (A.k >= 8 && n >= GS_STAGED_PAIR_MIN) return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);
+    if (A.k >= 8 && n >= GS_STAGED_PAIR_MIN && !on_cu_budget(stream))
+        return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);
     if (A.k <= 8 && tiles_of(A.begin, A.end, 256) <= cap) return launch_staged<64, 4, 2>(A, cap, d_out, accumulate, stream);
     return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);
 }
@@ -876,7 +914,7 @@ hipError_t launch_grad_sqnorm(const SqnormArgs &args, size_t workspace_bytes, do
 {
     const int64_t cap = partial_capacity(workspace_bytes);
     SqnormArgs A = args;
-    A.keep_from = keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate);
+    A.keep_from = keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate, stream);
     if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
     return launch_staged_norm(A, cap, d_out, accumulate, stream);
 }
@@ -889,7 +927,7 @@ static hipError_t launch_acc_norm(const float *acc, int64_t begin, int64_t end, 
     span = fit_span(tiles, span, U, cap);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, keep_from(begin, end, 4, accumulate), partials, 0, (int)span);
+    k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, keep_from(begin, end, 4, accumulate, stream), partials, 0, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(partials, cap, grid, d_out, accumulate, stream);
@@ -929,7 +967,8 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
 
 // us per launch, before (64 lanes, the buffer's load after the gradient's) -> now:
 //   first micro-batch, <= 2^22: 256 lanes               1 M 3.2 -> 2.6, 2 M 4.4 -> 3.6; level with 64 above
-//   later ones, <= 2^22: both loads in flight           1 M 3.7 -> 3.2, 2 M 5.2 -> 4.9; from 200 M on waiting
+//   later ones, <= 2^22 or on some of the CUs only: both loads in flight
+//                                                      1 M 3.7 -> 3.2, 2 M 5.2 -> 4.9; from 200 M on waiting
 //                                                       is 0.5 % ahead, level in between
 //   with the norm: both loads in flight; 256 lanes up to 2^19, 1024 up to 2^23 (fewer partials), then 64:
 //                                                       2 M 9.7 -> 7.5, 12.6 M 26.2 -> 25.1, 201 M 320 -> 306
@@ -938,10 +977,11 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
                             hipStream_t stream)
 {
     AccumAddArgs A = args;
-    A.keep_from = keep_from(A.begin, A.end, 4, 0);
+    A.keep_from = keep_from(A.begin, A.end, 4, 0, stream);
     const int64_t n = A.end - A.begin;
     if (!d_out) {
-        if (n > GS_ADD_SMALL_MAX) return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
+        if (n > GS_ADD_SMALL_MAX && !on_cu_budget(stream))
+            return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
         if (first) return launch_add<false, 256, 4, false>(A, first, 0, nullptr, 0, stream);
         return launch_add<false, 64, 4, false>(A, first, 0, nullptr, 0, stream);
     }

@@ -188,3 +188,46 @@ def test_largest_shape_equals_its_pieces(k):
         gs.gs_accum_adamw(*parts, case.grads, x, y, HP, case.sq)
     for a, b in zip(whole, parts):
         assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("k", [1, 8, 9])
+def test_cu_budget_shapes_give_the_same_bits(k):
+    """A stream on some of the CUs takes shapes of its own above 2^21 elements (and 2^25 for the staged
+    norm): same bits as on all of them; the look-up works under capture."""
+    n = (1 << 25) + 3
+    case = DeviceCase(n, k, seed=k, keep_host=False)
+    case.gpu_sqnorm()
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(n), dtype=torch.uint8, device=DEV)
+    raw = gs.gs_cu_stream_create(64)
+    try:
+        results = []
+        for stream in (None, raw):
+            got = case.clone_states()
+            acc = torch.zeros(n, dtype=torch.float32, device=DEV)
+            out = [torch.zeros(n, device=DEV) for _ in range(3)] + [torch.zeros_like(case.w)]
+            sq = torch.zeros(3, dtype=torch.float64, device=DEV)
+            torch.cuda.synchronize()
+            gs.gs_accum_adamw(*got, case.grads, 1, n, HP, case.sq, stream=stream)
+            gs.gs_grad_accum_sqnorm(case.grads, 1, n, acc, sq[0:1], ws, stream=stream)
+            gs.gs_adamw_from_acc(*got, acc, 1, n, HP, case.sq, stream=stream)
+            gs.gs_accum_add(acc, case.grads[0], False, 1, n, sq[1:2], ws, stream=stream)
+            gs.gs_accum_adamw_spec(case.p, case.m, case.v, *out, case.grads, 1, n, HP, sq[2:3], ws, stream=stream)
+            torch.cuda.synchronize()
+            results.append((*got, acc, *out, sq))
+        for a, b in zip(results[0][:-1], results[1][:-1]):
+            assert torch.equal(a, b)
+        assert torch.allclose(results[0][-1], results[1][-1], rtol=1e-13, atol=0.0)     # fp64 trees of other shapes
+    finally:
+        gs.gs_cu_stream_destroy(raw)
+    # the look-up of a stream's CUs under capture, on an ordinary stream
+    got = case.clone_states()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gs.gs_accum_adamw(*got, case.grads, 1, n, HP, case.sq)
+    want = case.clone_states()
+    for _ in range(3):
+        graph.replay()
+        gs.gs_accum_adamw(*want, case.grads, 1, n, HP, case.sq)
+        torch.cuda.synchronize()
+        for a, b in zip(got, want):
+            assert torch.equal(a, b)

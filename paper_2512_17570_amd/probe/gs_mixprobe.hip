@@ -3,7 +3,7 @@
 // and one bf16 stream out, 2k+26 bytes per element) and no arithmetic beyond what keeps the
 // compiler from dropping the accesses.  bench.py times them next to gs_accum_adamw so that the
 // step's bandwidth can be held against what the same device gives the same mix of streams:
-//   mode 0  the step kernel's own shape without its arithmetic: one tile per workgroup, the
+//   mode 0  the step kernel's shape for few streams (4 elements per lane) without its arithmetic: one tile per workgroup, the
 //           three state loads first, gradient loads one at a time, the four stores one by one;
 //   mode 1  the same tile with every load in flight at once and the stores back to back;
 //   mode 2  the read half only (the 2k+12 bytes in), loads one at a time;

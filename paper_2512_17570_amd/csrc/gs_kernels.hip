@@ -619,6 +619,9 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
     return (end - 1) / tile - begin / tile + 1;
 }
 
+// HIP launches fewer than 2^32 work items at a time: the workgroups of `block` lanes that is.
+static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
+
 // How a step over `elems` elements is laid out; every line below is where the two sides met when both
 // were timed with cold caches (us per launch, k = 1 / 4 / 8 / 16 / 32).  The chip holds 8192 waves
 // (256 CUs x 32): up to 2^20 elements the waves of a 2-element shape, and up to 2^21 those of a
@@ -687,10 +690,20 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
 template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
 static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
 {
-    int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
-    if (tiles < 1 || tiles > 0x7ffffffe) return hipErrorInvalidValue;
-    if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
+    constexpr int64_t TILE = (int64_t)BLOCK * EL;
+    int64_t tiles = tiles_of(A.begin, A.end, TILE);
+    if (tiles < 1) return hipErrorInvalidValue;
     const int cuts = A.begin % EL != 0 || A.end % EL != 0;
+    if (tiles + cuts > max_grid(BLOCK)) {                           // too long for one launch: two, cut where a tile starts
+        StepArgs half = A;
+        half.end = (A.begin / TILE + tiles / 2) * TILE;
+        const hipError_t e = launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT>(half, stream);
+        if (e != hipSuccess) return e;
+        half.begin = half.end;
+        half.end = A.end;
+        return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT>(half, stream);
+    }
+    if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
     k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT><<<(int)(tiles + cuts), BLOCK, 0, stream>>>(A, cuts);
     return hipGetLastError();
 }
@@ -722,18 +735,27 @@ static int64_t partial_capacity(size_t workspace_bytes)
     return (int64_t)(workspace_bytes / sizeof(double)) - GS_FINAL_SLICES;
 }
 
+// The span (tiles per workgroup) that keeps the partials within `cap` and the workgroups of `block` lanes
+// within one launch: `span` itself, or the next multiple of U that does.  0: not possible.
+static int64_t fit_span(int64_t tiles, int64_t span, int64_t U, int64_t cap, int block)
+{
+    if (cap > max_grid(block)) cap = max_grid(block);
+    if ((tiles + span - 1) / span > cap) span = ((tiles + cap - 1) / cap + U - 1) / U * U;
+    return span > 0x7fffffff ? 0 : span;
+}
+
 template <int BLOCK, int EL, int DEPTH, bool LWAIT, bool SWAIT>
 static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
     if (tiles < 1) tiles = 1;
-    const int64_t span = tiles > cap ? (tiles + cap - 1) / cap : 1;
-    const int64_t grid = (tiles + span - 1) / span;
-    if (span > 0x7fffffff || grid > 0x7fffffff) return hipErrorInvalidValue;
-    k_accum_adamw_spec<BLOCK, EL, DEPTH, LWAIT, SWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, partials, (int)span);
+    const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
+    if (span == 0) return hipErrorInvalidValue;
+    const int grid = (int)((tiles + span - 1) / span);
+    k_accum_adamw_spec<BLOCK, EL, DEPTH, LWAIT, SWAIT><<<grid, BLOCK, 0, stream>>>(A, partials, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    return launch_fold(partials, cap, (int)grid, d_out, accumulate, stream);
+    return launch_fold(partials, cap, grid, d_out, accumulate, stream);
 }
 
 // The step's shapes with a partial per workgroup; a wave reduction per 128 or 256 elements moves the
@@ -785,20 +807,12 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
-// The span (tiles per workgroup) that keeps the partials within `cap`: `span` itself, or the next
-// multiple of U that does.  0: not possible.
-static int64_t fit_span(int64_t tiles, int64_t span, int64_t U, int64_t cap)
-{
-    if ((tiles + span - 1) / span > cap) span = ((tiles + cap - 1) / cap + U - 1) / U * U;
-    return span > 0x7fffffff || (tiles + span - 1) / span > 0x7fffffff ? 0 : span;
-}
-
 template <int K, int U, int BLOCK>
 static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * 4);
     if (tiles < 1) tiles = 1;
-    span = fit_span(tiles, span, U, cap);
+    span = fit_span(tiles, span, U, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
     k_grad_sqnorm<K, U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(A, (int)span);
@@ -875,7 +889,7 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
     if (tiles < 1) tiles = 1;
-    const int64_t span = fit_span(tiles, 1, 1, cap);
+    const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
     k_grad_accum_sqnorm<BLOCK, EL, DEPTH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
@@ -924,7 +938,7 @@ static hipError_t launch_acc_norm(const float *acc, int64_t begin, int64_t end, 
                                   double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t tiles = tiles_of(begin, end, (int64_t)BLOCK * 4);
-    span = fit_span(tiles, span, U, cap);
+    span = fit_span(tiles, span, U, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
     k_acc_sqnorm<U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(acc, begin, end, keep_from(begin, end, 4, accumulate, stream), partials, 0, (int)span);
@@ -955,14 +969,14 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
     if (tiles < 1) tiles = 1;
-    const int64_t span = NORM ? fit_span(tiles, 1, 1, cap) : 1;
-    const int64_t grid = span == 0 ? 0 : (tiles + span - 1) / span;
-    if (grid < 1 || grid > 0x7fffffff) return hipErrorInvalidValue;
-    if (first) k_accum_add<true, NORM, BLOCK, EL, LWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, (int)span);
-    else k_accum_add<false, NORM, BLOCK, EL, LWAIT><<<(int)grid, BLOCK, 0, stream>>>(A, (int)span);
+    const int64_t span = fit_span(tiles, 1, 1, NORM ? cap : tiles, BLOCK);
+    if (span == 0) return hipErrorInvalidValue;
+    const int grid = (int)((tiles + span - 1) / span);
+    if (first) k_accum_add<true, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    else k_accum_add<false, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !NORM) return e;
-    return launch_fold(A.partials, cap, (int)grid, d_out, accumulate, stream);
+    return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
 
 // us per launch, before (64 lanes, the buffer's load after the gradient's) -> now:

@@ -549,3 +549,45 @@ def test_element_indices_beyond_2_to_31():
     assert_bf16_close(np_bf16(w[lo:hi]), o_w, "whole range w")
     assert int(torch.count_nonzero(w[:lo].view(torch.int16)).item()) == 0
     print(f"[2^31] N={N} window=[{lo},{hi}) S={S_o:.6e} c={c:.5f}", flush=True)
+
+
+@pytest.mark.timeout(600)
+def test_ranges_longer_than_one_launch():
+    """2^33 elements and more in one call (HIP launches fewer than 2^32 work items at a time, and a lane takes two
+    elements): the staged step, cut into two launches, and the staged norm with a workspace for every partial.
+    All elements are alike, so every one has to come out as in a range of 64."""
+    N, begin = (1 << 33) + 1021, 3
+    n = N - begin
+    need = 18 * N + 34 * (1 << 20)
+    torch.cuda.empty_cache()
+    if torch.cuda.mem_get_info()[0] < need + 24 * (1 << 30):
+        pytest.skip("needs 180 GB of device memory")
+    hp = gs.HParams(step=3)
+    sq = torch.full((1,), 4.0, dtype=torch.float64, device=DEV)
+
+    def make(size):
+        return [torch.full((size,), x, dtype=torch.float32, device=DEV) for x in (0.5, 1e-3, 1e-6)] + \
+               [torch.zeros(size, dtype=torch.bfloat16, device=DEV)]
+    small = make(64)
+    gs.gs_adamw_from_acc(*small, torch.full((64,), 0.25, device=DEV), 0, 64, hp, sq)
+    print(f"[2^33] gs_adamw_from_acc [{begin},{N})", flush=True)
+    big = make(N)
+    acc = torch.full((N,), 0.25, dtype=torch.float32, device=DEV)
+    gs.gs_adamw_from_acc(*big, acc, begin, N, hp, sq)
+    torch.cuda.synchronize()
+    for name, got, want, old in zip("pmvw", big, small, (0.5, 1e-3, 1e-6, 0.0)):
+        assert bool((got[:begin] == torch.tensor(old, dtype=got.dtype, device=DEV)).all()), name
+        for lo in range(begin, N, 1 << 30):
+            assert bool((got[lo:lo + (1 << 30)] == want[0]).all()), (name, lo)
+    del big
+    torch.cuda.empty_cache()
+    k = 8
+    g = torch.full((N,), 0.5, dtype=torch.bfloat16, device=DEV)          # one buffer k times: read only
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(n), dtype=torch.uint8, device=DEV)
+    print(f"[2^33] gs_grad_accum_sqnorm [{begin},{N}) k={k}", flush=True)
+    acc.fill_(7.0)
+    gs.gs_grad_accum_sqnorm([g] * k, begin, N, acc, sq, ws)
+    torch.cuda.synchronize()
+    assert float(sq.item()) == 16.0 * n and bool((acc[:begin] == 7.0).all())      # a sum of whole numbers: exact
+    for lo in range(begin, N, 1 << 30):
+        assert bool((acc[lo:lo + (1 << 30)] == 4.0).all()), lo

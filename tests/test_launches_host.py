@@ -1,0 +1,67 @@
+"""Every rule by which the library chooses and sizes its launches, on the CPU: the launchers are compiled for
+the host only against a HIP runtime that records launches (launches.py), and each recorded launch is checked for
+what the runtime accepts, for covering its range exactly, and for keeping its partials inside the workspace."""
+from __future__ import annotations
+
+import random
+
+import pytest
+
+from launches import FULL, MIN_WS, Recorder, build, check
+
+STEPS = ["step", "oop", "from_acc", "host_step"]
+NORMS = ["norm", "staged", "acc_norm", "add_norm", "spec", "noalloc"]
+ENTRIES = STEPS + ["add"] + NORMS
+
+
+@pytest.fixture(scope="module")
+def rec(tmp_path_factory):
+    return Recorder(build(str(tmp_path_factory.mktemp("launches"))))
+
+
+# HIP launches fewer than 2^32 work items at a time: with 2 elements per lane that is less than 2^33 elements,
+# with 4 less than 2^34.  A 309 GB card holds the staged step's 18 bytes per element up to 1.7e10 elements.
+@pytest.mark.parametrize("entry", ENTRIES)
+@pytest.mark.parametrize("length", [(1 << 33) - 1025, (1 << 33) - 1, 1 << 33, (1 << 33) + 1, (1 << 34) - 1024, (1 << 34) - 257])
+@pytest.mark.parametrize("begin", [0, 5])
+def test_longest_ranges_are_launched(rec, entry, length, begin):
+    for k in (1, 4, 8, 16, 32):
+        for ws in (MIN_WS, FULL):
+            for cus in (256, 64):
+                if entry == "noalloc" and length > 1 << 33:
+                    continue
+                st, launches, _, wsb = rec.call(entry, k, begin, begin + length, ws, cus=cus)
+                assert st == 0, (entry, k, ws, cus, [l.name for l in launches])
+                check(entry, launches, begin, begin + length, wsb)
+
+
+def _lengths(rng):
+    for p in range(0, 33):
+        yield rng.randrange(1 << p, 2 << p)
+    for line in (1 << 19, 3 << 19, 1 << 21, 7_000_000, 1 << 22, 1 << 23, 1 << 25, 80_000_000, 1 << 27, 1 << 28, 1 << 29):
+        yield from (line - 1, line, line + 1)
+
+
+@pytest.mark.parametrize("entry", ENTRIES)
+@pytest.mark.parametrize("seed", [0, 1])
+def test_launches_cover_any_range(rec, entry, seed):
+    rng = random.Random(seed)
+    for length in _lengths(rng):
+        for k in [1, 2, 3, 4, 5, 7, 8, 9, rng.randint(10, 32)]:
+            begin = rng.choice([0, 1, 2, 3, 4, 1023, 4096, rng.randrange(1 << 20), rng.randrange(1 << 33)])
+            ws = rng.choice([MIN_WS, FULL, MIN_WS + 8 * rng.randrange(1 << 20)])
+            st, launches, _, wsb = rec.call(entry, k, begin, begin + length, ws, accumulate=rng.randrange(2),
+                                            first=rng.randrange(2), cus=rng.choice([16, 128, 256]))
+            assert st == 0
+            check(entry, launches, begin, begin + length, wsb)
+
+
+@pytest.mark.parametrize("entry", NORMS)
+@pytest.mark.parametrize("begin", [0, 5, 4096])
+def test_empty_range_writes_a_zero_norm(rec, entry, begin):
+    for k in (1, 5):
+        st, launches, _, wsb = rec.call(entry, k, begin, begin)
+        assert st == 0
+        check(entry, launches, begin, begin, wsb)
+        st, launches, _, _ = rec.call(entry, k, begin, begin, accumulate=1)
+        assert st == 0 and not launches

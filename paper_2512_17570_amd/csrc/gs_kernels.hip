@@ -651,10 +651,11 @@ enum Shape {
 };
 
 // Whether `stream` may use only some of the device's CUs.  The runtime looks the mask up in the stream's own
-// host-side record; a stream it cannot tell about counts as unconfined (only the shape depends on this).
+// host-side record; a stream it cannot tell about counts as unconfined (only the shape depends on this), and so
+// do the null stream and the handles that only name a default stream, which have no record to look up.
 static bool on_cu_budget(hipStream_t stream)
 {
-    if (!stream) return false;
+    if (!stream || stream == hipStreamLegacy || stream == hipStreamPerThread) return false;
     uint32_t mask[64] = {0};
     int dev = 0, cus = 0, in_mask = 0;
     if (hipGetDevice(&dev) != hipSuccess ||

@@ -65,3 +65,15 @@ def test_empty_range_writes_a_zero_norm(rec, entry, begin):
         check(entry, launches, begin, begin, wsb)
         st, launches, _, _ = rec.call(entry, k, begin, begin, accumulate=1)
         assert st == 0 and not launches
+
+
+# hipStreamLegacy and hipStreamPerThread are names of streams, not streams: nothing but a launch is given them
+@pytest.mark.parametrize("entry", ENTRIES)
+@pytest.mark.parametrize("stream", [0, 1, 2])
+def test_cus_of_the_special_streams_are_not_asked_for(rec, entry, stream):
+    for length in (1000, 3_000_000, 100_000_000):
+        for k in (1, 8):
+            st, launches, asked, _ = rec.call(entry, k, 0, length, cus=64, stream=stream)
+            assert st == 0 and not asked
+            plain = rec.call(entry, k, 0, length, cus=256)[1]
+            assert [(l.name, l.grid) for l in launches] == [(l.name, l.grid) for l in plain]     # as on all CUs

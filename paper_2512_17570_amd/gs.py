@@ -178,6 +178,7 @@ def _table(grads, end: int, name: str = "grads"):
     """(address table, number of buffers) of the gradient buffers, each checked as in _ptr."""
     if grads is None:
         return None, 0
+    bool(grads)      # a stacked tensor is no list of buffers: it has no truth value, and is refused for that
     addrs = []
     for g in grads:
         # the same checks as _ptr; its call alone would double the cost per buffer

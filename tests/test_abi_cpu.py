@@ -306,6 +306,22 @@ def test_error_raises_through_binding():
     assert ei.value.status == gs.GS_ERR_INVALID_ARG
 
 
+def test_binding_refuses_a_stacked_tensor_as_the_list_of_gradients():
+    """Gradients are a list of buffers; a tensor that stacks them is refused before the library is called (an empty
+    range, which the library would accept without a HIP call)."""
+    import torch
+    buffers = [torch.zeros(64, dtype=torch.bfloat16) for _ in range(2)]
+    for ok in (buffers, tuple(buffers), (b for b in buffers), [FG0, FG1]):
+        assert gs.gs_grad_sqnorm(ok, 0, 0, FAKE, FAKE, 1 << 22, accumulate=True, stream=0) == gs.GS_OK
+    for stacked in (torch.stack(buffers), torch.stack(buffers[:1]), torch.zeros(0, 64, dtype=torch.bfloat16)):
+        with pytest.raises(RuntimeError, match="ambiguous"):
+            gs.gs_grad_sqnorm(stacked, 0, 0, FAKE, FAKE, 1 << 22, accumulate=True, stream=0)
+        with pytest.raises(RuntimeError, match="ambiguous"):
+            gs.gs_accum_adamw(FP, FM, FV, FW, stacked, 0, 0, GOOD_HP, stream=0)
+    with pytest.raises(ValueError, match=r"grads\[1\]: holds 64"):
+        gs.gs_accum_adamw(FP, FM, FV, FW, [torch.zeros(65, dtype=torch.bfloat16), buffers[1]], 0, 65, GOOD_HP, stream=0)
+
+
 def test_header_is_plain_c_and_cxx(tmp_path):
     """include/gs.h must be usable from a C99 translation unit (and from C++) on its own."""
     import subprocess

@@ -34,6 +34,7 @@
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup
+#define GS_BUDGET_RUN_MIN 49152       // elements per CU of a confined stream from which norm workgroups read long runs
 
 namespace gs {
 

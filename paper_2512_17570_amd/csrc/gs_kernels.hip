@@ -373,9 +373,9 @@ __device__ __forceinline__ void add_squares(const float (&a)[EL], double &acc0, 
 // Read-only, 2k bytes per element.  Workgroup b reads `span` consecutive tiles starting at tile
 // b*span: a short contiguous run per workgroup is what the read path likes best.  What else bounds
 // it is how much a wave has in flight: with few streams (compile-time K) the same groups of U tiles
-// are loaded together, otherwise (K == 0) up to 16 streams are.
+// are loaded together, otherwise (K == 0) up to DEPTH streams are.
 // ONE: a single workgroup reads the whole range and leaves the norm itself in A.out.
-template <int K, int U, int BLOCK, bool ONE>
+template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
 __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
 {
     constexpr int TILE = BLOCK * 4;
@@ -405,7 +405,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
             } else {
                 static_assert(K > 0 || U == 1, "tiles are grouped for a compile-time K only");
                 float a[4];
-                accumulate_batches<4, 16, KEEP>(A.gt, A.k, lo, a);
+                accumulate_batches<4, DEPTH, KEEP>(A.gt, A.k, lo, a);
                 add_squares(a, acc0, acc1);
             }
         } else {
@@ -414,7 +414,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
                 const int64_t l = lo + (int64_t)u * TILE;
                 if (l >= A.begin && l + 4 <= A.end) {
                     float a[4];
-                    accumulate_batches<4, K == 0 ? 16 : K, KEEP>(A.gt, A.k, l, a);
+                    accumulate_batches<4, K == 0 ? DEPTH : K, KEEP>(A.gt, A.k, l, a);
                     add_squares(a, acc0, acc1);
                     continue;
                 }
@@ -650,23 +650,25 @@ enum Shape {
     SHAPE_BUDGET      // 4 elements per lane, two gradient loads in flight, stores one at a time
 };
 
-// Whether `stream` may use only some of the device's CUs.  The runtime looks the mask up in the stream's own
+// The CUs that `stream` is confined to, or 0 if it may use all of them.  The runtime looks the mask up in the stream's own
 // host-side record; a stream it cannot tell about counts as unconfined (only the shape depends on this), and so
 // do the null stream and the handles that only name a default stream, which have no record to look up.
-static bool on_cu_budget(hipStream_t stream)
+static int budget_cus(hipStream_t stream)
 {
-    if (!stream || stream == hipStreamLegacy || stream == hipStreamPerThread) return false;
+    if (!stream || stream == hipStreamLegacy || stream == hipStreamPerThread) return 0;
     uint32_t mask[64] = {0};
     int dev = 0, cus = 0, in_mask = 0;
     if (hipGetDevice(&dev) != hipSuccess ||
         hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
         hipExtStreamGetCUMask(stream, 64, mask) != hipSuccess) {
         (void)hipGetLastError();
-        return false;
+        return 0;
     }
     for (uint32_t word : mask) in_mask += __builtin_popcount(word);
-    return in_mask > 0 && in_mask < cus;
+    return in_mask < cus ? in_mask : 0;
 }
+
+static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 
 //   A stream confined to some of the CUs (any size over 2^21) takes BUDGET: there the bytes each CU keeps in
 //             flight are the bound, and 4 elements per lane hold twice as many (k = 2 / 8, 100 M elements:
@@ -808,7 +810,7 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
-template <int K, int U, int BLOCK>
+template <int K, int U, int BLOCK, int DEPTH = 16>
 static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * 4);
@@ -816,7 +818,7 @@ static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d
     span = fit_span(tiles, span, U, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_grad_sqnorm<K, U, BLOCK, false><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    k_grad_sqnorm<K, U, BLOCK, false, DEPTH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
@@ -854,9 +856,19 @@ static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap
 //   100 k  k = 1/3/8/32  3.5/6.3/8.1/38 -> 2.4/2.6/3.3/4.5      12.6 M  8.4/15.8/35.4/151 -> 6.2/14.0/33.0/127
 //   1 M    k = 1/3/8/32  5.8/10.6/8.6/40 -> 2.9/3.4/5.2/11.9    201 M   89/191/474/1932 -> 61/176/466/1882
 //   3.3 M  k = 1/3/8/32  6.5/11.5/11.0/51 -> 4.0/5.4/11.0/37    805 M   347/737/1851/7903 -> 231/713/1848/7849
+//   On some of the CUs, 4 to 7 streams: once each CU has some tens of thousands of elements to read, 256 lanes,
+//   four loads in flight and eight tiles one after another (k = 4 / 5, 50 M elements: 16 CUs 523/694 us against
+//   651/860 in the shapes below, 128 CUs 84/110 against 97/122; 3.3 M on 128 CUs, 26 k elements each, 11.6/16.2
+//   against 10.9/14.1).  The two meet at 96 k elements per CU for four streams (12.6 M on 128 CUs 29.7 against
+//   30.6, 3.3 M on 64 CUs 16.2 against 14.5) and at 48 k above (3.3 M on 64 CUs, k = 5 18.2 against 20.2).
 static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t n = A.end - A.begin;
+    if (A.k >= 4 && A.k <= 7 && n > GS_LATENCY_MAX) {
+        const int cus = budget_cus(stream);
+        if (cus > 0 && n / cus >= (A.k == 4 ? 2 : 1) * GS_BUDGET_RUN_MIN)
+            return launch_norm<0, 1, 256, 4>(A, 8, cap, d_out, accumulate, stream);
+    }
     const bool small = n <= GS_NORM_SMALL_MAX;
     const int64_t run = n < GS_NORM_LONG_MIN ? 2 : 4;
     const int64_t tiles = tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4);

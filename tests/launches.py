@@ -161,7 +161,7 @@ def check(entry, launches, begin, end, wsb):
         return
     assert len(work) == 1
     l = work[0]
-    if l.kernel in ("k_grad_sqnorm", "k_acc_sqnorm") and l.targs[-1]:      # the norm in a single workgroup
+    if l.kernel in ("k_grad_sqnorm", "k_acc_sqnorm") and l.targs[3 if l.kernel == "k_grad_sqnorm" else 2]:   # in a single workgroup
         assert l.grid == 1 and l.out == SQ and not folds
         return
     assert l.partials == base and l.grid <= cap - 128

@@ -77,3 +77,19 @@ def test_cus_of_the_special_streams_are_not_asked_for(rec, entry, stream):
             assert st == 0 and not asked
             plain = rec.call(entry, k, 0, length, cus=256)[1]
             assert [(l.name, l.grid) for l in launches] == [(l.name, l.grid) for l in plain]     # as on all CUs
+
+
+def work_of(rec, *args, **kw):
+    """The launch that does the work of a call (the others fold partials)."""
+    return rec.call(*args, **kw)[1][0]
+
+
+# streams confined to some of the CUs: the limit of the norm's long runs is one of elements per CU
+@pytest.mark.parametrize("k", [1, 3, 4, 5, 7, 8, 16])
+def test_norm_on_some_of_the_cus(rec, k):
+    for cus in (16, 64, 128, 256):
+        for per_cu in (40_000, 49_152, 98_304, 1_000_000):
+            n = per_cu * cus
+            l = work_of(rec, "norm", k, 3, 3 + n, cus=cus)
+            long_runs = 4 <= k <= 7 and cus < 256 and per_cu >= (98_304 if k == 4 else 49_152) and n > 1 << 19
+            assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)

@@ -103,6 +103,24 @@ def test_speculative_step_at_shape_edges(length, k, big_ws):
     assert abs(float(case.sq.item()) - S) <= max(length * 2.0 ** -53, 1e-13) * S
 
 
+@pytest.mark.parametrize("k", [8, 9, 10, 11, 13, 14, 15])
+@pytest.mark.parametrize("length", [FEW + 1, 80_000_001])
+def test_speculative_step_leftover_streams(length, k):
+    """Batches of four streams and 0 to 3 left over, in the shapes of long ranges: the step's own bits (c = 1)
+    and the norm's value."""
+    b, e = 1, 1 + length
+    case = DeviceCase(e + 2, k, seed=k, keep_host=False)
+    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(length), dtype=torch.uint8, device=DEV)
+    want = case.clone_states()
+    gs.gs_accum_adamw(*want, case.grads, b, e, HP, None)
+    S = case.gpu_sqnorm(b, e)
+    out = [x.clone() for x in (case.p, case.m, case.v)] + [torch.zeros_like(case.w)]
+    gs.gs_accum_adamw_spec(case.p, case.m, case.v, *out, case.grads, b, e, HP, case.sq, ws)
+    for a, w in zip(out, want):
+        assert torch.equal(a, w)
+    assert abs(float(case.sq.item()) - S) <= 1e-12 * S           # two fp64 trees over exact squares
+
+
 # the norm's lines: one workgroup | many, and the sizes where the workgroups change; each with a range that
 # ends inside a group and one that does not
 NORM_SIZES = [1, 3, 4096, 4097, 16384, 16385, (1 << 20), (1 << 20) + 1, (1 << 21) + 2, (1 << 22) + 1, (1 << 23) + 3]

@@ -940,8 +940,10 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
 // flight, 64 lanes up to 8 streams, 128 beyond) -> now, k = 2 / 4 / 8 / 16:
 //   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.1/5.7/6.6/8.7 -> 5.0/5.1/5.6/6.4
 //   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4
-//   >= 2^25, from 8 streams on 2 elements per lane, 256 lanes, four in flight: 201 M  639/1159 -> 629/1136
-//            (not on some of the CUs only: 100 M, k = 8, 16 CUs 3.39 ms against 2.78)
+//   >= 2^25, 8 streams or more and a multiple of 4: 2 elements per lane, 256 lanes, four in flight: 617 M, k = 8 / 12 /
+//            16 / 20  1.92/2.70/3.53/4.39 ms against 1.93/2.75/3.59/4.43 in the shape below.  With streams left over
+//            after the batches of four that one wins (k = 9 / 10 / 14  2.14/2.41/3.19 against 2.27/2.60/3.33), and on
+//            some of the CUs (100 M, k = 8, 16 CUs 2.78 against 3.39)
 //   else the shape as before (12.6 M  24.1/29.4/44.8/76.3; 2 elements per lane lose 3-40 % there)
 static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
@@ -955,7 +957,7 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
         if (A.k < 8) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
         return launch_staged<1024, 4, 8>(A, cap, d_out, accumulate, stream);
     }
-    if (A.k >= 8 && n >= GS_STAGED_PAIR_MIN && !on_cu_budget(stream))
+    if (A.k >= 8 && A.k % 4 == 0 && n >= GS_STAGED_PAIR_MIN && !on_cu_budget(stream))
         return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);
     if (A.k <= 8 && tiles_of(A.begin, A.end, 256) <= cap) return launch_staged<64, 4, 2>(A, cap, d_out, accumulate, stream);
     return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);

@@ -93,3 +93,12 @@ def test_norm_on_some_of_the_cus(rec, k):
             l = work_of(rec, "norm", k, 3, 3 + n, cus=cus)
             long_runs = 4 <= k <= 7 and cus < 256 and per_cu >= (98_304 if k == 4 else 49_152) and n > 1 << 19
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
+
+
+def test_staged_norm_of_long_ranges_pairs_elements_for_whole_batches_only(rec):
+    for length in ((1 << 25) - 1, 1 << 25, 200_000_000):
+        for k in range(1, 33):
+            for cus in (64, 256):
+                l = work_of(rec, "staged", k, 0, length, ws=FULL, cus=cus)
+                pairs = length >= 1 << 25 and k >= 8 and k % 4 == 0 and cus == 256
+                assert l.targs[:3] == ((256, 2, 4) if pairs else (64, 4, 2) if k <= 8 else (128, 4, 2)), (length, k, cus)

@@ -463,8 +463,10 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
 // The same norm that also writes the fp32 sum a_i to A.acc (the staged two-pass variant: the step
 // then reads one fp32 stream instead of re-reading k bf16 streams).  Once a store stream is
 // involved, runs of tiles per workgroup cost bandwidth (stores want in-order, one-tile workgroups),
-// so it uses a span of 1 wherever the partials still fit the workspace.
-template <int BLOCK, int EL, int DEPTH>
+// so it uses a span of 1 wherever the partials still fit the workspace.  KEEPS: some of the sum is left
+// in the memory-side cache; where none is, the choice alone would cost the one tile of a wave 1-2 %
+// (50 M, k = 2, 16 CUs: 741 us against 752).
+template <int BLOCK, int EL, int DEPTH, bool KEEPS>
 __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int span)
 {
     typedef typename Group<EL>::F F;
@@ -472,7 +474,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
-    with_keep(first - (int64_t)threadIdx.x * EL >= A.keep_from, [&](auto keep) {
+    with_keep(KEEPS && first - (int64_t)threadIdx.x * EL >= A.keep_from, [&](auto keep) {
     constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
@@ -829,6 +831,9 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
 //   * On some of the CUs the memory is not the bound, and plain accesses cost 3-7 %.
+//   * The staged norm of more than 12 streams: the reads push the sum out again, and its plain stores cost the
+//     pass 5-9 % (norm + step, us, with the hint against without: k = 12 / 16 / 20 / 32, 12.6 M 124/139/155/202
+//     against 125/141/158/211; 50 M 454/514/577/769 against 449/513/582/793; 201 M 1783/2064/2325/3115 against 1776/2058/2332/3123).
 static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate, hipStream_t stream)
 {
     if (accumulate || end - begin <= GS_RESIDENT_MAX || on_cu_budget(stream)) return end;
@@ -922,7 +927,7 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
                     : launch_norm_many<0>(A, run, cap, d_out, accumulate, stream);
 }
 
-template <int BLOCK, int EL, int DEPTH>
+template <int BLOCK, int EL, int DEPTH, bool KEEPS = true>
 static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
@@ -930,7 +935,8 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
     const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_grad_accum_sqnorm<BLOCK, EL, DEPTH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    if (KEEPS && A.keep_from < A.end) k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    else k_grad_accum_sqnorm<BLOCK, EL, DEPTH, false><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
@@ -949,8 +955,8 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
 {
     const int64_t n = A.end - A.begin;
     if (n <= GS_LATENCY_MAX) {
-        if (A.k < 8) return launch_staged<128, 4, 4>(A, cap, d_out, accumulate, stream);
-        return launch_staged<64, 4, 8>(A, cap, d_out, accumulate, stream);
+        if (A.k < 8) return launch_staged<128, 4, 4, false>(A, cap, d_out, accumulate, stream);
+        return launch_staged<64, 4, 8, false>(A, cap, d_out, accumulate, stream);
     }
     if (n <= GS_STAGED_WIDE_MAX) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
     if (tiles_of(A.begin, A.end, 512) > cap) {
@@ -968,7 +974,7 @@ hipError_t launch_grad_sqnorm(const SqnormArgs &args, size_t workspace_bytes, do
 {
     const int64_t cap = partial_capacity(workspace_bytes);
     SqnormArgs A = args;
-    A.keep_from = keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate, stream);
+    A.keep_from = A.acc && A.k > GS_STAGED_KEEP_MAX_K ? A.end : keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate, stream);
     if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
     return launch_staged_norm(A, cap, d_out, accumulate, stream);
 }

@@ -102,3 +102,13 @@ def test_staged_norm_of_long_ranges_pairs_elements_for_whole_batches_only(rec):
                 l = work_of(rec, "staged", k, 0, length, ws=FULL, cus=cus)
                 pairs = length >= 1 << 25 and k >= 8 and k % 4 == 0 and cus == 256
                 assert l.targs[:3] == ((256, 2, 4) if pairs else (64, 4, 2) if k <= 8 else (128, 4, 2)), (length, k, cus)
+
+
+def test_staged_norm_keeps_its_sum_cached_for_few_streams_only(rec):
+    for length in (1 << 21, (1 << 21) + 1, 12_600_000, 200_000_000):
+        for k in range(1, 33):
+            for cus, accumulate in ((256, 0), (256, 1), (64, 0)):
+                l = work_of(rec, "staged", k, 5, 5 + length, ws=FULL, cus=cus, accumulate=accumulate)
+                keeps = k <= 12 and length > 1 << 21 and cus == 256 and not accumulate
+                assert l.keep_from == (5 + length - (64 << 20) if keeps else 5 + length)
+                assert l.targs[3] == keeps

@@ -23,6 +23,7 @@
 #define GS_SQNORM_MAX_BLOCKS 262144   // upper bound on block partials => workspace size (2 MB)
 // limits of the staged norm's and the adding kernel's shapes (launch_staged_norm, launch_accum_add)
 #define GS_STAGED_WIDE_MAX (1 << 22)  // elements up to which a workgroup takes 4096 of them
+#define GS_STAGED_WIDE_MANY_MAX (1 << 20)  // the same for more than 16 streams
 #define GS_STAGED_PAIR_MIN (1 << 25)  // elements from which, with 8 streams or more, a lane takes 2 of them
 #define GS_STAGED_KEEP_MAX_K 12       // streams up to which the end of the sum is left in the memory-side cache
 #define GS_ADD_SMALL_MAX (1 << 22)    // without the norm: elements up to which both loads are in flight together
@@ -35,7 +36,7 @@
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup
-#define GS_BUDGET_RUN_MIN 49152       // elements per CU of a confined stream from which norm workgroups read long runs
+#define GS_BUDGET_RUN_MIN 49152       // elements per CU of a confined stream from which the norms take shapes of their own
 
 namespace gs {
 

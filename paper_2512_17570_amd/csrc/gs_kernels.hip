@@ -945,7 +945,11 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
 // One tile per workgroup wherever the partials fit.  us per launch, before (two gradient loads in
 // flight, 64 lanes up to 8 streams, 128 beyond) -> now, k = 2 / 4 / 8 / 16:
 //   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.1/5.7/6.6/8.7 -> 5.0/5.1/5.6/6.4
-//   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4
+//   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4.
+//            More than 16 streams only up to 2^20 (600 k, k = 20 / 32  9.1/11.7 against 11.0/14.6; 1.5 M 15.9/22.2
+//            against 14.9/20.0), and on some of the CUs fewer than 8 streams only up to 48 k elements per CU, from
+//            where the many small workgroups win (16 CUs, k = 1 / 2 / 4: 1 M 14.9/16.0/22.9 against 16.6/18.7/25.6,
+//            3.3 M 51/57/72 against 57/64/77; 64 CUs, 1 M 8.3/8.5/10.5 against 7.7/8.2/9.9)
 //   >= 2^25, 8 streams or more and a multiple of 4: 2 elements per lane, 256 lanes, four in flight: 617 M, k = 8 / 12 /
 //            16 / 20  1.92/2.70/3.53/4.39 ms against 1.93/2.75/3.59/4.43 in the shape below.  With streams left over
 //            after the batches of four that one wins (k = 9 / 10 / 14  2.14/2.41/3.19 against 2.27/2.60/3.33), and on
@@ -958,7 +962,9 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
         if (A.k < 8) return launch_staged<128, 4, 4, false>(A, cap, d_out, accumulate, stream);
         return launch_staged<64, 4, 8, false>(A, cap, d_out, accumulate, stream);
     }
-    if (n <= GS_STAGED_WIDE_MAX) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
+    const int cus = n <= GS_STAGED_WIDE_MAX && A.k < 8 ? budget_cus(stream) : 0;
+    if (n <= (A.k <= 16 ? GS_STAGED_WIDE_MAX : GS_STAGED_WIDE_MANY_MAX) && !(cus > 0 && n / cus >= GS_BUDGET_RUN_MIN))
+        return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
     if (tiles_of(A.begin, A.end, 512) > cap) {
         if (A.k < 8) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
         return launch_staged<1024, 4, 8>(A, cap, d_out, accumulate, stream);

@@ -112,3 +112,14 @@ def test_staged_norm_keeps_its_sum_cached_for_few_streams_only(rec):
                 keeps = k <= 12 and length > 1 << 21 and cus == 256 and not accumulate
                 assert l.keep_from == (5 + length - (64 << 20) if keeps else 5 + length)
                 assert l.targs[3] == keeps
+
+
+def test_staged_norm_takes_wide_workgroups_in_the_middle(rec):
+    for k in range(1, 33):
+        for cus in (16, 64, 256):
+            for length in ((1 << 19) + 1, 40_000 * cus, 49_152 * cus, 1 << 20, (1 << 20) + 1, 3_300_000, 1 << 22, (1 << 22) + 1):
+                if length <= 1 << 19:
+                    continue
+                l = work_of(rec, "staged", k, 0, length, ws=FULL, cus=cus)
+                wide = length <= (1 << 22 if k <= 16 else 1 << 20) and not (cus < 256 and k < 8 and length >= 49_152 * cus)
+                assert l.targs[:3] == ((1024, 4, 4) if wide else (64, 4, 2) if k <= 8 else (128, 4, 2)), (k, cus, length)

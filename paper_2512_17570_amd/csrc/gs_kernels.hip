@@ -954,6 +954,9 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
 //            16 / 20  1.92/2.70/3.53/4.39 ms against 1.93/2.75/3.59/4.43 in the shape below.  With streams left over
 //            after the batches of four that one wins (k = 9 / 10 / 14  2.14/2.41/3.19 against 2.27/2.60/3.33), and on
 //            some of the CUs (100 M, k = 8, 16 CUs 2.78 against 3.39)
+//   workspace too small for a partial per 512 elements: up to 3 streams runs of 512-element tiles, else 4096-element tiles
+//            one after another, two loads in flight either way (500 M, k = 1 / 3 / 8 / 16  0.49/0.80/1.71/3.15 ms in runs,
+//            0.67/0.87/1.61/2.99 in wide tiles, 0.68/0.86/1.63/3.13 with four or eight in flight)
 //   else the shape as before (12.6 M  24.1/29.4/44.8/76.3; 2 elements per lane lose 3-40 % there)
 static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
@@ -966,8 +969,8 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
     if (n <= (A.k <= 16 ? GS_STAGED_WIDE_MAX : GS_STAGED_WIDE_MANY_MAX) && !(cus > 0 && n / cus >= GS_BUDGET_RUN_MIN))
         return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
     if (tiles_of(A.begin, A.end, 512) > cap) {
-        if (A.k < 8) return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
-        return launch_staged<1024, 4, 8>(A, cap, d_out, accumulate, stream);
+        if (A.k <= 3) return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);
+        return launch_staged<1024, 4, 2>(A, cap, d_out, accumulate, stream);
     }
     if (A.k >= 8 && A.k % 4 == 0 && n >= GS_STAGED_PAIR_MIN && !on_cu_budget(stream))
         return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);

@@ -123,3 +123,11 @@ def test_staged_norm_takes_wide_workgroups_in_the_middle(rec):
                 l = work_of(rec, "staged", k, 0, length, ws=FULL, cus=cus)
                 wide = length <= (1 << 22 if k <= 16 else 1 << 20) and not (cus < 256 and k < 8 and length >= 49_152 * cus)
                 assert l.targs[:3] == ((1024, 4, 4) if wide else (64, 4, 2) if k <= 8 else (128, 4, 2)), (k, cus, length)
+
+
+def test_staged_norm_with_a_small_workspace(rec):
+    for length in (1 << 27, (1 << 27) + 1, 500_000_000, 1 << 32):
+        for k in range(1, 33):
+            l = work_of(rec, "staged", k, 0, length, ws=MIN_WS)
+            if length > 1 << 27:                   # no room for a partial per 512 elements
+                assert l.targs[:3] == ((128, 4, 2) if k <= 3 else (1024, 4, 2))

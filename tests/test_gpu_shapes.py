@@ -57,7 +57,7 @@ def test_step_and_staged_step_at_shape_edges(length, k, begin):
         assert torch.equal(a, b)                 # same sum, same update: same bits
 
 
-@pytest.mark.parametrize("k", [1, 9, 32])
+@pytest.mark.parametrize("k", [1, 2, 3, 9, 32])
 @pytest.mark.parametrize("staged", [False, True])
 def test_every_cut_of_short_ranges(k, staged):
     """Begins and ends at every offset within a group, with and without whole groups between them: the

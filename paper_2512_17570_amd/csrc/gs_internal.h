@@ -25,7 +25,7 @@
 #define GS_STAGED_WIDE_MAX (1 << 22)  // elements up to which a workgroup takes 4096 of them
 #define GS_STAGED_WIDE_MANY_MAX (1 << 20)  // the same for more than 16 streams
 #define GS_STAGED_PAIR_MIN (1 << 25)  // elements from which, with 8 streams or more, a lane takes 2 of them
-#define GS_STAGED_KEEP_MAX_K 12       // streams up to which the end of the sum is left in the memory-side cache
+#define GS_STAGED_KEEP_MAX_K 16       // streams up to which the end of the sum is left in the memory-side cache
 #define GS_ADD_SMALL_MAX (1 << 22)    // without the norm: elements up to which both loads are in flight together
 #define GS_ADD_WIDE_MAX (1 << 23)     // with the norm: elements up to which a workgroup takes 4096 of them
 // limits of the norm's shapes (launch_grad_norm)

@@ -840,9 +840,10 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
 //   * On some of the CUs the memory is not the bound, and plain accesses cost 3-7 %.
-//   * The staged norm of more than 12 streams: the reads push the sum out again, and its plain stores cost the
-//     pass 5-9 % (norm + step, us, with the hint against without: k = 12 / 16 / 20 / 32, 12.6 M 124/139/155/202
-//     against 125/141/158/211; 50 M 454/514/577/769 against 449/513/582/793; 201 M 1783/2064/2325/3115 against 1776/2058/2332/3123).
+//   * The staged norm of more than 16 streams: the reads push the sum out again, and its plain stores cost the
+//     pass 4-9 % (norm + step, us, with the hint against without, k = 14 / 16 / 20 / 32: 3.3 M 41.9/43.5/47.8/59.1
+//     against 41.2/42.4/47.2/62.3; 12.6 M 132/139/155/202 against 133/141/159/209; 50 M 492/523/583/781 against
+//     486/520/586/794; 201 M 1940/2070/2328/3115 against 1932/2060/2330/3120).
 static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate, hipStream_t stream)
 {
     if (accumulate || end - begin <= GS_RESIDENT_MAX || on_cu_budget(stream)) return end;

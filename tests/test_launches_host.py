@@ -109,7 +109,7 @@ def test_staged_norm_keeps_its_sum_cached_for_few_streams_only(rec):
         for k in range(1, 33):
             for cus, accumulate in ((256, 0), (256, 1), (64, 0)):
                 l = work_of(rec, "staged", k, 5, 5 + length, ws=FULL, cus=cus, accumulate=accumulate)
-                keeps = k <= 12 and length > 1 << 21 and cus == 256 and not accumulate
+                keeps = k <= 16 and length > 1 << 21 and cus == 256 and not accumulate
                 assert l.keep_from == (5 + length - (64 << 20) if keeps else 5 + length)
                 assert l.targs[3] == keeps
 

@@ -752,8 +752,9 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
 {
     switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream)) {
     case SHAPE_LATENCY:
-        if (A.k <= 8) return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
-        return launch_step<64, 2, STAGED, 16, false, false>(A, stream);
+        if constexpr (!STAGED)
+            if (A.k > 8) return launch_step<64, 2, false, 16, false, false>(A, stream);
+        return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_FEW: return launch_step<128, 2, STAGED, 4, false, false>(A, stream);
@@ -1029,19 +1030,25 @@ hipError_t launch_acc_sqnorm(const float *acc, int64_t begin, int64_t end, doubl
     return launch_acc_norm<1, 256>(acc, begin, end, partials, 8, cap, d_out, accumulate, stream);
 }
 
-template <bool NORM, int BLOCK, int EL, bool LWAIT>
-static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT>
+static hipError_t launch_add_as(const AccumAddArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
     if (tiles < 1) tiles = 1;
     const int64_t span = fit_span(tiles, 1, 1, NORM ? cap : tiles, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    if (first) k_accum_add<true, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
-    else k_accum_add<false, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    k_accum_add<FIRST, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !NORM) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
+}
+
+template <bool NORM, int BLOCK, int EL, bool LWAIT>
+static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    if (first) return launch_add_as<true, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
+    return launch_add_as<false, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
 }
 
 // us per launch, before (64 lanes, the buffer's load after the gradient's) -> now:
@@ -1061,8 +1068,8 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
     if (!d_out) {
         if (n > GS_ADD_SMALL_MAX && !on_cu_budget(stream))
             return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
-        if (first) return launch_add<false, 256, 4, false>(A, first, 0, nullptr, 0, stream);
-        return launch_add<false, 64, 4, false>(A, first, 0, nullptr, 0, stream);
+        if (first) return launch_add_as<true, false, 256, 4, false>(A, 0, nullptr, 0, stream);
+        return launch_add_as<false, false, 64, 4, false>(A, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
     // 1024 lanes and plain stores: the fold waits for the write-back (3.3 M elements: 16.6 us against 13.3)

@@ -7,7 +7,8 @@ import random
 
 import pytest
 
-from launches import FULL, MIN_WS, Recorder, build, check
+from kernel_calls import BEGIN, CALLS
+from launches import FULL, MIN_WS, WORK, Recorder, build, check, parse_name
 
 STEPS = ["step", "oop", "from_acc", "host_step"]
 NORMS = ["norm", "staged", "acc_norm", "add_norm", "spec", "noalloc"]
@@ -131,3 +132,15 @@ def test_staged_norm_with_a_small_workspace(rec):
             l = work_of(rec, "staged", k, 0, length, ws=MIN_WS)
             if length > 1 << 27:                   # no room for a partial per 512 elements
                 assert l.targs[:3] == ((128, 4, 2) if k <= 3 else (1024, 4, 2))
+
+
+def test_the_gpu_tests_calls_reach_every_kernel(rec):
+    """test_gpu_kernels.py runs every kernel of the library, and the library holds none that no call reaches."""
+    names = {parse_name(n) for n in rec.kernels()}
+    reached = set()
+    for entry, k, length, ws, cus, first, accumulate in CALLS:
+        st, launches, _, _ = rec.call(entry, k, BEGIN, BEGIN + length, FULL if ws == "full" else MIN_WS, accumulate=accumulate, first=first, cus=cus)
+        assert st == 0
+        reached |= {(l.kernel, l.targs) for l in launches}
+    assert {n for n in names if n[0] in WORK} - reached == set()
+    assert len(names) == len(reached)              # the two folds too

@@ -1021,11 +1021,12 @@ def test_staged_and_speculative_fast_shapes_with_large_workspace(k):
 
 
 def test_workspace_size_picks_the_shape_not_the_result():
-    """The norm-carrying kernels have three shapes (one 256-element tile per single-wave workgroup,
-    one 512-element tile per two-wave workgroup, 4096-element tiles with several per workgroup) and
-    take the fastest one whose partials fit the workspace.  On a range large enough that the
-    minimum workspace forces the third, all three must leave the same bits (the norm: the same
-    value up to fp64 summation order), and those bits are the fused step's with c = 1."""
+    """The norm-carrying kernels leave a partial per workgroup and choose their tiles, and how many
+    of them a workgroup takes, by the partials that the workspace holds.  On a range for which the
+    minimum workspace holds no partial per 512 elements, and the one in the middle none per 256, all
+    three workspaces must give the same bits (the norm: the same value up to fp64 summation order), and
+    those bits are the fused step's with c = 1.  (One stream; test_gpu_kernels.py has the kernels that
+    more streams take.)"""
     n, k = 140_000_003, 1
     g = torch.Generator(device=DEV).manual_seed(77)
     p = torch.randn(n, device=DEV, generator=g) * 0.02

@@ -83,18 +83,18 @@ def test_every_cut_of_short_ranges(k, staged):
             untouched(got, (case.p, case.m, case.v, case.w), b, e)
 
 
+# (with the smallest workspace, which holds a partial per 256 elements up to 67 M: test_gpu_kernels.py has
+# longer ranges with both workspaces)
 @pytest.mark.parametrize("length,k", EDGES + [(RESIDENT, 2), (FEW, 16), (FEW + 1, 12)])
-@pytest.mark.parametrize("big_ws", [False, True])
-def test_speculative_step_at_shape_edges(length, k, big_ws):
+def test_speculative_step_at_shape_edges(length, k):
     begin, n = 5, length + 9
     case = DeviceCase(n, k, seed=length % 89 + k)
     e = begin + length
-    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(n), dtype=torch.uint8, device=DEV) if big_ws else case.ws
     want = case.oracle_step(HP, 1.0, begin, e)
     out = [torch.full((n,), 7.0, device=DEV) for _ in range(3)] + [torch.zeros_like(case.w)]
     before = [x.clone() for x in out]
     case.sq.fill_(float("nan"))                  # overwritten, not added to
-    gs.gs_accum_adamw_spec(case.p, case.m, case.v, *out, case.grads, begin, e, HP, case.sq, ws)
+    gs.gs_accum_adamw_spec(case.p, case.m, case.v, *out, case.grads, begin, e, HP, case.sq, case.ws)
     check(out, want, begin, e, "spec")
     untouched(out, before, begin, e)
     S = O.grad_sqnorm(case.h_g, begin, e)
@@ -127,7 +127,7 @@ NORM_SIZES = [1, 3, 4096, 4097, 16384, 16385, (1 << 20), (1 << 20) + 1, (1 << 21
 
 
 @pytest.mark.parametrize("length", NORM_SIZES)
-@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 16, 23])
+@pytest.mark.parametrize("k", [1, 2, 3, 4, 5, 8, 16, 23])
 @pytest.mark.parametrize("begin", [0, 7])
 def test_norms_at_shape_edges(length, k, begin):
     e = begin + length
@@ -151,15 +151,12 @@ def test_norms_at_shape_edges(length, k, begin):
     assert float(case.sq.item()) == 0.0           # an empty range writes 0, or adds nothing
 
 
-# the adding and the staged kernels' lines (2^19, 2^22, 2^23, 2^25), with a workspace for every partial and
-# with the smallest one
+# the adding and the staged kernels' lines (2^19, 2^22, 2^23, 2^25) with the smallest workspace, as above
 @pytest.mark.parametrize("length,k", [(1, 3), (LATENCY, 8), (LATENCY + 1, 5), ((1 << 22) + 2, 9), ((1 << 22) + 3, 2),
                                       ((1 << 23) + 1, 4), ((1 << 25) + 5, 8)])
-@pytest.mark.parametrize("big_ws", [False, True])
-def test_staged_and_adding_kernels_at_shape_edges(length, k, big_ws):
+def test_staged_and_adding_kernels_at_shape_edges(length, k):
     begin, e = 3, 3 + length
     case = DeviceCase(e + 2, k, seed=length % 79 + k, keep_host=False)
-    ws = torch.empty(gs.gs_sqnorm_workspace_bytes_for(length), dtype=torch.uint8, device=DEV) if big_ws else case.ws
     want = torch.zeros(e - begin, dtype=torch.float32, device=DEV)
     for g in case.grads:
         want += g[begin:e].float()                # fp32, in order: the exact same sum
@@ -168,11 +165,11 @@ def test_staged_and_adding_kernels_at_shape_edges(length, k, big_ws):
         acc = torch.full((case.n,), 5.0, device=DEV)
         case.sq.fill_(float("nan"))
         if staged:
-            gs.gs_grad_accum_sqnorm(case.grads, begin, e, acc, case.sq, ws)
+            gs.gs_grad_accum_sqnorm(case.grads, begin, e, acc, case.sq, case.ws)
         else:
             for j, g in enumerate(case.grads):
                 last = j == k - 1
-                gs.gs_accum_add(acc, g, j == 0, begin, e, case.sq if last else None, ws if last else None)
+                gs.gs_accum_add(acc, g, j == 0, begin, e, case.sq if last else None, case.ws if last else None)
         assert torch.equal(acc[begin:e], want)
         assert bool((acc[:begin] == 5.0).all()) and bool((acc[e:] == 5.0).all())
         assert abs(float(case.sq.item()) - S) <= 1e-12 * S       # two fp64 trees over exact squares

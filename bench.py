@@ -748,8 +748,10 @@ def _kernel_entry(ms, bytes_per_param, n):
 def same_mix_ceiling(torch, grads, p, m, v, w, n, k, reps, block):
     """What this device gives the fused step's own mix of streams (k bf16 + 3 fp32 in, 3 fp32 + 1 bf16
     out) when no arithmetic is attached: the probe kernels of probe/gs_mixprobe.hip, out of place
-    into scratch outputs.  (a) the step kernel's shape; (b) the same tile with all loads in flight;
-    (c) the read half and the write half as two kernels running at once on two streams."""
+    into scratch outputs.  (a) 2 elements per lane, four gradient loads in flight: the shape the step
+    takes on long ranges (from 2^27 elements on with 8 streams or more); (b) 4 elements per lane, one load
+    at a time; (c) 4 elements per lane, all loads in flight; (d) the read half and the write half as two
+    kernels running at once on two streams."""
     from paper_2512_17570_amd import mixprobe as MP
 
     dev = p.device
@@ -775,7 +777,8 @@ def same_mix_ceiling(torch, grads, p, m, v, w, n, k, reps, block):
             out.append(e0.elapsed_time(e1))
         return out
 
-    fused = timed_one(MP.FUSED_SHALLOW, block)
+    pairs = timed_one(MP.FUSED_PAIRS, 128)
+    shallow = timed_one(MP.FUSED_SHALLOW, block)
     deep = timed_one(MP.FUSED_ALL_IN_FLIGHT, 256)
     rd = timed_one(MP.READ_HALF, block)
     wr = timed_one(MP.WRITE_HALF, block)
@@ -798,12 +801,13 @@ def same_mix_ceiling(torch, grads, p, m, v, w, n, k, reps, block):
     def gbs(ms):
         return total / (_stats(ms)["avg_ms"] * 1e-3) / 1e9
     r_ms, w_ms = _stats(rd)["avg_ms"], _stats(wr)["avg_ms"]
-    res = {"same_mix_step_shape_GBps": gbs(fused), "same_mix_all_loads_in_flight_GBps": gbs(deep),
+    res = {"same_mix_pairs_GBps": gbs(pairs), "same_mix_one_load_at_a_time_GBps": gbs(shallow),
+           "same_mix_all_loads_in_flight_GBps": gbs(deep),
            "same_mix_read_kernel_beside_write_kernel_GBps": gbs(pair),
            "read_half_alone_GBps": n4 * (2 * k + 12) / (r_ms * 1e-3) / 1e9,
            "write_half_alone_GBps": n4 * 14 / (w_ms * 1e-3) / 1e9,
            "read_then_write_serial_GBps": total / ((r_ms + w_ms) * 1e-3) / 1e9}
-    res["same_mix_ceiling_GBps"] = max(res["same_mix_step_shape_GBps"], res["same_mix_all_loads_in_flight_GBps"])
+    res["same_mix_ceiling_GBps"] = max(res[f"same_mix_{s}_GBps"] for s in ("pairs", "one_load_at_a_time", "all_loads_in_flight"))
     return res
 
 
@@ -997,7 +1001,7 @@ def bench_resident(args, wl, full=True):
                   "note": "measured here after the timed region: torch's device-to-device copy of one fp32 state array "
                           "(bytes read + written), a read-only pass (gs_acc_sqnorm)"}
     if not args.no_ceiling:
-        block = 128 if k >= 15 else 64           # the step kernel's own workgroup size for this k
+        block = 128 if k >= 15 else 64           # of the 4-element kernels: what is best for this k
         try:
             mix = same_mix_ceiling(torch, grads, p, m, v, w, n, k, max(4, args.steps // 2), block)
         except Exception as exc:                 # the probe library is an extra: its absence must not cost the line
@@ -1008,8 +1012,9 @@ def bench_resident(args, wl, full=True):
         achievable["frac_of_same_mix"] = achieved / mix["same_mix_ceiling_GBps"]
         achievable["frac_of_read_kernel_beside_write_kernel"] = achieved / mix["same_mix_read_kernel_beside_write_kernel_GBps"]
         achievable["note"] += ("; and kernels with the step's own mix of streams and no arithmetic (probe/gs_mixprobe.hip): "
-                               "in the step kernel's shape and with all loads in flight (same_mix_ceiling = the better of "
-                               "the two single kernels), and split into a read-only kernel running beside a write-only "
+                               "2 elements per lane with four gradient loads in flight (the step kernel's main shape), 4 elements "
+                               "per lane with one load at a time and with all in flight (same_mix_ceiling = the best of these "
+                               "single kernels), and split into a read-only kernel running beside a write-only "
                                "kernel on a second stream (the same bytes issued from separate workgroups)")
     out["roofline"]["achievable"] = achievable
     out["staged_two_pass"] = {

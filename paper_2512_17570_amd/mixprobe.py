@@ -20,7 +20,7 @@ _lib.gs_mixprobe_launch.argtypes = [ctypes.c_int, ctypes.c_int, _vp, _vp, _vp, _
                                     ctypes.POINTER(_vp), ctypes.c_int, ctypes.c_int64, ctypes.c_uint32, _vp, _vp]
 _lib.gs_mixprobe_launch.restype = ctypes.c_int
 
-FUSED_SHALLOW, FUSED_ALL_IN_FLIGHT, READ_HALF, WRITE_HALF = 0, 1, 2, 3
+FUSED_SHALLOW, FUSED_ALL_IN_FLIGHT, READ_HALF, WRITE_HALF, FUSED_PAIRS = 0, 1, 2, 3, 4
 
 
 def launch(mode: int, block: int, p, m, v, po, mo, vo, w, grads, n: int, sink, stream) -> None:

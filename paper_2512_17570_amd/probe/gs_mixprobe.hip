@@ -3,14 +3,16 @@
 // and one bf16 stream out, 2k+26 bytes per element) and no arithmetic beyond what keeps the
 // compiler from dropping the accesses.  bench.py times them next to gs_accum_adamw so that the
 // step's bandwidth can be held against what the same device gives the same mix of streams:
-//   mode 0  the step kernel's shape for few streams (4 elements per lane) without its arithmetic: one tile per workgroup, the
-//           three state loads first, gradient loads one at a time, the four stores one by one;
+//   mode 0  4 elements per lane, one tile per workgroup: the three state loads first, gradient loads
+//           one at a time, the four stores one by one;
 //   mode 1  the same tile with every load in flight at once and the stores back to back;
 //   mode 2  the read half only (the 2k+12 bytes in), loads one at a time;
-//   mode 3  the write half only (the 14 bytes out), stores one by one.
+//   mode 3  the write half only (the 14 bytes out), stores one by one;
+//   mode 4  the step kernel's main shape without its arithmetic: 2 elements per lane, the three state
+//           loads first, gradient loads in batches of four, the four stores one by one.
 // Modes 2 and 3 launched together on two streams put the same bytes on the memory system from
-// separate workgroups: if that pair is no faster than mode 0, the mix itself -- not the way one
-// kernel interleaves its loads and stores -- sets the rate.
+// separate workgroups: if that pair is no faster than a single kernel, the mix itself -- not the way
+// one kernel interleaves its loads and stores -- sets the rate.
 //
 // Outputs are written out of place (po/mo/vo/w), so the caller's states survive; with mask = 0 the
 // values written are the values read.  Built into its own shared library; libgs.so does not
@@ -97,6 +99,47 @@ __global__ __launch_bounds__(BLOCK) void k_mix(MixArgs A)
     st_stream(reinterpret_cast<u32x2 *>(A.w + lo), wv);
 }
 
+template <int BLOCK>
+__global__ __launch_bounds__(BLOCK) void k_mix_pairs(MixArgs A)
+{
+    const int64_t lo = ((int64_t)blockIdx.x * BLOCK + threadIdx.x) * 2;
+    if (lo >= A.n) return;
+    u32x2 p = ld_stream(reinterpret_cast<const u32x2 *>(A.p + lo));
+    u32x2 m = ld_stream(reinterpret_cast<const u32x2 *>(A.m + lo));
+    u32x2 v = ld_stream(reinterpret_cast<const u32x2 *>(A.v + lo));
+    uint32_t acc = 0;
+    int j = 0;
+#pragma unroll 1
+    for (; j + 4 <= A.k; j += 4) {
+        uint32_t g[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) g[q] = ld_stream(reinterpret_cast<const uint32_t *>(A.g[j + q] + lo));
+#pragma unroll
+        for (int q = 0; q < 4; ++q) acc ^= g[q];
+    }
+#pragma unroll 1
+    for (; j < A.k; ++j) acc ^= ld_stream(reinterpret_cast<const uint32_t *>(A.g[j] + lo));
+    const uint32_t t = acc & A.mask;                  // 0 at run time
+    p.x ^= t; m.y ^= t; v.x ^= t;
+    const uint32_t w = (p.x >> 16) | (p.y & 0xffff0000u);
+    __builtin_amdgcn_sched_barrier(0);
+    st_stream(reinterpret_cast<u32x2 *>(A.po + lo), p);
+    wait_vm_idle();
+    st_stream(reinterpret_cast<u32x2 *>(A.mo + lo), m);
+    wait_vm_idle();
+    st_stream(reinterpret_cast<u32x2 *>(A.vo + lo), v);
+    wait_vm_idle();
+    st_stream(reinterpret_cast<uint32_t *>(A.w + lo), w);
+}
+
+hipError_t launch_pairs(const MixArgs &A, int block, hipStream_t s)
+{
+    const int64_t tiles = (A.n / 2 + block - 1) / block;
+    if (block != 128 || tiles < 1 || tiles * block > 0xffffffffLL) return hipErrorInvalidValue;
+    k_mix_pairs<128><<<(int)tiles, 128, 0, s>>>(A);
+    return hipGetLastError();
+}
+
 template <int MODE>
 hipError_t launch(const MixArgs &A, int block, hipStream_t s)
 {
@@ -113,13 +156,13 @@ hipError_t launch(const MixArgs &A, int block, hipStream_t s)
 
 // Returns 0, -1 for a rejected argument, or the hipError_t of a failed launch.  All tensor pointers
 // are device addresses, 16-byte aligned; n is a multiple of 4; grads is a host table of k device
-// pointers; block is 64, 128 or 256 lanes per workgroup; sink is a device word (mode 2).
+// pointers; block is 64, 128 or 256 lanes per workgroup (mode 4: 128); sink is a device word (mode 2).
 extern "C" int gs_mixprobe_launch(int mode, int block, const float *p, const float *m, const float *v,
                                   float *po, float *mo, float *vo, uint16_t *w,
                                   const uint16_t *const *grads, int k, int64_t n,
                                   uint32_t mask, uint32_t *sink, void *stream)
 {
-    if (mode < 0 || mode > 3 || k < 1 || k > kMaxK || n < 4 || (n & 3)) return -1;
+    if (mode < 0 || mode > 4 || k < 1 || k > kMaxK || n < 4 || (n & 3)) return -1;
     if (!grads || !sink) return -1;
     if (mode != 3 && (!p || !m || !v)) return -1;
     if (mode != 2 && (!po || !mo || !vo || !w)) return -1;
@@ -148,6 +191,7 @@ extern "C" int gs_mixprobe_launch(int mode, int block, const float *p, const flo
     case 0: e = launch<0>(A, block, s); break;
     case 1: e = launch<1>(A, block, s); break;
     case 2: e = launch<2>(A, block, s); break;
+    case 4: e = launch_pairs(A, block, s); break;
     default: e = launch<3>(A, block, s); break;
     }
     return (int)e;

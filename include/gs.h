@@ -345,7 +345,7 @@ int gs_stream_ctx_copies_overlap(const gs_stream_ctx *ctx);
 /*
  * In place: the context owns one stream, and the step kernel runs on the pinned host arrays
  * themselves -- each wave loads its tile of p, m, v over the link, updates it and stores it
- * back.  Nothing is staged in device memory and no copy engine is used: 46-47 GB/s each way,
+ * back.  Nothing is staged in device memory and no copy engine is used: 46-49 GB/s each way,
  * whatever else the process does with copies and streams.  num_cus = 0: an ordinary stream;
  * num_cus > 0: a stream confined to that many compute units, as from gs_cu_stream_create (the
  * link, not the CU count, bounds this step: 16 CUs sustain the full rate and leave the rest of

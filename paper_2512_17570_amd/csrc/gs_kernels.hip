@@ -350,9 +350,9 @@ __device__ __forceinline__ void step_one(const StepArgs &A, int64_t i)
 // and a wave's accesses stay line-aligned for any `begin` (a split point in the middle of a layer
 // would otherwise make every wave straddle two extra lines).
 // The elements of groups that a range end cuts (at most EL-1 at each end) are workgroup 0's (`cuts` = 1),
-// one lane each: in the wave of their neighbours they would come after its whole groups, and the range
-// would end one memory latency later (us, k = 1 / 8 / 32: 100 001 elements 3.5/4.0/7.2 -> 2.9/3.0/4.2, 1 000 001
-// elements 6.3/9.7/19.9 -> 5.8/8.9/17.0; from 3 M on within 2 %).
+// one lane each: in the wave of their neighbours they come after its whole groups, and the range
+// ends one memory latency later (us, k = 1 / 8 / 32: 100 001 elements 2.9/3.0/4.2 against 3.5/4.0/7.2 there, 1 000 001
+// elements 5.8/8.9/17.0 against 6.3/9.7/19.9; from 3 M on within 2 %).
 template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 {
@@ -799,8 +799,9 @@ static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, 
 }
 
 // The step's shapes with a partial per workgroup; a wave reduction per 128 or 256 elements moves the
-// lines a little (us or ms per launch, before = one load at a time, 4 elements per lane, 64 lanes):
-//   * up to 2 streams the shallow 64-lane shape stays (50 M, k = 1: 226 us against 239);
+// lines a little (us or ms per launch, each against the shallow shape: one load at a time, 4 elements per lane,
+// 64 lanes):
+//   * up to 2 streams the shallow shape itself (50 M, k = 1: 226 us against 239 with four loads in flight);
 //   * up to 7 M elements everything in flight, 256 lanes: 600 k, k = 3 / 8 / 16: 7.7/8.9/11.0 against
 //     9.7/11.9/16.3;
 //   * then 128 lanes with four loads in flight: 4 elements per lane (12.6 M, k = 3 / 8: 71.5/91.8
@@ -833,11 +834,19 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 // Where a pass leaves its lines in the 256 MB memory-side cache.  A step reads again what the norm has
 // just read (the gradients, or their fp32 sum), and the adding kernel what it wrote a micro-batch ago.
 // Accesses with the non-temporal hint hit lines that are in that cache but put none there, so if only the
-// last 256 MB of the re-read stream are accessed without it, they stay until the next pass.  norm + step,
-// us, with the hint everywhere -> now: 3.3 M k=3 32.8 -> 31.9, 12.6 M k=4 93.7 -> 89.2, 50 M k=8 457 -> 444,
-// 805 M k=16 11.23 -> 11.13 ms; fp32 norm + step 50 M 276 -> 264, 201 M 1058 -> 1042; adding a micro-batch
-// 50 M 79.0 -> 74.5.  192 and 320 MB gain less (201 M: 1749 and 1747 us against 1745).
-//   * Up to 2^21 elements the lines are there anyway, and plain accesses cost 2-3 %.
+// last 256 MB of the re-read stream are accessed without it, they stay until the next pass.  The two passes
+// together gain (us, plain against with the hint everywhere):
+//   norm + step, k = 1 / 3 / 8 / 16 / 32   6 M 36/42/59/87/143 against 37/45/62/92/155, 50 M 242/290/440/679/1203 against
+//                                        250/305/448/692/1221, 805 M k = 16 11.13 ms against 11.23
+//   fp32 norm + step                     50 M 255 against 268, 201 M 1031 against 1057
+//   8 micro-batches added, then the step   12.6 M 216 against 229, 50 M 766 against 832
+// and the first of them pays, which a caller feels who takes only that one or goes on elsewhere:
+//   norm alone, k = 8 / 16 / 32            6 M 20.7/36.8/66.4 against 18.9/32.2/61.3, 50 M 127/237/471 against 122/231/466
+//   fp32 norm alone                      50 M 37.5 against 34.4;  first micro-batch alone 5 M 8.7 against 7.3, 50 M 51 against 49
+// 192 and 320 MB gain less than 256 (norm + step, 201 M: 1749 and 1747 us against 1745).  Not done:
+//   * Up to 2^21 elements, so that the norm of a small range does not pay: 2 M, k = 8 / 16 / 32 on its own 10.0/14.8/24.4 us
+//     against 10.3/15.8/26.4 plain.  (With the step plain accesses would gain there too, 26.4/36.2/55.5 against
+//     24.3/34.1/53.4; the line is one of elements, not the bytes at which the pair breaks even.)
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
 //   * On some of the CUs the memory is not the bound, and plain accesses cost 3-7 %.
@@ -886,17 +895,19 @@ static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap
     return launch_norm<K, 1, 512>(A, run, cap, d_out, accumulate, stream);
 }
 
-// Up to four 4096-element tiles (one, from 5 streams on) a single workgroup has everything in flight at
-// once and no fold has to follow (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).
+// Up to four 4096-element tiles (one, from 5 streams on) a single workgroup reads the range and no fold has to
+// follow (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).  The lanes whose groups lie in all four
+// tiles have them in flight together; in a range that ends before, the others take them one after another.
 // Above that: with up to 4 streams 256 lanes and one group of U tiles up to 4 M elements, 512 lanes and
 // two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %); one stream is best in 256
 // lanes at every size.  From 5 streams on the workgroups grow with the range, so that they are many
 // enough to fill the chip and no more: 256, 512 and 1024 lanes up to 2^20, 2^21 and 2^23 elements (8 M,
-// k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, before (256 lanes, 8 tiles one
-// after another; k = 3, 7 and 32 in batches of 4, 2 and 1 loads) -> now:
-//   100 k  k = 1/3/8/32  3.5/6.3/8.1/38 -> 2.4/2.6/3.3/4.5      12.6 M  8.4/15.8/35.4/151 -> 6.2/14.0/33.0/127
-//   1 M    k = 1/3/8/32  5.8/10.6/8.6/40 -> 2.9/3.4/5.2/11.9    201 M   89/191/474/1932 -> 61/176/466/1882
-//   3.3 M  k = 1/3/8/32  6.5/11.5/11.0/51 -> 4.0/5.4/11.0/37    805 M   347/737/1851/7903 -> 231/713/1848/7849
+// k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, these shapes against 256 lanes with 8 tiles
+// one after another (k = 3, 7 and 32 in batches of 4, 2 and 1 loads):
+//   100 k  k = 1/3/8/32  2.4/2.6/3.3/4.5 against 3.5/6.3/8.1/38     12.6 M  6.2/14.0/33.0/127 against 8.4/15.8/35.4/151
+//   1 M    k = 1/3/8/32  2.9/3.4/5.2/11.9 against 5.8/10.6/8.6/40   201 M   61/176/466/1882 against 89/191/474/1932
+//   3.3 M  k = 1/3/8/32  4.0/5.4/11.0/37 against 6.5/11.5/11.0/51   805 M   231/713/1848/7849 against 347/737/1851/7903
+// (all reads with the non-temporal hint; keep_from says what leaving them in the cache costs)
 //   On some of the CUs, 4 to 7 streams: once each CU has some tens of thousands of elements to read, 256 lanes,
 //   four loads in flight and eight tiles one after another (k = 4 / 5, 50 M elements: 16 CUs 523/694 us against
 //   651/860 in the shapes below, 128 CUs 84/110 against 97/122; 3.3 M on 128 CUs, 26 k elements each, 11.6/16.2
@@ -953,22 +964,21 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
 
-// One tile per workgroup wherever the partials fit.  us per launch, before (two gradient loads in
-// flight, 64 lanes up to 8 streams, 128 beyond) -> now, k = 2 / 4 / 8 / 16:
-//   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.1/5.7/6.6/8.7 -> 5.0/5.1/5.6/6.4
-//   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  9.0/10.3/12.4/16.3 -> 7.0/8.4/10.4/15.4.
+// One tile per workgroup wherever the partials fit.  The plain shape has two gradient loads in flight, 4 elements per
+// lane, 64 lanes up to 8 streams and 128 beyond; us per launch, k = 2 / 4 / 8 / 16, against it:
+//   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.0/5.1/5.6/6.4 against 5.1/5.7/6.6/8.7
+//   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  7.0/8.4/10.4/15.4 against 9.0/10.3/12.4/16.3.
 //            More than 16 streams only up to 2^20 (600 k, k = 20 / 32  9.1/11.7 against 11.0/14.6; 1.5 M 15.9/22.2
 //            against 14.9/20.0), and on some of the CUs fewer than 8 streams only up to 48 k elements per CU, from
-//            where the many small workgroups win (16 CUs, k = 1 / 2 / 4: 1 M 14.9/16.0/22.9 against 16.6/18.7/25.6,
-//            3.3 M 51/57/72 against 57/64/77; 64 CUs, 1 M 8.3/8.5/10.5 against 7.7/8.2/9.9)
+//            where the many small workgroups win (16 CUs, k = 1 / 2 / 4: 1 M 16.6/18.7/25.6 against 14.9/16.0/22.9,
+//            3.3 M 57/64/77 against 51/57/72; 64 CUs, 1 M 7.7/8.2/9.9 against 8.3/8.5/10.5)
 //   >= 2^25, 8 streams or more and a multiple of 4: 2 elements per lane, 256 lanes, four in flight: 617 M, k = 8 / 12 /
-//            16 / 20  1.92/2.70/3.53/4.39 ms against 1.93/2.75/3.59/4.43 in the shape below.  With streams left over
-//            after the batches of four that one wins (k = 9 / 10 / 14  2.14/2.41/3.19 against 2.27/2.60/3.33), and on
-//            some of the CUs (100 M, k = 8, 16 CUs 2.78 against 3.39)
+//            16 / 20  1.92/2.70/3.53/4.39 ms against 1.93/2.75/3.59/4.43.  With streams left over
+//            after the batches of four the plain shape wins (k = 9 / 10 / 14  2.14/2.41/3.19 against 2.27/2.60/3.33), and on
+//            some of the CUs (100 M, k = 8, 16 CUs 2.78 against 3.39); so it does below 2^25, where 2 elements lose 3-40 %
 //   workspace too small for a partial per 512 elements: up to 3 streams runs of 512-element tiles, else 4096-element tiles
 //            one after another, two loads in flight either way (500 M, k = 1 / 3 / 8 / 16  0.49/0.80/1.71/3.15 ms in runs,
 //            0.67/0.87/1.61/2.99 in wide tiles, 0.68/0.86/1.63/3.13 with four or eight in flight)
-//   else the shape as before (12.6 M  24.1/29.4/44.8/76.3; 2 elements per lane lose 3-40 % there)
 static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t n = A.end - A.begin;
@@ -1051,13 +1061,13 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
     return launch_add_as<false, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
 }
 
-// us per launch, before (64 lanes, the buffer's load after the gradient's) -> now:
-//   first micro-batch, <= 2^22: 256 lanes               1 M 3.2 -> 2.6, 2 M 4.4 -> 3.6; level with 64 above
+// us per launch, each against 64 lanes with the buffer's load after the gradient's:
+//   first micro-batch, <= 2^22: 256 lanes               1 M 2.6 against 3.2, 2 M 3.6 against 4.4; level above
 //   later ones, <= 2^22 or on some of the CUs only: both loads in flight
-//                                                      1 M 3.7 -> 3.2, 2 M 5.2 -> 4.9; from 200 M on waiting
-//                                                       is 0.5 % ahead, level in between
+//                                                      1 M 3.2 against 3.7, 2 M 4.9 against 5.2; from 200 M on
+//                                                       waiting is 0.5 % ahead, level in between
 //   with the norm: both loads in flight; 256 lanes up to 2^19, 1024 up to 2^23 (fewer partials), then 64:
-//                                                       2 M 9.7 -> 7.5, 12.6 M 26.2 -> 25.1, 201 M 320 -> 306
+//                                             2 M 7.5 against 9.7, 12.6 M 25.1 against 26.2, 201 M 306 against 320
 //   with a workspace too small for a partial per 256 elements, per 1024 or 4096.
 hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspace_bytes, double *d_out, int accumulate,
                             hipStream_t stream)
@@ -1072,7 +1082,7 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
         return launch_add_as<false, false, 64, 4, false>(A, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
-    // 1024 lanes and plain stores: the fold waits for the write-back (3.3 M elements: 16.6 us against 13.3)
+    // 1024 lanes and plain stores: the fold waits for the write-back (3.3 M elements: 16.6 us against 13.3 with the hint)
     if (accumulate || n <= GS_ADD_WIDE_MAX) A.keep_from = A.end;
     if (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 256) <= cap)
         return launch_add<true, 64, 4, false>(A, first, cap, d_out, accumulate, stream);

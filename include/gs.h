@@ -345,11 +345,11 @@ int gs_stream_ctx_copies_overlap(const gs_stream_ctx *ctx);
 /*
  * In place: the context owns one stream, and the step kernel runs on the pinned host arrays
  * themselves -- each wave loads its tile of p, m, v over the link, updates it and stores it
- * back.  Nothing is staged in device memory and no copy engine is used: 46-49 GB/s each way,
+ * back.  Nothing is staged in device memory and no copy engine is used: 46-50 GB/s each way,
  * whatever else the process does with copies and streams.  num_cus = 0: an ordinary stream;
  * num_cus > 0: a stream confined to that many compute units, as from gs_cu_stream_create (the
- * link, not the CU count, bounds this step: 16 CUs sustain the full rate and leave the rest of
- * the GPU to other work).  num_cus < 0, or outside gs_cu_stream_create's range when positive, is
+ * link bounds this step, so 16 CUs give 47 of the 50 GB/s that all of them reach and leave the
+ * rest of the GPU to other work).  num_cus < 0, or outside gs_cu_stream_create's range when positive, is
  * GS_ERR_INVALID_ARG.
  */
 gs_status gs_stream_ctx_create_inplace(gs_stream_ctx **out, int num_cus);

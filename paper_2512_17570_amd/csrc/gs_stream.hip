@@ -8,7 +8,7 @@
 // wave loads its tile of p/m/v over the link, updates it and stores it back, thousands of waves
 // at different stages at any time.  Nothing is staged in HBM and no copy engine is involved.
 // Measured on MI355X, k = 8: 46-47 GB/s each way at once on a stream confined to 16 of the 256 CUs (12.6 M to
-// 100 M parameters), 48-49 on 32 CUs (805 M), the same whatever copy traffic the process ran before.
+// 805 M parameters), 50 on 64 or all of them, the same whatever copy traffic the process ran before.
 //
 // Staged (gs_stream_ctx_create).  Chunk c+1 is uploaded by hipMemcpyAsync into one of `slots` staging slots in HBM while
 // the kernel updates chunk c there and chunk c-1 is copied back: three streams, events per slot.

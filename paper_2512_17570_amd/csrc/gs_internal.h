@@ -10,10 +10,12 @@
 // limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
 #define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
 #define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
-#define GS_FEW_MAX 7000000            // elements up to which stores go out back to back
-#define GS_SERIAL_MIN (1 << 27)       // elements from which few gradient streams are taken one load at a time
-#define GS_SERIAL_MAX_K 7             // "few gradient streams"
-#define GS_SPEC_SERIAL_MIN 80000000   // GS_SERIAL_MIN of the speculative pass
+#define GS_DEEP_MAX (1 << 25)         // elements up to which 8 gradient loads are in flight from 5 streams on
+#define GS_SERIAL_MAX_K 7             // streams up to which waves take one load at a time where that wins
+#define GS_LDS_GRANULES 128           // a CU's 160 KB of LDS are handed out in this many pieces
+#define GS_LDS_GRANULE_BYTES 1280
+#define GS_SPEC_FEW_MAX 7000000       // speculative pass: elements up to which everything is in flight
+#define GS_SPEC_SERIAL_MIN 80000000   // and from which few streams are taken one load at a time
 #define GS_SPEC_RUN_MAX (1 << 28)     // small workspace, few streams: elements up to which 512-element tiles are run
 #define GS_KEEP_BYTES ((int64_t)256 << 20)  // of a re-read stream: left in the memory-side cache (keep_from)
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels

@@ -11,7 +11,9 @@
 //   * workgroups are NOT persistent: one 256-element tile per workgroup, dispatched in order, keeps
 //     the set of addresses in flight compact, which HBM rewards (a grid-stride loop costs 30-40 %
 //     on stores on this part);
-//   * up to four gradient loads of a wave are in flight; its four stores go out one by one;
+//   * the bytes in flight are held to what HBM serves best, by how many workgroups a CU may hold
+//     (room_for) and not by making waves wait between their accesses; stores go out back to back and are
+//     written through;
 //   * ranges that do not fill the chip are bound by the latency of a wave's serial chain instead,
 //     and take shapes that put every load in flight (step_shape);
 //   * every stream is touched once, so loads and stores carry the non-temporal hint.
@@ -56,6 +58,20 @@ __device__ __forceinline__ void st_stream(T *p, T v)
 {
     if constexpr (KEEP) *p = v;
     else __builtin_nontemporal_store(v, p);
+}
+
+// THROUGH: with the hint and past its XCD's L2 too, which otherwise keeps the line dirty and sends it out
+// later, in an order of its own (step, 805 M, k = 16, no other change: 7.39 ms against 7.50; 201 M, k = 8: 1289 us
+// against 1307).  No builtin gives this pair of cache bits.  A store of more than 64 bits goes on reading its
+// registers for up to two cycles, in which none may be written: hence the s_nop.
+template <bool THROUGH, typename T>
+__device__ __forceinline__ void st_once(T *p, T v)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8 || sizeof(T) == 16, "dword, dwordx2 or dwordx4");
+    if constexpr (!THROUGH) st_stream(p, v);
+    else if constexpr (sizeof(T) == 4) asm volatile("global_store_dword %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+    else if constexpr (sizeof(T) == 8) asm volatile("global_store_dwordx2 %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+    else asm volatile("global_store_dwordx4 %0, %1, off sc1 nt\n\ts_nop 1" ::"v"(p), "v"(v) : "memory");
 }
 
 // body(true_type) in a workgroup whose elements are to be kept, else body(false_type): the choice is
@@ -242,8 +258,9 @@ __device__ __forceinline__ double block_sum(double x, double *lds)
 // from A.p/m/v and written to A.po/mo/vo (the same arrays for the in-place entry points).
 // STAGED: the gradient sum comes from A.acc instead of the k streams.  NORM: also add the squares
 // of the accumulated gradients to acc0/acc1.  DEPTH: gradient loads in flight per batch.  LWAIT:
-// the fp32 loads are waited for one by one.  SWAIT: each store waits for the previous one.
-template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT>
+// the fp32 loads are waited for one by one.  SWAIT: each store waits for the previous one.  THROUGH: the
+// stores are written through.
+template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
 __device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
 {
     typedef typename Group<EL>::F F;
@@ -286,13 +303,13 @@ __device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const 
         if constexpr (EL == 2) w = W[0] | (W[1] << 16);
         else w = H{W[0] | (W[1] << 16), W[2] | (W[3] << 16)};
         if constexpr (SWAIT) __builtin_amdgcn_sched_barrier(0);
-        st_stream(reinterpret_cast<F *>(A.po + lo), P);
+        st_once<THROUGH>(reinterpret_cast<F *>(A.po + lo), P);
         if constexpr (SWAIT) wait_vm_idle();
-        st_stream(reinterpret_cast<F *>(A.mo + lo), M);
+        st_once<THROUGH>(reinterpret_cast<F *>(A.mo + lo), M);
         if constexpr (SWAIT) wait_vm_idle();
-        st_stream(reinterpret_cast<F *>(A.vo + lo), V);
+        st_once<THROUGH>(reinterpret_cast<F *>(A.vo + lo), V);
         if constexpr (SWAIT) wait_vm_idle();
-        st_stream(reinterpret_cast<H *>(A.w + lo), w);
+        st_once<THROUGH>(reinterpret_cast<H *>(A.w + lo), w);
     } else {
         const int64_t i0 = lo > A.begin ? lo : A.begin;
         const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
@@ -353,7 +370,7 @@ __device__ __forceinline__ void step_one(const StepArgs &A, int64_t i)
 // one lane each: in the wave of their neighbours they come after its whole groups, and the range
 // ends one memory latency later (us, k = 1 / 8 / 32: 100 001 elements 2.9/3.0/4.2 against 3.5/4.0/7.2 there, 1 000 001
 // elements 5.8/8.9/17.0 against 6.3/9.7/19.9; from 3 M on within 2 %).
-template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 {
     constexpr int TILE = BLOCK * EL;
@@ -369,7 +386,7 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
     const int64_t lo = (A.begin / TILE + b) * TILE + (int64_t)threadIdx.x * EL;
     if (lo < A.begin || lo + EL > A.end) return;
     double unused0 = 0.0, unused1 = 0.0;
-    step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT>(A, lo, A.d_sqnorm, unused0, unused1);
+    step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT, THROUGH>(A, lo, A.d_sqnorm, unused0, unused1);
 }
 
 // Speculative single pass (Sec. 2.1 of the paper: prior work steps before the global norm is
@@ -658,6 +675,13 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
 // HIP launches fewer than 2^32 work items at a time: the workgroups of `block` lanes that is.
 static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
 
+// LDS that a launch asks for and does not use, so that a CU holds `workgroups` of them (of the sizes used here
+// it would otherwise hold 16 or 32).  The 512 bytes less leave room for what the kernels do use.
+static constexpr uint32_t room_for(int workgroups)
+{
+    return (uint32_t)(GS_LDS_GRANULES / workgroups * GS_LDS_GRANULE_BYTES - 512);
+}
+
 // How a step over `elems` elements is laid out; every line below is where the two sides met when both
 // were timed with cold caches (us per launch, k = 1 / 4 / 8 / 16 / 32).  The chip holds 8192 waves
 // (256 CUs x 32): up to 2^20 elements the waves of a 2-element shape, and up to 2^21 those of a
@@ -666,23 +690,31 @@ static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
 //             100 k elements: 2.9/3.1/3.0/3.2/4.1 against 4.4/5.9/6.6/10.1/17.2 for loads one at a
 //             time; at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
 //   <= 2^21   RESIDENT: no second, nearly empty generation of waves: 1.3 M elements 6.7/8.5/10.3/14.7/20.7
-//             against 8.8/10.0/12.3/16.0/23.1 in the STREAM shape and 7.4/9.4/11.8/17.4/27.1 one at a
+//             against 8.8/10.0/12.3/16.0/23.1 with 2 elements per lane and 7.4/9.4/11.8/17.4/27.1 one at a
 //             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
 //             wins (2.0 M: 10.3/12.8 against 10.3/13.4 for k = 1 / 4).
-//   <= 7 M    FEW: 2.5 M elements 13.8/16.3/19.7/26.5/39.1 against 14.7/17.1/21.0/27.4/40.0 (STREAM)
-//             and 15.0/18.7/23.5/33.1/51.6 (one load at a time, 4 elements per lane).
-//   above     STREAM: 12.6 M 57.6/68.6/85.3/119/193 against 57.1/69.6/87.2/123/197 (FEW) and
-//             61.3/75.4/93.4/133/200 (one load at a time, 4 elements); 805 M, k = 16: 7.55 ms against 7.67.
-//   >= 2^27   with up to 7 streams SERIAL: reads and writes are nearly balanced, and waiting for each
-//             keeps the memory queues shallow (805 M elements, k = 1 / 4: 3.49 / 4.30 ms against
-//             3.53 / 4.34); from 8 streams on STREAM is ahead (201 M, k = 8: 1.31 ms against 1.34),
-//             and for the staged step it is ahead at every size (3.76 ms against 3.79).
+//   above     HBM serves this mix of reads and writes best when a fixed amount of it is asked for: more
+//             in flight and it turns between them more often, less and it idles.  A full CU of 32 waves
+//             overshoots by a half; waves that wait between their own accesses lower the number too, but leave
+//             gaps.  So the waves wait for nothing, and a CU holds as many as make up 50-60 KB of loads:
+//   STREAM    2 elements per lane, four gradient loads in flight, 11 workgroups of two waves (10 where k is a
+//             multiple of four).  Against a full CU with its stores one at a time (up to 7 streams, from 2^27 on, each
+//             load too), ms: 201 M, k = 1 / 2 / 3 / 4 / 8 / 11 / 16 / 24  0.85/0.91/0.97/1.04/1.28/1.47/1.80/2.34 against
+//             0.89/0.94/1.01/1.11/1.31/1.51/1.86/2.44; 805 M, k = 16  7.10 against 7.46; 402 M, k = 32  6.00 against 6.21;
+//             2.5 M, k = 4  14.3 us against 14.7.  One workgroup more or less is within 1 %, two cost 2-4 %.
+//   DEEP      eight in flight and 9 workgroups, for 5 to 7 streams, which are then one batch (201 M, k = 5 / 6 / 7
+//             1.10/1.15/1.22 ms against 1.13/1.16/1.22 in STREAM and 1.16/1.24/1.29 before), and from 5 on up to 2^25
+//             elements (norm + step, us, k = 8 / 16: 4.5 M 47.9/-, 6.3 M 62.0/93.8, 12.6 M 115.7/176.8 against
+//             49.1/-, 63.1/94.2, 117.3/180.9 in STREAM and 48.7/-, 62.3/96.0, 117.6/178.7 before; level at 25 M).
+//   The staged step reads four fp32 streams: 4 elements per lane, 10 workgroups of one wave: 2.5 M / 12.6 M / 100 M /
+//             617 M 11.6/59.6/443/2722 us against 12.0/60.2/457/2824 with 2 elements per lane, a full CU and
+//             stores one at a time.
 enum Shape {
     SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once
     SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
     SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
-    SHAPE_FEW,        // 2 elements per lane, stores back to back
-    SHAPE_STREAM,     // 2 elements per lane, stores one at a time
+    SHAPE_STREAM,     // 2 elements per lane (staged: 4), four loads in flight, stores written through
+    SHAPE_DEEP,       // 2 elements per lane, eight loads in flight, stores written through
     SHAPE_BUDGET      // 4 elements per lane, two gradient loads in flight, stores one at a time
 };
 
@@ -708,11 +740,11 @@ static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 
 //   A stream confined to some of the CUs (any size over 2^21) takes BUDGET: there the bytes each CU keeps in
 //             flight are the bound, and 4 elements per lane hold twice as many (k = 2 / 8, 100 M elements:
-//             16 CUs 3.39/4.97 ms against 4.71/5.95 in the STREAM shape and 4.11/5.83 one load at a time,
+//             16 CUs 3.39/4.97 ms against 4.71/5.95 with 2 elements per lane and 4.11/5.83 one load at a time,
 //             128 CUs 0.60/0.84 against 0.74/0.95 and 0.67/0.91).
 //   States in host memory take LATENCY at every size: the link is the bound, and a wave that waits between
 //             its accesses leaves it idle (16 CUs, 12.6 M elements, k = 2 / 8 / 16: 3.23/3.19/3.23 ms against
-//             3.26/3.37/3.35 in the STREAM shape and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
+//             3.26/3.37/3.35 with stores one at a time and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
 //             25.5 ms against 26.4 and 27.3).
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
 static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream)
@@ -722,12 +754,11 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
     if (elems <= GS_RESIDENT_MAX)
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
     if (on_cu_budget(stream)) return SHAPE_BUDGET;
-    if (elems <= GS_FEW_MAX) return SHAPE_FEW;
-    return elems >= GS_SERIAL_MIN && k > 0 && k <= GS_SERIAL_MAX_K ? SHAPE_SERIAL : SHAPE_STREAM;
+    return k >= 5 && (k <= 7 || elems <= GS_DEEP_MAX) ? SHAPE_DEEP : SHAPE_STREAM;
 }
 
-template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT>
-static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
+static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t room = 0)
 {
     constexpr int64_t TILE = (int64_t)BLOCK * EL;
     int64_t tiles = tiles_of(A.begin, A.end, TILE);
@@ -736,14 +767,14 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream)
     if (tiles + cuts > max_grid(BLOCK)) {                           // too long for one launch: two, cut where a tile starts
         StepArgs half = A;
         half.end = (A.begin / TILE + tiles / 2) * TILE;
-        const hipError_t e = launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT>(half, stream);
+        const hipError_t e = launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH>(half, stream, room);
         if (e != hipSuccess) return e;
         half.begin = half.end;
         half.end = A.end;
-        return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT>(half, stream);
+        return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH>(half, stream, room);
     }
     if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
-    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT><<<(int)(tiles + cuts), BLOCK, 0, stream>>>(A, cuts);
+    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH><<<(int)(tiles + cuts), BLOCK, room, stream>>>(A, cuts);
     return hipGetLastError();
 }
 
@@ -757,11 +788,14 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
         return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
-    case SHAPE_FEW: return launch_step<128, 2, STAGED, 4, false, false>(A, stream);
     case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);
+    case SHAPE_DEEP:
+        if constexpr (!STAGED) return launch_step<128, 2, false, 8, false, false, true>(A, stream, room_for(9));
+        break;
     case SHAPE_STREAM: break;
     }
-    return launch_step<128, 2, STAGED, 4, false, true>(A, stream);
+    if constexpr (STAGED) return launch_step<64, 4, true, 4, false, false, true>(A, stream, room_for(10));
+    else return launch_step<128, 2, false, 4, false, false, true>(A, stream, room_for(A.k % 4 == 0 ? 10 : 11));
 }
 
 hipError_t launch_accum_adamw(const StepArgs &A, hipStream_t stream)
@@ -821,7 +855,7 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
         return launch_spec<64, 4, 2, false, true>(A, partials, cap, d_out, accumulate, stream);
     if (fits256 && (A.k <= 2 ? n > GS_LATENCY_MAX : A.k <= GS_SERIAL_MAX_K && n >= GS_SPEC_SERIAL_MIN))
         return launch_spec<64, 4, 1, true, true>(A, partials, cap, d_out, accumulate, stream);
-    if (n <= GS_FEW_MAX) return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
+    if (n <= GS_SPEC_FEW_MAX) return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
     if (fits256 && (A.k >= 12 || n >= GS_SPEC_SERIAL_MIN))
         return launch_spec<128, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
     if (tiles_of(A.begin, A.end, 512) <= cap)

@@ -10,13 +10,16 @@
 // limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
 #define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
 #define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
-#define GS_DEEP_MAX (1 << 25)         // elements up to which 8 gradient loads are in flight from 5 streams on
-#define GS_SERIAL_MAX_K 7             // streams up to which waves take one load at a time where that wins
+#define GS_FULL_MAX 7000000           // elements up to which a CU holds as many workgroups as it can
+#define GS_FULL_ODD_MAX (1 << 24)     // the same line for 9 to 23 streams that are no multiple of 8
+#define GS_DEEP_MAX (1 << 25)         // elements up to which multiples of 8 streams have 8 loads in flight
+#define GS_DEEP_ODD_MAX (1 << 26)     // the same line for 9 to 19 streams that are no multiple of 8
+#define GS_SERIAL_MAX_K 7             // "few streams"
 #define GS_LDS_GRANULES 128           // a CU's 160 KB of LDS are handed out in this many pieces
 #define GS_LDS_GRANULE_BYTES 1280
 #define GS_SPEC_FEW_MAX 7000000       // speculative pass: elements up to which everything is in flight
-#define GS_SPEC_SERIAL_MIN 80000000   // and from which few streams are taken one load at a time
-#define GS_SPEC_RUN_MAX (1 << 28)     // small workspace, few streams: elements up to which 512-element tiles are run
+#define GS_SPEC_RUN_LONG (1 << 28)    // small workspace: elements from which runs of tiles are four and more
+#define GS_SPEC_RUN_MAX (1 << 29)     // and up to which they are of small tiles (up to 2 streams: the line before)
 #define GS_KEEP_BYTES ((int64_t)256 << 20)  // of a re-read stream: left in the memory-side cache (keep_from)
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels
 #define GS_FINAL_SLICES 128           // workgroups of the first folding stage for large partial counts
@@ -35,6 +38,9 @@
 #define GS_NORM_256_MAX (1 << 20)     // from 5 streams on: elements up to which they have 256, 512 and 1024 lanes
 #define GS_NORM_512_MAX (1 << 21)
 #define GS_NORM_1024_MAX (1 << 23)
+#define GS_NORM_RUN8_MIN (1 << 23)    // one stream: elements from which a workgroup reads eight tiles instead of four,
+#define GS_NORM_RUN8_MAX (1 << 26)    // up to which it does,
+#define GS_NORM_RUN8_AGAIN (1 << 28)  // and from which it does again
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup

@@ -393,7 +393,7 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 // known because clipping rarely changes the gradients): the step is applied with c = 1 and the
 // squared norm of the same accumulated gradients is reduced on the way, so the gradients are
 // read once.  Every workgroup leaves a partial for its `span` consecutive tiles.
-template <int BLOCK, int EL, int DEPTH, bool LWAIT, bool SWAIT>
+template <int BLOCK, int EL, int DEPTH, bool SWAIT, bool THROUGH>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *partials, int span)
 {
     constexpr int TILE = BLOCK * EL;
@@ -404,7 +404,7 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= A.end) break;
         if (lo + EL <= A.begin) continue;
-        step_group<EL, false, true, DEPTH, LWAIT, SWAIT>(A, lo, nullptr, acc0, acc1);
+        step_group<EL, false, true, DEPTH, false, SWAIT, THROUGH>(A, lo, nullptr, acc0, acc1);
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;
@@ -818,33 +818,38 @@ static int64_t fit_span(int64_t tiles, int64_t span, int64_t U, int64_t cap, int
     return span > 0x7fffffff ? 0 : span;
 }
 
-template <int BLOCK, int EL, int DEPTH, bool LWAIT, bool SWAIT>
-static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+template <int BLOCK, int EL, int DEPTH, bool SWAIT, bool THROUGH>
+static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, double *d_out, int accumulate, hipStream_t stream,
+                              uint32_t room = 0)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
     if (tiles < 1) tiles = 1;
     const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_accum_adamw_spec<BLOCK, EL, DEPTH, LWAIT, SWAIT><<<grid, BLOCK, 0, stream>>>(A, partials, (int)span);
+    k_accum_adamw_spec<BLOCK, EL, DEPTH, SWAIT, THROUGH><<<grid, BLOCK, room, stream>>>(A, partials, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_fold(partials, cap, grid, d_out, accumulate, stream);
 }
 
-// The step's shapes with a partial per workgroup; a wave reduction per 128 or 256 elements moves the
-// lines a little (us or ms per launch, each against the shallow shape: one load at a time, 4 elements per lane,
-// 64 lanes):
-//   * up to 2 streams the shallow shape itself (50 M, k = 1: 226 us against 239 with four loads in flight);
-//   * up to 7 M elements everything in flight, 256 lanes: 600 k, k = 3 / 8 / 16: 7.7/8.9/11.0 against
-//     9.7/11.9/16.3;
-//   * then 128 lanes with four loads in flight: 4 elements per lane (12.6 M, k = 3 / 8: 71.5/91.8
-//     against 73.9/100), or 2 from 12 streams on (k = 16: 50 M 465 us against 488; 478 with 4);
-//   * from 80 M elements the step's own choice: shallow up to 7 streams, else 2 elements per lane
-//     (201 M, k = 16: 1.81 ms against 1.83).
-// A workspace too small for a partial per 256 elements takes 512-element tiles, then runs of them (160 M
-// elements, 2 MB workspace, k = 3 / 8 / 16: 0.81/1.08/1.55 ms against 0.82/1.12/1.59 in 4096-element tiles); few
-// streams over 2^28 elements keep the 4096-element tiles (runs of 8 small ones lose 4 % at 805 M, k = 2).
+// The step with a partial per workgroup.  A wave also reduces its squares, so its chain is longer and a CU holds a few
+// workgroups more than in the step.  us or ms per launch and fold, against four loads in flight, a full CU and
+// stores one at a time (few streams: one load at a time), k as given:
+//   * up to 7 M elements everything in flight, 256 lanes (600 k, k = 3 / 8 / 16: 7.7/8.9/11.0 against 9.7/11.9/16.3);
+//     up to 2 streams written through, so that no lines are left for the fold to wait for (k = 1 / 2: 600 k 6.9/7.3
+//     against 8.2/8.5, 3 M 18.1/18.7 against 20.6/22.2), and up to 7 streams below 2^21 elements (1.5 M, k = 4 / 6 10.8/12.4
+//     against 11.7/13.2; 6.5 M 43.1/47.7 against 41.4/45.3; from 8 streams on level at every size);
+//   * then, a partial per 256 elements: single waves of 4 elements per lane, 16 workgroups per CU (14 from 9 streams
+//     on): 12.6 M, k = 3 / 8 / 16 69.2/90.4/123.9 against 72.3/91.8/127.6; 50 M, k = 1 / 8 217/335 against 224/342; 201 M,
+//     k = 1 / 4 / 8 / 11  867/1051/1289/1469 against 910/1091/1349/1525;
+//   * a workspace too small for that: a partial per 512, two waves, 7 workgroups per CU (8 up to 4 streams): 100 M,
+//     k = 1 / 4 / 8 / 11 448/553/656/756 against 459/566/698/805;
+//   * or runs of 512-element tiles, four waves of 2 elements per lane, 6 workgroups per CU, 5 from 2^28 elements on: 201 M,
+//     k = 2 / 8 / 11 0.96/1.33/1.51 against 1.03/1.36/1.56; 402 M, k = 4 / 8 2.30/2.85 against 2.43/2.92; 530 M, k = 16 5.20
+//     against 5.53;
+//   * from 2^29 elements on (2^28 up to 2 streams, where the two are within 1 %) runs of 4096-element tiles: 700 M,
+//     k = 2 / 6 3.59/4.62 against 3.70/4.75, 805 M, k = 8 5.71 against 6.18.
 hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t workspace_bytes, double *d_out,
                                    int accumulate, hipStream_t stream)
 {
@@ -852,17 +857,18 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
     const int64_t n = A.end - A.begin;
     const bool fits256 = tiles_of(A.begin, A.end, 256) <= cap;
     if (fits256 && n > GS_RESIDENT_MAX && on_cu_budget(stream))
-        return launch_spec<64, 4, 2, false, true>(A, partials, cap, d_out, accumulate, stream);
-    if (fits256 && (A.k <= 2 ? n > GS_LATENCY_MAX : A.k <= GS_SERIAL_MAX_K && n >= GS_SPEC_SERIAL_MIN))
-        return launch_spec<64, 4, 1, true, true>(A, partials, cap, d_out, accumulate, stream);
-    if (n <= GS_SPEC_FEW_MAX) return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
-    if (fits256 && (A.k >= 12 || n >= GS_SPEC_SERIAL_MIN))
-        return launch_spec<128, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+        return launch_spec<64, 4, 2, true, false>(A, partials, cap, d_out, accumulate, stream);
+    if (n <= GS_SPEC_FEW_MAX) {
+        if (A.k <= 2 || (A.k <= GS_SERIAL_MAX_K && n <= GS_RESIDENT_MAX))
+            return launch_spec<256, 4, 16, false, true>(A, partials, cap, d_out, accumulate, stream);
+        return launch_spec<256, 4, 16, false, false>(A, partials, cap, d_out, accumulate, stream);
+    }
+    if (fits256) return launch_spec<64, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream, room_for(A.k <= 8 ? 16 : 14));
     if (tiles_of(A.begin, A.end, 512) <= cap)
-        return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
-    if (A.k >= 8) return launch_spec<256, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
-    if (n < GS_SPEC_RUN_MAX) return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
-    return launch_spec<1024, 4, 8, false, false>(A, partials, cap, d_out, accumulate, stream);
+        return launch_spec<128, 4, 4, false, true>(A, partials, cap, d_out, accumulate, stream, room_for(A.k <= 4 ? 8 : 7));
+    if (n < (A.k <= 2 ? GS_SPEC_RUN_LONG : GS_SPEC_RUN_MAX))
+        return launch_spec<256, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream, room_for(n < GS_SPEC_RUN_LONG ? 6 : 5));
+    return launch_spec<1024, 4, 8, false, true>(A, partials, cap, d_out, accumulate, stream);
 }
 
 // Where a pass leaves its lines in the 256 MB memory-side cache.  A step reads again what the norm has

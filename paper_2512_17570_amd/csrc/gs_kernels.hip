@@ -940,8 +940,10 @@ static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap
 // follow (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).  The lanes whose groups lie in all four
 // tiles have them in flight together; in a range that ends before, the others take them one after another.
 // Above that: with up to 4 streams 256 lanes and one group of U tiles up to 4 M elements, 512 lanes and
-// two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %); one stream is best in 256
-// lanes at every size.  From 5 streams on the workgroups grow with the range, so that they are many
+// two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %, and always for three streams: 6.3 M / 12.6 M
+// / 201 M 9.7/15.2/174 us against 10.3/16.3/180; level at 50 M); one stream is best in 256 lanes at every size, in runs of
+// eight tiles from 2^23 to 2^26 and again from 2^28 elements on (12.6 M / 25 M / 402 M / 805 M 7.1/12.8/120/232 against
+// 7.9/13.6/123/244 in runs of four; between them runs of eight lose 2 %).  From 5 streams on the workgroups grow with the range, so that they are many
 // enough to fill the chip and no more: 256, 512 and 1024 lanes up to 2^20, 2^21 and 2^23 elements (8 M,
 // k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, these shapes against 256 lanes with 8 tiles
 // one after another (k = 3, 7 and 32 in batches of 4, 2 and 1 loads):
@@ -975,13 +977,16 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
         return launch_norm_one<0, 1>(A, d_out, accumulate, stream);
     }
     switch (A.k) {
-    case 1: return launch_norm<1, 4, 256>(A, 4, cap, d_out, accumulate, stream);
+    case 1: {
+        const bool long_run = n >= GS_NORM_RUN8_MIN && (n < GS_NORM_RUN8_MAX || n >= GS_NORM_RUN8_AGAIN);
+        return launch_norm<1, 4, 256>(A, long_run ? 8 : 4, cap, d_out, accumulate, stream);
+    }
     case 2:
         if (small) return launch_norm<2, 2, 256>(A, 2, cap, d_out, accumulate, stream);
         return launch_norm<2, 4, 512>(A, 4, cap, d_out, accumulate, stream);
     case 3:
         if (small) return launch_norm<3, 2, 256>(A, 2, cap, d_out, accumulate, stream);
-        return launch_norm<3, 2, 512>(A, run, cap, d_out, accumulate, stream);
+        return launch_norm<3, 2, 512>(A, 4, cap, d_out, accumulate, stream);
     case 4:
         if (small) return launch_norm<4, 2, 256>(A, 2, cap, d_out, accumulate, stream);
         return launch_norm<4, 2, 512>(A, run, cap, d_out, accumulate, stream);

@@ -694,28 +694,36 @@ static constexpr uint32_t room_for(int workgroups)
 //             against 8.8/10.0/12.3/16.0/23.1 with 2 elements per lane and 7.4/9.4/11.8/17.4/27.1 one at a
 //             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
 //             wins (2.0 M: 10.3/12.8 against 10.3/13.4 for k = 1 / 4).
+//   above     2 elements per lane, all stores back to back and written through.
+//   <= 7 M    FULL: as many workgroups as a CU holds, four gradient loads in flight, with 5 to 24 streams (FULL_DEEP) eight.
+//             norm + step on three sets of tensors in turn, k = 1 / 4 / 8 / 16: 2.3 M 19.1/23.0/29.5/42.8 us against
+//             19.4/23.4/30.8/43.7 with the hint alone and four loads, 4.7 M 30.1/36.6/49.9/78.9 against 30.5/37.5/50.6/80.1.
 //   above     HBM serves this mix of reads and writes best when a fixed amount of it is asked for: more
 //             in flight and it turns between them more often, less and it idles.  A full CU of 32 waves
 //             overshoots by a half; waves that wait between their own accesses lower the number too, but leave
 //             gaps.  So the waves wait for nothing, and a CU holds as many as make up 50-60 KB of loads:
-//   STREAM    2 elements per lane, four gradient loads in flight, 11 workgroups of two waves (10 where k is a
-//             multiple of four).  Against a full CU with its stores one at a time (up to 7 streams, from 2^27 on, each
-//             load too), ms: 201 M, k = 1 / 2 / 3 / 4 / 8 / 11 / 16 / 24  0.85/0.91/0.97/1.04/1.28/1.47/1.80/2.34 against
-//             0.89/0.94/1.01/1.11/1.31/1.51/1.86/2.44; 805 M, k = 16  7.10 against 7.46; 402 M, k = 32  6.00 against 6.21;
-//             2.5 M, k = 4  14.3 us against 14.7.  One workgroup more or less is within 1 %, two cost 2-4 %.
+//   STREAM    four gradient loads in flight, 11 workgroups of two waves (10 where k is a multiple of four).  Against a
+//             full CU with its stores one at a time (up to 7 streams, from 2^27 on, each load too), ms: 201 M, k = 1 / 2 /
+//             3 / 4 / 8 / 11 / 16 / 24  0.85/0.91/0.97/1.04/1.28/1.47/1.80/2.34 against 0.89/0.94/1.01/1.11/1.31/1.51/1.86/2.44;
+//             805 M, k = 16  7.10-7.35 against 7.46-7.56; 402 M, k = 32  5.83-6.00 against 6.11-6.21; norm + step, 12.6 M,
+//             k = 1 / 4  64.0/83.8 us against 67.4/85.5.  One workgroup more or less is within 1 %, two cost 2-4 %.
 //   DEEP      eight in flight and 9 workgroups, for 5 to 7 streams, which are then one batch (201 M, k = 5 / 6 / 7
-//             1.10/1.15/1.22 ms against 1.13/1.16/1.22 in STREAM and 1.16/1.24/1.29 before), and from 5 on up to 2^25
-//             elements (norm + step, us, k = 8 / 16: 4.5 M 47.9/-, 6.3 M 62.0/93.8, 12.6 M 115.7/176.8 against
-//             49.1/-, 63.1/94.2, 117.3/180.9 in STREAM and 48.7/-, 62.3/96.0, 117.6/178.7 before; level at 25 M).
-//   The staged step reads four fp32 streams: 4 elements per lane, 10 workgroups of one wave: 2.5 M / 12.6 M / 100 M /
-//             617 M 11.6/59.6/443/2722 us against 12.0/60.2/457/2824 with 2 elements per lane, a full CU and
-//             stores one at a time.
+//             1.10/1.15/1.22 ms against 1.13/1.16/1.22 in STREAM and 1.16/1.24/1.29 before), and for 8, 16 and 24 up to 2^25
+//             elements (norm + step, 12.6 M, k = 8 / 16 113.4/174.0 us against 114.0/174.8 in STREAM and 115.3/175.3 before).
+//   9 to 23 streams that are no multiple of 8 leave some over after any batches: FULL up to 2^24 elements (9.4 M,
+//             k = 9 / 13 / 17 93.3/116.8/139.6 us against 96.5/118.9/147 in STREAM and 94.2/117.4/141.4 before); then, below
+//             20 of them, DEEP up to 2^26 (36 M, k = 11 / 14 382/445 against 383/449 and 387/453; level for k = 9, 10, 12).
+//   The staged step reads four fp32 streams: 4 elements per lane, 10 workgroups of one wave at every size: with its norm,
+//             2.3 M / 6.7 M / 12.6 M / 36 M 19.1/39.5/67.2/178 us against 19.0/40.3/69.5/184, alone 617 M 2.72 ms against 2.82,
+//             with 2 elements per lane, a full CU and stores one at a time.
 enum Shape {
     SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once
     SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
     SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
-    SHAPE_STREAM,     // 2 elements per lane (staged: 4), four loads in flight, stores written through
-    SHAPE_DEEP,       // 2 elements per lane, eight loads in flight, stores written through
+    SHAPE_FULL,       // 2 elements per lane, four loads in flight, stores written through
+    SHAPE_FULL_DEEP,  // the same with eight
+    SHAPE_STREAM,     // FULL with fewer workgroups per CU (staged: 4 elements per lane)
+    SHAPE_DEEP,       // FULL_DEEP with fewer
     SHAPE_BUDGET      // 4 elements per lane, two gradient loads in flight, stores one at a time
 };
 
@@ -755,7 +763,13 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
     if (elems <= GS_RESIDENT_MAX)
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
     if (on_cu_budget(stream)) return SHAPE_BUDGET;
-    return k >= 5 && (k <= 7 || elems <= GS_DEEP_MAX) ? SHAPE_DEEP : SHAPE_STREAM;
+    if (k == 0) return SHAPE_STREAM;
+    if (elems <= GS_FULL_MAX) return k >= 5 && k <= 24 ? SHAPE_FULL_DEEP : SHAPE_FULL;
+    if (k < 5) return SHAPE_STREAM;
+    if (k < 8) return SHAPE_DEEP;
+    if (k % 8 == 0) return k <= 24 && elems <= GS_DEEP_MAX ? SHAPE_DEEP : SHAPE_STREAM;
+    if (k < 24 && elems <= GS_FULL_ODD_MAX) return SHAPE_FULL;
+    return k < 20 && elems <= GS_DEEP_ODD_MAX ? SHAPE_DEEP : SHAPE_STREAM;
 }
 
 template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
@@ -782,7 +796,8 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
 template <bool STAGED>
 static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
 {
-    switch (step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream)) {
+    const Shape shape = step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream);
+    switch (shape) {
     case SHAPE_LATENCY:
         if constexpr (!STAGED)
             if (A.k > 8) return launch_step<64, 2, false, 16, false, false>(A, stream);
@@ -790,13 +805,16 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);
-    case SHAPE_DEEP:
-        if constexpr (!STAGED) return launch_step<128, 2, false, 8, false, false, true>(A, stream, room_for(9));
-        break;
-    case SHAPE_STREAM: break;
+    default: break;
     }
-    if constexpr (STAGED) return launch_step<64, 4, true, 4, false, false, true>(A, stream, room_for(10));
-    else return launch_step<128, 2, false, 4, false, false, true>(A, stream, room_for(A.k % 4 == 0 ? 10 : 11));
+    if constexpr (STAGED) {
+        return launch_step<64, 4, true, 4, false, false, true>(A, stream, room_for(10));
+    } else {
+        const bool deep = shape == SHAPE_DEEP || shape == SHAPE_FULL_DEEP;
+        const bool full = shape == SHAPE_FULL || shape == SHAPE_FULL_DEEP;
+        if (deep) return launch_step<128, 2, false, 8, false, false, true>(A, stream, full ? 0 : room_for(9));
+        return launch_step<128, 2, false, 4, false, false, true>(A, stream, full ? 0 : room_for(A.k % 4 == 0 ? 10 : 11));
+    }
 }
 
 hipError_t launch_accum_adamw(const StepArgs &A, hipStream_t stream)
@@ -1109,6 +1127,8 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
 
 // us per launch, each against 64 lanes with the buffer's load after the gradient's:
 //   first micro-batch, <= 2^22: 256 lanes               1 M 2.6 against 3.2, 2 M 3.6 against 4.4; level above
+//   later ones: written through where the sum is not left in the cache (805 M 1167 us against 1195, 201 M 291 against
+//   294, 12.6 M 19.8 against 20.2; the first micro-batch, which only writes, loses 2-4 % by it);
 //   later ones, <= 2^22 or on some of the CUs only: both loads in flight
 //                                                      1 M 3.2 against 3.7, 2 M 4.9 against 5.2; from 200 M on
 //                                                       waiting is 0.5 % ahead, level in between
@@ -1132,8 +1152,6 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
     if (accumulate || n <= GS_ADD_WIDE_MAX) A.keep_from = A.end;
     if (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 256) <= cap)
         return launch_add<true, 64, 4, false>(A, first, cap, d_out, accumulate, stream);
-//   later ones: written through where the sum is not left in the cache (805 M 1167 us against 1195, 201 M 291 against
-//   294, 12.6 M 19.8 against 20.2; the first micro-batch, which only writes, loses 2-4 % by it);
     if (n <= GS_LATENCY_MAX || (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 1024) <= cap))
         return launch_add<true, 256, 4, false>(A, first, cap, d_out, accumulate, stream);
     return launch_add<true, 1024, 4, false>(A, first, cap, d_out, accumulate, stream);

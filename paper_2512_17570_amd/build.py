@@ -58,6 +58,28 @@ def build_probe(verbose: bool = True) -> str:
     return PROBE_LIB
 
 
+CALL_MODULE = os.path.join(PKG, "_gs_call.so")
+
+
+def build_call(verbose: bool = True) -> str:
+    """The binding's native marshalling (csrc/gs_call.cpp): a CPython extension over torch's headers."""
+    import sysconfig
+
+    from torch.utils import cpp_extension
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-isystem", sysconfig.get_paths()["include"], *[x for d in cpp_extension.include_paths() for x in ("-isystem", d)],
+           os.path.join(CSRC, "gs_call.cpp"), "-o", CALL_MODULE, *[f"-L{d}" for d in cpp_extension.library_paths()],
+           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+    if verbose:
+        print(" ".join(cmd), flush=True)
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        sys.stderr.write(r.stderr)
+        raise RuntimeError("g++ failed (gs_call)")
+    return CALL_MODULE
+
+
 if __name__ == "__main__":
     build()
+    build_call()
     build_probe()

@@ -40,6 +40,12 @@ import torch  # noqa: E402,F401
 
 _lib = ctypes.CDLL(LIB_PATH)
 
+try:
+    from . import _gs_call as _call  # noqa: E402
+except ImportError as err:
+    raise ImportError(f"{_PKG}/_gs_call.so not found: build the binding's native part first "
+                      "(python -m paper_2512_17570_amd.build, or __graft_entry__.build())") from err
+
 
 class gs_adamw_hparams(ctypes.Structure):
     _fields_ = [("lr", ctypes.c_float), ("beta1", ctypes.c_float), ("beta2", ctypes.c_float),
@@ -129,11 +135,11 @@ class GsError(RuntimeError):
 
 
 # A step of a small range is a few microseconds on the GPU, and a call's marshalling is what the host
-# adds to it.  So each tensor is checked and its address taken in one pass, the address table is packed
-# into bytes (ctypes hands their address over; the library copies the table before the call returns), and
-# the current stream is asked for as the raw handle: 13 k elements, k = 4 / 16 gradients 7.1 / 9.9 us per
-# gs_accum_adamw, of which 3.5 the launch, against 11.3 / 15.7 with checks in a pass of their own, a ctypes
-# array and a Stream object.
+# adds to it.  So the calls that a step is made of go to _gs_call first, which reads arguments of the usual
+# form natively (plain CUDA tensors, whole numbers, HParams) and answers None for any other.  Those, and
+# all calls whose arguments are not accepted, are read here: each tensor is checked and its address taken
+# in one pass, the address table is packed into bytes (ctypes hands their address over; the library copies
+# the table before the call returns), and the current stream is asked for as the raw handle.
 
 def _addr(x) -> int | None:
     if x is None:
@@ -145,6 +151,7 @@ def _addr(x) -> int | None:
 
 _raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
 _current_device = getattr(torch._C, "_cuda_getDevice", None)
+_in_bad_fork = getattr(torch._C, "_cuda_isInBadFork", None)
 _cuda_ready = torch.cuda.is_initialized
 
 
@@ -193,6 +200,11 @@ def _table(grads, end: int, name: str = "grads"):
     return _pack_table[n](*addrs), n
 
 
+_call.setup(*[ctypes.cast(getattr(_lib, name), _vp).value for name in (
+    "gs_grad_sqnorm", "gs_grad_sqnorm_noalloc", "gs_grad_accum_sqnorm", "gs_accum_add", "gs_acc_sqnorm", "gs_accum_adamw",
+    "gs_adamw_from_acc", "gs_accum_adamw_oop", "gs_accum_adamw_spec")], HParams, _current_device, _raw_stream, _in_bad_fork)
+
+
 def _hp(hp):
     if hp is None:
         return None
@@ -223,6 +235,9 @@ def gs_sqnorm_workspace_bytes_for(range_elems: int) -> int:
 
 def gs_grad_sqnorm(grads, begin: int, end: int, d_sqnorm, d_workspace, workspace_bytes: int | None = None,
                    accumulate: bool = False, stream=None, check: bool = True, k: int | None = None) -> int:
+    st = _call.grad_sqnorm(grads, begin, end, d_sqnorm, d_workspace, workspace_bytes, accumulate, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_grad_sqnorm", check)
     tab, kk = _table(grads, end)
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
@@ -233,6 +248,9 @@ def gs_grad_sqnorm(grads, begin: int, end: int, d_sqnorm, d_workspace, workspace
 
 def gs_grad_sqnorm_noalloc(grads, begin: int, end: int, d_sqnorm, accumulate: bool = False, stream=None,
                            check: bool = True, k: int | None = None) -> int:
+    st = _call.grad_sqnorm_noalloc(grads, begin, end, d_sqnorm, accumulate, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_grad_sqnorm_noalloc", check)
     tab, kk = _table(grads, end)
     st = _lib.gs_grad_sqnorm_noalloc(tab, kk if k is None else k, begin, end, _addr(d_sqnorm), int(bool(accumulate)),
                                      _stream(stream))
@@ -241,6 +259,9 @@ def gs_grad_sqnorm_noalloc(grads, begin: int, end: int, d_sqnorm, accumulate: bo
 
 def gs_accum_adamw(p, m, v, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=None, stream=None,
                    check: bool = True, k: int | None = None) -> int:
+    st = _call.accum_adamw(p, m, v, w_bf16, grads, begin, end, hp, d_sqnorm, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_accum_adamw", check)
     tab, kk = _table(grads, end)
     p = _ptr(p, end, 4, "p")
     m = _ptr(m, end, 4, "m")
@@ -254,6 +275,9 @@ def gs_accum_adamw(p, m, v, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=No
 def gs_grad_accum_sqnorm(grads, begin: int, end: int, acc_f32, d_sqnorm, d_workspace,
                          workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                          check: bool = True, k: int | None = None) -> int:
+    st = _call.grad_accum_sqnorm(grads, begin, end, acc_f32, d_sqnorm, d_workspace, workspace_bytes, accumulate, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_grad_accum_sqnorm", check)
     tab, kk = _table(grads, end)
     acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
     if workspace_bytes is None:
@@ -266,6 +290,9 @@ def gs_grad_accum_sqnorm(grads, begin: int, end: int, acc_f32, d_sqnorm, d_works
 def gs_accum_add(acc_f32, grad_bf16, first: bool, begin: int, end: int, d_sqnorm=None, d_workspace=None,
                  workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                  check: bool = True) -> int:
+    st = _call.accum_add(acc_f32, grad_bf16, first, begin, end, d_sqnorm, d_workspace, workspace_bytes, accumulate, stream)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_accum_add", check)
     acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
     grad_bf16 = _ptr(grad_bf16, end, 2, "grad_bf16")
     if workspace_bytes is None:
@@ -277,6 +304,9 @@ def gs_accum_add(acc_f32, grad_bf16, first: bool, begin: int, end: int, d_sqnorm
 
 def gs_acc_sqnorm(acc_f32, begin: int, end: int, d_sqnorm, d_workspace, workspace_bytes: int | None = None,
                   accumulate: bool = False, stream=None, check: bool = True) -> int:
+    st = _call.acc_sqnorm(acc_f32, begin, end, d_sqnorm, d_workspace, workspace_bytes, accumulate, stream)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_acc_sqnorm", check)
     acc_f32 = _ptr(acc_f32, end, 4, "acc_f32")
     if workspace_bytes is None:
         workspace_bytes = d_workspace.numel() * d_workspace.element_size() if hasattr(d_workspace, "numel") else 0
@@ -287,6 +317,9 @@ def gs_acc_sqnorm(acc_f32, begin: int, end: int, d_sqnorm, d_workspace, workspac
 
 def gs_adamw_from_acc(p, m, v, w_bf16, acc_f32, begin: int, end: int, hp, d_sqnorm=None, stream=None,
                       check: bool = True) -> int:
+    st = _call.adamw_from_acc(p, m, v, w_bf16, acc_f32, begin, end, hp, d_sqnorm, stream)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_adamw_from_acc", check)
     p = _ptr(p, end, 4, "p")
     m = _ptr(m, end, 4, "m")
     v = _ptr(v, end, 4, "v")
@@ -299,6 +332,9 @@ def gs_adamw_from_acc(p, m, v, w_bf16, acc_f32, begin: int, end: int, hp, d_sqno
 
 def gs_accum_adamw_oop(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, end: int, hp, d_sqnorm=None,
                        stream=None, check: bool = True, k: int | None = None) -> int:
+    st = _call.accum_adamw_oop(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin, end, hp, d_sqnorm, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_accum_adamw_oop", check)
     tab, kk = _table(grads, end)
     p = _ptr(p, end, 4, "p")
     m = _ptr(m, end, 4, "m")
@@ -316,6 +352,10 @@ def gs_accum_adamw_oop(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, 
 def gs_accum_adamw_spec(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin: int, end: int, hp, d_sqnorm,
                         d_workspace, workspace_bytes: int | None = None, accumulate: bool = False, stream=None,
                         check: bool = True, k: int | None = None) -> int:
+    st = _call.accum_adamw_spec(p, m, v, p_out, m_out, v_out, w_bf16, grads, begin, end, hp, d_sqnorm, d_workspace,
+                                workspace_bytes, accumulate, stream, k)
+    if st is not None:
+        return st if st == GS_OK else _check(st, "gs_accum_adamw_spec", check)
     tab, kk = _table(grads, end)
     p = _ptr(p, end, 4, "p")
     m = _ptr(m, end, 4, "m")

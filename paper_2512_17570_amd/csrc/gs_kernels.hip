@@ -717,7 +717,7 @@ static constexpr uint32_t room_for(int workgroups)
 //             2.3 M / 6.7 M / 12.6 M / 36 M 19.1/39.5/67.2/178 us against 19.0/40.3/69.5/184, alone 617 M 2.72 ms against 2.82,
 //             with 2 elements per lane, a full CU and stores one at a time.
 enum Shape {
-    SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once
+    SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once, stores written through
     SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
     SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
     SHAPE_FULL,       // 2 elements per lane, four loads in flight, stores written through
@@ -755,6 +755,20 @@ static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 //             its accesses leaves it idle (16 CUs, 12.6 M elements, k = 2 / 8 / 16: 3.23/3.19/3.23 ms against
 //             3.26/3.37/3.35 with stores one at a time and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
 //             25.5 ms against 26.4 and 27.3).
+// Of those waves only so many are resident as the link needs to be busy both ways: with all of them in flight the
+// first generation reads and then writes together, and the link carries one direction at a time.  On 16 / 32 / 64
+// CUs that is 11 / 5 / 2 single-wave workgroups each, on more of them 512 in all (twice that and half of it are up to
+// 8 % slower over 12.6 M elements).  Written through, as the resident LATENCY shape is (level there:
+// 400 k, k = 1 / 8 / 16 4.1/4.6/6.2 us either way).  16 CUs, k = 1 / 8 / 16: 300 k elements 114/115/121 us against 159/153/156 with
+// the hint and full CUs, 1 M 286/286/291 against 402/324/302, 12.6 M 3.12/3.09/3.24 ms against 3.22/3.22/3.23; 1.5 M, k = 8,
+// 32 / 64 / 128 / 256 CUs 406/404/412/406 us against 435/442/477/518.
+static uint32_t link_room(hipStream_t stream)
+{
+    const int cus = budget_cus(stream);
+    if (cus > 0 && cus <= 64) return room_for(cus < 16 ? GS_LINK_WAVES / 16 : GS_LINK_WAVES / cus);
+    return room_for(cus > 0 && cus <= GS_LINK_WAVES_WIDE / 4 ? 4 : 2);
+}
+
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
 static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream)
 {
@@ -798,10 +812,12 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
 {
     const Shape shape = step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream);
     switch (shape) {
-    case SHAPE_LATENCY:
+    case SHAPE_LATENCY: {
+        const uint32_t room = A.over_link ? link_room(stream) : 0;
         if constexpr (!STAGED)
-            if (A.k > 8) return launch_step<64, 2, false, 16, false, false>(A, stream);
-        return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
+            if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
+        return launch_step<64, 2, STAGED, 8, false, false, true>(A, stream, room);
+    }
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);

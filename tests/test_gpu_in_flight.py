@@ -93,3 +93,25 @@ def test_later_micro_batches_written_through_and_cached(length):
     gs.gs_accum_add(acc, case.grads[1], False, b, e)
     assert torch.equal(acc[b:e], case.grads[0][b:e].float() + case.grads[1][b:e].float())
     assert bool((acc[:b] == 9.0).all()) and bool((acc[e:] == 9.0).all())
+
+
+@pytest.mark.parametrize("cus", [0, 16, 32, 64, 128, 192])
+@pytest.mark.parametrize("n,k", [(130, 2), (100_003, 9), (700_001, 8)])
+def test_step_on_host_memory_by_cus(n, k, cus):
+    """Each number of workgroups that a CU is given over the link: the resident step's bits."""
+    case = DeviceCase(n, k, seed=k, keep_host=False)
+    case.sq.fill_(4.0)
+    host = []
+    for x in (case.p, case.m, case.v):
+        h = torch.empty(n, dtype=torch.float32, pin_memory=True)
+        h.copy_(x)
+        host.append(h)
+    want = case.clone_states()
+    gs.gs_accum_adamw(*want, case.grads, 0, n, HP, case.sq)
+    ctx = gs.gs_stream_ctx_create_inplace(cus)
+    w = torch.zeros_like(case.w)
+    gs.gs_stream_layer_step(ctx, *host, w, case.grads, n, HP, case.sq)
+    gs.gs_stream_ctx_sync(ctx)
+    gs.gs_stream_ctx_destroy(ctx)
+    for h, x in zip(host + [w.cpu()], want):
+        assert torch.equal(h, x.cpu())

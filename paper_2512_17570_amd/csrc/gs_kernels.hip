@@ -689,7 +689,10 @@ static constexpr uint32_t room_for(int workgroups)
 // 4-element shape, are resident together.
 //   <= 2^19   LATENCY: a wave's chain of dependent loads is the time, so all of them go out at once.
 //             100 k elements: 2.9/3.1/3.0/3.2/4.1 against 4.4/5.9/6.6/10.1/17.2 for loads one at a
-//             time; at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
+//             time; written through with 2 to 15 streams (100 k, k = 4 / 8 3.26/3.24 against 3.35/3.47, 400 k 4.30/4.41 against
+//             4.67/4.55; one stream loses 4 % by it at 100 k, the staged step 5-9 %, 16 streams 10 % at 400 k, and 8 over the
+//             last half of this range 2 %);
+//             at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
 //   <= 2^21   RESIDENT: no second, nearly empty generation of waves: 1.3 M elements 6.7/8.5/10.3/14.7/20.7
 //             against 8.8/10.0/12.3/16.0/23.1 with 2 elements per lane and 7.4/9.4/11.8/17.4/27.1 one at a
 //             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
@@ -713,11 +716,12 @@ static constexpr uint32_t room_for(int workgroups)
 //   9 to 23 streams that are no multiple of 8 leave some over after any batches: FULL up to 2^24 elements (9.4 M,
 //             k = 9 / 13 / 17 93.3/116.8/139.6 us against 96.5/118.9/147 in STREAM and 94.2/117.4/141.4 before); then, below
 //             20 of them, DEEP up to 2^26 (36 M, k = 11 / 14 382/445 against 383/449 and 387/453; level for k = 9, 10, 12).
-//   The staged step reads four fp32 streams: 4 elements per lane, 10 workgroups of one wave at every size: with its norm,
-//             2.3 M / 6.7 M / 12.6 M / 36 M 19.1/39.5/67.2/178 us against 19.0/40.3/69.5/184, alone 617 M 2.72 ms against 2.82,
-//             with 2 elements per lane, a full CU and stores one at a time.
+//   The staged step reads four fp32 streams: FULL up to 7 M elements (with its norm, 2.5 M / 5 M 19.3/30.9 us against 19.6/31.3
+//             with the hint alone), then 4 elements per lane, 10 workgroups of one wave: with its norm, 12.6 M / 36 M 67.2/178
+//             us against 69.5/184, alone 617 M 2.72 ms against 2.82, with 2 elements per lane, a full CU and stores one at a
+//             time (up to 7 M those are 1 % behind FULL where a range starts in the middle of a line).
 enum Shape {
-    SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once, stores written through
+    SHAPE_LATENCY,    // 2 elements per lane, everything in flight at once
     SHAPE_RESIDENT,   // 4 elements per lane, stores one at a time
     SHAPE_SERIAL,     // 4 elements per lane, every load and store of a wave waited for
     SHAPE_FULL,       // 2 elements per lane, four loads in flight, stores written through
@@ -758,8 +762,7 @@ static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 // Of those waves only so many are resident as the link needs to be busy both ways: with all of them in flight the
 // first generation reads and then writes together, and the link carries one direction at a time.  On 16 / 32 / 64
 // CUs that is 11 / 5 / 2 single-wave workgroups each, on more of them 512 in all (twice that and half of it are up to
-// 8 % slower over 12.6 M elements).  Written through, as the resident LATENCY shape is (level there:
-// 400 k, k = 1 / 8 / 16 4.1/4.6/6.2 us either way).  16 CUs, k = 1 / 8 / 16: 300 k elements 114/115/121 us against 159/153/156 with
+// 8 % slower over 12.6 M elements).  Written through with any number of streams.  16 CUs, k = 1 / 8 / 16: 300 k elements 114/115/121 us against 159/153/156 with
 // the hint and full CUs, 1 M 286/286/291 against 402/324/302, 12.6 M 3.12/3.09/3.24 ms against 3.22/3.22/3.23; 1.5 M, k = 8,
 // 32 / 64 / 128 / 256 CUs 406/404/412/406 us against 435/442/477/518.
 static uint32_t link_room(hipStream_t stream)
@@ -777,7 +780,7 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
     if (elems <= GS_RESIDENT_MAX)
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
     if (on_cu_budget(stream)) return SHAPE_BUDGET;
-    if (k == 0) return SHAPE_STREAM;
+    if (k == 0) return elems <= GS_FULL_MAX ? SHAPE_FULL : SHAPE_STREAM;
     if (elems <= GS_FULL_MAX) return k >= 5 && k <= 24 ? SHAPE_FULL_DEEP : SHAPE_FULL;
     if (k < 5) return SHAPE_STREAM;
     if (k < 8) return SHAPE_DEEP;
@@ -813,21 +816,28 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
     const Shape shape = step_shape(A.end - A.begin, STAGED ? 0 : A.k, A.over_link, stream);
     switch (shape) {
     case SHAPE_LATENCY: {
-        const uint32_t room = A.over_link ? link_room(stream) : 0;
-        if constexpr (!STAGED)
-            if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
-        return launch_step<64, 2, STAGED, 8, false, false, true>(A, stream, room);
+        if constexpr (!STAGED) {
+            const uint32_t room = A.over_link ? link_room(stream) : 0;
+            const bool through = A.k >= 2 && A.k < 16 && (A.k != 8 || A.end - A.begin <= GS_LATENCY_MAX / 2);
+            if (A.over_link || through) {
+                if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
+                return launch_step<64, 2, false, 8, false, false, true>(A, stream, room);
+            }
+            if (A.k > 8) return launch_step<64, 2, false, 16, false, false>(A, stream);
+        }
+        return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
     }
     case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
     case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);
     default: break;
     }
+    const bool full = shape == SHAPE_FULL || shape == SHAPE_FULL_DEEP;
     if constexpr (STAGED) {
+        if (full) return launch_step<128, 2, true, 4, false, false, true>(A, stream);
         return launch_step<64, 4, true, 4, false, false, true>(A, stream, room_for(10));
     } else {
         const bool deep = shape == SHAPE_DEEP || shape == SHAPE_FULL_DEEP;
-        const bool full = shape == SHAPE_FULL || shape == SHAPE_FULL_DEEP;
         if (deep) return launch_step<128, 2, false, 8, false, false, true>(A, stream, full ? 0 : room_for(9));
         return launch_step<128, 2, false, 4, false, false, true>(A, stream, full ? 0 : room_for(A.k % 4 == 0 ? 10 : 11));
     }

@@ -226,29 +226,49 @@ __device__ __forceinline__ void accumulate_cut(const GradTable &gt, int k, int64
 }
 
 // ---- block reduction used by the norm kernels ----------------------------------------------
-// Per-lane fp64 partial (each square is exact in fp64) -> wave64 butterfly -> LDS across the
+// Per-lane fp64 partial (each square is exact in fp64) -> across the lanes of a wave -> LDS across the
 // block's waves -> one partial per block; a second tiny kernel folds the block partials in a
 // fixed order, so the result is deterministic.
+// A small range waits for every step of this, so lanes are exchanged by DPP moves, a few cycles each, where
+// shuffles go through the LDS hardware, and the waves' sums are added across lanes and not one after another
+// (norm, 13 k / 200 k elements, k = 4 3.74/4.83 us against 3.99/5.14; fp32 norm, 13 k 2.32 against 2.66; staged norm, 520 k,
+// k = 4 5.32 against 5.80).
+template <int CTRL, int ROWS = 0xf>
+__device__ __forceinline__ double add_dpp(double x)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, ROWS, 0xf, false);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, ROWS, 0xf, false);
+    return x + __hiloint2double(hi, lo);       // lanes outside ROWS add 0
+}
+
+// the sum of a row of 16 lanes, in all of them
+__device__ __forceinline__ double row_sum(double x)
+{
+    x = add_dpp<0xb1>(x);                      // quad_perm [1,0,3,2]
+    x = add_dpp<0x4e>(x);                      // quad_perm [2,3,0,1]
+    x = add_dpp<0x141>(x);                     // row_half_mirror
+    return add_dpp<0x140>(x);                  // row_mirror
+}
+
+// the sum of a wave, in its last lane
 __device__ __forceinline__ double wave_sum(double x)
 {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, 64);
-    return x;
+    x = row_sum(x);
+    x = add_dpp<0x142, 0xa>(x);                // row_bcast:15 into rows 1 and 3
+    return add_dpp<0x143, 0xc>(x);             // row_bcast:31 into rows 2 and 3
 }
 
 template <int BLOCK>
 __device__ __forceinline__ double block_sum(double x, double *lds)
 {
     constexpr int NW = BLOCK / 64;
+    static_assert(NW >= 1 && NW <= 16, "the waves' sums lie in one row of lanes");
     x = wave_sum(x);
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    if (lane == 0) lds[wave] = x;
+    if (lane == 63) lds[wave] = x;
     __syncthreads();
     double t = 0.0;
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int w = 0; w < NW; ++w) t += lds[w];
-    }
+    if (wave == 0) t = row_sum(lane < NW ? lds[lane] : 0.0);
     return t;   // valid in thread 0
 }
 

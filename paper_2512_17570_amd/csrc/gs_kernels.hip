@@ -45,6 +45,10 @@ template <int EL> struct Group;
 template <> struct Group<2> { typedef f32x2 F; typedef uint32_t H; };
 template <> struct Group<4> { typedef f32x4 F; typedef u32x2 H; };
 
+template <typename T> using global_ptr = __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ global_ptr<T> in_global(T *p) { return (global_ptr<T>)p; }
+
 // ---- memory access helpers: streams are touched exactly once => non-temporal ------------
 // KEEP: without the hint, which leaves the line in the memory-side cache.
 template <bool KEEP = false, typename T>
@@ -103,12 +107,25 @@ __device__ __forceinline__ uint32_t f32_to_bf16_bits(float f)
 }
 
 // Clip coefficient from the total squared norm (Sec. 2.1: global L2 norm for clipping).
-__device__ __forceinline__ float clip_coefficient(const double *d_sqnorm, float max_norm)
+__device__ __forceinline__ float clip_from(double sqnorm, float max_norm)
 {
-    if (d_sqnorm == nullptr || !(max_norm > 0.0f)) return 1.0f;
-    float norm = (float)sqrt(*d_sqnorm);
+    float norm = (float)sqrt(sqnorm);
     float c = max_norm / (norm + 1e-6f);
     return c < 1.0f ? c : 1.0f;
+}
+__device__ __forceinline__ bool clips(const double *d_sqnorm, float max_norm) { return d_sqnorm != nullptr && max_norm > 0.0f; }
+__device__ __forceinline__ float clip_coefficient(const double *d_sqnorm, float max_norm)
+{
+    return clips(d_sqnorm, max_norm) ? clip_from(*d_sqnorm, max_norm) : 1.0f;
+}
+
+// *q by a vector load, which other loads overtake and are not held up by: the scalar load that a uniform address
+// otherwise gets has to be back before any scalar load after it can be used.
+__device__ __forceinline__ double ld_beside(const double *q)
+{
+    int zero = 0;
+    asm volatile("" : "+v"(zero));
+    return q[zero];
 }
 
 // The element update: clip, moments, master weight (Sec. 2.2: three fp32 states per weight,
@@ -151,7 +168,17 @@ __device__ __forceinline__ void add_bf16(float (&a)[2], uint32_t g)
     a[0] += bf16_lo(g); a[1] += bf16_hi(g);
 }
 
-template <int EL, int DEPTH, bool KEEP = false, bool APART = false>
+// TOGETHER: the addresses of a last, partial batch are read from the argument block together, and not one before
+// each load: that is a scalar load and a wait for every stream, in a chain.
+template <int N>
+__device__ __forceinline__ void all_at_once(global_ptr<const uint16_t> (&p)[N + 1])
+{
+    if constexpr (N >= 15)
+        asm volatile("" : "+s"(p[7]), "+s"(p[8]), "+s"(p[9]), "+s"(p[10]), "+s"(p[11]), "+s"(p[12]), "+s"(p[13]), "+s"(p[14]));
+    asm volatile("" : "+s"(p[0]), "+s"(p[1]), "+s"(p[2]), "+s"(p[3]), "+s"(p[4]), "+s"(p[5]), "+s"(p[6]));
+}
+
+template <int EL, int DEPTH, bool KEEP = false, bool APART = false, bool TOGETHER = false>
 __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, int64_t lo, float (&a)[EL])
 {
     typedef typename Group<EL>::H H;
@@ -189,9 +216,20 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
         }
     } else if (DEPTH > 1 && rest > 0) {
         H g[DEPTH];
+        if constexpr (TOGETHER && DEPTH >= 8) {
+            // j is a multiple of DEPTH, so the batch's entries lie in the table; those from k on are not followed
+            global_ptr<const uint16_t> from[DEPTH];
 #pragma unroll
-        for (int q = 0; q < DEPTH - 1; ++q)
-            if (q < rest) g[q] = ld_stream<KEEP>(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+            for (int q = 0; q < DEPTH - 1; ++q) from[q] = in_global(gt.g[j + q]);
+            all_at_once<DEPTH - 1>(from);
+#pragma unroll
+            for (int q = 0; q < DEPTH - 1; ++q)
+                if (q < rest) g[q] = ld_stream<KEEP>(reinterpret_cast<const H *>((const uint16_t *)from[q] + lo));
+        } else {
+#pragma unroll
+            for (int q = 0; q < DEPTH - 1; ++q)
+                if (q < rest) g[q] = ld_stream<KEEP>(reinterpret_cast<const H *>(gt.g[j + q] + lo));
+        }
 #pragma unroll
         for (int q = 0; q < DEPTH - 1; ++q)
             if (q < rest) add_bf16(a, g[q]);
@@ -273,6 +311,46 @@ __device__ __forceinline__ double block_sum(double x, double *lds)
 }
 
 // ---- fused accumulate + clip + AdamW + bf16 emit -----------------------------------------
+// A step's arguments in registers, read together as the kernel starts.  Left to themselves they are read where
+// each is needed, five times over the life of a wave, and each time is a wait of 0.1-0.3 us in a chain that is
+// all there is to a small range (13 k elements, k = 4 / 9 / 32 2.77/2.68/3.01 us against 3.00/3.26/3.52; 400 k, k = 9 / 32
+// 4.30/7.78 against 4.74/8.20; 6.5 M, k = 2 / 8 32.8/45.1 against 33.7/46.2; level from 12 M on).
+struct StepView {
+    const float *p, *m, *v;
+    float *po, *mo, *vo;
+    uint16_t *w;
+    const GradTable &gt;
+    int k;
+    int64_t begin, end;
+    StepConsts c;
+    float max_norm;
+    const double *d_sqnorm;
+    const float *acc;
+};
+// Where a wave waits between its accesses anyway it gains nothing, and the shapes that do lose (2 M elements, k = 1 / 4
+// 10.9/13.0 us against 10.1/11.9); so does the staged step of a small range (13 k 2.07 against 1.99).  Read late, but
+// through this view, 1 M elements take 5.61/6.73/8.41/10.8 us with k = 1 / 4 / 8 / 16, against 6.21/6.96/8.20/10.6 from the argument block.
+template <bool STAGED, bool LWAIT, bool SWAIT>
+constexpr bool reads_early = !STAGED && !LWAIT && !SWAIT;
+
+template <bool EARLY>
+__device__ __forceinline__ StepView view_of(const StepArgs &A)
+{
+    StepView V{A.p, A.m, A.v, A.po, A.mo, A.vo, A.w, A.gt, A.k, A.begin, A.end, A.c, A.max_norm, A.d_sqnorm, A.acc};
+    if constexpr (!EARLY) return V;
+    // as global addresses, which they are known to be only while they come straight from the argument block
+    global_ptr<const float> p = in_global(V.p), m = in_global(V.m), v = in_global(V.v), acc = in_global(V.acc);
+    global_ptr<float> po = in_global(V.po), mo = in_global(V.mo), vo = in_global(V.vo);
+    global_ptr<uint16_t> w = in_global(V.w);
+    global_ptr<const double> sq = in_global(V.d_sqnorm);
+    asm volatile("" : "+s"(po), "+s"(mo), "+s"(vo), "+s"(w), "+s"(V.k), "+s"(V.max_norm), "+s"(sq), "+s"(acc), "+s"(V.c.beta1),
+                 "+s"(V.c.beta2), "+s"(V.c.omb1), "+s"(V.c.omb2), "+s"(V.c.eps));
+    asm volatile("" : "+s"(p), "+s"(m), "+s"(v), "+s"(V.begin), "+s"(V.end), "+s"(V.c.step_size), "+s"(V.c.rsbc2), "+s"(V.c.decay));
+    V.p = (const float *)p, V.m = (const float *)m, V.v = (const float *)v, V.acc = (const float *)acc;
+    V.po = (float *)po, V.mo = (float *)mo, V.vo = (float *)vo, V.w = (uint16_t *)w, V.d_sqnorm = (const double *)sq;
+    return V;
+}
+
 // The group of EL elements starting at `lo` (a multiple of EL): vector path when the group lies
 // inside [begin,end), per-element path for ragged range ends -- same arithmetic.  States are read
 // from A.p/m/v and written to A.po/mo/vo (the same arrays for the in-place entry points).
@@ -281,10 +359,11 @@ __device__ __forceinline__ double block_sum(double x, double *lds)
 // the fp32 loads are waited for one by one.  SWAIT: each store waits for the previous one.  THROUGH: the
 // stores are written through.
 template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
-__device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
+__device__ __forceinline__ void step_group(const StepView &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
 {
     typedef typename Group<EL>::F F;
     typedef typename Group<EL>::H H;
+    constexpr bool EARLY = reads_early<STAGED, LWAIT, SWAIT>;
     const StepConsts &s = A.c;
     if (lo >= A.begin && lo + EL <= A.end) {
         float c = 1.0f;
@@ -295,15 +374,22 @@ __device__ __forceinline__ void step_group(const StepArgs &A, int64_t lo, const 
         if constexpr (LWAIT) wait_vm_idle();
         const F v = ld_stream(reinterpret_cast<const F *>(A.v + lo));
         if constexpr (LWAIT) wait_vm_idle();
+        const bool clip = EARLY && clips(d_sqnorm, A.max_norm);
+        double sqnorm = 0.0;
+        if (clip) sqnorm = ld_beside(d_sqnorm);
         float a[EL];
         if constexpr (STAGED) {
             const F av = ld_stream(reinterpret_cast<const F *>(A.acc + lo));
 #pragma unroll
             for (int e = 0; e < EL; ++e) a[e] = av[e];
         } else {
-            accumulate_batches<EL, DEPTH, false, NORM>(A.gt, A.k, lo, a);
+            accumulate_batches<EL, DEPTH, false, NORM, EARLY>(A.gt, A.k, lo, a);
         }
-        if constexpr (!LWAIT) c = clip_coefficient(d_sqnorm, A.max_norm);     // under the loads in flight
+        if constexpr (!LWAIT && !EARLY) c = clip_coefficient(d_sqnorm, A.max_norm);     // under the loads in flight
+        if (clip) {
+            asm volatile("" : "+v"(sqnorm));       // here, under the loads in flight, and not where it is loaded
+            c = clip_from(sqnorm, A.max_norm);
+        }
         F P, M, V;
         uint32_t W[EL];
 #pragma unroll
@@ -394,6 +480,7 @@ template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, boo
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 {
     constexpr int TILE = BLOCK * EL;
+    const StepView V = view_of<reads_early<STAGED, LWAIT, SWAIT>>(A);
     const int64_t b = (int64_t)blockIdx.x - cuts;
     if (b < 0) {
         const int64_t head = (A.begin + EL - 1) / EL * EL;         // where the first whole group starts
@@ -403,10 +490,10 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
         if (threadIdx.x < 2 * EL && i < A.end) step_one<STAGED>(A, i);
         return;
     }
-    const int64_t lo = (A.begin / TILE + b) * TILE + (int64_t)threadIdx.x * EL;
-    if (lo < A.begin || lo + EL > A.end) return;
+    const int64_t lo = (V.begin / TILE + b) * TILE + (int64_t)threadIdx.x * EL;
+    if (lo < V.begin || lo + EL > V.end) return;
     double unused0 = 0.0, unused1 = 0.0;
-    step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT, THROUGH>(A, lo, A.d_sqnorm, unused0, unused1);
+    step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT, THROUGH>(V, lo, V.d_sqnorm, unused0, unused1);
 }
 
 // Speculative single pass (Sec. 2.1 of the paper: prior work steps before the global norm is
@@ -420,11 +507,12 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw_spec(StepArgs A, double *
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
+    const StepView V = view_of<reads_early<false, false, SWAIT>>(A);
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
-        if (lo >= A.end) break;
-        if (lo + EL <= A.begin) continue;
-        step_group<EL, false, true, DEPTH, false, SWAIT, THROUGH>(A, lo, nullptr, acc0, acc1);
+        if (lo >= V.end) break;
+        if (lo + EL <= V.begin) continue;
+        step_group<EL, false, true, DEPTH, false, SWAIT, THROUGH>(V, lo, nullptr, acc0, acc1);
     }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) partials[blockIdx.x] = t;

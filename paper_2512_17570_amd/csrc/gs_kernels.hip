@@ -785,10 +785,11 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
 static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
 
 // LDS that a launch asks for and does not use, so that a CU holds `workgroups` of them (of the sizes used here
-// it would otherwise hold 16 or 32).  The 512 bytes less leave room for what the kernels do use.
+// it would otherwise hold 16 or 32): the fewest pieces of which one workgroup more would not get its share, 55 KB for
+// two.  The 512 bytes less leave room for what the kernels do use.
 static constexpr uint32_t room_for(int workgroups)
 {
-    return (uint32_t)(GS_LDS_GRANULES / workgroups * GS_LDS_GRANULE_BYTES - 512);
+    return (uint32_t)((GS_LDS_GRANULES / (workgroups + 1) + 1) * GS_LDS_GRANULE_BYTES - 512);
 }
 
 // How a step over `elems` elements is laid out; every line below is where the two sides met when both

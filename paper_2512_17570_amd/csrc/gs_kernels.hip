@@ -1004,14 +1004,25 @@ static hipError_t launch_spec(const StepArgs &A, double *partials, int64_t cap, 
 //     against 5.53;
 //   * from 2^29 elements on (2^28 up to 2 streams, where the two are within 1 %) runs of 4096-element tiles: 700 M,
 //     k = 2 / 6 3.59/4.62 against 3.70/4.75, 805 M, k = 8 5.71 against 6.18.
+// On a stream confined to some of the CUs it is the bytes that each of them has in flight that bound (step_shape), so
+// no workgroup is kept off it (ms on 16 / 64 / 128 CUs, with the small workspace):
+//   * a partial per 512, or runs of those with up to 7 streams below 2^28 elements: stores one at a time; 70 M, k = 1
+//     2.42/0.73/0.41 against 2.93/0.86/0.47 bounded, k = 8 3.53/1.03/0.61 against 4.31/1.23/0.67; 200 M, k = 2 7.18/2.18/1.25 against
+//     9.11/2.65/1.44 in runs of 512-element tiles with bounded CUs;
+//   * else runs of those tiles, two elements per lane: 200 M, k = 8 10.67/3.12/1.75 against 11.72/3.40/1.86 bounded; 300 M, k = 2 / 16
+//     11.65/3.53/1.95 and 21.92/6.17/3.62 against 14.86/4.01/2.17 in 4096-element tiles and 26.93/7.38/4.11 bounded.
 hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t workspace_bytes, double *d_out,
                                    int accumulate, hipStream_t stream)
 {
     const int64_t cap = partial_capacity(workspace_bytes);
     const int64_t n = A.end - A.begin;
     const bool fits256 = tiles_of(A.begin, A.end, 256) <= cap;
-    if (fits256 && n > GS_RESIDENT_MAX && on_cu_budget(stream))
-        return launch_spec<64, 4, 2, true, false>(A, partials, cap, d_out, accumulate, stream);
+    if (n > GS_RESIDENT_MAX && on_cu_budget(stream)) {
+        if (fits256) return launch_spec<64, 4, 2, true, false>(A, partials, cap, d_out, accumulate, stream);
+        if (tiles_of(A.begin, A.end, 512) <= cap || (A.k <= GS_SERIAL_MAX_K && n < GS_SPEC_RUN_LONG))
+            return launch_spec<128, 4, 4, true, false>(A, partials, cap, d_out, accumulate, stream);
+        return launch_spec<256, 2, 4, false, true>(A, partials, cap, d_out, accumulate, stream);
+    }
     if (n <= GS_SPEC_FEW_MAX) {
         if (A.k <= 2 || (A.k <= GS_SERIAL_MAX_K && n <= GS_RESIDENT_MAX))
             return launch_spec<256, 4, 16, false, true>(A, partials, cap, d_out, accumulate, stream);

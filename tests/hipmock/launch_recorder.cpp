@@ -20,6 +20,7 @@ struct Launch {
     char kernel[128];
     uint64_t grid, block;
     uint64_t stream;
+    uint64_t lds;            // bytes of LDS asked for beyond what the kernel itself declares
     int64_t begin, end;      // the elements it is given
     int64_t extra;           // the last integer argument: cuts, span, or the folds' number of partials
     int64_t keep_from;
@@ -80,7 +81,7 @@ hipError_t __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *shared, hi
     return hipSuccess;
 }
 
-hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t, hipStream_t stream)
+hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, size_t shared, hipStream_t stream)
 {
     Launch l;
     memset(&l, 0, sizeof l);
@@ -89,6 +90,7 @@ hipError_t hipLaunchKernel(const void *fn, dim3 grid, dim3 block, void **args, s
     l.grid = grid.x;
     l.block = block.x;
     l.stream = reinterpret_cast<uint64_t>(stream);
+    l.lds = shared;
     const uint64_t items = (uint64_t)grid.x * block.x;
     l.status = items == 0 || items >= (1ull << 32) || block.x > 1024 ? hipErrorInvalidConfiguration : hipSuccess;
     auto arg = [&](int i) { return args[i]; };

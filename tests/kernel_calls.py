@@ -25,6 +25,7 @@ CALLS = [
     *[_c("spec", k, n) for k in (2, 3, 9) for n in (66_000_000, 67_200_000, L27 - 20_000, L27 + 1)],
     *[_c("spec", k, n) for k in (2, 7, 8, 11) for n in (L28 - 1, L28)],
     _c("spec", 1, L21 + 1, cus=64),
+    *[_c("spec", k, n, cus=64) for k, n in ((6, 67_200_000), (7, 134_300_000), (9, 134_300_000))],
     # the norm: one workgroup, then by length for each number of streams with a kernel of its own; K = 8 and any k
     # in 256, 512 and 1024 lanes; long runs on some of the CUs
     *[_c("norm", k, n) for k in (1, 2, 3, 4) for n in (1, 16_000, 20_000, L22, L22 + 1)],

@@ -23,7 +23,7 @@ STREAM = 0x5000
 
 class _Launch(ctypes.Structure):
     _fields_ = [("kernel", ctypes.c_char * 128), ("grid", ctypes.c_uint64), ("block", ctypes.c_uint64),
-                ("stream", ctypes.c_uint64), ("begin", ctypes.c_int64), ("end", ctypes.c_int64), ("extra", ctypes.c_int64),
+                ("stream", ctypes.c_uint64), ("lds", ctypes.c_uint64), ("begin", ctypes.c_int64), ("end", ctypes.c_int64), ("extra", ctypes.c_int64),
                 ("keep_from", ctypes.c_int64), ("partials", ctypes.c_uint64), ("out", ctypes.c_uint64),
                 ("status", ctypes.c_int32)]
 
@@ -38,6 +38,7 @@ class Launch:
     targs: tuple           # those, as numbers (false/true as 0/1)
     grid: int
     block: int
+    lds: int               # bytes of LDS asked for beyond what the kernel itself declares
     begin: int
     end: int
     extra: int
@@ -115,7 +116,7 @@ class Recorder:
             r = _Launch()
             lib.rec_get(i, ctypes.byref(r))
             kernel, targs = parse_name(r.kernel.decode())
-            out.append(Launch(kernel, targs, r.grid, r.block, r.begin, r.end, r.extra, r.keep_from, r.partials, r.out, r.status))
+            out.append(Launch(kernel, targs, r.grid, r.block, r.lds, r.begin, r.end, r.extra, r.keep_from, r.partials, r.out, r.status))
         asked = [lib.rec_mask_query(i) for i in range(lib.rec_mask_queries())]
         return st, out, asked, wsb
 

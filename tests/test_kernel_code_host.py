@@ -47,4 +47,4 @@ def test_leftover_streams_of_the_speculative_pass_are_in_flight_together(kernels
             wait = next(j for j, l in enumerate(rest) if "s_waitcnt" in l and "vmcnt" in l)
             loads = sum("global_load" in l for l in rest[:wait])
             assert loads == int(m[1]), (name, line.strip(), loads)
-    assert found == 9          # three kernels, each with 1, 2 and 3 streams left
+    assert found == 12         # four kernels, each with 1, 2 and 3 streams left

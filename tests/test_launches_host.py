@@ -96,6 +96,20 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+# on a stream confined to some of the CUs the bytes that each of them has in flight are what counts
+@pytest.mark.parametrize("cus", [16, 64, 128, 192])
+def test_speculative_pass_on_some_of_the_cus_fills_them(rec, cus):
+    for k in (1, 2, 7, 8, 11, 16, 32):
+        for length in ((1 << 21) + 1, 12_600_000, 67_000_000, 67_200_000, 134_000_000, 134_300_000, (1 << 28) - 1, 1 << 28, 1 << 29, 1 << 32):
+            for ws in (MIN_WS, FULL):
+                l = work_of(rec, "spec", k, 3, 3 + length, ws, cus=cus)
+                assert l.lds == 0, (k, length, l.name)
+                # a partial per 256 elements; per 512, and up to 2^28 elements with few streams in runs; runs of as many
+                want = (64, 4, 2, 1, 0) if ws == FULL or length <= 67_000_000 else \
+                    (128, 4, 4, 1, 0) if length <= 134_000_000 or (k <= 7 and length < 1 << 28) else (256, 2, 4, 0, 1)
+                assert l.targs == want, (k, length, l.name)
+
+
 def test_staged_norm_of_long_ranges_pairs_elements_for_whole_batches_only(rec):
     for length in ((1 << 25) - 1, 1 << 25, 200_000_000):
         for k in range(1, 33):

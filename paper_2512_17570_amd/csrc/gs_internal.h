@@ -10,6 +10,9 @@
 // limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
 #define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
 #define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
+#define GS_LATE_MIN 960000            // elements above which a step of one generation of waves reads its arguments late;
+#define GS_LATE_MIN_STEP 140000       // the line lies that much higher for each stream below 7
+#define GS_LATE_MAX_MANY 1400000      // and up to which it does with 8 streams and more
 #define GS_FULL_MAX 7000000           // elements up to which a CU holds as many workgroups as it can
 #define GS_FULL_ODD_MAX (1 << 24)     // the same line for 9 to 23 streams that are no multiple of 8
 #define GS_DEEP_MAX (1 << 25)         // elements up to which multiples of 8 streams have 8 loads in flight

@@ -327,9 +327,10 @@ struct StepView {
     const double *d_sqnorm;
     const float *acc;
 };
-// Where a wave waits between its accesses anyway it gains nothing, and the shapes that do lose (2 M elements, k = 1 / 4
-// 10.9/13.0 us against 10.1/11.9); so does the staged step of a small range (13 k 2.07 against 1.99).  Read late, but
-// through this view, 1 M elements take 5.61/6.73/8.41/10.8 us with k = 1 / 4 / 8 / 16, against 6.21/6.96/8.20/10.6 from the argument block.
+// Where a wave waits between its stores, pinning them all and taking the norm early loses (2 M elements, k = 1 / 4
+// 10.9/13.0 us against 10.1/11.9), and so it does in the staged step of a small range (13 k 2.07 against 1.99).  There the
+// compiler is left to place the reads: through this view it puts all of them but the streams' addresses and the norm at
+// the entry, behind one wait; from the argument block itself (LATE) each where its value is needed (late_arguments says when).
 template <bool STAGED, bool LWAIT, bool SWAIT>
 constexpr bool reads_early = !STAGED && !LWAIT && !SWAIT;
 
@@ -351,6 +352,14 @@ __device__ __forceinline__ StepView view_of(const StepArgs &A)
     return V;
 }
 
+template <bool EARLY, bool LATE>
+__device__ __forceinline__ decltype(auto) arguments(const StepArgs &A)
+{
+    static_assert(!(EARLY && LATE), "one of them");
+    if constexpr (LATE) return static_cast<const StepArgs &>(A);
+    else return view_of<EARLY>(A);
+}
+
 // The group of EL elements starting at `lo` (a multiple of EL): vector path when the group lies
 // inside [begin,end), per-element path for ragged range ends -- same arithmetic.  States are read
 // from A.p/m/v and written to A.po/mo/vo (the same arrays for the in-place entry points).
@@ -358,8 +367,8 @@ __device__ __forceinline__ StepView view_of(const StepArgs &A)
 // of the accumulated gradients to acc0/acc1.  DEPTH: gradient loads in flight per batch.  LWAIT:
 // the fp32 loads are waited for one by one.  SWAIT: each store waits for the previous one.  THROUGH: the
 // stores are written through.
-template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
-__device__ __forceinline__ void step_group(const StepView &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
+template <int EL, bool STAGED, bool NORM, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false, typename Args>
+__device__ __forceinline__ void step_group(const Args &A, int64_t lo, const double *d_sqnorm, double &acc0, double &acc1)
 {
     typedef typename Group<EL>::F F;
     typedef typename Group<EL>::H H;
@@ -476,11 +485,11 @@ __device__ __forceinline__ void step_one(const StepArgs &A, int64_t i)
 // one lane each: in the wave of their neighbours they come after its whole groups, and the range
 // ends one memory latency later (us, k = 1 / 8 / 32: 100 001 elements 2.9/3.0/4.2 against 3.5/4.0/7.2 there, 1 000 001
 // elements 5.8/8.9/17.0 against 6.3/9.7/19.9; from 3 M on within 2 %).
-template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH>
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH, bool LATE>
 __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 {
     constexpr int TILE = BLOCK * EL;
-    const StepView V = view_of<reads_early<STAGED, LWAIT, SWAIT>>(A);
+    decltype(auto) V = arguments<reads_early<STAGED, LWAIT, SWAIT>, LATE>(A);
     const int64_t b = (int64_t)blockIdx.x - cuts;
     if (b < 0) {
         const int64_t head = (A.begin + EL - 1) / EL * EL;         // where the first whole group starts
@@ -898,7 +907,21 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
     return k < 20 && elems <= GS_DEEP_ODD_MAX ? SHAPE_DEEP : SHAPE_STREAM;
 }
 
-template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false>
+// Whether a step in one generation of waves (RESIDENT, SERIAL) reads its arguments late.  While the range is bound by the
+// latency of a wave's chain, each wait more is time (us, view / late, k = 4 / 8 / 16: 700 k 5.9/6.9/8.7 against 6.2/7.2/9.2); once
+// the memory is busy, a gap between a wave's state loads and its gradient loads spreads what the waves, which all start
+// together, ask for at a time (1 M, k = 7 / 16 8.4/11.3 against 8.2/11.0; 1.3 M, k = 9 / 11 12.3/13.0 against 11.1/11.9).  The memory is busy
+// later with few streams (k = 4 1.15 M 7.7 against 7.9, 1.5 M 9.8 against 9.1, and in SERIAL the view is 1 % ahead again; up to three
+// streams it wins throughout, 1 M, k = 1 5.8 against 6.5); with many the gain ends where the chip is half full (1.5 M, k = 9 / 16
+// 13.4/16.6 against 13.9/16.9).  On some of the CUs the view wins throughout (128 CUs, 1.3 M, k = 9 / 12 15.7/16.4 against 16.0/16.9).
+static bool late_arguments(int64_t elems, int k, hipStream_t stream)
+{
+    if (k < 4 || elems <= GS_LATE_MIN + (k < 7 ? 7 - k : 0) * GS_LATE_MIN_STEP) return false;
+    if (elems > (k == 4 ? GS_RESIDENT_MAX / 4 * 3 : k < 8 ? GS_RESIDENT_MAX : GS_LATE_MAX_MANY)) return false;
+    return !on_cu_budget(stream);
+}
+
+template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false, bool LATE = false>
 static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t room = 0)
 {
     constexpr int64_t TILE = (int64_t)BLOCK * EL;
@@ -908,14 +931,14 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
     if (tiles + cuts > max_grid(BLOCK)) {                           // too long for one launch: two, cut where a tile starts
         StepArgs half = A;
         half.end = (A.begin / TILE + tiles / 2) * TILE;
-        const hipError_t e = launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH>(half, stream, room);
+        const hipError_t e = launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>(half, stream, room);
         if (e != hipSuccess) return e;
         half.begin = half.end;
         half.end = A.end;
-        return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH>(half, stream, room);
+        return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>(half, stream, room);
     }
     if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
-    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH><<<(int)(tiles + cuts), BLOCK, room, stream>>>(A, cuts);
+    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE><<<(int)(tiles + cuts), BLOCK, room, stream>>>(A, cuts);
     return hipGetLastError();
 }
 
@@ -936,8 +959,14 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
         }
         return launch_step<64, 2, STAGED, 8, false, false>(A, stream);
     }
-    case SHAPE_RESIDENT: return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
-    case SHAPE_SERIAL: return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
+    case SHAPE_RESIDENT:
+        if constexpr (!STAGED)
+            if (late_arguments(A.end - A.begin, A.k, stream)) return launch_step<64, 4, false, 4, false, true, false, true>(A, stream);
+        return launch_step<64, 4, STAGED, 4, false, true>(A, stream);
+    case SHAPE_SERIAL:
+        if constexpr (!STAGED)
+            if (late_arguments(A.end - A.begin, A.k, stream)) return launch_step<64, 4, false, 1, true, true, false, true>(A, stream);
+        return launch_step<64, 4, STAGED, 1, true, true>(A, stream);
     case SHAPE_BUDGET: return launch_step<64, 4, STAGED, 2, false, true>(A, stream);
     default: break;
     }

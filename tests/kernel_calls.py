@@ -15,6 +15,7 @@ CALLS = [
     *[_c("step", k, n) for k, n in ((1, 1), (2, 1), (5, 3), (9, 1), (17, 1001), (1, L19 + 1), (3, 1_600_000), (7, L21 + 1), (13, 7_000_001),
                                     (6, L27 + 1), (10, L27 + 1))],
     *[_c("step", k, L21 + 1, cus=64) for k in (1, 5)],
+    *[_c("step", k, n) for k, n in ((4, 1_380_001), (6, 1_100_001), (9, 1_400_000), (9, 1_400_001), (7, 1_600_000))],
     *[_c("from_acc", 1, n) for n in (1, L19 + 1, 1_600_000, L21 + 1, 7_000_001, L27 + 1)],
     _c("from_acc", 1, L21 + 1, cus=64),
     # the speculative pass: by length, workspace and streams left over after batches of four; the lines at 80 M

@@ -33,6 +33,20 @@ def test_no_kernel_uses_scratch_memory(kernels, tmp_path):
         assert not any(re.search(r"\b(scratch|buffer)_(load|store)", l) for l in lines), name
 
 
+def test_late_arguments_are_read_where_they_are_needed(kernels):
+    """Read late, a wave's arguments are not all behind the wait at its entry: there is none of the states' loads'
+    addresses, the gradients' or the hyper-parameters' before the range's ends, and the last are read after the gradients."""
+    late = [lines for name, lines in kernels.items() if re.fullmatch(r"k_accum_adamw<(\d+, \d+, false, .*, )true>", name)]
+    assert len(late) == 2
+    for lines in late:
+        code = [l.strip() for l in lines]
+        first = next(i for i, l in enumerate(code) if "lgkmcnt" in l)
+        assert sum(l.startswith("s_load") for l in code[:first]) <= 2
+        body = code[next(i for i, l in enumerate(code) if l.startswith("global_load")):]
+        loads = [i for i, l in enumerate(body) if l.startswith("global_load")]
+        assert any(l.startswith("s_load_dwordx8") for l in body[loads[3]:])
+
+
 def test_leftover_streams_of_the_speculative_pass_are_in_flight_together(kernels):
     found = 0
     for name, lines in kernels.items():

@@ -96,6 +96,21 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+def test_step_of_one_generation_reads_its_arguments_late_while_the_memory_is_busy(rec):
+    for k in range(1, 33):
+        for cus in (64, 256):
+            for length in ((1 << 19) + 1, 960_000, 960_001, 1_100_000, 1_100_001, 1_240_001, 1_380_000, 1_400_000, 1_400_001, 3 << 19, (3 << 19) + 1, 1 << 21):
+                above = {4: 1_380_000, 5: 1_240_000, 6: 1_100_000}.get(k, 960_000)
+                upto = 3 << 19 if k == 4 else 1 << 21 if k < 8 else 1_400_000
+                late = k >= 4 and above < length <= upto and cus == 256
+                serial = k <= 7 and length > 3 << 19
+                for entry in ("step", "oop"):
+                    l = work_of(rec, entry, k, 0, length, cus=cus)
+                    assert l.targs == (64, 4, 0, *((1, 1, 1) if serial else (4, 0, 1)), 0, late), (k, length, cus, l.name)
+                l = work_of(rec, "from_acc", 1, 0, length, cus=cus)
+                assert l.targs[2] == 1 and l.targs[-1] == 0
+
+
 # on a stream confined to some of the CUs the bytes that each of them has in flight are what counts
 @pytest.mark.parametrize("cus", [16, 64, 128, 192])
 def test_speculative_pass_on_some_of_the_cus_fills_them(rec, cus):

@@ -9,6 +9,7 @@
 
 // limits of the step's shapes (step_shape and launch_accum_adamw_spec say why they lie there)
 #define GS_LATENCY_MAX (1 << 19)      // elements up to which every load is in flight at once
+#define GS_LATENCY_THROUGH_STEP 12000 // what each stream takes off that line for steps of 5 to 15 streams that write through
 #define GS_RESIDENT_MAX (1 << 21)     // elements up to which 4 per lane keep all waves resident together
 #define GS_LATE_MIN 960000            // elements above which a step of one generation of waves reads its arguments late;
 #define GS_LATE_MIN_STEP 140000       // the line lies that much higher for each stream below 7

@@ -807,10 +807,8 @@ static constexpr uint32_t room_for(int workgroups)
 // 4-element shape, are resident together.
 //   <= 2^19   LATENCY: a wave's chain of dependent loads is the time, so all of them go out at once.
 //             100 k elements: 2.9/3.1/3.0/3.2/4.1 against 4.4/5.9/6.6/10.1/17.2 for loads one at a
-//             time; written through with 2 to 15 streams (100 k, k = 4 / 8 3.26/3.24 against 3.35/3.47, 400 k 4.30/4.41 against
-//             4.67/4.55; one stream loses 4 % by it at 100 k, the staged step 5-9 %, 16 streams 10 % at 400 k, and 8 over the
-//             last half of this range 2 %);
-//             at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
+//             time, and with 2 to 15 streams written through while all loads are back before the stores take the
+//             memory (latency_through); at 800 k RESIDENT is level or ahead (5.1/6.1/7.7/9.6/13.2 against 5.6/6.5/7.7/9.6/13.6).
 //   <= 2^21   RESIDENT: no second, nearly empty generation of waves: 1.3 M elements 6.7/8.5/10.3/14.7/20.7
 //             against 8.8/10.0/12.3/16.0/23.1 with 2 elements per lane and 7.4/9.4/11.8/17.4/27.1 one at a
 //             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
@@ -907,6 +905,19 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
     return k < 20 && elems <= GS_DEEP_ODD_MAX ? SHAPE_DEEP : SHAPE_STREAM;
 }
 
+// Whether a LATENCY step is written through.  Stores that wait in the L2 go out when the kernel ends, others at once, which
+// is a gain as long as no wave's loads are held up by them (without the norm, 300 k elements, k = 4 / 6 / 10 / 15 4-5 % faster);
+// the more streams, the longer the loads last (500 k, k = 6 / 9 and 450 k, k = 12 9-10 % slower): level at 484/455/435/405/378/357 k
+// elements for k = 5/6/7/10/12/15, and ahead over the whole range for 2 to 4 (500 k, k = 3 4 % faster).  8 streams are one whole batch, loaded without the tests of a
+// partial one, and meet the line sooner (330 k 2 % faster, 400 k 13 % slower), 16 before 400 k (10 % slower there).  One stream and the
+// staged step lose by it from 100 k on (4 %, 5-9 %).
+static bool latency_through(int64_t elems, int k)
+{
+    if (k < 2 || k >= 16) return false;
+    if (k < 5) return true;
+    return elems <= (k == 8 ? GS_LATENCY_MAX / 2 : GS_LATENCY_MAX - k * GS_LATENCY_THROUGH_STEP);
+}
+
 // Whether a step in one generation of waves (RESIDENT, SERIAL) reads its arguments late.  While the range is bound by the
 // latency of a wave's chain, each wait more is time (us, view / late, k = 4 / 8 / 16: 700 k 5.9/6.9/8.7 against 6.2/7.2/9.2); once
 // the memory is busy, a gap between a wave's state loads and its gradient loads spreads what the waves, which all start
@@ -950,8 +961,7 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
     case SHAPE_LATENCY: {
         if constexpr (!STAGED) {
             const uint32_t room = A.over_link ? link_room(stream) : 0;
-            const bool through = A.k >= 2 && A.k < 16 && (A.k != 8 || A.end - A.begin <= GS_LATENCY_MAX / 2);
-            if (A.over_link || through) {
+            if (A.over_link || latency_through(A.end - A.begin, A.k)) {
                 if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
                 return launch_step<64, 2, false, 8, false, false, true>(A, stream, room);
             }

@@ -12,7 +12,7 @@ def _c(entry, k, length, ws="min", cus=256, first=0, accumulate=0):
 
 CALLS = [
     # the step and the staged step, by length and on some of the CUs
-    *[_c("step", k, n) for k, n in ((1, 1), (2, 1), (5, 3), (9, 1), (17, 1001), (1, L19 + 1), (3, 1_600_000), (7, L21 + 1), (13, 7_000_001),
+    *[_c("step", k, n) for k, n in ((1, 1), (2, 1), (5, 3), (9, 1), (17, 1001), (6, 500_000), (12, 500_000), (1, L19 + 1), (3, 1_600_000), (7, L21 + 1), (13, 7_000_001),
                                     (6, L27 + 1), (10, L27 + 1))],
     *[_c("step", k, L21 + 1, cus=64) for k in (1, 5)],
     *[_c("step", k, n) for k, n in ((4, 1_380_001), (6, 1_100_001), (9, 1_400_000), (9, 1_400_001), (7, 1_600_000))],

@@ -96,6 +96,17 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+def test_step_of_a_small_range_writes_through_while_its_loads_last(rec):
+    for k in range(1, 33):
+        upto = 0 if k == 1 or k >= 16 else 1 << 19 if k < 5 else 1 << 18 if k == 8 else (1 << 19) - 12_000 * k
+        for length in (1, 100_000, 1 << 18, (1 << 18) + 1, upto, upto + 1, 1 << 19):
+            if not 1 <= length <= 1 << 19:
+                continue
+            for cus in (16, 256):
+                l = work_of(rec, "step", k, 3, 3 + length, cus=cus)
+                assert l.targs == (64, 2, 0, 16 if k > 8 else 8, 0, 0, length <= upto, 0) and l.lds == 0, (k, length, l.name)
+
+
 def test_step_of_one_generation_reads_its_arguments_late_while_the_memory_is_busy(rec):
     for k in range(1, 33):
         for cus in (64, 256):

@@ -650,7 +650,7 @@ __global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int s
 // backward adds its gradient into it (Sec. 3.4, Sec. 4.3).  acc = (FIRST ? +0 : acc) + widen(g):
 // 2 + 4 bytes read and 4 written per element (2 + 4 for the first micro-batch).  NORM: the call
 // that adds the last micro-batch also reduces the squared norm of the finished sum.
-template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT>
+template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT, bool THROUGH>
 __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
 {
     typedef typename Group<EL>::F F;
@@ -677,7 +677,7 @@ __global__ __launch_bounds__(BLOCK) void k_accum_add(AccumAddArgs A, int span)
 #pragma unroll
             for (int e = 0; e < EL; ++e) sum[e] = a[e];
             if constexpr (KEEP) st_stream<true>(reinterpret_cast<F *>(A.acc + lo), sum);
-            else st_once<!FIRST && !NORM>(reinterpret_cast<F *>(A.acc + lo), sum);
+            else st_once<THROUGH>(reinterpret_cast<F *>(A.acc + lo), sum);
         } else {
 #pragma unroll
             for (int e = 0; e < EL; ++e) {
@@ -1289,7 +1289,7 @@ hipError_t launch_acc_sqnorm(const float *acc, int64_t begin, int64_t end, doubl
     return launch_acc_norm<1, 256>(acc, begin, end, partials, 8, cap, d_out, accumulate, stream);
 }
 
-template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT>
+template <bool FIRST, bool NORM, int BLOCK, int EL, bool LWAIT, bool THROUGH = false>
 static hipError_t launch_add_as(const AccumAddArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
@@ -1297,7 +1297,7 @@ static hipError_t launch_add_as(const AccumAddArgs &A, int64_t cap, double *d_ou
     const int64_t span = fit_span(tiles, 1, 1, NORM ? cap : tiles, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_accum_add<FIRST, NORM, BLOCK, EL, LWAIT><<<grid, BLOCK, 0, stream>>>(A, (int)span);
+    k_accum_add<FIRST, NORM, BLOCK, EL, LWAIT, THROUGH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || !NORM) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
@@ -1307,13 +1307,15 @@ template <bool NORM, int BLOCK, int EL, bool LWAIT>
 static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     if (first) return launch_add_as<true, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
-    return launch_add_as<false, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
+    return launch_add_as<false, NORM, BLOCK, EL, LWAIT, LWAIT && !NORM>(A, cap, d_out, accumulate, stream);
 }
 
 // us per launch, each against 64 lanes with the buffer's load after the gradient's:
 //   first micro-batch, <= 2^22: 256 lanes               1 M 2.6 against 3.2, 2 M 3.6 against 4.4; level above
-//   later ones: written through where the sum is not left in the cache (805 M 1167 us against 1195, 201 M 291 against
-//   294, 12.6 M 19.8 against 20.2; the first micro-batch, which only writes, loses 2-4 % by it);
+//   later ones: above 2^21 elements written through where the sum is not left in the cache (805 M 1167 us against 1195,
+//   201 M 291 against 294; 64 CUs, 5 M / 20 M 18.2/64.6 against 18.8/66.2; the first micro-batch, which only writes, loses 2-4 % by it).
+//   Up to there the L2s hold the sum for the next one: the hint alone (13 k / 800 k 1.97/3.03 against 2.26/3.26 written through; four
+//   micro-batches and the step, 0.8 M / 2 M 16.6/28.4 against 18.0/29.4);
 //   later ones, <= 2^22 or on some of the CUs only: both loads in flight
 //                                                      1 M 3.2 against 3.7, 2 M 4.9 against 5.2; from 200 M on
 //                                                       waiting is 0.5 % ahead, level in between
@@ -1330,6 +1332,7 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
         if (n > GS_ADD_SMALL_MAX && !on_cu_budget(stream))
             return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
         if (first) return launch_add_as<true, false, 256, 4, false>(A, 0, nullptr, 0, stream);
+        if (n > GS_RESIDENT_MAX) return launch_add_as<false, false, 64, 4, false, true>(A, 0, nullptr, 0, stream);
         return launch_add_as<false, false, 64, 4, false>(A, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);

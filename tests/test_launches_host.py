@@ -96,6 +96,16 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+@pytest.mark.parametrize("cus", [64, 256])
+def test_later_micro_batches_of_a_small_range_stay_in_the_cache(rec, cus):
+    for length in (1, 13_000, 1 << 20, 1 << 21, (1 << 21) + 1, 1 << 22, (1 << 22) + 1, 100_000_000):
+        l = work_of(rec, "add", 1, 5, 5 + length, cus=cus)
+        waits = length > 1 << 22 and cus == 256
+        assert l.targs == (0, 0, 64, 4, waits, length > 1 << 21), (length, l.name)
+        assert work_of(rec, "add", 1, 5, 5 + length, first=1, cus=cus).targs[-1] == 0
+        assert work_of(rec, "add_norm", 1, 5, 5 + length, cus=cus).targs[-1] == 0
+
+
 def test_step_of_a_small_range_writes_through_while_its_loads_last(rec):
     for k in range(1, 33):
         upto = 0 if k == 1 or k >= 16 else 1 << 19 if k < 5 else 1 << 18 if k == 8 else (1 << 19) - 12_000 * k

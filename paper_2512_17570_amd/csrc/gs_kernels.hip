@@ -814,7 +814,8 @@ static constexpr uint32_t room_for(int workgroups)
 //             time.  Over the last quarter with few streams the memory is busy enough that SERIAL
 //             wins (2.0 M: 10.3/12.8 against 10.3/13.4 for k = 1 / 4).
 //   above     2 elements per lane, all stores back to back and written through.
-//   <= 7 M    FULL: as many workgroups as a CU holds, four gradient loads in flight, with 5 to 24 streams (FULL_DEEP) eight.
+//   <= 7 M    FULL: as many workgroups as a CU holds, four gradient loads in flight, with 5 to 19 streams (FULL_DEEP) eight
+//             (with 20 to 24 those are level with the norm and 1-3 % behind without it: 4 M / 5 M, k = 24 2.0/2.1 % slower).
 //             norm + step on three sets of tensors in turn, k = 1 / 4 / 8 / 16: 2.3 M 19.1/23.0/29.5/42.8 us against
 //             19.4/23.4/30.8/43.7 with the hint alone and four loads, 4.7 M 30.1/36.6/49.9/78.9 against 30.5/37.5/50.6/80.1.
 //   above     HBM serves this mix of reads and writes best when a fixed amount of it is asked for: more
@@ -897,7 +898,7 @@ static Shape step_shape(int64_t elems, int k, bool over_link, hipStream_t stream
         return k <= GS_SERIAL_MAX_K && elems > GS_RESIDENT_MAX / 4 * 3 ? SHAPE_SERIAL : SHAPE_RESIDENT;
     if (on_cu_budget(stream)) return SHAPE_BUDGET;
     if (k == 0) return elems <= GS_FULL_MAX ? SHAPE_FULL : SHAPE_STREAM;
-    if (elems <= GS_FULL_MAX) return k >= 5 && k <= 24 ? SHAPE_FULL_DEEP : SHAPE_FULL;
+    if (elems <= GS_FULL_MAX) return k >= 5 && k < 20 ? SHAPE_FULL_DEEP : SHAPE_FULL;
     if (k < 5) return SHAPE_STREAM;
     if (k < 8) return SHAPE_DEEP;
     if (k % 8 == 0) return k <= 24 && elems <= GS_DEEP_MAX ? SHAPE_DEEP : SHAPE_STREAM;

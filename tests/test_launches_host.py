@@ -96,6 +96,13 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+def test_step_in_full_cus_has_eight_loads_in_flight_up_to_19_streams(rec):
+    for k in range(1, 33):
+        for length in ((1 << 21) + 1, 4_000_000, 7_000_000):
+            l = work_of(rec, "step", k, 3, 3 + length)
+            assert l.targs == (128, 2, 0, 8 if 5 <= k < 20 else 4, 0, 0, 1, 0) and l.lds == 0, (k, length, l.name)
+
+
 @pytest.mark.parametrize("cus", [64, 256])
 def test_later_micro_batches_of_a_small_range_stay_in_the_cache(rec, cus):
     for length in (1, 13_000, 1 << 20, 1 << 21, (1 << 21) + 1, 1 << 22, (1 << 22) + 1, 100_000_000):

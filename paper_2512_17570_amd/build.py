@@ -81,5 +81,5 @@ def build_call(verbose: bool = True) -> str:
 
 if __name__ == "__main__":
     build()
-    build_call()
     build_probe()
+    build_call()

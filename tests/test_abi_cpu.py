@@ -3,6 +3,8 @@ declares, and rejects bad arguments before touching HIP."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
 
 import pytest
 
@@ -41,6 +43,33 @@ def test_header_symbols_all_exported():
 def test_binding_has_same_names():
     for n in declared_functions():
         assert hasattr(gs, n), n
+
+
+@pytest.mark.parametrize("error", ["No module named '_gs_call'", "_gs_call.so: undefined symbol: THPVariableClass"])
+def test_binding_without_its_native_part(error):
+    """libgs.so is all that a call needs: where the native marshalling is not built or does not load, the package is
+    imported with a warning that says why, and the general reading takes every call."""
+    code = f"""
+import importlib.abc, sys, warnings
+class Broken(importlib.abc.MetaPathFinder):
+    def find_spec(self, name, path=None, target=None):
+        if name.endswith("._gs_call"):
+            raise ImportError({error!r})
+sys.meta_path.insert(0, Broken())
+with warnings.catch_warnings(record=True) as seen:
+    warnings.simplefilter("always")
+    from paper_2512_17570_amd import gs
+said = [str(w.message) for w in seen if issubclass(w.category, RuntimeWarning)]
+assert len(said) == 1 and {error!r} in said[0], said
+assert gs.gs_sqnorm_workspace_bytes() > 0
+bad = gs.GS_ERR_INVALID_ARG
+hp = gs.HParams(step=3)
+assert gs.gs_accum_adamw(0, 0, 0, 0, [{FG0}], 0, 16, hp, check=False) == bad
+assert gs.gs_accum_adamw({FP}, {FM}, {FV}, {FW}, [{FG0}, {FG1}], 0, 0, hp, stream=0) == gs.GS_OK
+assert gs.gs_acc_sqnorm({FACC}, 5, 0, {FP}, {FM}, workspace_bytes=1 << 22, check=False) == bad
+"""
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
 
 
 def test_hparams_struct_layout_matches_header():

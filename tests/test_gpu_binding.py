@@ -164,6 +164,10 @@ def test_left_to_the_general_reading(monkeypatch, i):
     assert taken == 0
 
 
+def test_native_part_is_loaded():
+    assert gs._call.__file__.endswith("_gs_call.so")
+
+
 def test_current_stream_is_the_callers(monkeypatch):
     """A side stream that is current at the call gets the launch: it is ordered behind what that stream holds."""
     side = torch.cuda.Stream()

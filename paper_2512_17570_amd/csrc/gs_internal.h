@@ -45,9 +45,8 @@
 #define GS_NORM_512_MAX (1 << 21)
 #define GS_NORM_1024_MAX (1 << 23)
 #define GS_NORM_RUN8_MIN (1 << 23)    // one stream: elements from which a workgroup reads eight tiles instead of four,
-#define GS_NORM_RUN8_MAX (1 << 26)    // up to which it does,
-#define GS_NORM_RUN8_AGAIN (1 << 28)  // and from which it does again
-#define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two
+#define GS_NORM_RUN8_MAX (3 << 24)    // and up to which it does
+#define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two (one stream: eight instead of four)
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup
 #define GS_BUDGET_RUN_MIN 49152       // elements per CU of a confined stream from which the norms take shapes of their own

@@ -96,6 +96,12 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+def test_norm_of_one_stream_takes_runs_of_eight_where_the_fold_counts(rec):
+    for length in (1 << 22, (1 << 23) - 1, 1 << 23, 3 << 24, (3 << 24) + 1, 1 << 26, 1 << 28, (1 << 29) - 1, 1 << 29, 1 << 30):
+        l = work_of(rec, "norm", 1, 3, 3 + length, ws=FULL)
+        assert l.targs[:3] == (1, 4, 256) and l.extra == (8 if 1 << 23 <= length <= 3 << 24 or length >= 1 << 29 else 4), length
+
+
 def test_step_in_full_cus_has_eight_loads_in_flight_up_to_19_streams(rec):
     for k in range(1, 33):
         for length in ((1 << 21) + 1, 4_000_000, 7_000_000):

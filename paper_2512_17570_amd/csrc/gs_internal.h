@@ -19,8 +19,10 @@
 #define GS_DEEP_MAX (1 << 25)         // elements up to which multiples of 8 streams have 8 loads in flight
 #define GS_DEEP_ODD_MAX (1 << 26)     // the same line for 9 to 19 streams that are no multiple of 8
 #define GS_SERIAL_MAX_K 7             // "few streams"
-#define GS_LINK_WAVES 176             // of a step on host memory in flight on up to 64 CUs
-#define GS_LINK_WAVES_WIDE 512        // and on more of them
+#define GS_LINK_WAVES 22              // of a step on host memory in flight on a die with up to 8 of its CUs
+#define GS_LINK_WAVES_WIDE 64         // and with more of them
+#define GS_LINK_BOUND_MAX (1 << 23)   // elements up to which their number is bounded on 4 CUs of a die and more,
+#define GS_LINK_BOUND_MAX_WIDE (1 << 25)  // and on 16 and more
 #define GS_LDS_GRANULES 128           // a CU's 160 KB of LDS are handed out in this many pieces
 #define GS_LDS_GRANULE_BYTES 1280
 #define GS_SPEC_FEW_MAX 7000000       // speculative pass: elements up to which everything is in flight

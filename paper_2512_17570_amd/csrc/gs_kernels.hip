@@ -876,17 +876,30 @@ static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 //             its accesses leaves it idle (16 CUs, 12.6 M elements, k = 2 / 8 / 16: 3.23/3.19/3.23 ms against
 //             3.26/3.37/3.35 with stores one at a time and 3.35/3.46/3.60 one load at a time; 100 M, k = 8:
 //             25.5 ms against 26.4 and 27.3).
-// Of those waves only so many are resident as the link needs to be busy both ways: with all of them in flight the
-// first generation reads and then writes together, and the link carries one direction at a time.  On 16 / 32 / 64
-// CUs that is 11 / 5 / 2 single-wave workgroups each, on more of them 512 in all (twice that and half of it are up to
-// 8 % slower over 12.6 M elements).  Written through with any number of streams.  16 CUs, k = 1 / 8 / 16: 300 k elements 114/115/121 us against 159/153/156 with
-// the hint and full CUs, 1 M 286/286/291 against 402/324/302, 12.6 M 3.12/3.09/3.24 ms against 3.22/3.22/3.23; 1.5 M, k = 8,
-// 32 / 64 / 128 / 256 CUs 406/404/412/406 us against 435/442/477/518.
-static uint32_t link_room(hipStream_t stream)
+// With all of those waves in flight the first generation reads and then writes together, and the link carries one direction at
+// a time; with as many as the link needs to be busy both ways, and their stores written through, it does not.  16 CUs, k = 1 / 8 /
+// 16: 300 k elements 114/115/121 us against 159/153/156 with the hint and full CUs, 1 M 286/286/291 against 402/324/302, 12.6 M
+// 3.12/3.09/3.24 ms against 3.22/3.22/3.23.  On up to 3 CUs of each die, and on all of them, that wins at every length (16 / 24 CUs, 200 M, k = 8
+// 48.4/48.5 ms against 50.2/50.6; all, 50 M, k = 2 12.06 against 12.27, 200 M level); between them the full CUs come to be busy both ways by themselves, and long ranges lose 0-5 % by the bound (200 M,
+// k = 8 64 / 112 CUs 48.6/49.8 ms against 47.9/48.1; 50 M, k = 2 / 16 32 CUs 12.30/12.20 against 12.13/12.58): there it holds up to 2^23
+// elements (3 M, 64 / 112 CUs 773/809 us against 852/869), on 16 CUs of each die and more up to 2^25 (12.6 M, 128 / 192 CUs 3.12/3.12 ms
+// against 3.14/3.17; 200 M 48.7/48.7 against 48.1/48.2).
+// Work is dealt to the eight dies in turn, and on a die to its four shader engines in turn; so are the CUs of a stream, and the
+// engine that got the fewest (once every engine has one) decides what the die takes: that many CUs count (48: 4 a die, not 6).  22
+// single-wave workgroups a die are in flight up to 8 such CUs, 64 on more (about half and one and a half times that: 8-15 % slower over
+// 12.6 M elements): 1.5 M, 48 / 72 / 136 / 256 CUs 417/407/417/388 us against 510/504/528/529.  Where the dies' shares differ, the smaller
+// ones would hold the others back (60 CUs, 5 a CU 446 us against 504) and no workgroup is kept off a CU (422).
+// Returns whether the stores are written through; `room`: the LDS that bounds.
+static bool link_bound(int64_t elems, hipStream_t stream, uint32_t &room)
 {
-    const int cus = budget_cus(stream);
-    if (cus > 0 && cus <= 64) return room_for(cus < 16 ? GS_LINK_WAVES / 16 : GS_LINK_WAVES / cus);
-    return room_for(cus > 0 && cus <= GS_LINK_WAVES_WIDE / 4 ? 4 : 2);
+    const auto counting = [](int cus_of_a_die) { return cus_of_a_die < 4 ? cus_of_a_die : cus_of_a_die / 4 * 4; };
+    const int budget = budget_cus(stream), cus = budget > 0 ? budget : 256;
+    const int share = counting(cus / 8);
+    const bool alike = share == counting((cus + 7) / 8);
+    room = 0;
+    if (!(alike && (share < 4 || share == 32)) && elems > (share < 16 ? GS_LINK_BOUND_MAX : GS_LINK_BOUND_MAX_WIDE)) return false;
+    if (alike) room = room_for(share <= 8 ? GS_LINK_WAVES / share : (GS_LINK_WAVES_WIDE + share / 2) / share);
+    return true;
 }
 
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
@@ -961,8 +974,8 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
     switch (shape) {
     case SHAPE_LATENCY: {
         if constexpr (!STAGED) {
-            const uint32_t room = A.over_link ? link_room(stream) : 0;
-            if (A.over_link || latency_through(A.end - A.begin, A.k)) {
+            uint32_t room = 0;
+            if (A.over_link ? link_bound(A.end - A.begin, stream, room) : latency_through(A.end - A.begin, A.k)) {
                 if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
                 return launch_step<64, 2, false, 8, false, false, true>(A, stream, room);
             }

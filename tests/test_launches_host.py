@@ -96,6 +96,29 @@ def test_norm_on_some_of_the_cus(rec, k):
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
 
 
+def held(l, declared=0):
+    """Workgroups of a launch that a CU holds by its LDS, which is handed out in 128 pieces of 1280 bytes."""
+    assert l.lds + declared <= 65536
+    return 128 // -(-(l.lds + declared) // 1280) if l.lds else None
+
+
+# CUs of the stream: workgroups a CU holds (None: no bound).  A die's share is what its least shader engine makes of
+# it; where the dies' shares differ (18, 20, 28, 60, 92 CUs) nothing is held back
+@pytest.mark.parametrize("cus,want,upto", [(8, 21, None), (16, 11, None), (18, None, 1 << 23), (20, None, 1 << 23), (24, 7, None),
+                                           (28, None, 1 << 23), (32, 5, 1 << 23), (36, 5, 1 << 23), (40, 5, 1 << 23), (48, 5, 1 << 23),
+                                           (56, 5, 1 << 23), (60, None, 1 << 23), (64, 2, 1 << 23), (72, 2, 1 << 23), (88, 2, 1 << 23),
+                                           (92, None, 1 << 23), (96, 5, 1 << 23), (120, 5, 1 << 23), (128, 4, 1 << 25), (136, 4, 1 << 25),
+                                           (160, 3, 1 << 25), (192, 3, 1 << 25), (224, 2, 1 << 25), (255, None, 1 << 25),
+                                           (256, 2, None)])
+def test_step_on_host_memory_keeps_as_many_waves_in_flight_as_the_link_needs(rec, cus, want, upto):
+    for k in (1, 4, 8, 9, 16, 32):
+        for length in (1, 1000, 300_000, 1 << 23, (1 << 23) + 1, 1 << 25, (1 << 25) + 1, 800_000_000):
+            bound = upto is None or length <= upto
+            l = work_of(rec, "host_step", k, 3, 3 + length, cus=cus)
+            assert l.targs == (64, 2, 0, 16 if k > 8 else 8, 0, 0, bound, 0), (k, length, l.name)
+            assert held(l) == (want if bound else None), (k, length, l.lds)
+
+
 def test_norm_of_one_stream_takes_runs_of_eight_where_the_fold_counts(rec):
     for length in (1 << 22, (1 << 23) - 1, 1 << 23, 3 << 24, (3 << 24) + 1, 1 << 26, 1 << 28, (1 << 29) - 1, 1 << 29, 1 << 30):
         l = work_of(rec, "norm", 1, 3, 3 + length, ws=FULL)

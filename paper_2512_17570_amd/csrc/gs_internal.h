@@ -26,7 +26,7 @@
 #define GS_LDS_GRANULES 128           // a CU's 160 KB of LDS are handed out in this many pieces
 #define GS_LDS_GRANULE_BYTES 1280
 #define GS_SPEC_FEW_MAX 7000000       // speculative pass: elements up to which everything is in flight
-#define GS_SPEC_RUN_LONG (1 << 28)    // small workspace: elements from which runs of tiles are four and more
+#define GS_SPEC_RUN_LONG (1 << 28)    // small workspace: elements from which a CU holds one workgroup fewer for the runs of tiles
 #define GS_SPEC_RUN_MAX (1 << 29)     // and up to which they are of small tiles (up to 2 streams: the line before)
 #define GS_KEEP_BYTES ((int64_t)256 << 20)  // of a re-read stream: left in the memory-side cache (keep_from)
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels

@@ -794,7 +794,7 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
 static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
 
 // LDS that a launch asks for and does not use, so that a CU holds `workgroups` of them (of the sizes used here
-// it would otherwise hold 16 or 32): the fewest pieces of which one workgroup more would not get its share, 55 KB for
+// it would otherwise hold 8 to 32): the fewest pieces of which one workgroup more would not get its share, 55 KB for
 // two.  The 512 bytes less leave room for what the kernels do use.
 static constexpr uint32_t room_for(int workgroups)
 {

@@ -18,8 +18,8 @@ CALLS = [
     *[_c("step", k, n) for k, n in ((4, 1_380_001), (6, 1_100_001), (9, 1_400_000), (9, 1_400_001), (7, 1_600_000))],
     *[_c("from_acc", 1, n) for n in (1, L19 + 1, 1_600_000, L21 + 1, 7_000_001, L27 + 1)],
     _c("from_acc", 1, L21 + 1, cus=64),
-    # the speculative pass: by length, workspace and streams left over after batches of four; the lines at 80 M
-    # elements and, with a small workspace, at a partial per 256 or 512 elements and at 2^28 elements
+    # the speculative pass: by length, workspace and streams left over after batches of four; a long range and the lines
+    # with a small workspace, at a partial per 256 or 512 elements and at 2^28 elements; on some of the CUs
     *[_c("spec", k, n) for k, n in ((1, 1), (5, 1001), (16, 7_000_000), (1, L19 + 1), (2, 7_000_001))],
     *[_c("spec", k, 7_000_001, "full") for k in (3, 4, 5, 6, 12, 13, 14, 15)],
     *[_c("spec", k, n, "full") for k in (3, 8) for n in (79_999_999, 80_000_000)],

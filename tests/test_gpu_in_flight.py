@@ -95,10 +95,10 @@ def test_later_micro_batches_written_through_and_cached(length):
     assert bool((acc[:b] == 9.0).all()) and bool((acc[e:] == 9.0).all())
 
 
-@pytest.mark.parametrize("cus", [0, 16, 32, 64, 128, 192])
-@pytest.mark.parametrize("n,k", [(130, 2), (100_003, 9), (700_001, 8)])
+@pytest.mark.parametrize("cus", [0, 16, 32, 60, 64, 128, 192])
+@pytest.mark.parametrize("n,k", [(130, 2), (100_003, 9), (700_001, 8), ((1 << 23) + 3, 3)])
 def test_step_on_host_memory_by_cus(n, k, cus):
-    """Each number of workgroups that a CU is given over the link: the resident step's bits."""
+    """Each number of workgroups that a CU is given over the link, and none: the resident step's bits."""
     case = DeviceCase(n, k, seed=k, keep_host=False)
     case.sq.fill_(4.0)
     host = []

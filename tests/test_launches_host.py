@@ -39,7 +39,8 @@ def test_longest_ranges_are_launched(rec, entry, length, begin):
 def _lengths(rng):
     for p in range(0, 33):
         yield rng.randrange(1 << p, 2 << p)
-    for line in (1 << 19, 3 << 19, 1 << 21, 7_000_000, 1 << 22, 1 << 23, 1 << 25, 80_000_000, 1 << 27, 1 << 28, 1 << 29):
+    for line in (1 << 18, 1 << 19, 960_000, 1_400_000, 3 << 19, 1 << 21, 7_000_000, 1 << 22, 1 << 23, 1 << 24, 1 << 25, 3 << 24, 1 << 26,
+                 1 << 27, 1 << 28, 1 << 29):
         yield from (line - 1, line, line + 1)
 
 
@@ -117,6 +118,62 @@ def test_step_on_host_memory_keeps_as_many_waves_in_flight_as_the_link_needs(rec
             l = work_of(rec, "host_step", k, 3, 3 + length, cus=cus)
             assert l.targs == (64, 2, 0, 16 if k > 8 else 8, 0, 0, bound, 0), (k, length, l.name)
             assert held(l) == (want if bound else None), (k, length, l.lds)
+
+
+# a step above 2^21 elements: (loads in flight, workgroups a CU holds)
+def long_step(k, length):
+    if length <= 7_000_000:
+        return (8, None) if 5 <= k < 20 else (4, None)
+    stream, deep = (4, 10 if k % 4 == 0 else 11), (8, 9)
+    if k < 5 or k > 24:
+        return stream
+    if k < 8:
+        return deep
+    if k % 8 == 0:
+        return deep if length <= 1 << 25 else stream
+    if length <= 1 << 24:
+        return 4, None
+    return deep if k < 20 and length <= 1 << 26 else stream
+
+
+def test_long_steps_hold_as_many_workgroups_as_meant(rec):
+    for length in ((1 << 21) + 1, 7_000_000, 7_000_001, 1 << 24, (1 << 24) + 1, 1 << 25, (1 << 25) + 1, 1 << 26, (1 << 26) + 1, 800_000_000):
+        for k in range(1, 33):
+            depth, workgroups = long_step(k, length)
+            for entry in ("step", "oop"):
+                l = work_of(rec, entry, k, 3, 3 + length)
+                assert l.targs == (128, 2, 0, depth, 0, 0, 1, 0) and held(l) == workgroups, (k, length, l.name, l.lds)
+            l = work_of(rec, "step", k, 3, 3 + length, cus=64)
+            assert l.targs == (64, 4, 0, 2, 0, 1, 0, 0) and l.lds == 0
+        l = work_of(rec, "from_acc", 1, 3, 3 + length)
+        short = length <= 7_000_000
+        assert l.targs == ((128, 2, 1, 4, 0, 0, 1, 0) if short else (64, 4, 1, 4, 0, 0, 1, 0)) and held(l) == (None if short else 10)
+
+
+@pytest.mark.parametrize("ws", [MIN_WS, FULL])
+def test_speculative_pass_holds_as_many_workgroups_as_meant(rec, ws):
+    for length in (1000, 1 << 21, (1 << 21) + 1, 7_000_000, 7_000_001, 67_000_000, 67_200_000, 134_000_000, 134_300_000, (1 << 28) - 1, 1 << 28,
+                   (1 << 29) - 1, 1 << 29):
+        for k in range(1, 33):
+            l = work_of(rec, "spec", k, 3, 3 + length, ws)
+            if length <= 7_000_000:
+                want, workgroups = (256, 4, 16, 0, int(k <= 2 or (k <= 7 and length <= 1 << 21))), None
+            elif ws == FULL or length <= 67_000_000:
+                want, workgroups = (64, 4, 4, 0, 1), 16 if k <= 8 else 14
+            elif length <= 134_000_000:
+                want, workgroups = (128, 4, 4, 0, 1), 8 if k <= 4 else 7
+            elif length < (1 << 28 if k <= 2 else 1 << 29):
+                want, workgroups = (256, 2, 4, 0, 1), 6 if length < 1 << 28 else 5
+            else:
+                want, workgroups = (1024, 4, 8, 0, 1), None
+            assert l.targs == want and held(l, declared=l.block // 64 * 8) == workgroups, (k, length, l.name, l.lds)
+
+
+def test_nothing_else_keeps_workgroups_off_a_cu(rec):
+    for entry in ("add", "norm", "noalloc", "staged", "acc_norm", "add_norm"):
+        for length in (1000, 1 << 20, 12_600_000, 500_000_000):
+            for k in (1, 3, 8, 16, 32):
+                assert all(l.lds == 0 for l in rec.call(entry, k, 3, 3 + length)[1])
 
 
 def test_norm_of_one_stream_takes_runs_of_eight_where_the_fold_counts(rec):

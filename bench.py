@@ -37,8 +37,8 @@ HEADLINE = "gpt65b_layer_h8192_k16"
 # HBM bytes per gs_accum_adamw launch on the headline workload from rocprofv3 --pmc runs
 # (FETCH_SIZE and WRITE_SIZE, each scaled by the same counter's reading on a plain copy kernel
 # of known size); see profiles/.  None until measured for the workload being run.
-MEASURED_TRAFFIC_BYTES = {"gpt65b_layer_h8192_k16": 46_713_207_922,    # profiles/gs_step_gpt65b_layer_h8192_k16.txt
-                          "gpt_h4096_k8": 8_457_819_593}               # profiles/gs_step_gpt_h4096_k8.txt
+MEASURED_TRAFFIC_BYTES = {"gpt65b_layer_h8192_k16": 46_713_204_851,    # profiles/gs_step_gpt65b_layer_h8192_k16.txt
+                          "gpt_h4096_k8": 8_457_893_036}               # profiles/gs_step_gpt_h4096_k8.txt
 
 
 def parse():
@@ -748,8 +748,8 @@ def _kernel_entry(ms, bytes_per_param, n):
 def same_mix_ceiling(torch, grads, p, m, v, w, n, k, reps, block):
     """What this device gives the fused step's own mix of streams (k bf16 + 3 fp32 in, 3 fp32 + 1 bf16
     out) when no arithmetic is attached: the probe kernels of probe/gs_mixprobe.hip, out of place
-    into scratch outputs.  (a) 2 elements per lane, four gradient loads in flight: the shape the step
-    takes on long ranges (from 2^27 elements on with 8 streams or more); (b) 4 elements per lane, one load
+    into scratch outputs.  (a) 2 elements per lane, four gradient loads in flight, 10 or 11 workgroups per CU and
+    stores written through: the shape the step takes on long ranges with up to 4 or at least 8 streams; (b) 4 elements per lane, one load
     at a time; (c) 4 elements per lane, all loads in flight; (d) the read half and the write half as two
     kernels running at once on two streams."""
     from paper_2512_17570_amd import mixprobe as MP
@@ -1012,7 +1012,8 @@ def bench_resident(args, wl, full=True):
         achievable["frac_of_same_mix"] = achieved / mix["same_mix_ceiling_GBps"]
         achievable["frac_of_read_kernel_beside_write_kernel"] = achieved / mix["same_mix_read_kernel_beside_write_kernel_GBps"]
         achievable["note"] += ("; and kernels with the step's own mix of streams and no arithmetic (probe/gs_mixprobe.hip): "
-                               "2 elements per lane with four gradient loads in flight (the step kernel's main shape), 4 elements "
+                               "2 elements per lane with four gradient loads in flight, workgroups bounded and stores written through "
+                               "(the step kernel's main shape), 4 elements "
                                "per lane with one load at a time and with all in flight (same_mix_ceiling = the best of these "
                                "single kernels), and split into a read-only kernel running beside a write-only "
                                "kernel on a second stream (the same bytes issued from separate workgroups)")

@@ -8,8 +8,9 @@
 //   mode 1  the same tile with every load in flight at once and the stores back to back;
 //   mode 2  the read half only (the 2k+12 bytes in), loads one at a time;
 //   mode 3  the write half only (the 14 bytes out), stores one by one;
-//   mode 4  the step kernel's main shape without its arithmetic: 2 elements per lane, the three state
-//           loads first, gradient loads in batches of four, the four stores one by one.
+//   mode 4  the step kernel's shape for long ranges without its arithmetic: 2 elements per lane, the three state
+//           loads first, gradient loads in batches of four, the four stores back to back and written through, and
+//           as many two-wave workgroups on a CU as the step has there (10 or 11).
 // Modes 2 and 3 launched together on two streams put the same bytes on the memory system from
 // separate workgroups: if that pair is no faster than a single kernel, the mix itself -- not the way
 // one kernel interleaves its loads and stores -- sets the rate.
@@ -40,6 +41,14 @@ struct MixArgs {
 
 template <typename T> __device__ __forceinline__ T ld_stream(const T *p) { return __builtin_nontemporal_load(p); }
 template <typename T> __device__ __forceinline__ void st_stream(T *p, T v) { __builtin_nontemporal_store(v, p); }
+
+// with the hint and past the L2; a store of more than 64 bits would need an s_nop behind it
+template <typename T> __device__ __forceinline__ void st_through(T *p, T v)
+{
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "dword or dwordx2");
+    if constexpr (sizeof(T) == 4) asm volatile("global_store_dword %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+    else asm volatile("global_store_dwordx2 %0, %1, off sc1 nt" ::"v"(p), "v"(v) : "memory");
+}
 
 __device__ __forceinline__ void wait_vm_idle()
 {
@@ -122,21 +131,19 @@ __global__ __launch_bounds__(BLOCK) void k_mix_pairs(MixArgs A)
     const uint32_t t = acc & A.mask;                  // 0 at run time
     p.x ^= t; m.y ^= t; v.x ^= t;
     const uint32_t w = (p.x >> 16) | (p.y & 0xffff0000u);
-    __builtin_amdgcn_sched_barrier(0);
-    st_stream(reinterpret_cast<u32x2 *>(A.po + lo), p);
-    wait_vm_idle();
-    st_stream(reinterpret_cast<u32x2 *>(A.mo + lo), m);
-    wait_vm_idle();
-    st_stream(reinterpret_cast<u32x2 *>(A.vo + lo), v);
-    wait_vm_idle();
-    st_stream(reinterpret_cast<uint32_t *>(A.w + lo), w);
+    st_through(reinterpret_cast<u32x2 *>(A.po + lo), p);
+    st_through(reinterpret_cast<u32x2 *>(A.mo + lo), m);
+    st_through(reinterpret_cast<u32x2 *>(A.vo + lo), v);
+    st_through(reinterpret_cast<uint32_t *>(A.w + lo), w);
 }
 
 hipError_t launch_pairs(const MixArgs &A, int block, hipStream_t s)
 {
     const int64_t tiles = (A.n / 2 + block - 1) / block;
     if (block != 128 || tiles < 1 || tiles * block > 0xffffffffLL) return hipErrorInvalidValue;
-    k_mix_pairs<128><<<(int)tiles, 128, 0, s>>>(A);
+    // a CU's 160 KB of LDS are handed out in 128 pieces of 1280 bytes: 12 pieces leave room for 10 workgroups, 11 for 11
+    const uint32_t room = (A.k % 4 == 0 ? 12 : 11) * 1280 - 512;
+    k_mix_pairs<128><<<(int)tiles, 128, room, s>>>(A);
     return hipGetLastError();
 }
 

@@ -21,8 +21,6 @@
 #define GS_SERIAL_MAX_K 7             // "few streams"
 #define GS_LINK_WAVES 22              // of a step on host memory in flight on a die with up to 8 of its CUs
 #define GS_LINK_WAVES_WIDE 64         // and with more of them
-#define GS_LINK_BOUND_MAX (1 << 23)   // elements up to which their number is bounded on 4 CUs of a die and more,
-#define GS_LINK_BOUND_MAX_WIDE (1 << 25)  // and on 16 and more
 #define GS_LDS_GRANULES 128           // a CU's 160 KB of LDS are handed out in this many pieces
 #define GS_LDS_GRANULE_BYTES 1280
 #define GS_SPEC_FEW_MAX 7000000       // speculative pass: elements up to which everything is in flight

@@ -879,27 +879,22 @@ static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 // With all of those waves in flight the first generation reads and then writes together, and the link carries one direction at
 // a time; with as many as the link needs to be busy both ways, and their stores written through, it does not.  16 CUs, k = 1 / 8 /
 // 16: 300 k elements 114/115/121 us against 159/153/156 with the hint and full CUs, 1 M 286/286/291 against 402/324/302, 12.6 M
-// 3.12/3.09/3.24 ms against 3.22/3.22/3.23.  On up to 3 CUs of each die, and on all of them, that wins at every length (16 / 24 CUs, 200 M, k = 8
-// 48.4/48.5 ms against 50.2/50.6; all, 50 M, k = 2 12.06 against 12.27, 200 M level); between them the full CUs come to be busy both ways by themselves, and long ranges lose 0-5 % by the bound (200 M,
-// k = 8 64 / 112 CUs 48.6/49.8 ms against 47.9/48.1; 50 M, k = 2 / 16 32 CUs 12.30/12.20 against 12.13/12.58): there it holds up to 2^23
-// elements (3 M, 64 / 112 CUs 773/809 us against 852/869), on 16 CUs of each die and more up to 2^25 (12.6 M, 128 / 192 CUs 3.12/3.12 ms
-// against 3.14/3.17; 200 M 48.7/48.7 against 48.1/48.2).
+// 3.12/3.09/3.24 ms against 3.22/3.22/3.23.  Over long ranges full CUs come to be busy both ways by themselves, and alone they are up to 5 % ahead
+// where a die has 4 to 15 CUs (50 M, k = 2, 32 / 64 / 112 CUs 12.1/12.1/12.1 ms against 12.3/12.15/12.6; on 16, 24 and all CUs the bound is 0-4 %
+// ahead).  But they hold up other work far more: with eight 1 ms GEMMs beside it, a step of 30 M elements on 32 / 64 / 96 / all CUs and they
+// take 12.7/15.7/15.7/15.9 ms together unbounded, 11.3/11.1/11.5/11.5 bounded (one after the other 15.5), so the bound holds at every length.
 // Work is dealt to the eight dies in turn, and on a die to its four shader engines in turn; so are the CUs of a stream, and the
 // engine that got the fewest (once every engine has one) decides what the die takes: that many CUs count (48: 4 a die, not 6).  22
 // single-wave workgroups a die are in flight up to 8 such CUs, 64 on more (about half and one and a half times that: 8-15 % slower over
 // 12.6 M elements): 1.5 M, 48 / 72 / 136 / 256 CUs 417/407/417/388 us against 510/504/528/529.  Where the dies' shares differ, the smaller
-// ones would hold the others back (60 CUs, 5 a CU 446 us against 504) and no workgroup is kept off a CU (422).
-// Returns whether the stores are written through; `room`: the LDS that bounds.
-static bool link_bound(int64_t elems, hipStream_t stream, uint32_t &room)
+// ones would hold the others back (50 M, 22 / 60 / 92 CUs 6/8/10 % slower alone) and no workgroup is kept off a CU.
+static uint32_t link_room(hipStream_t stream)
 {
     const auto counting = [](int cus_of_a_die) { return cus_of_a_die < 4 ? cus_of_a_die : cus_of_a_die / 4 * 4; };
     const int budget = budget_cus(stream), cus = budget > 0 ? budget : 256;
     const int share = counting(cus / 8);
-    const bool alike = share == counting((cus + 7) / 8);
-    room = 0;
-    if (!(alike && (share < 4 || share == 32)) && elems > (share < 16 ? GS_LINK_BOUND_MAX : GS_LINK_BOUND_MAX_WIDE)) return false;
-    if (alike) room = room_for(share <= 8 ? GS_LINK_WAVES / share : (GS_LINK_WAVES_WIDE + share / 2) / share);
-    return true;
+    if (share != counting((cus + 7) / 8)) return 0;
+    return room_for(share <= 8 ? GS_LINK_WAVES / share : (GS_LINK_WAVES_WIDE + share / 2) / share);
 }
 
 // k == 0: the staged step (one fp32 sum instead of gradient streams)
@@ -974,8 +969,8 @@ static hipError_t launch_step_shape(const StepArgs &A, hipStream_t stream)
     switch (shape) {
     case SHAPE_LATENCY: {
         if constexpr (!STAGED) {
-            uint32_t room = 0;
-            if (A.over_link ? link_bound(A.end - A.begin, stream, room) : latency_through(A.end - A.begin, A.k)) {
+            const uint32_t room = A.over_link ? link_room(stream) : 0;
+            if (A.over_link || latency_through(A.end - A.begin, A.k)) {
                 if (A.k > 8) return launch_step<64, 2, false, 16, false, false, true>(A, stream, room);
                 return launch_step<64, 2, false, 8, false, false, true>(A, stream, room);
             }

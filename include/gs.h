@@ -258,6 +258,10 @@ float gs_clip_coefficient(double sqnorm_total, float max_grad_norm);
  * its layer executes).  A bandwidth-bound step that fills every CU slows a concurrent GEMM far
  * more than it is slowed itself; a stream confined to a subset of the CUs leaves the rest of the
  * chip, and part of the memory system, to the forward pass.
+ *   On an unconfined stream, steps of more than 7 million elements and speculative passes reserve LDS that
+ * they do not use (up to 55 KB a workgroup, nearly all of a CU together), to bound how many of
+ * their workgroups a CU holds; steps on pinned host memory do so on confined streams too.  A concurrent
+ * kernel that needs LDS gets on a CU as those workgroups end.
  * ------------------------------------------------------------------------------------------ */
 
 /*
@@ -348,7 +352,7 @@ int gs_stream_ctx_copies_overlap(const gs_stream_ctx *ctx);
  * back.  Nothing is staged in device memory and no copy engine is used: 46-50 GB/s each way,
  * whatever else the process does with copies and streams.  num_cus = 0: an ordinary stream;
  * num_cus > 0: a stream confined to that many compute units, as from gs_cu_stream_create (the
- * link bounds this step, so 16 CUs give 47 of the 50 GB/s that all of them reach and leave the
+ * link bounds this step, so 16 CUs give 49 of the 50 GB/s that all of them reach and leave the
  * rest of the GPU to other work).  num_cus < 0, or outside gs_cu_stream_create's range when positive, is
  * GS_ERR_INVALID_ARG.
  */

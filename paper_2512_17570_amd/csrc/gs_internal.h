@@ -45,7 +45,7 @@
 #define GS_NORM_512_MAX (1 << 21)
 #define GS_NORM_1024_MAX (1 << 23)
 #define GS_NORM_RUN8_MIN (1 << 23)    // one stream: elements from which a workgroup reads eight tiles instead of four,
-#define GS_NORM_RUN8_MAX (3 << 24)    // and up to which it does
+#define GS_NORM_RUN8_MAX (3 << 24)    // and up to which it does on all CUs
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two (one stream: eight instead of four)
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup

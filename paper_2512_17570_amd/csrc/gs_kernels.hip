@@ -1156,7 +1156,8 @@ static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap
 // / 201 M 9.7/15.2/174 us against 10.3/16.3/180; level at 50 M); one stream is best in 256 lanes at every size, in runs of
 // four tiles, and of eight from 2^29 elements on (805 M with the fold 236 against 240) and from 2^23 to 3 * 2^24: there the fold, which takes
 // a latency for each 1024 partials and one launch more above 8192 of them, is long beside the reading (with it 8.4 M / 12.6 M / 34 M
-// 7.0/8.0/14.9 against 8.1/8.6/16.4; 67 M / 200 M / 400 M 28.3/71.7/126 against 27.8/67.4/124).  From 5 streams on the workgroups grow with the range, so that they are many
+// 7.0/8.0/14.9 against 8.1/8.6/16.4; 67 M / 200 M / 400 M 28.3/71.7/126 against 27.8/67.4/124).  On some of the CUs the longer runs
+// win at every length from 2^23 on (16 / 64 / 128 CUs, 100 M 321/88.7/54.7 against 363/98.3/55.1; 300 M 942/250/150 against 1068/283/153).  From 5 streams on the workgroups grow with the range, so that they are many
 // enough to fill the chip and no more: 256, 512 and 1024 lanes up to 2^20, 2^21 and 2^23 elements (8 M,
 // k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, these shapes against 256 lanes with 8 tiles
 // one after another (k = 3, 7 and 32 in batches of 4, 2 and 1 loads):
@@ -1191,7 +1192,7 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
     }
     switch (A.k) {
     case 1: {
-        const bool long_run = (n >= GS_NORM_RUN8_MIN && n <= GS_NORM_RUN8_MAX) || n >= GS_NORM_LONG_MIN;
+        const bool long_run = n >= GS_NORM_RUN8_MIN && (n <= GS_NORM_RUN8_MAX || n >= GS_NORM_LONG_MIN || on_cu_budget(stream));
         return launch_norm<1, 4, 256>(A, long_run ? 8 : 4, cap, d_out, accumulate, stream);
     }
     case 2:

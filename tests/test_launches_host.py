@@ -171,10 +171,12 @@ def test_nothing_else_keeps_workgroups_off_a_cu(rec):
                 assert all(l.lds == 0 for l in rec.call(entry, k, 3, 3 + length)[1])
 
 
-def test_norm_of_one_stream_takes_runs_of_eight_where_the_fold_counts(rec):
+@pytest.mark.parametrize("cus", [16, 128, 256])
+def test_norm_of_one_stream_takes_runs_of_eight_where_the_fold_counts(rec, cus):
     for length in (1 << 22, (1 << 23) - 1, 1 << 23, 3 << 24, (3 << 24) + 1, 1 << 26, 1 << 28, (1 << 29) - 1, 1 << 29, 1 << 30):
-        l = work_of(rec, "norm", 1, 3, 3 + length, ws=FULL)
-        assert l.targs[:3] == (1, 4, 256) and l.extra == (8 if 1 << 23 <= length <= 3 << 24 or length >= 1 << 29 else 4), length
+        l = work_of(rec, "norm", 1, 3, 3 + length, ws=FULL, cus=cus)
+        long_run = length >= 1 << 23 and (length <= 3 << 24 or length >= 1 << 29 or cus < 256)
+        assert l.targs[:3] == (1, 4, 256) and l.extra == (8 if long_run else 4), length
 
 
 def test_step_in_full_cus_has_eight_loads_in_flight_up_to_19_streams(rec):

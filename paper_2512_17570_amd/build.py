@@ -18,6 +18,7 @@ FLAGS = [
     "-ffp-contract=off",                     # one rounding per operation: partition-independent results
     "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",   # no packed-fp32 VALU forms
+    "-mllvm", "-amdgpu-kernarg-preload-count=14",   # leading arguments in registers as a wave starts, up to all there is room for
     "-Wall", "-Wno-unused-command-line-argument",
 ]
 

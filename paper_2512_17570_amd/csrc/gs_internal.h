@@ -58,9 +58,10 @@ struct StepConsts {
     float beta1, beta2, omb1, omb2, eps, step_size, rsbc2, decay;
 };
 
-struct GradTable {
-    const uint16_t *g[GS_MAX_K];
+template <int STREAMS> struct GradTableOf {
+    const uint16_t *g[STREAMS];
 };
+typedef GradTableOf<GS_MAX_K> GradTable;
 
 struct StepArgs {
     const float *p, *m, *v;   // states in
@@ -77,9 +78,9 @@ struct StepArgs {
 };
 
 struct SqnormArgs {
+    int64_t begin, end;
     GradTable gt;
     int k;
-    int64_t begin, end;
     double *partials;
     float *acc;         // non-null: also write the fp32 gradient sum here
     int64_t keep_from;  // elements from here on are left in the memory-side cache

@@ -178,8 +178,8 @@ __device__ __forceinline__ void all_at_once(global_ptr<const uint16_t> (&p)[N + 
     asm volatile("" : "+s"(p[0]), "+s"(p[1]), "+s"(p[2]), "+s"(p[3]), "+s"(p[4]), "+s"(p[5]), "+s"(p[6]));
 }
 
-template <int EL, int DEPTH, bool KEEP = false, bool APART = false, bool TOGETHER = false>
-__device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, int64_t lo, float (&a)[EL])
+template <int EL, int DEPTH, bool KEEP = false, bool APART = false, bool TOGETHER = false, typename Table>
+__device__ __forceinline__ void accumulate_batches(const Table &gt, int k, int64_t lo, float (&a)[EL])
 {
     typedef typename Group<EL>::H H;
 #pragma unroll
@@ -239,8 +239,8 @@ __device__ __forceinline__ void accumulate_batches(const GradTable &gt, int k, i
 // The same sum for the elements [i0,i1) of a group that a range end cuts (the others get 0).  One lane
 // works alone here while the rest of the chip runs dry, so its loads go out several streams at a time: at
 // 16 streams one load after another took longer than all the whole groups of a small range together.
-template <int EL>
-__device__ __forceinline__ void accumulate_cut(const GradTable &gt, int k, int64_t lo, int64_t i0, int64_t i1, float (&a)[EL])
+template <int EL, typename Table>
+__device__ __forceinline__ void accumulate_cut(const Table &gt, int k, int64_t lo, int64_t i0, int64_t i1, float (&a)[EL])
 {
 #pragma unroll
     for (int e = 0; e < EL; ++e) a[e] = 0.0f;
@@ -542,27 +542,29 @@ __device__ __forceinline__ void add_squares(const float (&a)[EL], double &acc0, 
 // b*span: a short contiguous run per workgroup is what the read path likes best.  What else bounds
 // it is how much a wave has in flight: with few streams (compile-time K) the same groups of U tiles
 // are loaded together, otherwise (K == 0) up to DEPTH streams are.
-// ONE: a single workgroup reads the whole range and leaves the norm itself in A.out.
-template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
-__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
+// ONE: a single workgroup reads the whole range and leaves the norm itself in `out`.  Workgroups from keep_block on
+// leave what they read in the memory-side cache.
+template <int K, int U, int BLOCK, bool ONE, int DEPTH, typename Table>
+__device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, const Table &gt, int k, double *partials,
+                                            double *out, int accumulate)
 {
     constexpr int TILE = BLOCK * 4;
     __shared__ double lds[BLOCK / 64];
-    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
+    const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
-    with_keep(first - (int64_t)threadIdx.x * 4 >= A.keep_from, [&](auto keep) {
+    with_keep((int)blockIdx.x >= keep_block, [&](auto keep) {
     constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
-        if (lo >= A.end) break;
-        if (lo >= A.begin && lo + (int64_t)(U - 1) * TILE + 4 <= A.end) {
+        if (lo >= end) break;
+        if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
             if constexpr (K > 0) {
                 u32x2 g[U][K];
 #pragma unroll
                 for (int u = 0; u < U; ++u)
 #pragma unroll
                     for (int j = 0; j < K; ++j)
-                        g[u][j] = ld_stream<KEEP>(reinterpret_cast<const u32x2 *>(A.gt.g[j] + lo + (int64_t)u * TILE));
+                        g[u][j] = ld_stream<KEEP>(reinterpret_cast<const u32x2 *>(gt.g[j] + lo + (int64_t)u * TILE));
 #pragma unroll
                 for (int u = 0; u < U; ++u) {
                     float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -573,24 +575,24 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
             } else {
                 static_assert(K > 0 || U == 1, "tiles are grouped for a compile-time K only");
                 float a[4];
-                accumulate_batches<4, DEPTH, KEEP>(A.gt, A.k, lo, a);
+                accumulate_batches<4, DEPTH, KEEP>(gt, k, lo, a);
                 add_squares(a, acc0, acc1);
             }
         } else {
             // a range end lies among these tiles: group by group, and by element in the group it cuts
             for (int u = 0; u < U; ++u) {
                 const int64_t l = lo + (int64_t)u * TILE;
-                if (l >= A.begin && l + 4 <= A.end) {
+                if (l >= begin && l + 4 <= end) {
                     float a[4];
-                    accumulate_batches<4, K == 0 ? DEPTH : K, KEEP>(A.gt, A.k, l, a);
+                    accumulate_batches<4, K == 0 ? DEPTH : K, KEEP>(gt, k, l, a);
                     add_squares(a, acc0, acc1);
                     continue;
                 }
-                const int64_t i0 = l > A.begin ? l : A.begin;
-                const int64_t i1 = l + 4 < A.end ? l + 4 : A.end;
+                const int64_t i0 = l > begin ? l : begin;
+                const int64_t i1 = l + 4 < end ? l + 4 : end;
                 if (i0 >= i1) continue;
                 float a[4];
-                accumulate_cut<4>(A.gt, A.k, l, i0, i1, a);
+                accumulate_cut<4>(gt, k, l, i0, i1, a);
                 add_squares(a, acc0, acc1);
             }
         }
@@ -598,9 +600,34 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(SqnormArgs A, int span)
     });
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) {
-        if constexpr (ONE) *A.out = A.accumulate ? *A.out + t : t;
-        else A.partials[blockIdx.x] = t;
+        if constexpr (ONE) *out = accumulate ? *out + t : t;
+        else partials[blockIdx.x] = t;
     }
+}
+
+template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
+__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, GradTable gt, int k, int accumulate,
+                                                       double *partials, double *out)
+{
+    grad_sqnorm<K, U, BLOCK, ONE, DEPTH>(begin, span, keep_block, end, gt, k, partials, out, accumulate);
+}
+
+// up to eight streams
+template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
+__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, GradTableOf<8> gt, int k, int accumulate,
+                                                       double *partials, double *out)
+{
+    grad_sqnorm<K, U, BLOCK, ONE, (DEPTH < 8 ? DEPTH : 8)>(begin, span, keep_block, end, gt, k, partials, out, accumulate);
+}
+
+// up to four (entries of the table beyond K are not read)
+template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
+__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, const uint16_t *g0, const uint16_t *g1,
+                                                       const uint16_t *g2, const uint16_t *g3, double *partials, double *out, int accumulate)
+{
+    static_assert(K >= 1 && K <= 4, "streams by compile-time number");
+    const GradTableOf<4> gt{{g0, g1, g2, g3}};
+    grad_sqnorm<K, U, BLOCK, ONE, DEPTH>(begin, span, keep_block, end, gt, K, partials, out, accumulate);
 }
 
 // The same norm that also writes the fp32 sum a_i to A.acc (the staged two-pass variant: the step
@@ -792,6 +819,16 @@ static int64_t tiles_of(int64_t begin, int64_t end, int64_t tile)
 
 // HIP launches fewer than 2^32 work items at a time: the workgroups of `block` lanes that is.
 static constexpr int64_t max_grid(int block) { return 0xffffffffLL / block; }
+
+// A launch whose arguments are given by reference, each of exactly the kernel's own type.
+template <typename... P, typename... V>
+static hipError_t launch(void (*kernel)(P...), int grid, int block, uint32_t lds, hipStream_t stream, V &...v)
+{
+    static_assert((std::is_same_v<P, std::remove_const_t<V>> && ...), "the runtime copies as many bytes as the kernel's arguments have");
+    void *args[] = {const_cast<void *>(static_cast<const void *>(&v))...};
+    (void)hipLaunchKernel(reinterpret_cast<const void *>(kernel), dim3(grid), dim3(block), args, lds, stream);
+    return hipGetLastError();
+}
 
 // LDS that a launch asks for and does not use, so that a CU holds `workgroups` of them (of the sizes used here
 // it would otherwise hold 8 to 32): the fewest pieces of which one workgroup more would not get its share, 55 KB for
@@ -1113,6 +1150,38 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
+// A norm's launch.  Its kernels take their arguments one by one and not as a block: leading arguments that fit 14 registers are
+// in them as a wave starts (the build asks for that), where a block is fetched from memory by every workgroup before its first load,
+// and by all CUs at once as the kernel starts.  Up to four streams everything a load needs is there, from five on all but the streams'
+// addresses, in a table no longer than it has to be up to eight.  With the fold, us, against a block of 300 bytes: 13 k, k = 4 3.47 against
+// 3.73; 4 k, k = 8 2.88 against 3.15; 3.3 M, k = 3 7.2 against 7.7; 5 M, k = 4 9.9 against 11.1; 7 M, k = 5 16.2 against 17.3; 12.6 M,
+// k = 1 / 4 / 8 7.85/19.8/38.0 against 8.04/20.9/38.8; fp32 norm, 5 M / 10 M 6.35/9.1 against 6.8/9.5; within 1 % from 200 M on.  On the
+// host a launch with up to 112 bytes of arguments takes 2.7 us, one with more 3.3-3.5 (a step, and no slope: 416 bytes 3.5).
+template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
+static hipError_t launch_norm_kernel(SqnormArgs &A, int grid, int span, hipStream_t stream)
+{
+    constexpr int64_t TILE = (int64_t)BLOCK * 4;
+    // the first workgroup whose tiles start at keep_from or beyond
+    const int64_t past = A.keep_from - A.begin / TILE * TILE;
+    const int64_t keep = past > 0 ? (past + span * TILE - 1) / (span * TILE) : 0;
+    int keep_block = keep < grid ? (int)keep : grid;
+    typedef const uint16_t *G;
+    G *const g = A.gt.g;
+    if constexpr (K >= 1 && K <= 4) {
+        void (*const kernel)(int64_t, int, int, int64_t, G, G, G, G, double *, double *, int) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
+        return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, g[0], g[1], g[2], g[3], A.partials, A.out, A.accumulate);
+    } else {
+        if constexpr (K == 0 && DEPTH > 8) {
+            void (*const kernel)(int64_t, int, int, int64_t, GradTable, int, int, double *, double *) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
+            if (A.k > 8) return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.gt, A.k, A.accumulate, A.partials, A.out);
+        }
+        GradTableOf<8> gt;
+        for (int j = 0; j < 8; ++j) gt.g[j] = g[j];
+        void (*const kernel)(int64_t, int, int, int64_t, GradTableOf<8>, int, int, double *, double *) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
+        return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, gt, A.k, A.accumulate, A.partials, A.out);
+    }
+}
+
 template <int K, int U, int BLOCK, int DEPTH = 16>
 static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
@@ -1121,8 +1190,7 @@ static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d
     span = fit_span(tiles, span, U, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    k_grad_sqnorm<K, U, BLOCK, false, DEPTH><<<grid, BLOCK, 0, stream>>>(A, (int)span);
-    hipError_t e = hipGetLastError();
+    hipError_t e = launch_norm_kernel<K, U, BLOCK, false, DEPTH>(A, grid, (int)span, stream);
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
@@ -1133,8 +1201,7 @@ static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, h
 {
     A.out = d_out;
     A.accumulate = accumulate;
-    k_grad_sqnorm<K, U, GS_ONE_BLOCK, true><<<1, GS_ONE_BLOCK, 0, stream>>>(A, U);
-    return hipGetLastError();
+    return launch_norm_kernel<K, U, GS_ONE_BLOCK, true>(A, 1, U, stream);
 }
 
 // from 5 streams on (K = 8: without the tests for streams that are not there, 1-2 % at 8 streams)

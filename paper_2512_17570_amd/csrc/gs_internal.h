@@ -18,6 +18,12 @@
 #define GS_FULL_ODD_MAX (1 << 24)     // the same line for 9 to 23 streams that are no multiple of 8
 #define GS_DEEP_MAX (1 << 25)         // elements up to which multiples of 8 streams have 8 loads in flight
 #define GS_DEEP_ODD_MAX (1 << 26)     // the same line for 9 to 19 streams that are no multiple of 8
+#define GS_NEAR_MAX 1200000           // elements up to which a step's arrays are given by distances; with all loads in flight only up to
+#define GS_NEAR_LATENCY_MAX 430000    // this many with one and eight streams, with two to seven
+#define GS_NEAR_THROUGH_MAX 330000    // up to this line less
+#define GS_NEAR_THROUGH_STEP 9000     // this for each of them
+#define GS_NEAR_CLIP_BIT (1u << 22)   // such a step: whether the norm clips and the distances' unit, above its number of elements
+#define GS_NEAR_UNIT_BIT (1u << 23)
 #define GS_SERIAL_MAX_K 7             // "few streams"
 #define GS_LINK_WAVES 22              // of a step on host memory in flight on a die with up to 8 of its CUs
 #define GS_LINK_WAVES_WIDE 64         // and with more of them
@@ -64,12 +70,12 @@ template <int STREAMS> struct GradTableOf {
 typedef GradTableOf<GS_MAX_K> GradTable;
 
 struct StepArgs {
+    int64_t begin, end;
     const float *p, *m, *v;   // states in
     float *po, *mo, *vo;      // states out (the same arrays for the in-place entry points)
     uint16_t *w;
     GradTable gt;
     int k;
-    int64_t begin, end;
     StepConsts c;
     float max_norm;
     const double *d_sqnorm;

@@ -505,6 +505,157 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
     step_group<EL, STAGED, false, DEPTH, LWAIT, SWAIT, THROUGH>(V, lo, V.d_sqnorm, unused0, unused1);
 }
 
+// The same for up to eight streams in place, with the arrays given by their distances from p (near_to).  A range of one generation of
+// waves is bound by the chain launch, arguments, loads, update, stores: at four bytes an array all that the loads of up to four streams need
+// is in registers as a wave starts, the others' distances and the constants arrive under the states' loads, and with 112 bytes in all instead of 396
+// the launch takes 0.5-0.7 us less of the host as well (launch_norm_kernel).  us, against addresses in a block: 1 k / 13 k / 100 k, k = 4
+// 2.39/2.48/2.67 against 2.55/2.64/2.91; 200 k, k = 1 / 4 / 7 3.10/2.96/3.06 against 3.34/3.25/3.35; 600 k, k = 1 / 5 4.31/5.04 against 4.67/5.81;
+// 900 k, k = 2 / 6 / 8 5.4/7.2/7.9 against 5.6/7.6/8.3.  near_args says where not.
+// With 4 elements per lane (SWAIT) the memory is busy: there the gradients' loads go first, and from seven streams on only when the states are
+// back (states first / gradients first / waited for: 700 k, k = 4 / 6 / 8 5.44/6.18/6.89, 5.41/6.07/6.91, 5.74/5.99/6.58; 550 k, k = 6 / 8
+// 4.98/5.47, 4.95/5.39, 5.41/5.67).
+template <int K> struct NearRest {
+    int g[4];            // streams 4 to 7
+    int w;
+    float max_norm;
+    StepConsts c;
+};
+
+// the address `at` units of 2^unit bytes from `base`
+template <typename T>
+__device__ __forceinline__ T *near_to(float *base, int at, int unit)
+{
+    return reinterpret_cast<T *>(reinterpret_cast<char *>(base) + ((int64_t)at << unit));
+}
+
+template <int K, int BLOCK, int EL, int DEPTH, bool SWAIT, bool THROUGH>
+__device__ __forceinline__ void step_near(int64_t begin, int cuts, uint32_t packed, float *p, const double *d_sqnorm, int m_at, int v_at, int g0, int g1,
+                                          int g2, int g3, NearRest<K> R)
+{
+    typedef typename Group<EL>::F F;
+    typedef typename Group<EL>::H H;
+    constexpr int TILE = BLOCK * EL;
+    const int64_t end = begin + (packed % GS_NEAR_CLIP_BIT);
+    const bool clip = packed & GS_NEAR_CLIP_BIT;
+    const int unit = packed & GS_NEAR_UNIT_BIT ? 8 : 4;
+    float *const m = near_to<float>(p, m_at, unit), *const v = near_to<float>(p, v_at, unit);
+    const int64_t b = (int64_t)blockIdx.x - cuts;
+    if (b < 0) {
+        const int64_t head = (begin + EL - 1) / EL * EL;         // where the first whole group starts
+        const int64_t tail = end / EL * EL;                      // where the last one ends
+        int64_t i = begin + threadIdx.x;
+        if (i >= head) i += (tail > head ? tail : head) - head;    // past the first cut group: on to the last
+        if (threadIdx.x >= 2 * EL || i >= end) return;
+        const int at[8] = {g0, g1, g2, g3, R.g[0], R.g[1], R.g[2], R.g[3]};
+        float pe = p[i], me = m[i], ve = v[i], a = 0.0f;
+        uint32_t g[K];
+#pragma unroll
+        for (int q = 0; q < K; ++q) g[q] = near_to<const uint16_t>(p, at[q], unit)[i];
+#pragma unroll
+        for (int q = 0; q < K; ++q) a += __uint_as_float(g[q] << 16);
+        adamw_element(a, clip ? clip_from(*d_sqnorm, R.max_norm) : 1.0f, R.c, pe, me, ve);
+        p[i] = pe;
+        m[i] = me;
+        v[i] = ve;
+        near_to<uint16_t>(p, R.w, unit)[i] = (uint16_t)f32_to_bf16_bits(pe);
+        return;
+    }
+    const int64_t lo = ((int64_t)((uint64_t)begin / TILE) + b) * TILE + (int64_t)threadIdx.x * EL;
+    if (lo < begin || lo + EL > end) return;
+    const int at[8] = {g0, g1, g2, g3, R.g[0], R.g[1], R.g[2], R.g[3]};
+    F pv, mv, vv;
+    H g[DEPTH];
+    double sqnorm = 0.0;
+    auto load_states = [&] {
+        pv = ld_stream(reinterpret_cast<const F *>(p + lo));
+        mv = ld_stream(reinterpret_cast<const F *>(m + lo));
+        vv = ld_stream(reinterpret_cast<const F *>(v + lo));
+    };
+    auto load_batch = [&](int j) {
+#pragma unroll
+        for (int q = 0; q < DEPTH; ++q)
+            if (j + q < K) g[q] = ld_stream(reinterpret_cast<const H *>(near_to<const uint16_t>(p, at[j + q], unit) + lo));
+    };
+    if constexpr (SWAIT && K < 7) {
+        load_batch(0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_states();
+        __builtin_amdgcn_sched_barrier(0);
+    } else {
+        load_states();
+        if (!SWAIT && clip) sqnorm = ld_beside(d_sqnorm);
+        __builtin_amdgcn_sched_barrier(0);
+        if constexpr (SWAIT) {
+            wait_vm_idle();
+        } else {
+            // the states' loads are on their way: now the arguments that came through memory, together
+            asm volatile("" : "+s"(R.g[0]), "+s"(R.g[1]), "+s"(R.g[2]), "+s"(R.g[3]), "+s"(R.w), "+s"(R.max_norm), "+s"(R.c.beta1), "+s"(R.c.beta2),
+                         "+s"(R.c.omb1), "+s"(R.c.omb2), "+s"(R.c.eps), "+s"(R.c.step_size), "+s"(R.c.rsbc2), "+s"(R.c.decay));
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        load_batch(0);
+    }
+    float a[EL];
+#pragma unroll
+    for (int e = 0; e < EL; ++e) a[e] = 0.0f;
+#pragma unroll
+    for (int j = 0; j < K; j += DEPTH) {
+        if (j > 0) load_batch(j);
+#pragma unroll
+        for (int q = 0; q < DEPTH; ++q)
+            if (j + q < K) add_bf16(a, g[q]);
+        if (j + DEPTH < K) __builtin_amdgcn_sched_barrier(0);
+    }
+    float c = 1.0f;
+    if (SWAIT) {
+        if (clip) c = clip_from(*d_sqnorm, R.max_norm);
+    } else if (clip) {
+        asm volatile("" : "+v"(sqnorm));       // here, under the loads in flight, and not where it is loaded
+        c = clip_from(sqnorm, R.max_norm);
+    }
+    F P, M, V;
+    uint32_t W[EL];
+#pragma unroll
+    for (int e = 0; e < EL; ++e) {
+        float pe = pv[e], me = mv[e], ve = vv[e];
+        adamw_element(a[e], c, R.c, pe, me, ve);
+        P[e] = pe;
+        M[e] = me;
+        V[e] = ve;
+        W[e] = f32_to_bf16_bits(pe);
+    }
+    H w;
+    if constexpr (EL == 2) w = W[0] | (W[1] << 16);
+    else w = H{W[0] | (W[1] << 16), W[2] | (W[3] << 16)};
+    if constexpr (SWAIT) __builtin_amdgcn_sched_barrier(0);
+    st_once<THROUGH>(reinterpret_cast<F *>(p + lo), P);
+    if constexpr (SWAIT) wait_vm_idle();
+    st_once<THROUGH>(reinterpret_cast<F *>(m + lo), M);
+    if constexpr (SWAIT) wait_vm_idle();
+    st_once<THROUGH>(reinterpret_cast<F *>(v + lo), V);
+    if constexpr (SWAIT) wait_vm_idle();
+    st_once<THROUGH>(reinterpret_cast<H *>(near_to<uint16_t>(p, R.w, unit) + lo), w);
+}
+
+// a kernel for each number of streams: told at run time, the compiler waits for each of two or three loads before the next
+#define GS_NEAR_STEP(K)                                                                                                                        \
+    template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH, bool LATE>                                      \
+    __global__ __launch_bounds__(BLOCK) void k_accum_adamw(int64_t begin, int cuts, uint32_t packed, float *p, const double *d_sqnorm, int m_at, \
+                                                           int v_at, int g0, int g1, int g2, int g3, NearRest<K> R)                            \
+    {                                                                                                                                          \
+        static_assert(!STAGED && !LWAIT, "the shapes of ranges that are one generation of waves");                                             \
+        step_near<K, BLOCK, EL, DEPTH, SWAIT, THROUGH>(begin, cuts, packed, p, d_sqnorm, m_at, v_at, g0, g1, g2, g3, R);                       \
+    }
+GS_NEAR_STEP(1)
+GS_NEAR_STEP(2)
+GS_NEAR_STEP(3)
+GS_NEAR_STEP(4)
+GS_NEAR_STEP(5)
+GS_NEAR_STEP(6)
+GS_NEAR_STEP(7)
+GS_NEAR_STEP(8)
+#undef GS_NEAR_STEP
+
 // Speculative single pass (Sec. 2.1 of the paper: prior work steps before the global norm is
 // known because clipping rarely changes the gradients): the step is applied with c = 1 and the
 // squared norm of the same accumulated gradients is reduced on the way, so the gradients are
@@ -978,6 +1129,44 @@ static bool late_arguments(int64_t elems, int k, hipStream_t stream)
     return !on_cu_budget(stream);
 }
 
+struct NearArgs {
+    uint32_t packed;     // elements, whether the norm clips, and the distances' unit
+    float *p;
+    int m, v, g[8], w;
+};
+
+// The arguments of a step in place with up to eight streams as distances from p, if all of its arrays lie within 32 GB of
+// it, or within 512 GB and as many bytes beyond multiples of 256 as it does (an allocator deals out such addresses; even in a small process some are
+// 32 GB apart).  In LATENCY loads that go out sooner run into the stores of the waves before, where those are written through: level at
+// 325/300/310/295/285/270 k elements for 2 to 7 streams (350 k, k = 4 / 7 3.9/4.5 us against 3.8/4.3), at 450 k for one and eight.  In RESIDENT they
+// come all at once as the memory gets busy: 2-7 % behind from 1.3 M on for 6 to 8 streams (up to five 1 % ahead there, and level above).
+static bool near_args(const StepArgs &A, NearArgs &N)
+{
+    const int64_t n = A.end - A.begin;
+    if (A.over_link || A.k > 8 || A.po != A.p || A.mo != A.m || A.vo != A.v) return false;
+    if (n > GS_NEAR_MAX) return false;
+    if (n <= GS_LATENCY_MAX && n > (A.k == 1 || A.k == 8 ? GS_NEAR_LATENCY_MAX : GS_NEAR_THROUGH_MAX - A.k * GS_NEAR_THROUGH_STEP)) return false;
+    static_assert(GS_NEAR_MAX < GS_NEAR_CLIP_BIT, "the parts of `packed`");
+    const auto bytes_from_p = [&](const void *q) { return (int64_t)(reinterpret_cast<uintptr_t>(q) - reinterpret_cast<uintptr_t>(A.p)); };
+    int64_t any = bytes_from_p(A.m) | bytes_from_p(A.v) | bytes_from_p(A.w);
+    for (int j = 0; j < A.k; ++j) any |= bytes_from_p(A.gt.g[j]);
+    const int unit = any % 256 == 0 ? 8 : 4;
+    bool fits = true;
+    const auto from_p = [&](const void *q) {
+        const int64_t d = bytes_from_p(q) >> unit;
+        if (d != (int)d) fits = false;
+        return (int)d;
+    };
+    const bool clip = A.d_sqnorm && A.max_norm > 0.0f;
+    N.packed = (uint32_t)n + (clip ? GS_NEAR_CLIP_BIT : 0) + (unit == 8 ? GS_NEAR_UNIT_BIT : 0);
+    N.p = A.po;
+    N.m = from_p(A.m);
+    N.v = from_p(A.v);
+    for (int j = 0; j < 8; ++j) N.g[j] = j < A.k ? from_p(A.gt.g[j]) : 0;
+    N.w = from_p(A.w);
+    return fits;
+}
+
 template <int BLOCK, int EL, bool STAGED, int DEPTH, bool LWAIT, bool SWAIT, bool THROUGH = false, bool LATE = false>
 static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t room = 0)
 {
@@ -995,8 +1184,36 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
         return launch_step<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>(half, stream, room);
     }
     if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
-    k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE><<<(int)(tiles + cuts), BLOCK, room, stream>>>(A, cuts);
-    return hipGetLastError();
+    const int grid = (int)(tiles + cuts);
+    if constexpr (BLOCK == 64 && !STAGED && !LWAIT && !LATE && (DEPTH == 4 || DEPTH == 8)) {
+        NearArgs N;
+        if (near_args(A, N)) {
+            const auto go = [&](auto streams) {
+                constexpr int K = decltype(streams)::value;
+                // one stream is not written through, two to seven are as long as they are near
+                if constexpr (EL == 2 && ((THROUGH && K == 1) || (!THROUGH && K > 1 && K < 8))) {
+                    return hipErrorInvalidValue;
+                } else {
+                    NearRest<K> R{{N.g[4], N.g[5], N.g[6], N.g[7]}, N.w, A.max_norm, A.c};
+                    void (*const kernel)(int64_t, int, uint32_t, float *, const double *, int, int, int, int, int, int, NearRest<K>) =
+                        k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>;
+                    return launch(kernel, grid, BLOCK, room, stream, A.begin, cuts, N.packed, N.p, A.d_sqnorm, N.m, N.v, N.g[0], N.g[1], N.g[2], N.g[3], R);
+                }
+            };
+            switch (A.k) {
+            case 1: return go(std::integral_constant<int, 1>{});
+            case 2: return go(std::integral_constant<int, 2>{});
+            case 3: return go(std::integral_constant<int, 3>{});
+            case 4: return go(std::integral_constant<int, 4>{});
+            case 5: return go(std::integral_constant<int, 5>{});
+            case 6: return go(std::integral_constant<int, 6>{});
+            case 7: return go(std::integral_constant<int, 7>{});
+            case 8: return go(std::integral_constant<int, 8>{});
+            }
+        }
+    }
+    void (*const kernel)(StepArgs, int) = k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>;
+    return launch(kernel, grid, BLOCK, room, stream, A, cuts);
 }
 
 template <bool STAGED>

@@ -47,9 +47,9 @@
 #define GS_ADD_WIDE_MAX (1 << 23)     // with the norm: elements up to which a workgroup takes 4096 of them
 // limits of the norm's shapes (launch_grad_norm)
 #define GS_NORM_SMALL_MAX (1 << 22)   // up to 4 streams: elements up to which workgroups are kept small
-#define GS_NORM_256_MAX (1 << 20)     // from 5 streams on: elements up to which they have 256, 512 and 1024 lanes
-#define GS_NORM_512_MAX (1 << 21)
-#define GS_NORM_1024_MAX (1 << 23)
+#define GS_NORM_256_MAX (3 << 18)     // from 5 streams on: elements up to which workgroups have 256 lanes
+#define GS_NORM_512_MAX 5500000       // and up to which one of 512 lanes reads one tile; above that two, with 5 to 7 streams
+#define GS_NORM_1024_MAX (1 << 25)    // up to this line with 1024 lanes
 #define GS_NORM_RUN8_MIN (1 << 23)    // one stream: elements from which a workgroup reads eight tiles instead of four,
 #define GS_NORM_RUN8_MAX (3 << 24)    // and up to which it does on all CUs
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two (one stream: eight instead of four)

@@ -507,8 +507,8 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 
 // The same for up to eight streams in place, with the arrays given by their distances from p (near_to).  A range of one generation of
 // waves is bound by the chain launch, arguments, loads, update, stores: at four bytes an array all that the loads of up to four streams need
-// is in registers as a wave starts, the others' distances and the constants arrive under the states' loads, and with 112 bytes in all instead of 396
-// the launch takes 0.5-0.7 us less of the host as well (launch_norm_kernel).  us, against addresses in a block: 1 k / 13 k / 100 k, k = 4
+// is in registers as a wave starts, the others' distances and the constants arrive under the states' loads, and 112 bytes in all instead of 396
+// shorten the host's launch as well (launch_norm_kernel).  us, against addresses in a block: 1 k / 13 k / 100 k, k = 4
 // 2.39/2.48/2.67 against 2.55/2.64/2.91; 200 k, k = 1 / 4 / 7 3.10/2.96/3.06 against 3.34/3.25/3.35; 600 k, k = 1 / 5 4.31/5.04 against 4.67/5.81;
 // 900 k, k = 2 / 6 / 8 5.4/7.2/7.9 against 5.6/7.6/8.3.  near_args says where not.
 // With 4 elements per lane (SWAIT) the memory is busy: there the gradients' loads go first, and from seven streams on only when the states are
@@ -691,8 +691,11 @@ __device__ __forceinline__ void add_squares(const float (&a)[EL], double &acc0, 
 
 // Read-only, 2k bytes per element.  Workgroup b reads `span` consecutive tiles starting at tile
 // b*span: a short contiguous run per workgroup is what the read path likes best.  What else bounds
-// it is how much a wave has in flight: with few streams (compile-time K) the same groups of U tiles
-// are loaded together, otherwise (K == 0) up to DEPTH streams are.
+// it is how much a wave has in flight: with up to four streams the same groups of U tiles are loaded together, with more
+// of them up to DEPTH streams are.  K: the number of streams, or 0 where it is told at run time (the long runs on some of the CUs).  Told
+// at run time, each stream of a partial batch is a test, a scalar load and a wait before its load: with the fold, us, a kernel for each
+// number against that, 4 k elements, k = 5 / 17 2.37/3.76 against 2.65/4.33; 13 k, k = 9 / 24 3.91/5.00 against 4.35/5.70; 100 k, k = 12 / 29
+// 4.51/5.54 against 4.93/6.23; 1 M, k = 13 / 17 7.75/8.97 against 8.26/9.66; 12 M, k = 11 / 17 46.6/67.2 against 47.6/69.2; 1 % from 50 M on.
 // ONE: a single workgroup reads the whole range and leaves the norm itself in `out`.  Workgroups from keep_block on
 // leave what they read in the memory-side cache.
 template <int K, int U, int BLOCK, bool ONE, int DEPTH, typename Table>
@@ -700,29 +703,36 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
                                             double *out, int accumulate)
 {
     constexpr int TILE = BLOCK * 4;
+    constexpr bool KEEPS = !ONE && (BLOCK > 256 || (K > 0 && K <= 4));       // the others read up to 2^20 elements, or on some of the CUs
     __shared__ double lds[BLOCK / 64];
     const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
-    with_keep((int)blockIdx.x >= keep_block, [&](auto keep) {
+    with_keep(KEEPS && (int)blockIdx.x >= keep_block, [&](auto keep) {
     constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
         if (lo >= end) break;
         if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
             if constexpr (K > 0) {
-                u32x2 g[U][K];
+                static_assert(K <= DEPTH || U == 1, "tiles are grouped for one batch of streams");
+                constexpr int BATCH = K < DEPTH ? K : DEPTH;
+                u32x2 g[U][BATCH];
+                float a[U][4] = {};
 #pragma unroll
-                for (int u = 0; u < U; ++u)
+                for (int from = 0; from < K; from += BATCH) {
 #pragma unroll
-                    for (int j = 0; j < K; ++j)
-                        g[u][j] = ld_stream<KEEP>(reinterpret_cast<const u32x2 *>(gt.g[j] + lo + (int64_t)u * TILE));
+                    for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int u = 0; u < U; ++u) {
-                    float a[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+                        for (int j = 0; j < BATCH; ++j)
+                            if (from + j < K) g[u][j] = ld_stream<KEEP>(reinterpret_cast<const u32x2 *>(gt.g[from + j] + lo + (int64_t)u * TILE));
 #pragma unroll
-                    for (int j = 0; j < K; ++j) add_bf16(a, g[u][j]);
-                    add_squares(a, acc0, acc1);
+                    for (int u = 0; u < U; ++u)
+#pragma unroll
+                        for (int j = 0; j < BATCH; ++j)
+                            if (from + j < K) add_bf16(a[u], g[u][j]);
                 }
+#pragma unroll
+                for (int u = 0; u < U; ++u) add_squares(a[u], acc0, acc1);
             } else {
                 static_assert(K > 0 || U == 1, "tiles are grouped for a compile-time K only");
                 float a[4];
@@ -735,7 +745,7 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
                 const int64_t l = lo + (int64_t)u * TILE;
                 if (l >= begin && l + 4 <= end) {
                     float a[4];
-                    accumulate_batches<4, K == 0 ? DEPTH : K, KEEP>(gt, k, l, a);
+                    accumulate_batches<4, (K == 0 || K > DEPTH ? DEPTH : K), KEEP>(gt, k, l, a);
                     add_squares(a, acc0, acc1);
                     continue;
                 }
@@ -756,20 +766,17 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
     }
 }
 
-template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
-__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, GradTable gt, int k, int accumulate,
-                                                       double *partials, double *out)
-{
-    grad_sqnorm<K, U, BLOCK, ONE, DEPTH>(begin, span, keep_block, end, gt, k, partials, out, accumulate);
-}
-
-// up to eight streams
-template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
-__global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, GradTableOf<8> gt, int k, int accumulate,
-                                                       double *partials, double *out)
-{
-    grad_sqnorm<K, U, BLOCK, ONE, (DEPTH < 8 ? DEPTH : 8)>(begin, span, keep_block, end, gt, k, partials, out, accumulate);
-}
+#define GS_NORM_KERNEL(STREAMS)                                                                                                                \
+    template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>                                                                               \
+    __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, int keep_block, int64_t end, GradTableOf<STREAMS> gt, int k, \
+                                                           int accumulate, double *partials, double *out)                                      \
+    {                                                                                                                                          \
+        grad_sqnorm<K, U, BLOCK, ONE, DEPTH>(begin, span, keep_block, end, gt, K > 0 ? K : k, partials, out, accumulate);                      \
+    }
+GS_NORM_KERNEL(8)
+GS_NORM_KERNEL(16)
+GS_NORM_KERNEL(32)
+#undef GS_NORM_KERNEL
 
 // up to four (entries of the table beyond K are not read)
 template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
@@ -1146,6 +1153,7 @@ static bool near_args(const StepArgs &A, NearArgs &N)
     if (A.over_link || A.k > 8 || A.po != A.p || A.mo != A.m || A.vo != A.v) return false;
     if (n > GS_NEAR_MAX) return false;
     if (n <= GS_LATENCY_MAX && n > (A.k == 1 || A.k == 8 ? GS_NEAR_LATENCY_MAX : GS_NEAR_THROUGH_MAX - A.k * GS_NEAR_THROUGH_STEP)) return false;
+    static_assert(GS_NEAR_THROUGH_MAX <= GS_LATENCY_MAX - 7 * GS_LATENCY_THROUGH_STEP, "two to seven streams are written through as long as they are near");
     static_assert(GS_NEAR_MAX < GS_NEAR_CLIP_BIT, "the parts of `packed`");
     const auto bytes_from_p = [&](const void *q) { return (int64_t)(reinterpret_cast<uintptr_t>(q) - reinterpret_cast<uintptr_t>(A.p)); };
     int64_t any = bytes_from_p(A.m) | bytes_from_p(A.v) | bytes_from_p(A.w);
@@ -1190,7 +1198,6 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
         if (near_args(A, N)) {
             const auto go = [&](auto streams) {
                 constexpr int K = decltype(streams)::value;
-                // one stream is not written through, two to seven are as long as they are near
                 if constexpr (EL == 2 && ((THROUGH && K == 1) || (!THROUGH && K > 1 && K < 8))) {
                     return hipErrorInvalidValue;
                 } else {
@@ -1373,7 +1380,8 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
 // addresses, in a table no longer than it has to be up to eight.  With the fold, us, against a block of 300 bytes: 13 k, k = 4 3.47 against
 // 3.73; 4 k, k = 8 2.88 against 3.15; 3.3 M, k = 3 7.2 against 7.7; 5 M, k = 4 9.9 against 11.1; 7 M, k = 5 16.2 against 17.3; 12.6 M,
 // k = 1 / 4 / 8 7.85/19.8/38.0 against 8.04/20.9/38.8; fp32 norm, 5 M / 10 M 6.35/9.1 against 6.8/9.5; within 1 % from 200 M on.  On the
-// host a launch with up to 112 bytes of arguments takes 2.7 us, one with more 3.3-3.5 (a step, and no slope: 416 bytes 3.5).
+// host a launch with up to 112 bytes of arguments takes 2.28 us, one with more 2.33, and on a core that another program shares 2.7 against 3.3
+// (a step, and no slope: 416 bytes 3.35).
 template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
 static hipError_t launch_norm_kernel(SqnormArgs &A, int grid, int span, hipStream_t stream)
 {
@@ -1388,13 +1396,10 @@ static hipError_t launch_norm_kernel(SqnormArgs &A, int grid, int span, hipStrea
         void (*const kernel)(int64_t, int, int, int64_t, G, G, G, G, double *, double *, int) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
         return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, g[0], g[1], g[2], g[3], A.partials, A.out, A.accumulate);
     } else {
-        if constexpr (K == 0 && DEPTH > 8) {
-            void (*const kernel)(int64_t, int, int, int64_t, GradTable, int, int, double *, double *) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
-            if (A.k > 8) return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.gt, A.k, A.accumulate, A.partials, A.out);
-        }
-        GradTableOf<8> gt;
-        for (int j = 0; j < 8; ++j) gt.g[j] = g[j];
-        void (*const kernel)(int64_t, int, int, int64_t, GradTableOf<8>, int, int, double *, double *) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
+        constexpr int STREAMS = K > 16 ? 32 : K > 8 ? 16 : 8;                 // K == 0: the long runs on some of the CUs, up to seven streams
+        GradTableOf<STREAMS> gt;
+        for (int j = 0; j < STREAMS; ++j) gt.g[j] = g[j];
+        void (*const kernel)(int64_t, int, int, int64_t, GradTableOf<STREAMS>, int, int, double *, double *) = k_grad_sqnorm<K, U, BLOCK, ONE, DEPTH>;
         return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, gt, A.k, A.accumulate, A.partials, A.out);
     }
 }
@@ -1421,15 +1426,25 @@ static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, h
     return launch_norm_kernel<K, U, GS_ONE_BLOCK, true>(A, 1, U, stream);
 }
 
-// from 5 streams on (K = 8: without the tests for streams that are not there, 1-2 % at 8 streams)
+// from 5 streams on
 template <int K>
 static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t n = A.end - A.begin;
+    if (tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4) <= 1) return launch_norm_one<K, 1>(A, d_out, accumulate, stream);
     if (n <= GS_NORM_256_MAX) return launch_norm<K, 1, 256>(A, 1, cap, d_out, accumulate, stream);
     if (n <= GS_NORM_512_MAX) return launch_norm<K, 1, 512>(A, 1, cap, d_out, accumulate, stream);
-    if (n <= GS_NORM_1024_MAX) return launch_norm<K, 1, 1024>(A, 2, cap, d_out, accumulate, stream);
+    if constexpr (K < 8)
+        if (n <= GS_NORM_1024_MAX) return launch_norm<K, 1, 1024>(A, 2, cap, d_out, accumulate, stream);
     return launch_norm<K, 1, 512>(A, run, cap, d_out, accumulate, stream);
+}
+
+template <int K>
+static hipError_t launch_norm_by_streams(const SqnormArgs &A, int64_t run, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+{
+    if (A.k == K) return launch_norm_many<K>(A, run, cap, d_out, accumulate, stream);
+    if constexpr (K < GS_MAX_K) return launch_norm_by_streams<K + 1>(A, run, cap, d_out, accumulate, stream);
+    return hipErrorInvalidValue;
 }
 
 // Up to four 4096-element tiles (one, from 5 streams on) a single workgroup reads the range and no fold has to
@@ -1441,13 +1456,16 @@ static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap
 // four tiles, and of eight from 2^29 elements on (805 M with the fold 236 against 240) and from 2^23 to 3 * 2^24: there the fold, which takes
 // a latency for each 1024 partials and one launch more above 8192 of them, is long beside the reading (with it 8.4 M / 12.6 M / 34 M
 // 7.0/8.0/14.9 against 8.1/8.6/16.4; 67 M / 200 M / 400 M 28.3/71.7/126 against 27.8/67.4/124).  On some of the CUs the longer runs
-// win at every length from 2^23 on (16 / 64 / 128 CUs, 100 M 321/88.7/54.7 against 363/98.3/55.1; 300 M 942/250/150 against 1068/283/153).  From 5 streams on the workgroups grow with the range, so that they are many
-// enough to fill the chip and no more: 256, 512 and 1024 lanes up to 2^20, 2^21 and 2^23 elements (8 M,
-// k = 8: 23.0 us in 1024 lanes, 23.5 in 512, 24.6 in 256).  us without the fold, these shapes against 256 lanes with 8 tiles
-// one after another (k = 3, 7 and 32 in batches of 4, 2 and 1 loads):
-//   100 k  k = 1/3/8/32  2.4/2.6/3.3/4.5 against 3.5/6.3/8.1/38     12.6 M  6.2/14.0/33.0/127 against 8.4/15.8/35.4/151
-//   1 M    k = 1/3/8/32  2.9/3.4/5.2/11.9 against 5.8/10.6/8.6/40   201 M   61/176/466/1882 against 89/191/474/1932
-//   3.3 M  k = 1/3/8/32  4.0/5.4/11.0/37 against 6.5/11.5/11.0/51   805 M   231/713/1848/7849 against 347/737/1851/7903
+// win at every length from 2^23 on (16 / 64 / 128 CUs, 100 M 321/88.7/54.7 against 363/98.3/55.1; 300 M 942/250/150 against 1068/283/153).
+// From 5 streams on a workgroup reads one tile while that makes no more workgroups than the chip holds a few times over, and two
+// beyond: 256 lanes up to 3 * 2^18 elements (600 k, k = 11 / 32 6.15/10.7 us against 6.5/11.6 in 512; 900 k 7.1/13.1 against 6.8/12.4), 512 and one
+// tile up to 5.5 M (against two tiles of 1024 lanes, with the end of the range left in the cache: 2.2 M, k = 5 / 8 / 16 / 32 7.1/9.9/16.1/28.7
+// against 8.1/12.1/20.5/38.3, 3 M 8.7/11.8/19.9/36.1 against 9.2/12.9/22.2/40.9, 5 M 12.5/17.4/30.4/58.3 against 12.4/18.2/33.3/62.6), then two tiles (8 M,
+// k = 8 / 16 / 32 24.8/47.3/83.2 against 25.0/46.1/82.5 with one, 10 M 30.3/55.7/103.7 against 31.7/56.5/105.5); 5 to 7 streams read those in 1024 lanes up
+// to 2^25 (k = 5, 8 M / 20 M 16.5/36.3 against 17.0/37.6).  us, all with the fold, against 256 lanes with 8 tiles one after another, without it:
+//   100 k  k = 1/3/8/32  3.9/4.0/4.3/5.7 against 3.5/6.3/8.1/38     12.6 M  7.8/15.2/35.5/120 against 8.4/15.8/35.4/151
+//   1 M    k = 1/3/8/32  4.4/4.8/6.3/12.4 against 5.8/10.6/8.6/40   201 M   67/176/466/1882 against 89/191/474/1932
+//   3 M    k = 1/3/8/32  4.9/6.5/11.8/36 against 6.5/11.5/11.0/51   805 M   236/713/1848/7849 against 347/737/1851/7903
 // (all reads with the non-temporal hint; keep_from says what leaving them in the cache costs)
 //   On some of the CUs, 4 to 7 streams: once each CU has some tens of thousands of elements to read, 256 lanes,
 //   four loads in flight and eight tiles one after another (k = 4 / 5, 50 M elements: 16 CUs 523/694 us against
@@ -1465,14 +1483,13 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
     const bool small = n <= GS_NORM_SMALL_MAX;
     const int64_t run = n < GS_NORM_LONG_MIN ? 2 : 4;
     const int64_t tiles = tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4);
-    if (tiles <= (A.k <= 4 ? 4 : 1)) {
+    if (tiles <= 4) {
         switch (A.k) {
         case 1: return launch_norm_one<1, 4>(A, d_out, accumulate, stream);
         case 2: return launch_norm_one<2, 4>(A, d_out, accumulate, stream);
         case 3: return launch_norm_one<3, 4>(A, d_out, accumulate, stream);
         case 4: return launch_norm_one<4, 4>(A, d_out, accumulate, stream);
         }
-        return launch_norm_one<0, 1>(A, d_out, accumulate, stream);
     }
     switch (A.k) {
     case 1: {
@@ -1489,8 +1506,7 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
         if (small) return launch_norm<4, 2, 256>(A, 2, cap, d_out, accumulate, stream);
         return launch_norm<4, 2, 512>(A, run, cap, d_out, accumulate, stream);
     }
-    return A.k == 8 ? launch_norm_many<8>(A, run, cap, d_out, accumulate, stream)
-                    : launch_norm_many<0>(A, run, cap, d_out, accumulate, stream);
+    return launch_norm_by_streams<5>(A, run, cap, d_out, accumulate, stream);
 }
 
 template <int BLOCK, int EL, int DEPTH, bool KEEPS = true>

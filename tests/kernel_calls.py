@@ -27,10 +27,11 @@ CALLS = [
     *[_c("spec", k, n) for k in (2, 7, 8, 11) for n in (L28 - 1, L28)],
     _c("spec", 1, L21 + 1, cus=64),
     *[_c("spec", k, n, cus=64) for k, n in ((6, 67_200_000), (7, 134_300_000), (9, 134_300_000))],
-    # the norm: one workgroup, then by length for each number of streams with a kernel of its own; K = 8 and any k
-    # in 256, 512 and 1024 lanes; long runs on some of the CUs
+    # the norm: one workgroup, then by length for each number of streams with a kernel of its own; from
+    # five on in 256 and 512 lanes, up to seven in 1024; long runs on some of the CUs
     *[_c("norm", k, n) for k in (1, 2, 3, 4) for n in (1, 16_000, 20_000, L22, L22 + 1)],
     *[_c("norm", k, n) for k in (5, 8, 23) for n in (1, 5000, L20, L20 + 1, L21, L21 + 1, L23, L23 + 1)],
+    *[_c("norm", k, n) for k in range(5, 33) for n in (1, 5000, L20)], *[_c("norm", k, 6_000_000) for k in (5, 6, 7)],
     *[_c("norm", k, 1_000_000, cus=16) for k in (5, 7)], _c("norm", 4, 6_400_000, cus=64),
     _c("norm", 8, 12_600_000, accumulate=1),
     # the norm of an fp32 sum

@@ -41,6 +41,8 @@
 // limits of the staged norm's and the adding kernel's shapes (launch_staged_norm, launch_accum_add)
 #define GS_STAGED_WIDE_MAX (1 << 22)  // elements up to which a workgroup takes 4096 of them
 #define GS_STAGED_WIDE_MANY_MAX (1 << 20)  // the same for more than 16 streams
+#define GS_STAGED_WIDE_AGAIN_MIN 4500000   // and, up to 16 streams on all CUs, from this length
+#define GS_STAGED_WIDE_AGAIN_MAX 10000000  // to this one
 #define GS_STAGED_PAIR_MIN (1 << 25)  // elements from which, with 8 streams or more, a lane takes 2 of them
 #define GS_STAGED_KEEP_MAX_K 16       // streams up to which the end of the sum is left in the memory-side cache
 #define GS_ADD_SMALL_MAX (1 << 22)    // without the norm: elements up to which both loads are in flight together

@@ -794,40 +794,54 @@ __global__ __launch_bounds__(BLOCK) void k_grad_sqnorm(int64_t begin, int span, 
 // so it uses a span of 1 wherever the partials still fit the workspace.  KEEPS: some of the sum is left
 // in the memory-side cache; where none is, the choice alone would cost the one tile of a wave 1-2 %
 // (50 M, k = 2, 16 CUs: 741 us against 752).
-template <int BLOCK, int EL, int DEPTH, bool KEEPS>
-__global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(SqnormArgs A, int span)
+template <int BLOCK, int EL, int DEPTH, bool KEEPS, typename Table>
+__device__ __forceinline__ void grad_accum_sqnorm(int64_t begin, int span, int keep_block, int64_t end, float *acc, const Table &gt, int k, double *partials)
 {
     typedef typename Group<EL>::F F;
     constexpr int TILE = BLOCK * EL;
     __shared__ double lds[BLOCK / 64];
-    const int64_t first = (A.begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
+    const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * EL;
     double acc0 = 0.0, acc1 = 0.0;
-    with_keep(KEEPS && first - (int64_t)threadIdx.x * EL >= A.keep_from, [&](auto keep) {
+    with_keep(KEEPS && (int)blockIdx.x >= keep_block, [&](auto keep) {
     constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; ++it) {
         const int64_t lo = first + (int64_t)it * TILE;
-        if (lo >= A.end) break;
-        if (lo + EL <= A.begin) continue;
+        if (lo >= end) break;
+        if (lo + EL <= begin) continue;
         float a[EL];
-        if (lo >= A.begin && lo + EL <= A.end) {
-            accumulate_batches<EL, DEPTH>(A.gt, A.k, lo, a);
+        if (lo >= begin && lo + EL <= end) {
+            accumulate_batches<EL, DEPTH>(gt, k, lo, a);
             F sum;
 #pragma unroll
             for (int e = 0; e < EL; ++e) sum[e] = a[e];
-            st_stream<KEEP>(reinterpret_cast<F *>(A.acc + lo), sum);
+            st_stream<KEEP>(reinterpret_cast<F *>(acc + lo), sum);
         } else {
-            const int64_t i0 = lo > A.begin ? lo : A.begin;
-            const int64_t i1 = lo + EL < A.end ? lo + EL : A.end;
-            accumulate_cut<EL>(A.gt, A.k, lo, i0, i1, a);
+            const int64_t i0 = lo > begin ? lo : begin;
+            const int64_t i1 = lo + EL < end ? lo + EL : end;
+            accumulate_cut<EL>(gt, k, lo, i0, i1, a);
 #pragma unroll
             for (int e = 0; e < EL; ++e)
-                if (lo + e >= i0 && lo + e < i1) A.acc[lo + e] = a[e];
+                if (lo + e >= i0 && lo + e < i1) acc[lo + e] = a[e];
         }
         add_squares(a, acc0, acc1);
     }
     });
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
-    if (threadIdx.x == 0) A.partials[blockIdx.x] = t;
+    if (threadIdx.x == 0) partials[blockIdx.x] = t;
+}
+
+// up to eight streams, and any number
+template <int BLOCK, int EL, int DEPTH, bool KEEPS>
+__global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(int64_t begin, int span, int keep_block, int64_t end, float *acc, GradTableOf<8> gt, int k,
+                                                             double *partials)
+{
+    grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>(begin, span, keep_block, end, acc, gt, k, partials);
+}
+template <int BLOCK, int EL, int DEPTH, bool KEEPS>
+__global__ __launch_bounds__(BLOCK) void k_grad_accum_sqnorm(int64_t begin, int span, int keep_block, int64_t end, float *acc, GradTable gt, int k,
+                                                             double *partials)
+{
+    grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>(begin, span, keep_block, end, acc, gt, k, partials);
 }
 
 // ---- accumulate as you go ------------------------------------------------------------------
@@ -1374,6 +1388,14 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
+// The first of `grid` workgroups, of `run` elements each from the tile on that `begin` lies in, that starts at keep_from or beyond.
+static int first_kept(int64_t begin, int64_t keep_from, int64_t run, int64_t tile, int grid)
+{
+    const int64_t past = keep_from - begin / tile * tile;
+    const int64_t first = past > 0 ? (past + run - 1) / run : 0;
+    return first < grid ? (int)first : grid;
+}
+
 // A norm's launch.  Its kernels take their arguments one by one and not as a block: leading arguments that fit 14 registers are
 // in them as a wave starts (the build asks for that), where a block is fetched from memory by every workgroup before its first load,
 // and by all CUs at once as the kernel starts.  Up to four streams everything a load needs is there, from five on all but the streams'
@@ -1385,11 +1407,7 @@ static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int acc
 template <int K, int U, int BLOCK, bool ONE, int DEPTH = 16>
 static hipError_t launch_norm_kernel(SqnormArgs &A, int grid, int span, hipStream_t stream)
 {
-    constexpr int64_t TILE = (int64_t)BLOCK * 4;
-    // the first workgroup whose tiles start at keep_from or beyond
-    const int64_t past = A.keep_from - A.begin / TILE * TILE;
-    const int64_t keep = past > 0 ? (past + span * TILE - 1) / (span * TILE) : 0;
-    int keep_block = keep < grid ? (int)keep : grid;
+    const int keep_block = first_kept(A.begin, A.keep_from, (int64_t)span * BLOCK * 4, BLOCK * 4, grid);
     typedef const uint16_t *G;
     G *const g = A.gt.g;
     if constexpr (K >= 1 && K <= 4) {
@@ -1509,6 +1527,20 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
     return launch_norm_by_streams<5>(A, run, cap, d_out, accumulate, stream);
 }
 
+template <int BLOCK, int EL, int DEPTH, bool KEEPS>
+static hipError_t launch_staged_kernel(const SqnormArgs &A, int grid, int span, hipStream_t stream)
+{
+    const int keep_block = first_kept(A.begin, A.keep_from, (int64_t)span * BLOCK * EL, BLOCK * EL, grid);
+    if (A.k <= 8) {
+        GradTableOf<8> gt;
+        for (int j = 0; j < 8; ++j) gt.g[j] = A.gt.g[j];
+        void (*const kernel)(int64_t, int, int, int64_t, float *, GradTableOf<8>, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
+        return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, gt, A.k, A.partials);
+    }
+    void (*const kernel)(int64_t, int, int, int64_t, float *, GradTable, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
+    return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, A.gt, A.k, A.partials);
+}
+
 template <int BLOCK, int EL, int DEPTH, bool KEEPS = true>
 static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
@@ -1517,17 +1549,21 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
     const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    if (KEEPS && A.keep_from < A.end) k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS><<<grid, BLOCK, 0, stream>>>(A, (int)span);
-    else k_grad_accum_sqnorm<BLOCK, EL, DEPTH, false><<<grid, BLOCK, 0, stream>>>(A, (int)span);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = KEEPS && A.keep_from < A.end ? launch_staged_kernel<BLOCK, EL, DEPTH, KEEPS>(A, grid, (int)span, stream)
+                                                      : launch_staged_kernel<BLOCK, EL, DEPTH, false>(A, grid, (int)span, stream);
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
 
+// The arguments one by one, as in the norm (launch_norm_kernel): 3 M, k = 2 / 4 / 8 8.4/9.9/12.8 us with the fold against 8.9/10.3/13.2 with a block
+// of 330 bytes, 400 k 4.7/5.0/5.6 against 4.85/5.1/5.75; level from 16 M on.
 // One tile per workgroup wherever the partials fit.  The plain shape has two gradient loads in flight, 4 elements per
 // lane, 64 lanes up to 8 streams and 128 beyond; us per launch, k = 2 / 4 / 8 / 16, against it:
 //   <= 2^19  four (below 8 streams) or eight in flight:  300 k  5.0/5.1/5.6/6.4 against 5.1/5.7/6.6/8.7
 //   <= 2^22  1024 lanes, four in flight (a sixteenth of the partials):  2 M  7.0/8.4/10.4/15.4 against 9.0/10.3/12.4/16.3.
+//            Up to 16 streams also from 4.5 to 10 M elements, with the end of the sum left in the cache: 4.6 M, k = 1 / 4 / 8 / 16
+//            10.1/13.6/18.3/30.9 us against 12.3/15.1/20.9/35.2 in the plain shape, 9 M 15.6/22.7/32.5/57.1 against 18.0/23.5/34.4/59.5; with the
+//            step 5 M 34.9/38.8/44.1/57.8 against 37.4/40.3/46.6/60.8.  Over 16 M the two are level, above that the plain shape wins.
 //            More than 16 streams only up to 2^20 (600 k, k = 20 / 32  9.1/11.7 against 11.0/14.6; 1.5 M 15.9/22.2
 //            against 14.9/20.0), and on some of the CUs fewer than 8 streams only up to 48 k elements per CU, from
 //            where the many small workgroups win (16 CUs, k = 1 / 2 / 4: 1 M 16.6/18.7/25.6 against 14.9/16.0/22.9,
@@ -1546,6 +1582,8 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
         if (A.k < 8) return launch_staged<128, 4, 4, false>(A, cap, d_out, accumulate, stream);
         return launch_staged<64, 4, 8, false>(A, cap, d_out, accumulate, stream);
     }
+    if (A.k <= 16 && n >= GS_STAGED_WIDE_AGAIN_MIN && n <= GS_STAGED_WIDE_AGAIN_MAX && !on_cu_budget(stream))
+        return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);
     const int cus = n <= GS_STAGED_WIDE_MAX && A.k < 8 ? budget_cus(stream) : 0;
     if (n <= (A.k <= 16 ? GS_STAGED_WIDE_MAX : GS_STAGED_WIDE_MANY_MAX) && !(cus > 0 && n / cus >= GS_BUDGET_RUN_MIN))
         return launch_staged<1024, 4, 4>(A, cap, d_out, accumulate, stream);

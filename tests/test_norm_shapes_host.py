@@ -29,3 +29,15 @@ def test_norm_has_a_kernel_for_each_number_of_streams(rec, k):
                     lanes_, tiles_ = (256, 1) if length <= 4097 else (lanes, tiles)
                 assert l.targs == (k, 1, lanes_, one, 16), (length, l.name)
                 assert l.extra == tiles_ or ws == MIN_WS, (length, l.extra)
+
+
+@pytest.mark.parametrize("k", [1, 8, 16, 17, 32])
+def test_staged_norm_takes_wide_workgroups_again(rec, k):
+    for length in ((1 << 22) + 1, 4_499_999, 4_500_000, 10_000_000, 10_000_001, 12_600_000):
+        for cus in (64, 256):
+            for ws in (MIN_WS, FULL):
+                st, launches, _, wsb = rec.call("staged", k, 5, 5 + length, ws, cus=cus)
+                assert st == 0
+                check("staged", launches, 5, 5 + length, wsb)
+                wide = k <= 16 and 4_500_000 <= length <= 10_000_000 and cus == 256
+                assert launches[0].targs[:3] == ((1024, 4, 4) if wide else (64, 4, 2) if k <= 8 else (128, 4, 2)), (length, cus)

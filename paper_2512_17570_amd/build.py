@@ -68,9 +68,10 @@ def build_call(verbose: bool = True) -> str:
 
     from torch.utils import cpp_extension
     cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-I", os.path.join(ROOT, "include"),
+           "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1", "-isystem", os.path.join(os.path.dirname(os.path.dirname(HIPCC)), "include"),
            "-isystem", sysconfig.get_paths()["include"], *[x for d in cpp_extension.include_paths() for x in ("-isystem", d)],
            os.path.join(CSRC, "gs_call.cpp"), "-o", CALL_MODULE, *[f"-L{d}" for d in cpp_extension.library_paths()],
-           "-ltorch_python", "-ltorch_cpu", "-lc10"]
+           "-ltorch_python", "-ltorch_cpu", "-lc10_hip", "-lc10"]
     if verbose:
         print(" ".join(cmd), flush=True)
     r = subprocess.run(cmd, capture_output=True, text=True)

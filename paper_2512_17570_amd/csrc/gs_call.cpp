@@ -3,7 +3,8 @@
 // A call on a small range takes 2-4 us on the GPU and as much in the runtime's launch, and reading the arguments
 // in Python (four attributes of each tensor, a struct from the hyper-parameters, ctypes' own conversions) took as
 // long again: 13 k elements, k = 4 / 16, 7.7/10.4 us of host time per gs_accum_adamw against 3.9/4.1 here, of which 3.3
-// are the launch.
+// are the launch (on a core that another program shares; 3.0 and 2.3 on one that none does).  The current stream is asked of torch natively
+// too: all of a call but its launch takes 0.38 us, k = 4, against 0.50 through torch's Python functions.
 //
 // Every function here either makes the call and returns its status, or touches nothing and returns None: gs.py
 // then reads the same arguments in its general way, which decides what is accepted and raises what it raises.
@@ -13,6 +14,9 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <ATen/PythonTorchFunctionTLS.h>
+#include <c10/hip/HIPStream.h>
+
+#include <pthread.h>
 
 #include <cstdint>
 
@@ -31,7 +35,8 @@ decltype(&::gs_adamw_from_acc) f_adamw_from_acc;
 decltype(&::gs_accum_adamw_oop) f_accum_adamw_oop;
 decltype(&::gs_accum_adamw_spec) f_accum_adamw_spec;
 PyTypeObject *hparams_type;
-PyObject *current_device, *current_raw_stream, *in_bad_fork;
+PyObject *in_bad_fork;
+bool forked;                       // this process is a child of the one that made the set-up
 PyObject *hp_names[7];
 
 // The reading of one call's arguments; `usual` turns false at the first that is not of the usual form.
@@ -130,12 +135,13 @@ struct Reader {
         if (!usual) return nullptr;
         PyObject *h = nullptr;
         if (o == Py_None) {
-            PyObject *bad = PyObject_CallNoArgs(in_bad_fork);
-            const bool forked = bad != Py_False;
-            Py_XDECREF(bad);
-            PyObject *dev = forked ? nullptr : PyObject_CallNoArgs(current_device);
-            h = dev ? PyObject_CallOneArg(current_raw_stream, dev) : nullptr;
-            Py_XDECREF(dev);
+            if (forked) {                      // before the GPU was first used: as ever; after: torch refuses
+                PyObject *bad = PyObject_CallNoArgs(in_bad_fork);
+                const bool refuse = bad != Py_False;
+                Py_XDECREF(bad);
+                if (refuse) return no(), nullptr;
+            }
+            return c10::hip::getCurrentHIPStream().stream();
         } else if (PyLong_CheckExact(o)) {
             h = Py_NewRef(o);
         } else {
@@ -350,11 +356,11 @@ PyObject *accum_adamw_spec(PyObject *, PyObject *const *a, Py_ssize_t n)
     });
 }
 
-// entry points by name (addresses in the order below), HParams, current device, current raw stream, in a bad fork
+// entry points by name (addresses in the order below), HParams, in a bad fork
 PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n)
 {
     void *f[9];
-    if (n != 13) return PyErr_Format(PyExc_TypeError, "setup takes 13 arguments"), nullptr;
+    if (n != 11) return PyErr_Format(PyExc_TypeError, "setup takes 11 arguments"), nullptr;
     for (int i = 0; i < 9; ++i)
         if (!(f[i] = PyLong_AsVoidPtr(a[i]))) return PyErr_Occurred() ? nullptr : PyErr_Format(PyExc_ValueError, "null entry point");
     if (!PyType_Check(a[9])) return PyErr_Format(PyExc_TypeError, "HParams is not a class");
@@ -371,9 +377,8 @@ PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n)
     for (int i = 0; i < 7; ++i)
         if (!(hp_names[i] = PyUnicode_InternFromString(names[i]))) return nullptr;
     hparams_type = reinterpret_cast<PyTypeObject *>(Py_NewRef(a[9]));       // kept until the process ends
-    current_device = Py_NewRef(a[10]);
-    current_raw_stream = Py_NewRef(a[11]);
-    in_bad_fork = Py_NewRef(a[12]);
+    in_bad_fork = Py_NewRef(a[10]);
+    if (pthread_atfork(nullptr, nullptr, [] { forked = true; }) != 0) return PyErr_NoMemory();
     Py_RETURN_NONE;
 }
 

@@ -214,7 +214,7 @@ def _table(grads, end: int, name: str = "grads"):
 
 _call.setup(*[ctypes.cast(getattr(_lib, name), _vp).value for name in (
     "gs_grad_sqnorm", "gs_grad_sqnorm_noalloc", "gs_grad_accum_sqnorm", "gs_accum_add", "gs_acc_sqnorm", "gs_accum_adamw",
-    "gs_adamw_from_acc", "gs_accum_adamw_oop", "gs_accum_adamw_spec")], HParams, _current_device, _raw_stream, _in_bad_fork)
+    "gs_adamw_from_acc", "gs_accum_adamw_oop", "gs_accum_adamw_spec")], HParams, _in_bad_fork)
 
 
 def _hp(hp):

@@ -1652,15 +1652,19 @@ static hipError_t launch_add_as(const AccumAddArgs &A, int64_t cap, double *d_ou
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
 
-template <bool NORM, int BLOCK, int EL, bool LWAIT>
-static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
+template <int BLOCK>
+static hipError_t launch_add_norm(const AccumAddArgs &A, int first, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
-    if (first) return launch_add_as<true, NORM, BLOCK, EL, LWAIT>(A, cap, d_out, accumulate, stream);
-    return launch_add_as<false, NORM, BLOCK, EL, LWAIT, LWAIT && !NORM>(A, cap, d_out, accumulate, stream);
+    if (first) return launch_add_as<true, true, BLOCK, 4, false>(A, cap, d_out, accumulate, stream);
+    return launch_add_as<false, true, BLOCK, 4, false>(A, cap, d_out, accumulate, stream);
 }
 
 // us per launch, each against 64 lanes with the buffer's load after the gradient's:
-//   first micro-batch, <= 2^22: 256 lanes               1 M 2.6 against 3.2, 2 M 3.6 against 4.4; level above
+//   first micro-batch: it is made of stores, and fewer, wider workgroups issue them sooner.  256 lanes up to 900 k elements (1 M 2.6
+//                                                       against 3.2), 512 up to 2^21 (2 M 3.5 against 4.6, and 3.85 in 256), then, where the
+//                                                       end of the sum stays in the cache and the stores are plain, 128 (5 M / 15 M 7.8/16.9
+//                                                       against 8.7/18.0, in 256 8.2/18.0) up to 2^25, where they are level (200 M on 0.3 % behind); 256 on
+//                                                       some of the CUs
 //   later ones: above 2^21 elements written through where the sum is not left in the cache (805 M 1167 us against 1195,
 //   201 M 291 against 294; 64 CUs, 5 M / 20 M 18.2/64.6 against 18.8/66.2; the first micro-batch, which only writes, loses 2-4 % by it).
 //   Up to there the L2s hold the sum for the next one: the hint alone (13 k / 800 k 1.97/3.03 against 2.26/3.26 written through; four
@@ -1668,8 +1672,13 @@ static hipError_t launch_add(const AccumAddArgs &A, int first, int64_t cap, doub
 //   later ones, <= 2^22 or on some of the CUs only: both loads in flight
 //                                                      1 M 3.2 against 3.7, 2 M 4.9 against 5.2; from 200 M on
 //                                                       waiting is 0.5 % ahead, level in between
-//   with the norm: both loads in flight; 256 lanes up to 2^19, 1024 up to 2^23 (fewer partials), then 64:
-//                                             2 M 7.5 against 9.7, 12.6 M 25.1 against 26.2, 201 M 306 against 320
+//   with the norm: both loads in flight; 256 lanes up to 2^19, then 1024 where the sum is not left in the cache (fewer partials: 2 M 7.5 against
+//                                             9.7), up to 2^23; else, and beyond, 64 (12.6 M 25.1 against 26.2, 201 M 306 against 320).  That
+//                                             call on its own takes longer while the partials count (5 M 13.3 against 12.2 in 1024 lanes that leave
+//                                             nothing), and the step after it less: both and the three micro-batches before them, 2.6 M / 5.5 M / 7 M
+//                                             37.6/65.1/78.2 against 39.3/70.3/83.8.  A sum of one micro-batch alone loses that way (5 M 37.4
+//                                             against 35.8), and wide workgroups that leave it in the cache make the fold wait for the write-back
+//                                             (3.3 M 16.6 against 13.3).
 //   with a workspace too small for a partial per 256 elements, per 1024 or 4096.
 hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspace_bytes, double *d_out, int accumulate,
                             hipStream_t stream)
@@ -1678,20 +1687,24 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
     A.keep_from = keep_from(A.begin, A.end, 4, 0, stream);
     const int64_t n = A.end - A.begin;
     if (!d_out) {
-        if (n > GS_ADD_SMALL_MAX && !on_cu_budget(stream))
-            return launch_add<false, 64, 4, true>(A, first, 0, nullptr, 0, stream);
-        if (first) return launch_add_as<true, false, 256, 4, false>(A, 0, nullptr, 0, stream);
+        if (first) {
+            if (n <= GS_ADD_FIRST_256_MAX || on_cu_budget(stream)) return launch_add_as<true, false, 256, 4, false>(A, 0, nullptr, 0, stream);
+            if (n <= GS_RESIDENT_MAX) return launch_add_as<true, false, 512, 4, false>(A, 0, nullptr, 0, stream);
+            if (n <= GS_ADD_FIRST_128_MAX) return launch_add_as<true, false, 128, 4, false>(A, 0, nullptr, 0, stream);
+            return launch_add_as<true, false, 64, 4, false>(A, 0, nullptr, 0, stream);
+        }
+        if (n > GS_ADD_SMALL_MAX && !on_cu_budget(stream)) return launch_add_as<false, false, 64, 4, true, true>(A, 0, nullptr, 0, stream);
         if (n > GS_RESIDENT_MAX) return launch_add_as<false, false, 64, 4, false, true>(A, 0, nullptr, 0, stream);
         return launch_add_as<false, false, 64, 4, false>(A, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
-    // 1024 lanes and plain stores: the fold waits for the write-back (3.3 M elements: 16.6 us against 13.3 with the hint)
-    if (accumulate || n <= GS_ADD_WIDE_MAX) A.keep_from = A.end;
-    if (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 256) <= cap)
-        return launch_add<true, 64, 4, false>(A, first, cap, d_out, accumulate, stream);
+    if (accumulate || (first && n <= GS_ADD_WIDE_MAX)) A.keep_from = A.end;
+    const bool keeps = A.keep_from < A.end;
+    if ((n > GS_ADD_WIDE_MAX || keeps) && tiles_of(A.begin, A.end, 256) <= cap)
+        return launch_add_norm<64>(A, first, cap, d_out, accumulate, stream);
     if (n <= GS_LATENCY_MAX || (n > GS_ADD_WIDE_MAX && tiles_of(A.begin, A.end, 1024) <= cap))
-        return launch_add<true, 256, 4, false>(A, first, cap, d_out, accumulate, stream);
-    return launch_add<true, 1024, 4, false>(A, first, cap, d_out, accumulate, stream);
+        return launch_add_norm<256>(A, first, cap, d_out, accumulate, stream);
+    return launch_add_norm<1024>(A, first, cap, d_out, accumulate, stream);
 }
 
 }  // namespace gs

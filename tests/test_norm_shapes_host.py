@@ -41,3 +41,22 @@ def test_staged_norm_takes_wide_workgroups_again(rec, k):
                 check("staged", launches, 5, 5 + length, wsb)
                 wide = k <= 16 and 4_500_000 <= length <= 10_000_000 and cus == 256
                 assert launches[0].targs[:3] == ((1024, 4, 4) if wide else (64, 4, 2) if k <= 8 else (128, 4, 2)), (length, cus)
+
+
+@pytest.mark.parametrize("cus", [64, 256])
+def test_adding_kernel_by_length(rec, cus):
+    all_cus = cus == 256
+    for length in (1, 900_000, 900_001, 1 << 21, (1 << 21) + 1, 1 << 22, (1 << 22) + 1, 1 << 23, (1 << 23) + 1, 60_000_000):
+        l = rec.call("add", 1, 5, 5 + length, first=1, cus=cus)[1][0]
+        lanes = 256 if length <= 900_000 or not all_cus else 512 if length <= 1 << 21 else 128 if length <= 1 << 25 else 64
+        assert l.targs == (1, 0, lanes, 4, 0, 0), (length, l.name)
+        for first in (0, 1):
+            for accumulate in (0, 1):
+                st, launches, _, wsb = rec.call("add_norm", 1, 5, 5 + length, first=first, accumulate=accumulate, cus=cus)
+                assert st == 0
+                check("add_norm", launches, 5, 5 + length, wsb)
+                l = launches[0]
+                keeps = length > 1 << 21 and all_cus and not accumulate and (not first or length > 1 << 23)
+                assert (l.keep_from < l.end) == keeps, (length, first, accumulate)
+                lanes = 256 if length <= 1 << 19 else 64 if keeps or length > 1 << 23 else 1024
+                assert l.targs == (first, 1, lanes, 4, 0, 0), (length, first, accumulate, l.name)

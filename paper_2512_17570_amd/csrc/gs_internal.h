@@ -33,6 +33,8 @@
 #define GS_SPEC_RUN_LONG (1 << 28)    // small workspace: elements from which a CU holds one workgroup fewer for the runs of tiles
 #define GS_SPEC_RUN_MAX (1 << 29)     // and up to which they are of small tiles (up to 2 streams: the line before)
 #define GS_KEEP_BYTES ((int64_t)256 << 20)  // of a re-read stream: left in the memory-side cache (keep_from)
+#define GS_KEEP_FEW_MIN 1300000       // elements from which the norm of two and three streams leaves its lines there,
+#define GS_KEEP_MANY_MIN (3 << 18)    // and of four and more (the other passes: above GS_RESIDENT_MAX)
 #define GS_FINAL_BLOCK 1024           // threads of the partial-folding kernels
 #define GS_FINAL_SLICES 128           // workgroups of the first folding stage for large partial counts
 #define GS_FINAL_DIRECT_MAX 8192      // up to this many partials are folded by one workgroup directly

@@ -1372,9 +1372,12 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //   norm alone, k = 8 / 16 / 32            6 M 20.7/36.8/66.4 against 18.9/32.2/61.3, 50 M 127/237/471 against 122/231/466
 //   fp32 norm alone                      50 M 37.5 against 34.4;  first micro-batch alone 5 M 8.7 against 7.3, 50 M 51 against 49
 // 192 and 320 MB gain less than 256 (norm + step, 201 M: 1749 and 1747 us against 1745).  Not done:
-//   * Up to 2^21 elements, so that the norm of a small range does not pay: 2 M, k = 8 / 16 / 32 on its own 10.0/14.8/24.4 us
-//     against 10.3/15.8/26.4 plain.  (With the step plain accesses would gain there too, 26.4/36.2/55.5 against
-//     24.3/34.1/53.4; the line is one of elements, not the bytes at which the pair breaks even.)
+//   * Up to 2^21 elements, but for the gradient norm of four streams and more only up to 3 * 2^18, of two and three up to 1.3 M.  The
+//     two passes, plain from there on against the hint up to 2^21, k = 4 / 8 / 12 / 32: 800 k 11.0/12.8/14.8/24.3 against 11.1/13.5/15.7/25.6, 1.3 M
+//     13.8/16.3/19.3/35.5 against 14.3/17.5/21.9/38.0, 2 M 17.6/23.5/28.4/52.2 against 18.9/25.5/30.2/54.8; k = 2, 1 M / 2 M 10.7/15.6 against
+//     10.6/16.3.  The norm alone: k = 4 / 8 / 16 / 32 800 k 5.0/5.7/8.2/12.9 against 5.1/5.8/7.8/12.0, 2 M 6.2/9.1/14.4/25.4 against
+//     6.5/8.7/13.4/23.2.  Below, the gain goes up and down with the range (600 k, k = 4 / 32 +4/-6 %); the fp32 norm gains from about 2 M on and
+//     loses at 800 k (6 %), the staged norm likewise.
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
 //   * On some of the CUs the memory is not the bound, and plain accesses cost 3-7 %.
@@ -1382,9 +1385,9 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //     pass 4-9 % (norm + step, us, with the hint against without, k = 14 / 16 / 20 / 32: 3.3 M 41.9/43.5/47.8/59.1
 //     against 41.2/42.4/47.2/62.3; 12.6 M 132/139/155/202 against 133/141/159/209; 50 M 492/523/583/781 against
 //     486/520/586/794; 201 M 1940/2070/2328/3115 against 1932/2060/2330/3120).
-static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate, hipStream_t stream)
+static int64_t keep_from(int64_t begin, int64_t end, int bytes_per_elem, int accumulate, hipStream_t stream, int64_t upto = GS_RESIDENT_MAX)
 {
-    if (accumulate || end - begin <= GS_RESIDENT_MAX || on_cu_budget(stream)) return end;
+    if (accumulate || end - begin <= upto || on_cu_budget(stream)) return end;
     return end - GS_KEEP_BYTES / bytes_per_elem;
 }
 
@@ -1602,7 +1605,8 @@ hipError_t launch_grad_sqnorm(const SqnormArgs &args, size_t workspace_bytes, do
 {
     const int64_t cap = partial_capacity(workspace_bytes);
     SqnormArgs A = args;
-    A.keep_from = A.acc && A.k > GS_STAGED_KEEP_MAX_K ? A.end : keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate, stream);
+    const int64_t upto = A.acc || A.k < 2 ? GS_RESIDENT_MAX : A.k < 4 ? GS_KEEP_FEW_MIN : GS_KEEP_MANY_MIN;
+    A.keep_from = A.acc && A.k > GS_STAGED_KEEP_MAX_K ? A.end : keep_from(A.begin, A.end, A.acc ? 4 : 2 * A.k, accumulate, stream, upto);
     if (!A.acc) return launch_grad_norm(A, cap, d_out, accumulate, stream);
     return launch_staged_norm(A, cap, d_out, accumulate, stream);
 }

@@ -1440,11 +1440,11 @@ static hipError_t launch_norm(SqnormArgs A, int64_t span, int64_t cap, double *d
 
 // the whole range in one workgroup and one launch
 template <int K, int U>
-static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, hipStream_t stream)
+static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, hipStream_t stream, int span = U)
 {
     A.out = d_out;
     A.accumulate = accumulate;
-    return launch_norm_kernel<K, U, GS_ONE_BLOCK, true>(A, 1, U, stream);
+    return launch_norm_kernel<K, U, GS_ONE_BLOCK, true>(A, 1, span, stream);
 }
 
 // from 5 streams on
@@ -1452,7 +1452,8 @@ template <int K>
 static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t n = A.end - A.begin;
-    if (tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4) <= 1) return launch_norm_one<K, 1>(A, d_out, accumulate, stream);
+    const int64_t tiles = tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4);
+    if (tiles <= 1 || n * K <= GS_ONE_MAX_LOADS) return launch_norm_one<K, 1>(A, d_out, accumulate, stream, tiles > 1 ? (int)tiles : 1);
     if (n <= GS_NORM_256_MAX) return launch_norm<K, 1, 256>(A, 1, cap, d_out, accumulate, stream);
     if (n <= GS_NORM_512_MAX) return launch_norm<K, 1, 512>(A, 1, cap, d_out, accumulate, stream);
     if constexpr (K < 8)
@@ -1468,8 +1469,9 @@ static hipError_t launch_norm_by_streams(const SqnormArgs &A, int64_t run, int64
     return hipErrorInvalidValue;
 }
 
-// Up to four 4096-element tiles (one, from 5 streams on) a single workgroup reads the range and no fold has to
-// follow (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).  The lanes whose groups lie in all four
+// Up to four 4096-element tiles a single workgroup reads the range and no fold has to follow, from 5 streams on while there are
+// up to 2^16 values to read, or one tile (6 k elements, k = 5 / 8 2.8/3.35 us against 3.8/3.8 with the fold, 8 k 3.5/4.2 against 3.8/3.9, 13 k
+// 4.5/6.3 against 4.0/4.1; called one after the other the second launch's host time counts too: norm and step, 8 k, k = 8 8.3 against 10.4) (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).  The lanes whose groups lie in all four
 // tiles have them in flight together; in a range that ends before, the others take them one after another.
 // Above that: with up to 4 streams 256 lanes and one group of U tiles up to 4 M elements, 512 lanes and
 // two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %, and always for three streams: 6.3 M / 12.6 M

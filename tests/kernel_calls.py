@@ -31,7 +31,7 @@ CALLS = [
     # five on in 256 and 512 lanes, up to seven in 1024; long runs on some of the CUs
     *[_c("norm", k, n) for k in (1, 2, 3, 4) for n in (1, 16_000, 20_000, L22, L22 + 1)],
     *[_c("norm", k, n) for k in (5, 8, 23) for n in (1, 5000, L20, L20 + 1, L21, L21 + 1, L23, L23 + 1)],
-    *[_c("norm", k, n) for k in range(5, 33) for n in (1, 5000, L20)], *[_c("norm", k, 6_000_000) for k in (5, 6, 7)],
+    *[_c("norm", k, n) for k in range(5, 33) for n in (1, 5000, 20_000, L20)], *[_c("norm", k, 6_000_000) for k in (5, 6, 7)],
     *[_c("norm", k, 1_000_000, cus=16) for k in (5, 7)], _c("norm", 4, 6_400_000, cus=64),
     _c("norm", 8, 12_600_000, accumulate=1),
     # the norm of an fp32 sum

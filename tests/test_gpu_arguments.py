@@ -67,7 +67,7 @@ def test_step_with_one_array_far_away(far, odd):
 
 @pytest.mark.parametrize("k", [1, 4, 5, 7, 8, 9, 17])
 def test_norm_with_each_table_of_streams(k):
-    for length in (1, 3, 4095, 4096, 16384, 16385, 100_001, (1 << 21) + 5):
+    for length in (1, 3, 4095, 4096, 4097, 65536 // k, 65536 // k + 1, 16384, 16385, 100_001, (1 << 21) + 5):
         n = B + length + 2
         grads = [I.normal_f32(n, 1e-3, 9, j, DEV).to(torch.bfloat16) for j in range(k)]
         a = torch.zeros(length, dtype=torch.float32, device=DEV)

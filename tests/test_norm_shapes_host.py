@@ -13,20 +13,21 @@ def rec(tmp_path_factory):
 
 @pytest.mark.parametrize("k", range(5, 33))
 def test_norm_has_a_kernel_for_each_number_of_streams(rec, k):
-    for length, lanes, tiles in ((1, 1024, 1), (4096, 1024, 1), (4097, 256, 1), (3 << 18, 256, 1), ((3 << 18) + 1, 512, 1), (5_500_000, 512, 1),
+    for length, lanes, tiles in ((1, 1024, 1), (4096, 1024, 1), (4097, 256, 1), (65536 // k, 256, 1), (65536 // k + 1, 256, 1), (3 << 18, 256, 1), ((3 << 18) + 1, 512, 1), (5_500_000, 512, 1),
                                  (5_500_001, 1024 if k < 8 else 512, 2), (1 << 25, 1024 if k < 8 else 512, 2), ((1 << 25) + 1, 512, 2),
                                  ((1 << 29) - 1, 512, 2), (1 << 29, 512, 4)):
         for ws in (MIN_WS, FULL):
             for begin in (0, 5):
-                one = length + begin % 4096 <= 4096
+                spanned = (begin + length - 1) // 4096 + 1
+                one = spanned == 1 or length * k <= 65536
                 st, launches, _, wsb = rec.call("norm", k, begin, begin + length, ws)
                 assert st == 0
                 check("norm", launches, begin, begin + length, wsb)
                 l = launches[0]
                 if one:
-                    lanes_, tiles_ = 1024, 1
+                    lanes_, tiles_ = 1024, spanned
                 else:
-                    lanes_, tiles_ = (256, 1) if length <= 4097 else (lanes, tiles)
+                    lanes_, tiles_ = (256, 1) if length <= 65536 else (lanes, tiles)
                 assert l.targs == (k, 1, lanes_, one, 16), (length, l.name)
                 assert l.extra == tiles_ or ws == MIN_WS, (length, l.extra)
 

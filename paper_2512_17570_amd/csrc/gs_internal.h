@@ -22,8 +22,9 @@
 #define GS_NEAR_LATENCY_MAX 430000    // this many with one and eight streams, with two to seven
 #define GS_NEAR_THROUGH_MAX 330000    // up to this line less
 #define GS_NEAR_THROUGH_STEP 9000     // this for each of them
-#define GS_NEAR_CLIP_BIT (1u << 22)   // such a step: whether the norm clips and the distances' unit, above its number of elements
-#define GS_NEAR_UNIT_BIT (1u << 23)
+#define GS_NEAR_FULL_MAX 5000000      // and above 2^21 up to this many again
+#define GS_NEAR_CLIP_BIT (1u << 23)   // such a step: whether the norm clips and the distances' unit, above its number of elements
+#define GS_NEAR_UNIT_BIT (1u << 24)
 #define GS_SERIAL_MAX_K 7             // "few streams"
 #define GS_LINK_WAVES 22              // of a step on host memory in flight on a die with up to 8 of its CUs
 #define GS_LINK_WAVES_WIDE 64         // and with more of them

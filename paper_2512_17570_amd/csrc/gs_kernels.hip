@@ -643,7 +643,7 @@ __device__ __forceinline__ void step_near(int64_t begin, int cuts, uint32_t pack
     __global__ __launch_bounds__(BLOCK) void k_accum_adamw(int64_t begin, int cuts, uint32_t packed, float *p, const double *d_sqnorm, int m_at, \
                                                            int v_at, int g0, int g1, int g2, int g3, NearRest<K> R)                            \
     {                                                                                                                                          \
-        static_assert(!STAGED && !LWAIT, "the shapes of ranges that are one generation of waves");                                             \
+        static_assert(!STAGED && !LWAIT, "waves that do not wait between their loads");                                                        \
         step_near<K, BLOCK, EL, DEPTH, SWAIT, THROUGH>(begin, cuts, packed, p, d_sqnorm, m_at, v_at, g0, g1, g2, g3, R);                       \
     }
 GS_NEAR_STEP(1)
@@ -1161,14 +1161,16 @@ struct NearArgs {
 // 32 GB apart).  In LATENCY loads that go out sooner run into the stores of the waves before, where those are written through: level at
 // 325/300/310/295/285/270 k elements for 2 to 7 streams (350 k, k = 4 / 7 3.9/4.5 us against 3.8/4.3), at 450 k for one and eight.  In RESIDENT they
 // come all at once as the memory gets busy: 2-7 % behind from 1.3 M on for 6 to 8 streams (up to five 1 % ahead there, and level above).
+// In full CUs above 2^21 they are ahead again, by less and less (with the norm, k = 2 / 5 / 8: 2.2 M 17.4/20.7/24.6 us against 17.7/21.1/24.9, 3.3 M
+// 22.6/27.8/33.9 against 22.9/28.3/34.3, 5 M within 1 %; alone four streams are 0.8 % behind from 6 M on).
 static bool near_args(const StepArgs &A, NearArgs &N)
 {
     const int64_t n = A.end - A.begin;
     if (A.over_link || A.k > 8 || A.po != A.p || A.mo != A.m || A.vo != A.v) return false;
-    if (n > GS_NEAR_MAX) return false;
+    if (n > GS_NEAR_MAX && !(n > GS_RESIDENT_MAX && n <= GS_NEAR_FULL_MAX)) return false;
     if (n <= GS_LATENCY_MAX && n > (A.k == 1 || A.k == 8 ? GS_NEAR_LATENCY_MAX : GS_NEAR_THROUGH_MAX - A.k * GS_NEAR_THROUGH_STEP)) return false;
     static_assert(GS_NEAR_THROUGH_MAX <= GS_LATENCY_MAX - 7 * GS_LATENCY_THROUGH_STEP, "two to seven streams are written through as long as they are near");
-    static_assert(GS_NEAR_MAX < GS_NEAR_CLIP_BIT, "the parts of `packed`");
+    static_assert(GS_NEAR_MAX < GS_NEAR_FULL_MAX && GS_NEAR_FULL_MAX < GS_NEAR_CLIP_BIT && GS_NEAR_FULL_MAX <= GS_FULL_MAX, "the parts of `packed`");
     const auto bytes_from_p = [&](const void *q) { return (int64_t)(reinterpret_cast<uintptr_t>(q) - reinterpret_cast<uintptr_t>(A.p)); };
     int64_t any = bytes_from_p(A.m) | bytes_from_p(A.v) | bytes_from_p(A.w);
     for (int j = 0; j < A.k; ++j) any |= bytes_from_p(A.gt.g[j]);
@@ -1207,12 +1209,12 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
     }
     if ((A.begin + EL - 1) / EL >= A.end / EL) tiles = 0;           // no whole group
     const int grid = (int)(tiles + cuts);
-    if constexpr (BLOCK == 64 && !STAGED && !LWAIT && !LATE && (DEPTH == 4 || DEPTH == 8)) {
+    if constexpr (!STAGED && !LWAIT && !LATE && (DEPTH == 4 || DEPTH == 8)) {
         NearArgs N;
         if (near_args(A, N)) {
             const auto go = [&](auto streams) {
                 constexpr int K = decltype(streams)::value;
-                if constexpr (EL == 2 && ((THROUGH && K == 1) || (!THROUGH && K > 1 && K < 8))) {
+                if constexpr (BLOCK == 128 ? (DEPTH == 8) != (K >= 5) : EL == 2 && ((THROUGH && K == 1) || (!THROUGH && K > 1 && K < 8))) {
                     return hipErrorInvalidValue;
                 } else {
                     NearRest<K> R{{N.g[4], N.g[5], N.g[6], N.g[7]}, N.w, A.max_norm, A.c};

@@ -10,7 +10,7 @@ from paper_2512_17570_amd import inputs as I
 pytestmark = pytest.mark.gpu
 
 B = 5                                        # begin of every range
-LENGTHS = [1, 2, 3, 127, 130, 1001, 200_000, 267_000, 267_001, 312_001, 430_000, 430_001, 1 << 19, (1 << 19) + 1, 960_001, 1_200_000, 1_200_001, 3 << 19]
+LENGTHS = [1, 2, 3, 127, 130, 1001, 200_000, 267_000, 267_001, 312_001, 430_000, 430_001, 1 << 19, (1 << 19) + 1, 960_001, 1_200_000, 1_200_001, 3 << 19, (1 << 21) + 1, 5_000_000, 5_000_001]
 
 
 def the_same(k, length, hp, sq, place=None):

@@ -36,8 +36,17 @@ decltype(&::gs_accum_adamw_oop) f_accum_adamw_oop;
 decltype(&::gs_accum_adamw_spec) f_accum_adamw_spec;
 PyTypeObject *hparams_type;
 PyObject *in_bad_fork;
-bool forked;                       // this process is a child of the one that made the set-up
+bool forked;                       // this process is a child of the one that made the set-up, or torch called it a bad fork then
 PyObject *hp_names[7];
+
+// torch's word on whether this process was forked from one that used the GPU before; any answer but False counts
+bool is_bad_fork()
+{
+    PyObject *bad = PyObject_CallNoArgs(in_bad_fork);
+    const bool yes = bad != Py_False;
+    Py_XDECREF(bad);
+    return yes;
+}
 
 // The reading of one call's arguments; `usual` turns false at the first that is not of the usual form.
 struct Reader {
@@ -135,12 +144,8 @@ struct Reader {
         if (!usual) return nullptr;
         PyObject *h = nullptr;
         if (o == Py_None) {
-            if (forked) {                      // before the GPU was first used: as ever; after: torch refuses
-                PyObject *bad = PyObject_CallNoArgs(in_bad_fork);
-                const bool refuse = bad != Py_False;
-                Py_XDECREF(bad);
-                if (refuse) return no(), nullptr;
-            }
+            // forked before the GPU was first used: as ever; after: torch refuses
+            if (forked && is_bad_fork()) return no(), nullptr;
             return c10::hip::getCurrentHIPStream().stream();
         } else if (PyLong_CheckExact(o)) {
             h = Py_NewRef(o);
@@ -378,6 +383,8 @@ PyObject *setup(PyObject *, PyObject *const *a, Py_ssize_t n)
         if (!(hp_names[i] = PyUnicode_InternFromString(names[i]))) return nullptr;
     hparams_type = reinterpret_cast<PyTypeObject *>(Py_NewRef(a[9]));       // kept until the process ends
     in_bad_fork = Py_NewRef(a[10]);
+    forked = is_bad_fork();                    // a child that makes the set-up itself: the handler below did not run in it
+    PyErr_Clear();
     if (pthread_atfork(nullptr, nullptr, [] { forked = true; }) != 0) return PyErr_NoMemory();
     Py_RETURN_NONE;
 }

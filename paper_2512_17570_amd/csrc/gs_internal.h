@@ -91,6 +91,14 @@ struct StepArgs {
     bool over_link;     // the states are host memory, reached over PCIe
 };
 
+// what a step whose arrays are given by their distances from p takes as a block (K: a kernel for each number of streams)
+template <int K> struct NearRest {
+    int g[4];           // streams 4 to 7
+    int w;
+    float max_norm;
+    StepConsts c;
+};
+
 struct SqnormArgs {
     int64_t begin, end;
     GradTable gt;

@@ -514,13 +514,6 @@ __global__ __launch_bounds__(BLOCK) void k_accum_adamw(StepArgs A, int cuts)
 // With 4 elements per lane (SWAIT) the memory is busy: there the gradients' loads go first, and from seven streams on only when the states are
 // back (states first / gradients first / waited for: 700 k, k = 4 / 6 / 8 5.44/6.18/6.89, 5.41/6.07/6.91, 5.74/5.99/6.58; 550 k, k = 6 / 8
 // 4.98/5.47, 4.95/5.39, 5.41/5.67).
-template <int K> struct NearRest {
-    int g[4];            // streams 4 to 7
-    int w;
-    float max_norm;
-    StepConsts c;
-};
-
 // the address `at` units of 2^unit bytes from `base`
 template <typename T>
 __device__ __forceinline__ T *near_to(float *base, int at, int unit)
@@ -1534,21 +1527,24 @@ static hipError_t launch_grad_norm(const SqnormArgs &A, int64_t cap, double *d_o
     return launch_norm_by_streams<5>(A, run, cap, d_out, accumulate, stream);
 }
 
-template <int BLOCK, int EL, int DEPTH, bool KEEPS>
+// MOST: the streams that a call of this shape has
+template <int BLOCK, int EL, int DEPTH, bool KEEPS, int MOST>
 static hipError_t launch_staged_kernel(const SqnormArgs &A, int grid, int span, hipStream_t stream)
 {
     const int keep_block = first_kept(A.begin, A.keep_from, (int64_t)span * BLOCK * EL, BLOCK * EL, grid);
-    if (A.k <= 8) {
-        GradTableOf<8> gt;
-        for (int j = 0; j < 8; ++j) gt.g[j] = A.gt.g[j];
-        void (*const kernel)(int64_t, int, int, int64_t, float *, GradTableOf<8>, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
-        return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, gt, A.k, A.partials);
+    if constexpr (MOST > 8) {
+        if (A.k > 8) {
+            void (*const kernel)(int64_t, int, int, int64_t, float *, GradTable, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
+            return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, A.gt, A.k, A.partials);
+        }
     }
-    void (*const kernel)(int64_t, int, int, int64_t, float *, GradTable, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
-    return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, A.gt, A.k, A.partials);
+    GradTableOf<8> gt;
+    for (int j = 0; j < 8; ++j) gt.g[j] = A.gt.g[j];
+    void (*const kernel)(int64_t, int, int, int64_t, float *, GradTableOf<8>, int, double *) = k_grad_accum_sqnorm<BLOCK, EL, DEPTH, KEEPS>;
+    return launch(kernel, grid, BLOCK, 0, stream, A.begin, span, keep_block, A.end, A.acc, gt, A.k, A.partials);
 }
 
-template <int BLOCK, int EL, int DEPTH, bool KEEPS = true>
+template <int BLOCK, int EL, int DEPTH, bool KEEPS = true, int MOST = GS_MAX_K>
 static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     int64_t tiles = tiles_of(A.begin, A.end, (int64_t)BLOCK * EL);
@@ -1556,8 +1552,8 @@ static hipError_t launch_staged(const SqnormArgs &A, int64_t cap, double *d_out,
     const int64_t span = fit_span(tiles, 1, 1, cap, BLOCK);
     if (span == 0) return hipErrorInvalidValue;
     const int grid = (int)((tiles + span - 1) / span);
-    const hipError_t e = KEEPS && A.keep_from < A.end ? launch_staged_kernel<BLOCK, EL, DEPTH, KEEPS>(A, grid, (int)span, stream)
-                                                      : launch_staged_kernel<BLOCK, EL, DEPTH, false>(A, grid, (int)span, stream);
+    const hipError_t e = KEEPS && A.keep_from < A.end ? launch_staged_kernel<BLOCK, EL, DEPTH, KEEPS, MOST>(A, grid, (int)span, stream)
+                                                      : launch_staged_kernel<BLOCK, EL, DEPTH, false, MOST>(A, grid, (int)span, stream);
     if (e != hipSuccess) return e;
     return launch_fold(A.partials, cap, grid, d_out, accumulate, stream);
 }
@@ -1586,7 +1582,7 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
 {
     const int64_t n = A.end - A.begin;
     if (n <= GS_LATENCY_MAX) {
-        if (A.k < 8) return launch_staged<128, 4, 4, false>(A, cap, d_out, accumulate, stream);
+        if (A.k < 8) return launch_staged<128, 4, 4, false, 7>(A, cap, d_out, accumulate, stream);
         return launch_staged<64, 4, 8, false>(A, cap, d_out, accumulate, stream);
     }
     if (A.k <= 16 && n >= GS_STAGED_WIDE_AGAIN_MIN && n <= GS_STAGED_WIDE_AGAIN_MAX && !on_cu_budget(stream))
@@ -1600,7 +1596,7 @@ static hipError_t launch_staged_norm(const SqnormArgs &A, int64_t cap, double *d
     }
     if (A.k >= 8 && A.k % 4 == 0 && n >= GS_STAGED_PAIR_MIN && !on_cu_budget(stream))
         return launch_staged<256, 2, 4>(A, cap, d_out, accumulate, stream);
-    if (A.k <= 8 && tiles_of(A.begin, A.end, 256) <= cap) return launch_staged<64, 4, 2>(A, cap, d_out, accumulate, stream);
+    if (A.k <= 8 && tiles_of(A.begin, A.end, 256) <= cap) return launch_staged<64, 4, 2, true, 8>(A, cap, d_out, accumulate, stream);
     return launch_staged<128, 4, 2>(A, cap, d_out, accumulate, stream);
 }
 

@@ -11,7 +11,10 @@ def _c(entry, k, length, ws="min", cus=256, first=0, accumulate=0):
 
 
 CALLS = [
-    # the step and the staged step, by length and on some of the CUs
+    # the step with its arrays by distances, a kernel for each number of streams: arrays of one training program lie near enough
+    *[_c("step", k, n) for k in range(1, 9) for n in (1001, 600_001, L21 + 1)], _c("step", 8, 300_001),
+    # the step given addresses, in place and out of place, and the staged step, by length and on some of the CUs
+    *[_c("oop", k, n) for k, n in ((1, 1), (2, 1), (5, 3), (6, 500_000), (1, L19 + 1), (7, L21 + 1), (2, L21 + 1))],
     *[_c("step", k, n) for k, n in ((1, 1), (2, 1), (5, 3), (9, 1), (17, 1001), (6, 500_000), (12, 500_000), (1, L19 + 1), (3, 1_600_000), (7, L21 + 1), (13, 7_000_001),
                                     (6, L27 + 1), (10, L27 + 1))],
     *[_c("step", k, L21 + 1, cus=64) for k in (1, 5)],
@@ -38,6 +41,7 @@ CALLS = [
     *[_c("acc_norm", 1, n) for n in (1, 20_000, L22 + 1, L27 - 1, L27 + 1)],
     # the staged norm: by length, streams, workspace and CUs; with and without the sum's end left in the cache
     *[_c("staged", k, n) for k, n in ((1, 1), (8, 1), (3, L19 + 1), (17, L20), (17, L20 + 1), (7, L21 + 1), (1, L22 + 1), (9, L22 + 1), (20, L22 + 1))],
+    *[_c("staged", k, n) for k, n in ((9, 1001), (9, 5_000_001), (12, L25))], _c("staged", 9, L27 + 1, accumulate=1),
     _c("staged", 2, L22 + 1, accumulate=1), _c("staged", 9, L22 + 1, accumulate=1), _c("staged", 2, 1_000_000, cus=16),
     *[_c("staged", k, n) for k in (8, 9) for n in (L25 - 1, L25)],
     _c("staged", 8, L25, accumulate=1), _c("staged", 20, L25),

@@ -45,14 +45,14 @@ def test_kernel(entry, k, length, ws, cus, first, accumulate):
     b, e = BEGIN, BEGIN + length
     n = e + 2
     grads = [I.normal_f32(n, 1e-3, 7, j, DEV).to(torch.bfloat16) for j in range(k)] if entry != "acc_norm" else []
-    sq = torch.full((1,), 4.0 if accumulate or entry in ("step", "from_acc") else float("nan"), dtype=torch.float64, device=DEV)
+    sq = torch.full((1,), 4.0 if accumulate or entry in ("step", "oop", "from_acc") else float("nan"), dtype=torch.float64, device=DEV)
     nbytes = gs.gs_sqnorm_workspace_bytes() if ws == "min" else gs.gs_sqnorm_workspace_bytes_for(length)
     work = torch.full((nbytes,), 0xff, dtype=torch.uint8, device=DEV)          # NaNs: nothing may be taken from it unwritten
     raw = gs.gs_cu_stream_create(cus) if cus < 256 else None
     torch.cuda.synchronize()
     try:
         S = 0.0
-        if entry in ("step", "from_acc", "spec"):
+        if entry in ("step", "oop", "from_acc", "spec"):
             states = I.make_states(n, 3, DEV)
             acc = fp32_sum(grads, 0, n) if entry == "from_acc" else None
             want = [x.clone() for x in states] + [torch.zeros(n, dtype=torch.bfloat16, device=DEV)]
@@ -61,6 +61,8 @@ def test_kernel(entry, k, length, ws, cus, first, accumulate):
             torch.cuda.synchronize()
             if entry == "step":
                 gs.gs_accum_adamw(*got, grads, b, e, HP, sq, stream=raw)
+            elif entry == "oop":
+                gs.gs_accum_adamw_oop(*states, *got, grads, b, e, HP, sq, stream=raw)
             elif entry == "from_acc":
                 gs.gs_adamw_from_acc(*got, acc, b, e, HP, sq, stream=raw)
             else:

@@ -13,7 +13,7 @@ from paper_2512_17570_amd import build as B
 
 @pytest.fixture(scope="module")
 def kernels(tmp_path_factory):
-    """{name with template arguments: assembly lines}"""
+    """{name with template arguments and parameter list: assembly lines}"""
     out = str(tmp_path_factory.mktemp("asm") / "gs_kernels.s")
     flags = [f for f in B.FLAGS if f != "-shared"]
     subprocess.run([B.HIPCC, *flags, "--offload-device-only", "-S", "-I", os.path.join(B.ROOT, "include"), "-I", B.CSRC,
@@ -22,7 +22,9 @@ def kernels(tmp_path_factory):
     marks = [(m.start(), m[1]) for m in re.finditer(r"^(_ZN2gs\w+):", text, re.M)]
     names = subprocess.run(["c++filt"], input="\n".join(n for _, n in marks), capture_output=True, text=True, check=True).stdout.split("\n")
     ends = [a for a, _ in marks[1:]] + [len(text)]
-    return {re.sub(r"^(void )?gs::|\(.*", "", name): text[a:e].split(".section")[0].split("\n") for (a, _), e, name in zip(marks, ends, names)}
+    found = {re.sub(r"^(void )?gs::", "", name): text[a:e].split(".section")[0].split("\n") for (a, _), e, name in zip(marks, ends, names)}
+    assert len(found) == len(marks) == len(re.findall(r"^\s*\.amdhsa_kernel ", text, re.M))
+    return found
 
 
 def test_no_kernel_uses_scratch_memory(kernels, tmp_path):
@@ -36,7 +38,7 @@ def test_no_kernel_uses_scratch_memory(kernels, tmp_path):
 def test_late_arguments_are_read_where_they_are_needed(kernels):
     """Read late, a wave's arguments are not all behind the wait at its entry: there is none of the states' loads'
     addresses, the gradients' or the hyper-parameters' before the range's ends, and the last are read after the gradients."""
-    late = [lines for name, lines in kernels.items() if re.fullmatch(r"k_accum_adamw<(\d+, \d+, false, .*, )true>", name)]
+    late = [lines for name, lines in kernels.items() if re.fullmatch(r"k_accum_adamw<(\d+, \d+, false, .*, )true>\(.*\)", name)]
     assert len(late) == 2
     for lines in late:
         code = [l.strip() for l in lines]

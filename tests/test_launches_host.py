@@ -8,7 +8,7 @@ import random
 import pytest
 
 from kernel_calls import BEGIN, CALLS
-from launches import FULL, MIN_WS, WORK, Recorder, build, check, parse_name
+from launches import FAR, FULL, MIN_WS, NEAR, NEAR16, WORK, Recorder, build, check, parse_name, shape
 
 STEPS = ["step", "oop", "from_acc", "host_step"]
 NORMS = ["norm", "staged", "acc_norm", "add_norm", "spec", "noalloc"]
@@ -95,6 +95,14 @@ def test_norm_on_some_of_the_cus(rec, k):
             l = work_of(rec, "norm", k, 3, 3 + n, cus=cus)
             long_runs = 4 <= k <= 7 and cus < 256 and per_cu >= (98_304 if k == 4 else 49_152) and n > 1 << 19
             assert (l.targs == (0, 1, 256, 0, 4) and l.extra == 8) == long_runs, (cus, per_cu, l.name)
+
+
+def first_kept(l, keep_from):
+    """The first element of the first workgroup that starts at keep_from or beyond."""
+    block, el, _ = shape(l)
+    run = block * el * l.extra
+    base = l.begin // (block * el) * block * el
+    return max(l.begin, base + -(-(keep_from - base) // run) * run)
 
 
 def held(l, declared=0):
@@ -222,6 +230,67 @@ def test_step_of_one_generation_reads_its_arguments_late_while_the_memory_is_bus
                 assert l.targs[2] == 1 and l.targs[-1] == 0
 
 
+def takes_distances(k, length, cus):
+    """Whether a step in place, all of whose arrays lie near p, is given them by their distances."""
+    if k > 8:
+        return False
+    if length <= 1 << 19:
+        return length <= (430_000 if k in (1, 8) else 330_000 - 9_000 * k)
+    if length <= 1_200_000:
+        late = {6: 1_100_000, 7: 960_000, 8: 960_000}.get(k, 1_200_000)
+        return length <= late or cus < 256
+    return 1 << 21 < length <= 5_000_000 and cus == 256
+
+
+NEAR_LINES = [1, 1001, 1 << 18, *(330_000 - 9_000 * k for k in range(2, 8)), 430_000, 1 << 19, 960_000, 1_100_000, 1_200_000, 3 << 19, 1 << 21,
+              5_000_000, 7_000_000, 12_600_000]
+
+
+@pytest.mark.parametrize("k", range(1, 10))
+@pytest.mark.parametrize("cus", [64, 256])
+def test_step_in_place_is_given_distances(rec, k, cus):
+    for length in sorted({n + d for n in NEAR_LINES for d in (0, 1)}):
+        for begin in (0, 3):
+            for at, near in ((NEAR, True), (NEAR16, True), (FAR, False)):
+                for more in ({}, {"sqnorm": False}, {"max_norm": 0.0}):
+                    consts = work_of(rec, "oop", k, begin, begin + length, **more).consts
+                    st, launches, _, wsb = rec.call("step", k, begin, begin + length, cus=cus, at=at, **more)
+                    assert st == 0
+                    check("step", launches, begin, begin + length, wsb, at)
+                    assert launches[0].consts == consts and len(set(consts)) > 7
+                    assert launches[0].near == (near and takes_distances(k, length, cus)), (k, length, cus, launches[0].name)
+            for entry in ("oop", "from_acc"):
+                assert not work_of(rec, entry, k, begin, begin + length, cus=cus, at=NEAR).near
+
+
+@pytest.mark.parametrize("name", ["p", "m", "v", "w", "g0", "g3", "g4", "g7"])
+def test_step_with_an_array_too_far_away_is_given_addresses(rec, name):
+    """A distance is 32 bits of 256 bytes if all of them are multiples of that, else of 16."""
+    for at, unit in ((NEAR, 256), (NEAR16, 16)):
+        for length in (1, 1001, 200_000, 600_001, (1 << 21) + 1):
+            for distance in (-(1 << 31) - 1, -(1 << 31), (1 << 31) - 1, 1 << 31):
+                other = at.m if name == "p" else getattr(at, name) if name[0] != "g" else at.g[int(name[1:])]
+                by = distance * unit + (other - at.p if name == "p" else at.p - other)
+                moved = at.moved(name, by)
+                l = work_of(rec, "step", 8, 3, 3 + length, at=moved)
+                fits = all(-(1 << 31) <= (x - moved.p) // unit < 1 << 31 for x in (moved.m, moved.v, moved.w, *moved.g[:8]))
+                assert l.near == fits, (length, unit, distance)
+                assert fits or name == "p" or distance not in (-(1 << 31), (1 << 31) - 1)
+    # one array off the multiples of 256: the unit is 16 for all of them
+    assert not work_of(rec, "step", 8, 0, 1001, at=NEAR.moved(name, 16).moved("v" if name != "v" else "m", 1 << 36)).near
+
+
+@pytest.mark.parametrize("k", range(1, 33))
+def test_norm_leaves_its_last_lines_in_the_cache(rec, k):
+    line = 1 << 21 if k == 1 else 1_300_000 if k < 4 else 3 << 18
+    for length in (1, 20_000, 1 << 19, line, line + 1, (1 << 21) + 1, 5_500_001, 12_600_000, 300_000_000):
+        for cus, accumulate in ((256, 0), (256, 1), (64, 0)):
+            for ws in (MIN_WS, FULL):
+                l = work_of(rec, "norm", k, 5, 5 + length, ws=ws, cus=cus, accumulate=accumulate)
+                keeps = length > line and cus == 256 and not accumulate
+                assert l.keep_from == (first_kept(l, 5 + length - (1 << 28) // (2 * k)) if keeps else 5 + length), (length, cus, accumulate)
+
+
 # on a stream confined to some of the CUs the bytes that each of them has in flight are what counts
 @pytest.mark.parametrize("cus", [16, 64, 128, 192])
 def test_speculative_pass_on_some_of_the_cus_fills_them(rec, cus):
@@ -251,7 +320,7 @@ def test_staged_norm_keeps_its_sum_cached_for_few_streams_only(rec):
             for cus, accumulate in ((256, 0), (256, 1), (64, 0)):
                 l = work_of(rec, "staged", k, 5, 5 + length, ws=FULL, cus=cus, accumulate=accumulate)
                 keeps = k <= 16 and length > 1 << 21 and cus == 256 and not accumulate
-                assert l.keep_from == (5 + length - (64 << 20) if keeps else 5 + length)
+                assert l.keep_from == (first_kept(l, 5 + length - (64 << 20)) if keeps else 5 + length)
                 assert l.targs[3] == keeps
 
 
@@ -279,8 +348,8 @@ def test_the_gpu_tests_calls_reach_every_kernel(rec):
     names = {parse_name(n) for n in rec.kernels()}
     reached = set()
     for entry, k, length, ws, cus, first, accumulate in CALLS:
-        st, launches, _, _ = rec.call(entry, k, BEGIN, BEGIN + length, FULL if ws == "full" else MIN_WS, accumulate=accumulate, first=first, cus=cus)
+        st, launches, _, _ = rec.call(entry, k, BEGIN, BEGIN + length, FULL if ws == "full" else MIN_WS, accumulate=accumulate, first=first, cus=cus, at=NEAR)
         assert st == 0
-        reached |= {(l.kernel, l.targs) for l in launches}
-    assert {n for n in names if n[0] in WORK} - reached == set()
-    assert len(names) == len(reached)              # the two folds too
+        reached |= {(l.kernel, l.targs, l.params) for l in launches}
+    assert names - reached == set()                # the two folds too
+    assert reached - names == set()

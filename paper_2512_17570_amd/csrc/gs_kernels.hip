@@ -1070,6 +1070,16 @@ static int budget_cus(hipStream_t stream)
 
 static bool on_cu_budget(hipStream_t stream) { return budget_cus(stream) > 0; }
 
+// Whether launches on `stream` go into a graph (the null stream's cannot, and it is not asked about: beside another
+// thread's capture that is an error).
+static bool is_captured(hipStream_t stream)
+{
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (!stream || stream == hipStreamLegacy) return false;
+    if (hipStreamIsCapturing(stream, &status) != hipSuccess) (void)hipGetLastError();
+    return status != hipStreamCaptureStatusNone;
+}
+
 //   A stream confined to some of the CUs (any size over 2^21) takes BUDGET: there the bytes each CU keeps in
 //             flight are the bound, and 4 elements per lane hold twice as many (k = 2 / 8, 100 M elements:
 //             16 CUs 3.39/4.97 ms against 4.71/5.95 with 2 elements per lane and 4.11/5.83 one load at a time,
@@ -1442,13 +1452,30 @@ static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, h
     return launch_norm_kernel<K, U, GS_ONE_BLOCK, true>(A, 1, span, stream);
 }
 
+// From 5 streams on, whether one workgroup reads a range of more than one tile.  Called one after the other, the second launch's host
+// time counts (launch_grad_norm).  A captured norm has none, and there it is the GPU's time alone: us in a graph, one workgroup against
+// norm and fold, k = 5 / 6 / 8 / 9, 6 k elements 2.5/3.0/3.5/3.8 against 4.0/4.2/4.1/4.4, 48 k values 3.5/3.4/3.5/4.1 against 4.1/4.2/4.1/4.9,
+// 60 k 4.0/4.0/4.4/5.5 against 4.1/4.4/4.1/5.7, 2^16 5.2/5.2/4.5/6.2 against 5.0/5.1/4.1/5.3.  Each tile is a latency of its own there, so not where the
+// begin lies so late in its tile that the range takes one tile more (begin 4093, 4.9 k, k = 10 5.9 against 5.2), and so is a group that a range
+// end cuts, so not where one wave would have both (4.2 k, k = 13 8.4 against 7.0).
+static bool one_workgroup(const SqnormArgs &A, int64_t tiles, hipStream_t stream)
+{
+    constexpr int64_t TILE = GS_ONE_BLOCK * 4, WAVE = 64 * 4;
+    const int64_t n = A.end - A.begin;
+    if (tiles <= 1) return true;
+    if (n * A.k > GS_ONE_MAX_LOADS) return false;
+    const bool cuts_meet = A.begin % 4 != 0 && A.end % 4 != 0 && A.begin % TILE / WAVE == A.end % TILE / WAVE;
+    const bool one_latency_each = tiles == (n + TILE - 1) / TILE && !cuts_meet;
+    return (n * A.k <= GS_ONE_MAX_LOADS_CAPTURED && one_latency_each) || !is_captured(stream);
+}
+
 // from 5 streams on
 template <int K>
 static hipError_t launch_norm_many(const SqnormArgs &A, int64_t run, int64_t cap, double *d_out, int accumulate, hipStream_t stream)
 {
     const int64_t n = A.end - A.begin;
     const int64_t tiles = tiles_of(A.begin, A.end, GS_ONE_BLOCK * 4);
-    if (tiles <= 1 || n * K <= GS_ONE_MAX_LOADS) return launch_norm_one<K, 1>(A, d_out, accumulate, stream, tiles > 1 ? (int)tiles : 1);
+    if (one_workgroup(A, tiles, stream)) return launch_norm_one<K, 1>(A, d_out, accumulate, stream, tiles > 1 ? (int)tiles : 1);
     if (n <= GS_NORM_256_MAX) return launch_norm<K, 1, 256>(A, 1, cap, d_out, accumulate, stream);
     if (n <= GS_NORM_512_MAX) return launch_norm<K, 1, 512>(A, 1, cap, d_out, accumulate, stream);
     if constexpr (K < 8)

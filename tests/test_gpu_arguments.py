@@ -81,3 +81,26 @@ def test_norm_with_each_table_of_streams(k):
             got = float(sq.item())
             # two fp64 trees over exact squares (deeper than 2^-40 of the sum needs more than 2^12 additions in a chain)
             assert abs(got - want * (2 if accumulate else 1)) <= 1e-12 * want, (k, length, accumulate)
+
+
+@pytest.mark.parametrize("k,length", [(5, 9830), (5, 13_107), (8, 6144), (8, 6145), (8, 8192), (13, 4153)])
+def test_captured_norm_of_a_few_tiles(k, length):
+    """Captured, such a range is read by one workgroup less often than called one after the other."""
+    n = B + length + 2
+    grads = [I.normal_f32(n, 1e-3, 9, j, DEV).to(torch.bfloat16) for j in range(k)]
+    sq, eager = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
+    gs.gs_grad_sqnorm_noalloc(grads, B, B + length, sq)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        gs.gs_grad_sqnorm_noalloc(grads, B, B + length, sq)
+    for times in (1, 2, 3):
+        for g in grads:
+            g.mul_(times)
+        gs.gs_grad_sqnorm_noalloc(grads, B, B + length, eager)
+        torch.cuda.synchronize()
+        sq.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        # two fp64 trees over the same squares, as above
+        assert abs(float(sq) - float(eager)) <= 1e-12 * float(eager)

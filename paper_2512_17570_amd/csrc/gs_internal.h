@@ -51,7 +51,8 @@
 #define GS_ADD_SMALL_MAX (1 << 22)    // without the norm: elements up to which both loads are in flight together
 #define GS_ADD_FIRST_256_MAX 900000   // first micro-batch: elements up to which workgroups have 256 lanes
 #define GS_ADD_FIRST_128_MAX (1 << 25) // and, above 2^21, 128
-#define GS_ADD_WIDE_MAX (1 << 23)     // with the norm: elements up to which a workgroup takes 4096 of them unless the sum stays in the cache
+#define GS_ADD_WIDE_MAX (1 << 23)     // with the norm: elements up to which a workgroup takes 4096 of them unless the sum stays in the cache,
+#define GS_ADD_KEEP_MIN (1 << 22)     // which after a later micro-batch it does from here on (after the first from the line before)
 // limits of the norm's shapes (launch_grad_norm)
 #define GS_NORM_SMALL_MAX (1 << 22)   // up to 4 streams: elements up to which workgroups are kept small
 #define GS_NORM_256_MAX (3 << 18)     // from 5 streams on: elements up to which workgroups have 256 lanes

@@ -1705,11 +1705,12 @@ static hipError_t launch_add_norm(const AccumAddArgs &A, int first, int64_t cap,
 //                                                       waiting is 0.5 % ahead, level in between
 //   with the norm: both loads in flight; 256 lanes up to 2^19, then 1024 where the sum is not left in the cache (fewer partials: 2 M 7.5 against
 //                                             9.7), up to 2^23; else, and beyond, 64 (12.6 M 25.1 against 26.2, 201 M 306 against 320).  That
-//                                             call on its own takes longer while the partials count (5 M 13.3 against 12.2 in 1024 lanes that leave
-//                                             nothing), and the step after it less: both and the three micro-batches before them, 2.6 M / 5.5 M / 7 M
-//                                             37.6/65.1/78.2 against 39.3/70.3/83.8.  A sum of one micro-batch alone loses that way (5 M 37.4
-//                                             against 35.8), and wide workgroups that leave it in the cache make the fold wait for the write-back
-//                                             (3.3 M 16.6 against 13.3).
+//                                             call on its own takes longer while the partials count (5 M / 8 M 13.1/17.6 against 11.7/16.3 in 1024 lanes
+//                                             that leave nothing), and what comes before and after it less: all micro-batches and the step, 5 M / 7 M,
+//                                             2 of them 44.5/57.9 against 44.9/58.9, 4 62.0/79.8 against 63.6/82.0, 16 165/211 against 167/214.  Up to
+//                                             2^22 that is no gain with two (2.3 M / 3 M 26.7/31.5 against 25.9/30.6) and up to 1 % with four and
+//                                             more.  A sum of one micro-batch alone loses that way (5 M 37.4 against 35.8), and wide workgroups that
+//                                             leave it in the cache make the fold wait for the write-back (3.3 M 16.6 against 13.3).
 //   with a workspace too small for a partial per 256 elements, per 1024 or 4096.
 hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspace_bytes, double *d_out, int accumulate,
                             hipStream_t stream)
@@ -1729,7 +1730,7 @@ hipError_t launch_accum_add(const AccumAddArgs &args, int first, size_t workspac
         return launch_add_as<false, false, 64, 4, false>(A, 0, nullptr, 0, stream);
     }
     const int64_t cap = partial_capacity(workspace_bytes);
-    if (accumulate || (first && n <= GS_ADD_WIDE_MAX)) A.keep_from = A.end;
+    if (accumulate || n <= (first ? GS_ADD_WIDE_MAX : GS_ADD_KEEP_MIN)) A.keep_from = A.end;
     const bool keeps = A.keep_from < A.end;
     if ((n > GS_ADD_WIDE_MAX || keeps) && tiles_of(A.begin, A.end, 256) <= cap)
         return launch_add_norm<64>(A, first, cap, d_out, accumulate, stream);

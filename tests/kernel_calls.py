@@ -50,7 +50,7 @@ CALLS = [
     # adding a micro-batch, without and with the norm
     *[_c("add", 1, n, first=f) for f in (0, 1) for n in (1, L22, L22 + 1)],
     _c("add", 1, L21 + 1), _c("add", 1, L22 + 1, cus=64), *[_c("add", 1, n, first=1) for n in (900_000, 900_001, L21, L21 + 1, L25, L25 + 1)],
-    *[_c("add_norm", 1, n, first=f, accumulate=a) for n in (L21, L21 + 1) for f in (0, 1) for a in (0, 1)],
+    *[_c("add_norm", 1, n, first=f, accumulate=a) for n in (L21, L21 + 1, L22, L22 + 1) for f in (0, 1) for a in (0, 1)],
     *[_c("add_norm", 1, n, first=f) for f in (0, 1) for n in (1, L19, L19 + 1, L23, L23 + 1)],
     *[_c("add_norm", 1, n) for n in (67_200_000, L28 + 1)],
 ]

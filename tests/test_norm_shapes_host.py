@@ -77,7 +77,7 @@ def test_adding_kernel_by_length(rec, cus):
                 assert st == 0
                 check("add_norm", launches, 5, 5 + length, wsb)
                 l = launches[0]
-                keeps = length > 1 << 21 and all_cus and not accumulate and (not first or length > 1 << 23)
+                keeps = length > (1 << 23 if first else 1 << 22) and all_cus and not accumulate
                 assert (l.keep_from < l.end) == keeps, (length, first, accumulate)
                 lanes = 256 if length <= 1 << 19 else 64 if keeps or length > 1 << 23 else 1024
                 assert l.targs == (first, 1, lanes, 4, 0, 0), (length, first, accumulate, l.name)

@@ -1215,27 +1215,31 @@ static hipError_t launch_step(const StepArgs &A, hipStream_t stream, uint32_t ro
     if constexpr (!STAGED && !LWAIT && !LATE && (DEPTH == 4 || DEPTH == 8)) {
         NearArgs N;
         if (near_args(A, N)) {
+            hipError_t e = hipSuccess;
             const auto go = [&](auto streams) {
                 constexpr int K = decltype(streams)::value;
-                if constexpr (BLOCK == 128 ? (DEPTH == 8) != (K >= 5) : EL == 2 && ((THROUGH && K == 1) || (!THROUGH && K > 1 && K < 8))) {
-                    return hipErrorInvalidValue;
-                } else {
+                // the numbers of streams that this shape is taken with; any other is given addresses
+                constexpr bool taken = BLOCK == 128 ? (DEPTH == 8) == (K >= 5) : EL == 4 || K == 8 || THROUGH == (K > 1);
+                if constexpr (taken) {
                     NearRest<K> R{{N.g[4], N.g[5], N.g[6], N.g[7]}, N.w, A.max_norm, A.c};
                     void (*const kernel)(int64_t, int, uint32_t, float *, const double *, int, int, int, int, int, int, NearRest<K>) =
                         k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>;
-                    return launch(kernel, grid, BLOCK, room, stream, A.begin, cuts, N.packed, N.p, A.d_sqnorm, N.m, N.v, N.g[0], N.g[1], N.g[2], N.g[3], R);
+                    e = launch(kernel, grid, BLOCK, room, stream, A.begin, cuts, N.packed, N.p, A.d_sqnorm, N.m, N.v, N.g[0], N.g[1], N.g[2], N.g[3], R);
                 }
+                return taken;
             };
+            bool gone = false;
             switch (A.k) {
-            case 1: return go(std::integral_constant<int, 1>{});
-            case 2: return go(std::integral_constant<int, 2>{});
-            case 3: return go(std::integral_constant<int, 3>{});
-            case 4: return go(std::integral_constant<int, 4>{});
-            case 5: return go(std::integral_constant<int, 5>{});
-            case 6: return go(std::integral_constant<int, 6>{});
-            case 7: return go(std::integral_constant<int, 7>{});
-            case 8: return go(std::integral_constant<int, 8>{});
+            case 1: gone = go(std::integral_constant<int, 1>{}); break;
+            case 2: gone = go(std::integral_constant<int, 2>{}); break;
+            case 3: gone = go(std::integral_constant<int, 3>{}); break;
+            case 4: gone = go(std::integral_constant<int, 4>{}); break;
+            case 5: gone = go(std::integral_constant<int, 5>{}); break;
+            case 6: gone = go(std::integral_constant<int, 6>{}); break;
+            case 7: gone = go(std::integral_constant<int, 7>{}); break;
+            case 8: gone = go(std::integral_constant<int, 8>{}); break;
             }
+            if (gone) return e;
         }
     }
     void (*const kernel)(StepArgs, int) = k_accum_adamw<BLOCK, EL, STAGED, DEPTH, LWAIT, SWAIT, THROUGH, LATE>;

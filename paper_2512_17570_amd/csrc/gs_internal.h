@@ -63,7 +63,7 @@
 #define GS_NORM_LONG_MIN (1 << 29)    // elements from which a workgroup reads four tiles instead of two (one stream: eight instead of four)
 #define GS_ACC_NORM_LONG_MIN (1 << 27)  // the same line of the fp32 norm (eight tiles)
 #define GS_ONE_MAX_LOADS 65536        // from 5 streams on: elements times streams up to which that workgroup takes more than one tile
-#define GS_ONE_MAX_LOADS_CAPTURED 49152  // and in a captured norm
+#define GS_ONE_MAX_LOADS_CAPTURED 40960  // and in a captured norm
 #define GS_ONE_BLOCK 1024             // threads of the norm in a single workgroup
 #define GS_BUDGET_RUN_MIN 49152       // elements per CU of a confined stream from which the norms take shapes of their own
 

@@ -697,15 +697,23 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
 {
     constexpr int TILE = BLOCK * 4;
     constexpr bool KEEPS = !ONE && (BLOCK > 256 || (K > 0 && K <= 4));       // the others read up to 2^20 elements, or on some of the CUs
-    __shared__ double lds[BLOCK / 64];
+    // Of several tiles one after the other, each by itself: the sums are then those of workgroups of 256 lanes and their fold, in that order, so
+    // that a range has the same norm to the bit whichever of the two it is given to.  That takes 0.05-0.1 us a tile (captured, 7.2 k / 9.6 k, k = 5
+    // 3.0/3.8 us against 2.9/3.6; kept in registers and summed beside each other at the end, 10 % in all against 5).
+    constexpr bool FOLDS = ONE && K > 4;
+    constexpr int TILES = FOLDS ? GS_ONE_MAX_LOADS / K / TILE + 2 : 1, WAVES = BLOCK / 64;
+    __shared__ double lds[TILES * WAVES];
+    const bool folds = FOLDS && span > 1;
     const int64_t first = (begin / TILE + (int64_t)blockIdx.x * span) * TILE + (int64_t)threadIdx.x * 4;
     double acc0 = 0.0, acc1 = 0.0;
     with_keep(KEEPS && (int)blockIdx.x >= keep_block, [&](auto keep) {
     constexpr bool KEEP = decltype(keep)::value;
     for (int it = 0; it < span; it += U) {
         const int64_t lo = first + (int64_t)it * TILE;
-        if (lo >= end) break;
-        if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
+        if (!FOLDS && lo >= end) break;
+        if (FOLDS && lo >= end) {
+            // all lanes go on to the tile's sum
+        } else if (lo >= begin && lo + (int64_t)(U - 1) * TILE + 4 <= end) {
             if constexpr (K > 0) {
                 static_assert(K <= DEPTH || U == 1, "tiles are grouped for one batch of streams");
                 constexpr int BATCH = K < DEPTH ? K : DEPTH;
@@ -750,8 +758,27 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
                 add_squares(a, acc0, acc1);
             }
         }
+        if constexpr (FOLDS) {
+            if (folds) {
+                const double wave = wave_sum(acc0 + acc1);
+                if (threadIdx.x % 64 == 63) lds[it * WAVES + threadIdx.x / 64] = wave;
+                acc0 = acc1 = 0.0;
+            }
+        }
     }
     });
+    if constexpr (FOLDS) {
+        static_assert(BLOCK == 1024 && U == 1 && TILES <= 16, "four workgroups of 256 lanes a tile, in one wave's lanes");
+        if (folds) {
+            __syncthreads();
+            if (threadIdx.x >= 64) return;
+            const int part = (int)threadIdx.x + (int)(begin % TILE / 1024);        // the first such workgroup's is lane 0's
+            const double *w = lds + 4 * part;
+            const double t = wave_sum(part < 4 * span ? (w[0] + w[1]) + (w[2] + w[3]) : 0.0);
+            if (threadIdx.x == 63) *out = accumulate ? *out + t : t;
+            return;
+        }
+    }
     double t = block_sum<BLOCK>(acc0 + acc1, lds);
     if (threadIdx.x == 0) {
         if constexpr (ONE) *out = accumulate ? *out + t : t;
@@ -1458,10 +1485,11 @@ static hipError_t launch_norm_one(SqnormArgs A, double *d_out, int accumulate, h
 
 // From 5 streams on, whether one workgroup reads a range of more than one tile.  Called one after the other, the second launch's host
 // time counts (launch_grad_norm).  A captured norm has none, and there it is the GPU's time alone: us in a graph, one workgroup against
-// norm and fold, k = 5 / 6 / 8 / 9, 6 k elements 2.5/3.0/3.5/3.8 against 4.0/4.2/4.1/4.4, 48 k values 3.5/3.4/3.5/4.1 against 4.1/4.2/4.1/4.9,
-// 60 k 4.0/4.0/4.4/5.5 against 4.1/4.4/4.1/5.7, 2^16 5.2/5.2/4.5/6.2 against 5.0/5.1/4.1/5.3.  Each tile is a latency of its own there, so not where the
-// begin lies so late in its tile that the range takes one tile more (begin 4093, 4.9 k, k = 10 5.9 against 5.2), and so is a group that a range
-// end cuts, so not where one wave would have both (4.2 k, k = 13 8.4 against 7.0).
+// norm and fold, k = 5 / 6 / 7 / 8, 6 k elements 2.7/3.2/3.4/3.8 against 3.7/3.9/3.9/4.0, 8 k, k = 6 3.65 against 3.85, 60 k and 2^16 values, k = 5 / 8
+// 4.1/4.55 and 5.3/4.7 against 3.85/4.0 and 4.5/4.0.  The mean over ranges of any begin is 12, 7, 3.5 and 1 % ahead from 24, 32, 36 and 40 k values on and
+// 2 % behind from 44 k on.  Each tile is a latency of its own there, so not where the begin lies so late in its tile that the range
+// takes one tile more (begin 4093, 4.9 k, k = 10 5.9 against 4.9), and so is a group that a range end cuts, so not where one wave would have both
+// (4.2 k, k = 13 8.6 against 6.4).  Both shapes leave the same bits.
 static bool one_workgroup(const SqnormArgs &A, int64_t tiles, hipStream_t stream)
 {
     constexpr int64_t TILE = GS_ONE_BLOCK * 4, WAVE = 64 * 4;

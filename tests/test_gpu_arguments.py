@@ -83,24 +83,29 @@ def test_norm_with_each_table_of_streams(k):
             assert abs(got - want * (2 if accumulate else 1)) <= 1e-12 * want, (k, length, accumulate)
 
 
-@pytest.mark.parametrize("k,length", [(5, 9830), (5, 13_107), (8, 6144), (8, 6145), (8, 8192), (13, 4153)])
-def test_captured_norm_of_a_few_tiles(k, length):
+@pytest.mark.parametrize("k", [5, 6, 7, 8, 9, 10, 13, 15])
+@pytest.mark.parametrize("begin", [0, 5, 1021, 1024, 3000, 4093])
+def test_captured_norm_of_a_few_tiles_has_the_same_bits(k, begin):
     """Captured, such a range is read by one workgroup less often than called one after the other."""
-    n = B + length + 2
+    top = 65536 // k
+    lengths = sorted({4097, 40960 // k, 40960 // k + 1, top, top + 1, 8200 - begin, 8192, (4097 + top) // 2, 4096 * 3 - begin} & set(range(4097, top + 2)))
+    n = begin + top + 3
     grads = [I.normal_f32(n, 1e-3, 9, j, DEV).to(torch.bfloat16) for j in range(k)]
-    sq, eager = (torch.zeros(1, dtype=torch.float64, device=DEV) for _ in range(2))
-    gs.gs_grad_sqnorm_noalloc(grads, B, B + length, sq)
+    sq, eager = (torch.zeros(len(lengths), dtype=torch.float64, device=DEV) for _ in range(2))
+    gs.gs_grad_sqnorm_noalloc(grads, begin, n, sq)
+    ws = torch.full((gs.gs_sqnorm_workspace_bytes(),), 0xff, dtype=torch.uint8, device=DEV)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph):
-        gs.gs_grad_sqnorm_noalloc(grads, B, B + length, sq)
-    for times in (1, 2, 3):
+        for i, length in enumerate(lengths):
+            gs.gs_grad_sqnorm_noalloc(grads, begin, begin + length, sq[i:])
+    for times in (1, 3, 5):
         for g in grads:
             g.mul_(times)
-        gs.gs_grad_sqnorm_noalloc(grads, B, B + length, eager)
+        for i, length in enumerate(lengths):
+            gs.gs_grad_sqnorm(grads, begin, begin + length, eager[i:], ws)
         torch.cuda.synchronize()
         sq.fill_(float("nan"))
         graph.replay()
         torch.cuda.synchronize()
-        # two fp64 trees over the same squares, as above
-        assert abs(float(sq) - float(eager)) <= 1e-12 * float(eager)
+        assert torch.equal(sq, eager), (lengths, (sq - eager).tolist())

@@ -36,7 +36,7 @@ def test_norm_has_a_kernel_for_each_number_of_streams(rec, k):
 @pytest.mark.parametrize("k", range(5, 33))
 def test_captured_norm_is_left_to_one_workgroup_where_its_gpu_time_is_less(rec, entry, k):
     for begin in (0, 4, 5, 13, 1021, 4093):
-        for length in (1, 4096 - begin % 4096, 4097, 49152 // k, 49152 // k + 1, 65536 // k, 65536 // k + 1, 8192, 8200 - begin, 100_000):
+        for length in (1, 4096 - begin % 4096, 4097, 40960 // k, 40960 // k + 1, 65536 // k, 65536 // k + 1, 8192, 8200 - begin, 100_000):
             end, tiles = begin + length, (begin + length - 1) // 4096 - begin // 4096 + 1
             in_one_wave = begin % 4 and end % 4 and begin % 4096 // 256 == end % 4096 // 256
             for capturing in (False, True):
@@ -44,7 +44,7 @@ def test_captured_norm_is_left_to_one_workgroup_where_its_gpu_time_is_less(rec, 
                 assert st == 0
                 check(entry, launches, begin, end, wsb)
                 if capturing:
-                    one = length * k <= 49152 and tiles == -(-length // 4096) and not in_one_wave
+                    one = length * k <= 40960 and tiles == -(-length // 4096) and not in_one_wave
                 else:
                     one = length * k <= 65536
                 assert launches[0].targs[3] == (one or tiles == 1), (begin, length, capturing)

@@ -696,7 +696,9 @@ __device__ __forceinline__ void grad_sqnorm(int64_t begin, int span, int keep_bl
                                             double *out, int accumulate)
 {
     constexpr int TILE = BLOCK * 4;
-    constexpr bool KEEPS = !ONE && (BLOCK > 256 || (K > 0 && K <= 4));       // the others read up to 2^20 elements, or on some of the CUs
+    // from five streams on 256 lanes read ranges below GS_KEEP_MANY_MIN, or on some of the CUs
+    constexpr bool KEEPS = !ONE && (BLOCK > 256 || (K > 0 && K <= 4));
+    static_assert(GS_NORM_256_MAX <= GS_KEEP_MANY_MIN, "else 256 lanes would have to leave lines in the cache");
     // Of several tiles one after the other, each by itself: the sums are then those of workgroups of 256 lanes and their fold, in that order, so
     // that a range has the same norm to the bit whichever of the two it is given to.  That takes 0.05-0.1 us a tile (captured, 7.2 k / 9.6 k, k = 5
     // 3.0/3.8 us against 2.9/3.6; kept in registers and summed beside each other at the end, 10 % in all against 5).

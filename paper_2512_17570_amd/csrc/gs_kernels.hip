@@ -688,7 +688,8 @@ __device__ __forceinline__ void add_squares(const float (&a)[EL], double &acc0, 
 // of them up to DEPTH streams are.  K: the number of streams, or 0 where it is told at run time (the long runs on some of the CUs).  Told
 // at run time, each stream of a partial batch is a test, a scalar load and a wait before its load: with the fold, us, a kernel for each
 // number against that, 4 k elements, k = 5 / 17 2.37/3.76 against 2.65/4.33; 13 k, k = 9 / 24 3.91/5.00 against 4.35/5.70; 100 k, k = 12 / 29
-// 4.51/5.54 against 4.93/6.23; 1 M, k = 13 / 17 7.75/8.97 against 8.26/9.66; 12 M, k = 11 / 17 46.6/67.2 against 47.6/69.2; 1 % from 50 M on.
+// 4.51/5.54 against 4.93/6.23; 1 M, k = 13 / 17 7.75/8.97 against 8.26/9.66; 12 M, k = 11 / 17 46.6/67.2 against 47.6/69.2, 50 M 162.3/244.6
+// against 163.7/247.0; level from 200 M on, and everywhere with 8, 16, 24 and 32, whose batches are whole.
 // ONE: a single workgroup reads the whole range and leaves the norm itself in `out`.  Workgroups from keep_block on
 // leave what they read in the memory-side cache.
 template <int K, int U, int BLOCK, bool ONE, int DEPTH, typename Table>
@@ -1195,6 +1196,11 @@ struct NearArgs {
 // come all at once as the memory gets busy: 2-7 % behind from 1.3 M on for 6 to 8 streams (up to five 1 % ahead there, and level above).
 // In full CUs above 2^21 they are ahead again, by less and less (with the norm, k = 2 / 5 / 8: 2.2 M 17.4/20.7/24.6 us against 17.7/21.1/24.9, 3.3 M
 // 22.6/27.8/33.9 against 22.9/28.3/34.3, 5 M within 1 %; alone four streams are 0.8 % behind from 6 M on).
+// On some of the CUs they are ahead as well (16 / 64 / 128 CUs, 100 k, k = 4 5.9/3.6/2.7 us against 6.8/4.4/3.3, 900 k, k = 2 32.0/10.5/6.8 against
+// 32.9/11.8/7.3), but with seven and eight streams in RESIDENT level only: 0.5-1.5 % behind on 16 and 32 CUs (600 k, k = 8 31.3/17.9 against
+// 31.0/17.7), from 8 % ahead to 4 % behind on more of them, as the last waves of a range happen to fall (600 k / 1.19 M, k = 8, 64 CUs 11.1/19.9
+// against 11.7/19.7, 128 CUs 7.7/13.1 against 8.0/14.3, 192 CUs 7.3/10.9 against 7.6/10.5).  To ask for the stream's CUs takes the host 0.5 us,
+// which every call with so many streams would pay.
 static bool near_args(const StepArgs &A, NearArgs &N)
 {
     const int64_t n = A.end - A.begin;
@@ -1410,11 +1416,14 @@ hipError_t launch_accum_adamw_spec(const StepArgs &A, double *partials, size_t w
 //   norm alone, k = 8 / 16 / 32            6 M 20.7/36.8/66.4 against 18.9/32.2/61.3, 50 M 127/237/471 against 122/231/466
 //   fp32 norm alone                      50 M 37.5 against 34.4;  first micro-batch alone 5 M 8.7 against 7.3, 50 M 51 against 49
 // 192 and 320 MB gain less than 256 (norm + step, 201 M: 1749 and 1747 us against 1745).  Not done:
-//   * Up to 2^21 elements, but for the gradient norm of four streams and more only up to 3 * 2^18, of two and three up to 1.3 M.  The
+//   * Up to 2^21 elements (the last of several micro-batches: 2^22, launch_accum_add), but for the gradient norm of four streams and more only
+//     up to 3 * 2^18, of two and three up to 1.3 M.  The
 //     two passes, plain from there on against the hint up to 2^21, k = 4 / 8 / 12 / 32: 800 k 11.0/12.8/14.8/24.3 against 11.1/13.5/15.7/25.6, 1.3 M
 //     13.8/16.3/19.3/35.5 against 14.3/17.5/21.9/38.0, 2 M 17.6/23.5/28.4/52.2 against 18.9/25.5/30.2/54.8; k = 2, 1 M / 2 M 10.7/15.6 against
-//     10.6/16.3.  The norm alone: k = 4 / 8 / 16 / 32 800 k 5.0/5.7/8.2/12.9 against 5.1/5.8/7.8/12.0, 2 M 6.2/9.1/14.4/25.4 against
-//     6.5/8.7/13.4/23.2.  Below, the gain goes up and down with the range (600 k, k = 4 / 32 +4/-6 %); the fp32 norm gains from about 2 M on and
+//     10.6/16.3.  Several norms into scalars of their own before their steps gain while their lines fit the cache together, and a little beyond (12 of
+//     each, against the tree in which this began at 2^21, 800 k / 1.3 M, k = 16 216/294 against 232/311), and lose where they are several times
+//     as long (2 M, k = 16 / 32 433/704 against 433/680).  The norm alone: k = 4 / 8 / 16 / 32 800 k 5.0/5.7/8.2/12.9 against 5.1/5.8/7.8/12.0,
+//     2 M 6.2/9.1/14.4/25.4 against 6.5/8.7/13.4/23.2.  Below, the gain goes up and down with the range (600 k, k = 4 / 32 +4/-6 %); the fp32 norm gains from about 2 M on and
 //     loses at 800 k (6 %), the staged norm likewise.
 //   * accumulate: the norm goes on over other ranges before the step comes, and the next range's lines
 //     would push these out again.
@@ -1525,9 +1534,11 @@ static hipError_t launch_norm_by_streams(const SqnormArgs &A, int64_t run, int64
     return hipErrorInvalidValue;
 }
 
-// Up to four 4096-element tiles a single workgroup reads the range and no fold has to follow, from 5 streams on while there are
-// up to 2^16 values to read, or one tile (6 k elements, k = 5 / 8 2.8/3.35 us against 3.8/3.8 with the fold, 8 k 3.5/4.2 against 3.8/3.9, 13 k
-// 4.5/6.3 against 4.0/4.1; called one after the other the second launch's host time counts too: norm and step, 8 k, k = 8 8.3 against 10.4) (13 k elements, k = 1 / 3: 3.0/4.5 us against 5.5/9.4 with the fold).  The lanes whose groups lie in all four
+// Up to four 4096-element tiles a single workgroup reads the range and no fold has to follow (13 k elements, k = 1 / 3: 3.3/3.9 us against
+// 5.5/9.4 with the fold), from 5 streams on while there are up to 2^16 values to read, or one tile.  On the GPU alone those 2^16 are too many, 6 k
+// elements, k = 5 / 8 2.8/3.35 us against 3.8/3.8 with the fold, 8 k 3.5/4.2 against 3.8/3.9, 13 k, k = 5 4.5 against 4.0; but called one after the other
+// the second launch's host time counts too: norm and step, 8 k, k = 8 9.7 against 11.8, 13 k, k = 5 9.7 against 11.7 (one_workgroup has the line for
+// captured ones).  The lanes whose groups lie in all four
 // tiles have them in flight together; in a range that ends before, the others take them one after another.
 // Above that: with up to 4 streams 256 lanes and one group of U tiles up to 4 M elements, 512 lanes and
 // two tiles beyond (four from 2^29 elements on, where longer runs win 2-3 %, and always for three streams: 6.3 M / 12.6 M
@@ -1541,11 +1552,16 @@ static hipError_t launch_norm_by_streams(const SqnormArgs &A, int64_t run, int64
 // tile up to 5.5 M (against two tiles of 1024 lanes, with the end of the range left in the cache: 2.2 M, k = 5 / 8 / 16 / 32 7.1/9.9/16.1/28.7
 // against 8.1/12.1/20.5/38.3, 3 M 8.7/11.8/19.9/36.1 against 9.2/12.9/22.2/40.9, 5 M 12.5/17.4/30.4/58.3 against 12.4/18.2/33.3/62.6), then two tiles (8 M,
 // k = 8 / 16 / 32 24.8/47.3/83.2 against 25.0/46.1/82.5 with one, 10 M 30.3/55.7/103.7 against 31.7/56.5/105.5); 5 to 7 streams read those in 1024 lanes up
-// to 2^25 (k = 5, 8 M / 20 M 16.5/36.3 against 17.0/37.6).  us, all with the fold, against 256 lanes with 8 tiles one after another, without it:
-//   100 k  k = 1/3/8/32  3.9/4.0/4.3/5.7 against 3.5/6.3/8.1/38     12.6 M  7.8/15.2/35.5/120 against 8.4/15.8/35.4/151
-//   1 M    k = 1/3/8/32  4.4/4.8/6.3/12.4 against 5.8/10.6/8.6/40   201 M   67/176/466/1882 against 89/191/474/1932
-//   3 M    k = 1/3/8/32  4.9/6.5/11.8/36 against 6.5/11.5/11.0/51   805 M   236/713/1848/7849 against 347/737/1851/7903
-// (all reads with the non-temporal hint; keep_from says what leaving them in the cache costs)
+// to 2^25 (k = 5, 8 M / 20 M 16.5/36.3 against 17.0/37.6).
+// The lines are the same where nothing is left in the cache.  Accumulating, against 256 lanes up to 2^20 and 1024 with two tiles above 2^21 (and a
+// number of streams told at run time): 1 M, k = 8 / 32 6.4/15.2 us against 7.2/16.9, 2.2 M 9.3/25.6 against 11.3/33.1, 3 M 11.0/32.6 against 11.9/35.2; 1-2.6 %
+// behind at 4 and 5.6 M from eight streams on (k = 32 40.5/57.0 against 39.8/55.5), level at 5.4 and 8 M.  On 16 / 64 / 128 CUs, 2.2 M, k = 8 50.9/16.5/11.3
+// against 52.1/19.1/13.8, 5.4 M, k = 16 226/63.8/38.3 against 229/66.7/41.6; where the workgroups happen to leave a last wave nearly empty 1-4 %
+// behind (800 k, k = 16 on 16 CUs 38.4 against 37.8; 3 M, k = 32 on 128 44.6 against 42.9).
+// us, all with the fold and the last lines left in the cache, against 256 lanes with 8 tiles one after another, without either:
+//   100 k  k = 1/3/8/32  4.2/4.3/4.2/5.5 against 3.5/6.3/8.1/38     12.6 M  8.1/16.0/36.1/124 against 8.4/15.8/35.4/151
+//   1 M    k = 1/3/8/32  4.3/4.9/6.4/13.6 against 5.8/10.6/8.6/40   201 M   65/176/455/1797 against 89/191/474/1932
+//   3 M    k = 1/3/8/32  4.9/6.8/11.3/35 against 6.5/11.5/11.0/51   805 M   236/713/1848/7849 against 347/737/1851/7903
 //   On some of the CUs, 4 to 7 streams: once each CU has some tens of thousands of elements to read, 256 lanes,
 //   four loads in flight and eight tiles one after another (k = 4 / 5, 50 M elements: 16 CUs 523/694 us against
 //   651/860 in the shapes below, 128 CUs 84/110 against 97/122; 3.3 M on 128 CUs, 26 k elements each, 11.6/16.2

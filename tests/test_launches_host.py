@@ -237,8 +237,7 @@ def takes_distances(k, length, cus):
     if length <= 1 << 19:
         return length <= (430_000 if k in (1, 8) else 330_000 - 9_000 * k)
     if length <= 1_200_000:
-        late = {6: 1_100_000, 7: 960_000, 8: 960_000}.get(k, 1_200_000)
-        return length <= late or cus < 256
+        return cus < 256 or length <= {6: 1_100_000, 7: 960_000, 8: 960_000}.get(k, 1_200_000)
     return 1 << 21 < length <= 5_000_000 and cus == 256
 
 
